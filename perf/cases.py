@@ -1,0 +1,473 @@
+"""Performance cases: what a program that uses this library has it do, through the package's public entry points.
+
+A case is a dict of plain values.  `kind` names the work of one pass:
+
+  table    build a stage's neighbourhoods from raw coordinates: curve clustering, gather of the coordinates into curve
+           order, neighbour search, plan.  A pre-training step does this for every stage, because the mask, hence the
+           token set, changes with the step; a fine-tuning step does it when the coordinates change.
+  fwd      one attention block's forward on a cached table and plan (inference, validation).
+  train    one attention block's forward and backward, bias given as a tensor.  `search` puts the neighbour search into
+           the pass as well (small programs that keep no table); `promise` false calls without the near-cluster
+           promise (a table that did not come from the clustered search).
+  relpos   the same with the bias looked up in a per-head table over relative positions.
+  decoder  the point decoder's virtual sampled tokens: nearest-visible-token table, sampling forward and backward.
+  merge    neighbourhood merging between stages: anchor selection, aggregation forward and backward.
+
+Coordinates: `uniform`, `masked` (patch centres left by a random mask), `jitter` (patch centres with a jitter of 2 px),
+`blobs` (Gaussian mixture).  Everything is made from the seed with torch on the GPU.
+"""
+import math
+
+import torch
+
+import paper_2602_16249_amd as aff
+
+DEV = "cuda"
+PITCH = 8.0  # pixels per patch
+
+
+# ---------------------------------------------------------------------------------------------------------- the cases
+
+def _attn(name, kind, dtype, B, N, H, d, K, S, M, coords, **kw):
+    c = {"kind": kind, "dtype": dtype, "B": B, "N": N, "H": H, "d": d, "K": K, "S": S, "M": M, "coords": coords,
+         "blank": False, "promise": True, "search": False, "R": 0}
+    c.update(kw)
+    if name:
+        c["name"] = name
+    return c
+
+
+def listed():
+    return [
+        # the smallest call there is: one image of 256 tokens in fp32 with exact search; latency and launches count
+        _attn("tiny_f32", "train", "f32", 1, 256, 2, 32, 16, 256, 1, "uniform", promise=False, search=True),
+        # neighbourhoods of a 1024-px pre-training step: 75 % of the 128 x 128 patch centres masked away
+        _attn("table_pretrain", "table", "bf16", 16, 4096, 2, 32, 48, 64, 8, "masked"),
+        # neighbour search at scale: structures in clumps, 16 images of 16384 tokens
+        _attn("table_blobs", "table", "bf16", 16, 16384, 4, 32, 48, 64, 8, "blobs"),
+        # inference on 1024-px images, first stage
+        _attn("fwd_finetune", "fwd", "bf16", 8, 16384, 2, 32, 48, 64, 8, "jitter"),
+        # fine-tuning on 1024-px images, first stage: the framework's headline work
+        _attn("train_finetune", "train", "bf16", 8, 16384, 2, 32, 48, 64, 8, "jitter"),
+        # a deeper stage after merging: few tokens, many heads
+        _attn("train_merged", "train", "bf16", 64, 1024, 8, 32, 48, 32, 8, "uniform"),
+        # the largest: clumped tokens, four heads, 16 images
+        _attn("train_blobs", "train", "bf16", 16, 16384, 4, 32, 48, 64, 8, "blobs"),
+        # whatever a mask leaves: a small batch, N that nothing divides, odd K and H, blank tokens
+        _attn("train_ragged", "train", "bf16", 3, 4001, 3, 32, 37, 64, 8, "masked", blank=True),
+        # fine-tuning with the bias from a relative-position table (9 x 9 cells of one patch per head)
+        _attn("relpos_finetune", "relpos", "bf16", 8, 16384, 2, 32, 48, 64, 8, "jitter", R=4),
+        # the full-precision run that a mixed-precision result is checked against
+        _attn("train_f32", "train", "f32", 4, 4096, 2, 32, 48, 64, 8, "masked"),
+        # point decoder: 48 images, 2048 mask tokens of 4 sample points each, 1024 visible tokens of a 64 x 64 grid
+        {"name": "decoder", "kind": "decoder", "dtype": "bf16", "B": 48, "Mq": 8192, "Nv": 1024, "C": 128, "side": 64,
+         "Kt": 4},
+        # merging after the first fine-tuning stage: a quarter of the tokens is kept
+        {"name": "merge_finetune", "kind": "merge", "dtype": "bf16", "B": 8, "N": 16384, "C": 64, "K": 48, "S": 64,
+         "M": 8, "coords": "jitter", "keep": 4096},
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["table", "fwd", "train", "train", "train", "relpos", "general", "decoder", "merge"])
+    if kind == "decoder":
+        side = rng.randint(16, 80)
+        Nv = max(64, int(side * side * rng.uniform(0.15, 0.4)))
+        Kt = rng.choice([3, 4, 4, 4, 8])
+        Mq = _log(rng, 256, 8192)
+        B = max(1, min(48, _log(rng, 1, 48), 48 * 8192 * 4 // (Mq * Kt)))
+        return {"kind": kind, "dtype": rng.choice(["bf16", "bf16", "f32"]), "B": B, "Mq": Mq, "Nv": Nv,
+                "C": rng.choice([64, 128, 256]) if B * Mq < 200000 else 128, "side": side, "Kt": Kt}
+    S = rng.choice([16, 32, 48, 64, 64, 64])
+    M = rng.randint(4, 10)
+    N = _log(rng, 500, 16384)
+    if rng.random() < 0.4:
+        N = max(512, N // 64 * 64)
+    K = min(rng.choice([16, 24, 32, 48, 48, 64, rng.randint(9, 64)]), (M - 1) * S + N - (-(-N // S) - 1) * S)
+    coords = rng.choice(["uniform", "masked", "jitter", "blobs"])
+    if kind == "merge":
+        B = max(1, min(64, _log(rng, 1, 64), 131072 // N))
+        return {"kind": kind, "dtype": rng.choice(["bf16", "bf16", "f32"]), "B": B, "N": N, "C": rng.choice([64, 128, 256]),
+                "K": K, "S": S, "M": M, "coords": coords, "keep": max(1, int(N * rng.uniform(0.2, 0.5)))}
+    if kind == "general":  # what the cluster-tiled kernels do not take: fp32, other head sizes, tables without the promise
+        B = max(1, min(16, _log(rng, 1, 16), 16384 // N))
+        dtype = rng.choice(["f32", "bf16"])
+        d = rng.choice([16, 32, 64])
+        return _attn(None, "train", dtype, B, N, rng.randint(1, 4), d, K, S, M, coords,
+                     promise=not (dtype == "bf16" and d == 32), blank=rng.random() < 0.3)
+    H = rng.randint(1, 8)
+    most = 262144 // N if kind == "table" else 600000 // (N * H)  # no drawn case costs more than the largest listed one
+    B = max(1, min(64, _log(rng, 1, 64), most))
+    if kind == "relpos":
+        K = max(8, K // 8 * 8)
+        return _attn(None, kind, "bf16", B, N, H, 32, K, S, M, coords, R=rng.randint(2, 7))
+    return _attn(None, kind, "bf16", B, N, H, 32, K, S, M, coords, blank=kind != "table" and rng.random() < 0.3)
+
+
+# --------------------------------------------------------------------------------------------------------- the inputs
+
+def _dtype(case):
+    return torch.bfloat16 if case["dtype"] == "bf16" else torch.float32
+
+
+def _generator(seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    return g
+
+
+def _rand(g, *shape):
+    return torch.rand(shape, generator=g, device=DEV)
+
+
+def _randn(g, *shape):
+    return torch.randn(shape, generator=g, device=DEV)
+
+
+def _raw_coords(case, g):
+    """(coords [B,N,2] fp32 in no particular order, side of the square frame)."""
+    B, N, recipe = case["B"], case["N"], case["coords"]
+    if recipe in ("masked", "jitter"):
+        # a quarter of the patches stays visible under the mask; without a mask (nearly) all of them
+        side = math.ceil(math.sqrt(4 * N if recipe == "masked" else N))
+        kept = _rand(g, B, side * side).argsort(dim=1)[:, :N].sort(dim=1).values
+        xy = torch.stack([kept % side, kept // side], dim=-1).float() * PITCH + PITCH / 2
+        if recipe == "jitter":
+            xy = xy + (_rand(g, B, N, 2) * 4.0 - 2.0)
+        return xy.contiguous(), side * PITCH
+    frame = 1024.0
+    if recipe == "uniform":
+        return _rand(g, B, N, 2) * frame, frame
+    centres = _rand(g, B, 64, 2) * frame
+    which = torch.randint(0, 64, (B, N, 1), generator=g, device=DEV).expand(B, N, 2)
+    xy = torch.gather(centres, 1, which) + 20.0 * _randn(g, B, N, 2)
+    return xy.clamp_(0.0, frame - 0.001), frame
+
+
+def _curve_order(coords, frame):
+    """Places of the tokens along the Z-order curve (16 bits per axis), equal keys in index order."""
+    q = (coords.double() / frame * 65536.0).floor().clamp(0, 65535).long()
+    for shift, mask in ((8, 0x00FF00FF), (4, 0x0F0F0F0F), (2, 0x33333333), (1, 0x55555555)):
+        q = (q | (q << shift)) & mask
+    return (q[..., 0] | (q[..., 1] << 1)).sort(dim=1, stable=True).indices
+
+
+def _ordered_coords(case, g):
+    xy, frame = _raw_coords(case, g)
+    order = _curve_order(xy, frame)
+    return torch.gather(xy, 1, order[..., None].expand_as(xy)).contiguous()
+
+
+def _attn_inputs(case, seed):
+    g = _generator(seed)
+    B, N, H, d, K, dt = case["B"], case["N"], case["H"], case["d"], case["K"], _dtype(case)
+    s = {"coords": _ordered_coords(case, g)}
+    for name in ("q", "k", "v", "dout"):
+        s[name] = _randn(g, B, N, H, d).to(dt)
+    if case["kind"] == "relpos":
+        W = 2 * case["R"] + 1
+        s["rel_table"] = (0.1 * _randn(g, H, W, W)).to(dt)
+    else:
+        s["bias"] = (0.1 * _randn(g, B, N, H, K)).to(dt)
+    s["k_blank"] = _randn(g, H, d).to(dt) if case["blank"] else None
+    s["v_blank"] = _randn(g, H, d).to(dt) if case["blank"] else None
+    return s
+
+
+def _decoder_inputs(case, seed):
+    g = _generator(seed)
+    B, side, Nv = case["B"], case["side"], case["Nv"]
+    kept = _rand(g, B, side * side).argsort(dim=1)[:, :Nv].sort(dim=1).values
+    dt = _dtype(case)
+    return {"vis_xy": (torch.stack([kept % side, kept // side], dim=-1).float() * PITCH + PITCH / 2).contiguous(),
+            "query_xy": _rand(g, B, case["Mq"], 2) * (side * PITCH),
+            "feat": _randn(g, B, Nv, case["C"]).to(dt), "dout": _randn(g, B, case["Mq"], case["C"]).to(dt),
+            "grid": (side, side, 0.0, 0.0, PITCH), "p": 0.25, "eps": 1e-6}
+
+
+def _merge_inputs(case, seed):
+    g = _generator(seed)
+    B, N, C, dt = case["B"], case["N"], case["C"], _dtype(case)
+    return {"coords": _ordered_coords(case, g), "feat": _randn(g, B, N, C).to(dt), "score": _randn(g, B, N),
+            "dout": _randn(g, B, case["keep"], C).to(dt), "p": 0.2}
+
+
+def prepare(case, seed):
+    s = {"case": case}
+    if case["kind"] == "decoder":
+        s.update(_decoder_inputs(case, seed))
+        return s
+    if case["kind"] == "merge":
+        s.update(_merge_inputs(case, seed))
+        s["nbr"], _ = aff.affmae_knn(s["coords"], None, case["S"], case["M"], case["K"])
+        return s
+    if case["kind"] == "table":
+        s["coords"], s["frame"] = _raw_coords(case, _generator(seed))
+        return s
+    s.update(_attn_inputs(case, seed))
+    s["scale"] = 1.0 / math.sqrt(case["d"])
+    s["rate"] = 1.0 / PITCH
+    if not case["search"]:
+        nbr, near = aff.affmae_knn(s["coords"], None, case["S"], case["M"], case["K"])
+        s["nbr"] = nbr
+        if case["promise"]:
+            s["near"] = near
+            s["plan"] = aff.affmae_pla_plan(nbr, near, case["S"], case["M"])
+    return s
+
+
+# ----------------------------------------------------------------------------------------------------------- the passes
+
+def run(s):
+    return {"table": _run_table, "fwd": _run_attention, "train": _run_attention, "relpos": _run_relpos,
+            "decoder": _run_decoder, "merge": _run_merge}[s["case"]["kind"]](s)
+
+
+def _run_table(s):
+    c = s["case"]
+    frame = (0.0, 0.0, s["frame"], s["frame"])
+    order, cluster_id = aff.affmae_cluster(s["coords"], c["S"], frame)
+    xy = torch.gather(s["coords"], 1, order.long()[..., None].expand(-1, -1, 2))
+    nbr, near = aff.affmae_knn(xy, None, c["S"], c["M"], c["K"])
+    s["plan"] = aff.affmae_pla_plan(nbr, near, c["S"], c["M"])  # opaque: kept for the stage's blocks
+    return {"order": order, "cluster_id": cluster_id, "coords": xy, "nbr": nbr, "near": near}
+
+
+def _run_attention(s):
+    c = s["case"]
+    r = {}
+    nbr = s.get("nbr")
+    if c["search"]:
+        nbr, _ = aff.affmae_knn(s["coords"], None, c["S"], c["M"], c["K"])
+        r["nbr"] = nbr
+    table = dict(near_clusters=s.get("near"), S=c["S"], M=c["M"], k_blank=s["k_blank"], v_blank=s["v_blank"],
+                 plan=s.get("plan")) if c["promise"] else dict(k_blank=s["k_blank"], v_blank=s["v_blank"])
+    r["out"], r["lse"] = aff.affmae_pla_fwd(s["q"], s["k"], s["v"], s["bias"], nbr, s["scale"], **table)
+    if c["kind"] == "train":
+        r.update(aff.affmae_pla_bwd(s["q"], s["k"], s["v"], s["bias"], nbr, r["out"], r["lse"], s["dout"], s["scale"],
+                                    **table))
+    return r
+
+
+def _run_relpos(s):
+    c = s["case"]
+    table = dict(near_clusters=s["near"], S=c["S"], M=c["M"], k_blank=s["k_blank"], v_blank=s["v_blank"], plan=s["plan"])
+    out, lse = aff.affmae_pla_fwd_relpos(s["q"], s["k"], s["v"], s["coords"], s["rel_table"], s["nbr"], s["scale"],
+                                         s["rate"], **table)
+    r = aff.affmae_pla_bwd_relpos(s["q"], s["k"], s["v"], s["coords"], s["rel_table"], s["nbr"], out, lse, s["dout"],
+                                  s["scale"], s["rate"], **table)
+    r.update(out=out, lse=lse)
+    return r
+
+
+def _run_decoder(s):
+    a = (s["query_xy"], s["vis_xy"], s["feat"])
+    table = aff.affmae_vts_table(s["vis_xy"], s["grid"], s["case"]["Kt"])
+    out = aff.affmae_vts_fwd(*a, table, s["grid"], s["p"], s["eps"])
+    r = aff.affmae_vts_bwd(*a, table, s["dout"], s["grid"], s["p"], s["eps"])
+    r.update(table=table, out=out)
+    return r
+
+
+def _run_merge(s):
+    anchors, xy = aff.affmae_merge_select(s["score"], s["case"]["keep"], s["coords"])
+    a = (s["feat"], s["coords"], s["score"], s["nbr"], anchors)
+    out = aff.affmae_merge_fwd(*a, s["p"])
+    r = aff.affmae_merge_bwd(*a, s["dout"], s["p"])
+    r.update(anchors=anchors, anchor_xy=xy, out=out)
+    return r
+
+
+# ------------------------------------------------------------------------------------------------ what a pass has to do
+
+def work(case):
+    """Every input read once, every output written once; multiply-adds count two."""
+    el = 2 if case["dtype"] == "bf16" else 4
+    if case["kind"] == "decoder":
+        B, Mq, Nv, C, Kt, cells = case["B"], case["Mq"], case["Nv"], case["C"], case["Kt"], case["side"] ** 2
+        fwd = B * (Mq * (8 + C * el) + Nv * (8 + C * el) + cells * Kt * 4)
+        bwd = B * (Mq * (8 + C * el + 8) + Nv * (8 + 2 * C * el) + cells * Kt * 4)
+        return {"bytes": fwd + bwd + B * (Nv * 8 + cells * Kt * 4), "flops": B * Mq * Kt * C * 2 * 3}
+    if case["kind"] == "merge":
+        B, N, C, K, keep = case["B"], case["N"], case["C"], case["K"], case["keep"]
+        select = B * (N * 4 + keep * (4 + 16))
+        fwd = B * (N * (12 + C * el) + keep * (4 + 4 * K + C * el))
+        bwd = B * (N * (12 + 2 * C * el + 4) + keep * (4 + 4 * K + C * el))
+        return {"bytes": select + fwd + bwd, "flops": B * keep * K * C * 2 * 3}
+    B, N, H, d, K, S, M = (case[n] for n in ("B", "N", "H", "d", "K", "S", "M"))
+    search = {"bytes": B * N * (8 + 4 * K), "flops": B * N * M * S * 5}
+    if case["kind"] == "table":
+        return {"bytes": search["bytes"] + B * (N * (8 + 8 + 8) + -(-N // S) * M * 4), "flops": search["flops"]}
+    bias = 8 if case["kind"] == "relpos" else H * K * el
+    fwd = {"bytes": B * N * (4 * H * d * el + bias + 4 * K + 4 * H), "flops": B * N * H * K * d * 4}
+    if case["kind"] == "fwd":
+        return fwd
+    bwd = {"bytes": B * N * (8 * H * d * el + (1 if case["kind"] == "relpos" else 2) * bias + 4 * K + 4 * H),
+           "flops": B * N * H * K * d * 10}
+    extra = search if case["search"] else {"bytes": 0, "flops": 0}
+    return {n: fwd[n] + bwd[n] + extra[n] for n in ("bytes", "flops")}
+
+
+def tolerance(case):
+    if case["kind"] == "table":
+        return "exact"
+    if case["dtype"] == "f32":
+        return {"rel": 1e-5, "max": 2e-4}  # seen: 2.4e-7 against 64 bits; dp is a scalar sum of terms of both signs
+    return {"rel": 1e-2, "max": 0.1}  # seen: 2.9e-3 against 64 bits (operands of the second products are bf16)
+
+
+# ------------------------------------------------------------------------------------------------- 64-bit ground truth
+
+def _search(xy, S, M, K):
+    """The clustered neighbour search of one image [N,2]: fp32 distances one operation at a time, ties to the lower index."""
+    N = xy.shape[0]
+    G = -(-N // S)
+    sums = torch.zeros(G, 2, dtype=torch.float64, device=DEV)
+    count = torch.zeros(G, 1, dtype=torch.float64, device=DEV)
+    for i in range(min(S, N)):
+        member = xy[i::S].double()
+        sums[: member.shape[0]] += member
+        count[: member.shape[0]] += 1
+    centre = (sums / count).float()
+
+    def keys(a, b, ids):  # [n, m] ordered like (distance, id)
+        dx, dy = a[:, None, 0] - b[..., 0], a[:, None, 1] - b[..., 1]
+        dx *= dx
+        dy *= dy
+        return ((dx + dy).view(torch.int32).long() << 32) | ids
+
+    near = (keys(centre, centre[None], torch.arange(G, device=DEV)[None]).topk(M, dim=1, largest=False).values & 0xFFFFFFFF)
+    ids = (near[:, :, None] * S + torch.arange(S, device=DEV)).reshape(G, M * S)
+    nbr = torch.empty(N, K, dtype=torch.int64, device=DEV)
+    for c0 in range(0, G, 64):
+        c = torch.arange(c0, min(G, c0 + 64), device=DEV)
+        tok = (c[:, None] * S + torch.arange(S, device=DEV)).reshape(-1)
+        tok = tok[tok < N]
+        cand = ids[tok // S]
+        key = keys(xy[tok], xy[cand.clamp(max=N - 1)], cand)
+        key[cand >= N] = torch.iinfo(torch.int64).max
+        nbr[tok] = key.topk(K, dim=1, largest=False, sorted=True).values & 0xFFFFFFFF
+    return nbr
+
+
+def _tables(case, coords):
+    return torch.stack([_search(coords[b], case["S"], case["M"], case["K"]) for b in range(case["B"])])
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind == "table":
+        return None
+    if kind == "decoder":
+        return _exact_decoder(case, _decoder_inputs(case, seed))
+    if kind == "merge":
+        return _exact_merge(case, _merge_inputs(case, seed))
+    return _exact_attention(case, _attn_inputs(case, seed))
+
+
+def _exact_attention(case, s):
+    B, N, H, d, K = (case[n] for n in ("B", "N", "H", "d", "K"))
+    scale, relpos, train = 1.0 / math.sqrt(d), case["kind"] == "relpos", case["kind"] != "fwd"
+    nbr = _tables(case, s["coords"])
+    r = {n: torch.zeros(B, N, H, d, dtype=torch.float64, device=DEV) for n in (("out", "dq", "dk", "dv") if train else ("out",))}
+    r["lse"] = torch.zeros(B, N, H, dtype=torch.float64, device=DEV)
+    if train and relpos:
+        r["drel_table"] = torch.zeros(s["rel_table"].shape, dtype=torch.float64, device=DEV)
+    elif train:
+        r["dbias"] = torch.zeros(B, N, H, K, dtype=torch.float64, device=DEV)
+    if train and case["blank"]:
+        r["dk_blank"], r["dv_blank"] = (torch.zeros(H, d, dtype=torch.float64, device=DEV) for _ in range(2))
+    for b in range(B):
+        n = nbr[b]
+        if relpos:
+            W, R = 2 * case["R"] + 1, case["R"]
+            xy = s["coords"][b]
+            cell = ((xy[n] - xy[:, None]) * (1.0 / PITCH)).round().clamp(-R, R).long() + R
+            cell = cell[..., 1] * W + cell[..., 0]
+        for h in range(H):
+            q, k, v, g = (s[x][b, :, h].double() for x in ("q", "k", "v", "dout"))
+            bias = s["rel_table"][h].double().reshape(-1)[cell] if relpos else s["bias"][b, :, h].double()
+            kn, vn = k[n], v[n]
+            logit = (q[:, None] * kn).sum(-1) * scale + bias
+            if case["blank"]:
+                kb, vb = s["k_blank"][h].double(), s["v_blank"][h].double()
+                logit = torch.cat([logit, (q @ kb)[:, None] * scale], dim=1)
+                kn, vn = (torch.cat([x, y.expand(N, 1, d)], dim=1) for x, y in ((kn, kb), (vn, vb)))
+            lse = logit.logsumexp(dim=1)
+            p = (logit - lse[:, None]).exp()
+            r["out"][b, :, h], r["lse"][b, :, h] = (p[..., None] * vn).sum(1), lse
+            if not train:
+                continue
+            dp = (g[:, None] * vn).sum(-1)
+            ds = p * (dp - (p * dp).sum(1, keepdim=True))
+            r["dq"][b, :, h] = scale * (ds[..., None] * kn).sum(1)
+            dk, dv = (torch.zeros(N, d, dtype=torch.float64, device=DEV) for _ in range(2))
+            dk.index_add_(0, n.reshape(-1), (scale * ds[:, :K, None] * q[:, None]).reshape(-1, d))
+            dv.index_add_(0, n.reshape(-1), (p[:, :K, None] * g[:, None]).reshape(-1, d))
+            r["dk"][b, :, h], r["dv"][b, :, h] = dk, dv
+            if relpos:
+                r["drel_table"][h].view(-1).index_add_(0, cell.reshape(-1), ds[:, :K].reshape(-1))
+            else:
+                r["dbias"][b, :, h] = ds[:, :K]
+            if case["blank"]:
+                r["dk_blank"][h] += scale * (ds[:, K, None] * q).sum(0)
+                r["dv_blank"][h] += (p[:, K, None] * g).sum(0)
+    if case["search"]:
+        r["nbr"] = None
+    return r
+
+
+def _exact_decoder(case, s):
+    B, Mq, Nv, C, side, Kt = (case[n] for n in ("B", "Mq", "Nv", "C", "side", "Kt"))
+    r = {"table": None, "out": torch.empty(B, Mq, C, dtype=torch.float64, device=DEV),
+         "dfeat": torch.zeros(B, Nv, C, dtype=torch.float64, device=DEV),
+         "dquery": torch.empty(B, Mq, 2, dtype=torch.float64, device=DEV),
+         "dp": torch.zeros(1, dtype=torch.float64, device=DEV)}
+    axis = (torch.arange(side, device=DEV).float() + 0.5) * PITCH
+    grid = torch.stack([axis[None].expand(side, side), axis[:, None].expand(side, side)], dim=-1).reshape(-1, 2)
+    for b in range(B):
+        vis, query, feat = s["vis_xy"][b], s["query_xy"][b], s["feat"][b].double()
+        dx, dy = grid[:, None, 0] - vis[None, :, 0], grid[:, None, 1] - vis[None, :, 1]
+        key = ((dx * dx + dy * dy).view(torch.int32).long() << 32) | torch.arange(Nv, device=DEV)
+        table = key.topk(Kt, dim=1, largest=False).values & 0xFFFFFFFF
+        cell = (query / PITCH).floor().long().clamp(0, side - 1)
+        n = table[cell[:, 1] * side + cell[:, 0]]
+        diff = query.double()[:, None] - vis.double()[n]
+        dist = diff.square().sum(-1).sqrt()
+        far = dist + s["eps"]
+        w = (-s["p"] * far).softmax(dim=1)
+        fn, g = feat[n], s["dout"][b].double()
+        r["out"][b] = (w[..., None] * fn).sum(1)
+        gi = (g[:, None] * fn).sum(-1)
+        dz = w * (gi - (w * gi).sum(1, keepdim=True))
+        unit = torch.where(dist[..., None] > 0, diff / dist.clamp(min=1e-300)[..., None], torch.zeros_like(diff))
+        r["dquery"][b] = (-s["p"] * dz[..., None] * unit).sum(1)
+        r["dp"] -= (dz * far).sum()
+        r["dfeat"][b].index_add_(0, n.reshape(-1), (w[..., None] * g[:, None]).reshape(-1, C))
+    return r
+
+
+def _exact_merge(case, s):
+    B, N, C, K, keep = (case[n] for n in ("B", "N", "C", "K", "keep"))
+    nbr = _tables(case, s["coords"])
+    top = s["score"].sort(dim=1, descending=True, stable=True).indices[:, :keep].sort(dim=1).values
+    r = {"anchors": None, "anchor_xy": torch.gather(s["coords"], 1, top[..., None].expand(-1, -1, 2)),
+         "out": torch.empty(B, keep, C, dtype=torch.float64, device=DEV),
+         "dfeat": torch.zeros(B, N, C, dtype=torch.float64, device=DEV),
+         "dscore": torch.zeros(B, N, dtype=torch.float64, device=DEV), "dp": torch.zeros((), dtype=torch.float64, device=DEV)}
+    for b in range(B):
+        n, xy, feat, g = nbr[b][top[b]], s["coords"][b].double(), s["feat"][b].double(), s["dout"][b].double()
+        dist = (xy[n] - xy[top[b]][:, None]).square().sum(-1).sqrt()
+        w = (s["score"][b].double()[n] - s["p"] * dist).softmax(dim=1)
+        fn = feat[n]
+        r["out"][b] = (w[..., None] * fn).sum(1)
+        gi = (g[:, None] * fn).sum(-1)
+        dz = w * (gi - (w * gi).sum(1, keepdim=True))
+        r["dfeat"][b].index_add_(0, n.reshape(-1), (w[..., None] * g[:, None]).reshape(-1, C))
+        r["dscore"][b].index_add_(0, n.reshape(-1), dz.reshape(-1))
+        r["dp"] -= (dz * dist).sum()
+    return r
