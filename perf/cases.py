@@ -83,10 +83,10 @@ def draw(rng):
         return {"kind": kind, "dtype": rng.choice(["bf16", "bf16", "f32"]), "B": B, "Mq": Mq, "Nv": Nv,
                 "C": rng.choice([64, 128, 256]) if B * Mq < 200000 else 128, "side": side, "Kt": Kt}
     S = rng.choice([16, 32, 48, 64, 64, 64])
-    M = rng.randint(4, 10)
     N = _log(rng, 500, 16384)
     if rng.random() < 0.4:
         N = max(512, N // 64 * 64)
+    M = min(rng.randint(4, 10), -(-N // S))
     K = min(rng.choice([16, 24, 32, 48, 48, 64, rng.randint(9, 64)]), (M - 1) * S + N - (-(-N // S) - 1) * S)
     coords = rng.choice(["uniform", "masked", "jitter", "blobs"])
     if kind == "merge":
