@@ -5,15 +5,17 @@
 //   centroid : double-precision mean of each cluster's coordinates -> fp32
 //   near     : per cluster the M clusters with nearest centroids
 //   knn      : per token the K nearest among the members of those M clusters
-//              (up to 512 candidates: kept in registers, selected by a counted
-//              distance threshold and one sort; more: staged in LDS and merged)
+//              (staged in LDS, selected by a counted distance threshold and one sort)
 // Selection is exact and unique: 64-bit keys (fp32 distance bits, index) compared
 // as integers; distances are evaluated without fused multiply-add.  This file is
 // compiled with -ffp-contract=off.
+#include "cluster_common.h"
 #include "device_util.h"
 #include "launch.h"
 #include "select_util.h"
 #include "timing.h"
+
+#include <algorithm>
 
 namespace affmae {
 namespace {
@@ -105,133 +107,113 @@ __global__ __launch_bounds__(256) void near_kernel(const float* __restrict__ cen
   if (lane < M) near[(size_t)gc * M + lane] = (int32_t)(uint32_t)best;
 }
 
-// One workgroup per cluster.  The coordinates and token ids of the M*S candidate
-// tokens are staged in LDS once; each wave then serves the cluster's tokens in
-// turn.  The first 64 candidates (the nearest cluster's) are sorted to give a
-// first bound on the K-th key; later candidates are compared against the
-// current bound, 64 at a time, and only those below it are queued (compacted in
-// a per-wave LDS buffer).  Whenever 64 are queued they are merged into the
-// running top-64, which tightens the bound for what follows.  A candidate is
-// dropped only when K smaller keys are already known, so the result is exact.
+// The K nearest among the members of a cluster's M near clusters, for the cluster's tokens; a wave serves every
+// (4 parts)-th of them.  Coordinates and token ids of the candidates are staged in LDS once per workgroup, in rows of
+// 64; up to 1024 candidates a wave then holds all its tokens long, a lane one candidate of every row (ROWS > 0), more
+// are read from LDS as they are needed (ROWS = 0).
+// Per token the wave looks for a distance threshold T with K <= #{candidates with d2 <= T} <= 64 by counting
+// (ballots), starting from the previous token's threshold, and sorts the counted candidates once by (d2, index): see
+// select_nearest.  The near clusters are taken in index order, so that candidates are queued in token order
+// (contiguous clusters) and the sort of the queue nearly always succeeds on its short words (sort_queued).
+// Bound by instruction issue, vector and scalar.  (Leaving out the rows whose bounding box is too far - a token's
+// neighbours lie in 3.3 of its 8 rows - saved a third of the vector instructions and was no faster, in four forms: the
+// tests and branches per row are scalar instructions, of which a SIMD issues no more than of the others.)
+// `parts` workgroups share a cluster's tokens: with one per cluster a batch of few or large clusters leaves most of
+// the chip idle (one cluster of 256 tokens: 85 us with one workgroup, 5 us with 64).
 constexpr int kKnnWaves = 4;
+constexpr int kFullChipWaves = 8192;  // 256 CUs x 4 SIMDs x 8 waves
+size_t knn_lds_bytes(int rows) {
+  return kKnnWaves * kWave * sizeof(key_t) + (size_t)rows * kWave * (sizeof(float2) + sizeof(int32_t));
+}
+template <int ROWS, bool MEMBERS>
 __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __restrict__ coords,
                                                               const int32_t* __restrict__ members,
                                                               const int32_t* __restrict__ near, int N, int S, int M,
-                                                              int K, int G, int32_t* __restrict__ nbr_idx) {
-  extern __shared__ float4 cand[];  // x, y, token id (bits), unused
-  __shared__ key_t pend_all[kKnnWaves][2 * kWave];
-  const int b = blockIdx.x / G, c = blockIdx.x % G;
+                                                              int K, int G, int rows, int parts, uint32_t s_magic,
+                                                              int32_t* __restrict__ nbr_idx) {
+  extern __shared__ key_t lds[];
+  float2* cxy = reinterpret_cast<float2*>(lds + kKnnWaves * kWave);        // [rows][64]
+  int32_t* ctok = reinterpret_cast<int32_t*>(cxy + (size_t)rows * kWave);  // [rows][64]
+  const int gc = blockIdx.x / parts, part = blockIdx.x - gc * parts;
+  const int b = gc / G, c = gc - b * G;
   const int Cn = M * S;
   const float* xy = coords + (size_t)b * N * 2;
-  const int32_t* mem = members ? members + (size_t)b * N : nullptr;
-  for (int p = threadIdx.x; p < Cn; p += blockDim.x) {
-    const int m = p / S, r = p - m * S;
-    int e = near[((size_t)b * G + c) * M + m];
-    e = min(max(e, 0), G - 1);
-    const bool real = r < cluster_size(e, N, S, G);  // a short last cluster fills only part of its places
+  const int32_t* mem = MEMBERS ? members + (size_t)b * N : nullptr;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  key_t* pend = lds + wave * kWave;
+  // lane m: the m-th of the near clusters in index order (M <= 64; they are distinct)
+  int near_sorted;
+  {
+    const int id = lane < M ? min(max(near[(size_t)gc * M + lane], 0), G - 1) : 0x7fffffff;
+    int rank = 0;
+    for (int m = 0; m < M; ++m) rank += __builtin_amdgcn_readlane(id, m) < id ? 1 : 0;
+    near_sorted = __builtin_amdgcn_ds_permute((lane < M ? rank : lane) * 4, id);
+  }
+  for (int p = threadIdx.x; p < rows * kWave; p += kKnnWaves * kWave) {  // (whole waves: all lanes take part)
+    const int pp = p < Cn ? p : 0;
+    const int m = fast_div(pp, s_magic), r = pp - m * S;
+    const int e = __shfl(near_sorted, m);
     int tok = min(e * S + r, N - 1);
-    if (mem) tok = min(max(mem[tok], 0), N - 1);
-    cand[p] = make_float4(xy[2 * (size_t)tok], xy[2 * (size_t)tok + 1], __int_as_float(real ? tok : -1), 0.f);
+    if (MEMBERS) tok = min(max(mem[tok], 0), N - 1);
+    const bool real = p < Cn && r < cluster_size(e, N, S, G);  // a short last cluster fills only part of its places
+    // an empty place: its distance to any point is a NaN, whose bits lie above those of every distance
+    cxy[p] = make_float2(real ? xy[2 * (size_t)tok] : __uint_as_float(0x7fc00000u), xy[2 * (size_t)tok + 1]);
+    ctok[p] = real ? tok : -1;
   }
   __syncthreads();
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  key_t* pend = pend_all[wave];
-  auto cand_key = [&](int p, float qx, float qy) -> key_t {
-    if (p >= Cn) return kKeyMax;
-    const float4 cp = cand[p];
-    if (__float_as_int(cp.z) < 0) return kKeyMax;  // an empty place of a short cluster
-    return make_key(dist2(qx, qy, cp.x, cp.y), __float_as_int(cp.z));
-  };
-  const int my_size = cluster_size(c, N, S, G);
-  for (int r = wave; r < my_size; r += kKnnWaves) {
-    int qtok = c * S + r;
-    if (mem) qtok = min(max(mem[qtok], 0), N - 1);
-    const float qx = xy[2 * (size_t)qtok], qy = xy[2 * (size_t)qtok + 1];
-    key_t best = wave_sort(cand_key(lane, qx, qy), lane);
-    key_t bound = shfl_key(best, K - 1);
-    int fill = 0;  // queued keys, wave-uniform, always < 64 between rows
-    for (int base = kWave; base < Cn; base += kWave) {
-      const key_t key = cand_key(base + lane, qx, qy);
-      const bool in = key < bound;
-      const unsigned long long mask = __ballot(in);
-      if (mask == 0ull) continue;  // wave-uniform
-      const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-      if (in) pend[fill + rank] = key;
-      fill += __popcll(mask);
-      if (fill >= kWave) {
-        wave_lds_sync();
-        const key_t row = pend[lane];
-        const key_t rest = pend[kWave + lane];
-        wave_lds_sync();
-        fill -= kWave;
-        if (lane < fill) pend[lane] = rest;
-        best = topk_push(best, row, lane, K - 1);
-        bound = shfl_key(best, K - 1);
-      }
-    }
-    if (fill > 0) {
-      wave_lds_sync();
-      const key_t row = (lane < fill) ? pend[lane] : kKeyMax;
-      best = topk_push(best, row, lane, K - 1);
-    }
-    wave_lds_sync();  // the next token's queue starts after this one's reads
-    if (lane < K) nbr_idx[((size_t)b * N + qtok) * K + lane] = (int32_t)(uint32_t)best;
-  }
-}
-
-// At most 512 candidates: each lane keeps its 8 candidates in registers for all of the
-// cluster's tokens.  Per token the wave looks for a distance threshold T with
-// K <= #{candidates with d2 <= T} <= 64 by counting (ballots), starting from the previous
-// token's threshold and scaling it by the ratio of the wanted to the found count (the count grows
-// like the area, i.e. like d2), then by bisection on the bit pattern.  Everything at or below T is
-// closer than everything above it, so the K nearest are among the counted candidates: they are
-// compacted into one row and sorted once by (d2, index).  When no such T exists (more than
-// 64 - K + 1 candidates at one distance) the token takes the queue-and-merge route of the
-// general kernel.  Either way the result is the exact, unique answer.
-constexpr int kFastRows = 8;
-__global__ __launch_bounds__(kKnnWaves* kWave) void knn_fast_kernel(const float* __restrict__ coords,
-                                                                   const int32_t* __restrict__ members,
-                                                                   const int32_t* __restrict__ near, int N, int S,
-                                                                   int M, int K, int G,
-                                                                   int32_t* __restrict__ nbr_idx) {
-  __shared__ key_t pend_all[kKnnWaves][2 * kWave];
-  const int b = blockIdx.x / G, c = blockIdx.x % G;
-  const int Cn = M * S;
-  const float* xy = coords + (size_t)b * N * 2;
-  const int32_t* mem = members ? members + (size_t)b * N : nullptr;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  key_t* pend = pend_all[wave];
-  float cx[kFastRows], cy[kFastRows];
-  uint32_t cid[kFastRows];
-  bool cok[kFastRows];
+  float cx[ROWS ? ROWS : 1], cy[ROWS ? ROWS : 1];
 #pragma unroll
-  for (int row = 0; row < kFastRows; ++row) {
-    const int p = row * kWave + lane;
-    const int pp = p < Cn ? p : 0;
-    const int m = pp / S, r = pp - m * S;
-    int e = near[((size_t)b * G + c) * M + m];
-    e = min(max(e, 0), G - 1);
-    cok[row] = p < Cn && r < cluster_size(e, N, S, G);  // a short last cluster fills only part of its places
-    int tok = min(e * S + r, N - 1);
-    if (mem) tok = min(max(mem[tok], 0), N - 1);
-    cx[row] = xy[2 * (size_t)tok];
-    cy[row] = xy[2 * (size_t)tok + 1];
-    cid[row] = cok[row] ? (uint32_t)tok : 0xffffffffu;
+  for (int row = 0; row < ROWS; ++row) {
+    const float2 v = cxy[min(row, rows - 1) * kWave + lane];  // (ROWS is rounded up: the surplus rows are empty)
+    cx[row] = row < rows ? v.x : __uint_as_float(0x7fc00000u);
+    cy[row] = v.y;
   }
+  const int my_size = cluster_size(c, N, S, G);
+  const int step = parts * kKnnWaves, first = part * kKnnWaves + wave;
+  const int served = first < my_size ? (my_size - 1 - first) / step + 1 : 0;  // tokens of this wave
   uint32_t guess = 0u;  // threshold that worked for the previous token (0: none yet)
-  const int my_size = cluster_size(c, N, S, G);
-  for (int r = wave; r < my_size; r += kKnnWaves) {
-    int qtok = c * S + r;
-    if (mem) qtok = min(max(mem[qtok], 0), N - 1);
-    const float qx = xy[2 * (size_t)qtok], qy = xy[2 * (size_t)qtok + 1];
-    uint32_t d2[kFastRows];  // bit pattern of the squared distance: ordered like the value (d2 >= +0)
+  for (int base = 0; base < served; base += kWave) {
+    // lane i: token and coordinates of the i-th of the next 64
+    int my_tok = c * S + first + min(base + lane, served - 1) * step;
+    if (MEMBERS) my_tok = min(max(mem[my_tok], 0), N - 1);
+    float my_x = xy[2 * (size_t)my_tok], my_y = xy[2 * (size_t)my_tok + 1];
+    // a use of them here, so that the wait for the loads sits here: inside the loop it would also wait for the previous
+    // token's store to reach memory
+    asm volatile("" : "+v"(my_tok), "+v"(my_x), "+v"(my_y));
+    for (int at = 0; at < min(kWave, served - base); ++at) {
+      const int qtok = __builtin_amdgcn_readlane(my_tok, at);
+      const float qx = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_x), at));
+      const float qy = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_y), at));
+      auto row_d2 = [&](int row) -> uint32_t {
+        const float2 v = cxy[row * kWave + lane];
+        return __float_as_uint(dist2(qx, qy, v.x, v.y));
+      };
+      auto row_low = [&](int row) -> uint32_t {  // contiguous clusters: the place stands for the token, ordered alike
+        return MEMBERS ? (uint32_t)ctok[row * kWave + lane] : (uint32_t)(row * kWave + lane);
+      };
+      uint32_t d2[ROWS ? ROWS : 1];
 #pragma unroll
-    for (int row = 0; row < kFastRows; ++row)
-      d2[row] = cok[row] ? __float_as_uint(dist2(qx, qy, cx[row], cy[row])) : 0xffffffffu;
-    const key_t best = select_nearest<kFastRows>(d2, cid, K, guess, pend, lane);
-    if (lane < K) nbr_idx[((size_t)b * N + qtok) * K + lane] = (int32_t)(uint32_t)best;
+      for (int row = 0; row < ROWS; ++row) d2[row] = __float_as_uint(dist2(qx, qy, cx[row], cy[row]));
+      if (guess == 0u)  // no estimate: one of the distances, so that the count is not 0
+        guess = min((uint32_t)__builtin_amdgcn_readlane(row_d2(0), kWave / 2), 0x7f800000u);
+      const uint32_t best = select_nearest<!MEMBERS>(
+          rows, K, guess, pend, lane,
+          [&](auto f) {
+#pragma unroll
+            for (int row = 0; row < ROWS; ++row) f(d2[row], row_low(MEMBERS ? min(row, rows - 1) : row));
+            if (ROWS == 0)
+              for (int row = 0; row < rows; ++row) f(row_d2(row), row_low(row));
+          },
+          [&](int row, int l) -> key_t {
+            const float2 v = cxy[row * kWave + l];
+            const int tok = ctok[row * kWave + l];
+            return tok >= 0 ? make_key(dist2(qx, qy, v.x, v.y), MEMBERS ? tok : row * kWave + l) : kKeyMax;
+          });
+      int tok = (int)best;
+      if (!MEMBERS) tok = ctok[lane < K ? tok : 0];
+      if (lane < K) nbr_idx[((size_t)b * N + qtok) * K + lane] = tok;
+    }
   }
 }
 
@@ -248,14 +230,27 @@ hipError_t launch_knn(const KnnArgs& a, hipStream_t stream) {
                      a.S, a.G, a.centroid);
   AFFMAE_LAUNCH("near_kernel", stream, near_kernel, dim3((BG + 3) / 4), dim3(256), 0, stream, a.centroid, a.B, a.G, a.M,
                      a.near_clusters);
-  if (a.M * a.S <= kFastRows * kWave) {
-    AFFMAE_LAUNCH("knn_kernel", stream, knn_fast_kernel, dim3(BG), dim3(kKnnWaves * kWave), 0, stream, a.coords, members,
-                  a.near_clusters, a.N, a.S, a.M, a.K, a.G, a.nbr_idx);
-  } else {
-    const size_t lds = (size_t)a.M * a.S * sizeof(float4);
-    AFFMAE_LAUNCH("knn_kernel", stream, knn_kernel, dim3(BG), dim3(kKnnWaves * kWave), lds, stream, a.coords, members,
-                  a.near_clusters, a.N, a.S, a.M, a.K, a.G, a.nbr_idx);
-  }
+  const int rows = (a.M * a.S + kWave - 1) / kWave;  // at most 64
+  // enough workgroups for eight waves on every SIMD, while a wave still has a token to serve
+  const int parts = std::max(1, std::min((kFullChipWaves / kKnnWaves + BG - 1) / BG, (std::min(a.S, a.N) + kKnnWaves - 1) / kKnnWaves));
+  const dim3 grid((unsigned)BG * parts), block(kKnnWaves * kWave);
+#define AFFMAE_KNN(R)                                                                                               \
+  do {                                                                                                              \
+    if (members)                                                                                                    \
+      AFFMAE_LAUNCH("knn_kernel", stream, (knn_kernel<R, true>), grid, block, knn_lds_bytes(rows), stream, a.coords, members, \
+                    a.near_clusters, a.N, a.S, a.M, a.K, a.G, rows, parts, div_magic(a.S), a.nbr_idx);              \
+    else                                                                                                            \
+      AFFMAE_LAUNCH("knn_kernel", stream, (knn_kernel<R, false>), grid, block, knn_lds_bytes(rows), stream, a.coords, members, \
+                    a.near_clusters, a.N, a.S, a.M, a.K, a.G, rows, parts, div_magic(a.S), a.nbr_idx);              \
+  } while (0)
+  if (rows <= 2) AFFMAE_KNN(2);
+  else if (rows <= 4) AFFMAE_KNN(4);
+  else if (rows <= 6) AFFMAE_KNN(6);
+  else if (rows <= 8) AFFMAE_KNN(8);
+  else if (rows <= 12) AFFMAE_KNN(12);
+  else if (rows <= 16) AFFMAE_KNN(16);
+  else AFFMAE_KNN(0);
+#undef AFFMAE_KNN
   return hipGetLastError();
 }
 

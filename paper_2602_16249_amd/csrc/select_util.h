@@ -109,99 +109,171 @@ __device__ __forceinline__ key_t topk_push(key_t best, key_t row, int lane, int 
   return wave_bitonic_merge(best, lane);
 }
 
-// The K nearest of up to 64 * ROWS candidates held one per lane and row: d2[row] = bit pattern of the lane's
-// squared distance (ordered like the value, since d2 >= +0; all ones where the lane has no candidate), id[row] =
-// its index (all ones likewise).  Returns the keys ascending across the lanes (the first K are the answer).
+// The value of the next lane (lane 63: its own): a whole-wave shift on the vector ALU.
+__device__ __forceinline__ uint32_t next_lane_u32(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x130, 0xf, 0xf, false);  // wave_shl:1
+}
+
+// Sort of 64 distinct 32-bit keys, one per lane, ascending: a bitonic network whose compare-exchange is one lane move
+// and one three-operand median.  With a third operand of 0 the median is the minimum, with all ones the maximum, so
+// the lane's role in a step of distance J (keep the smaller or the larger key) is that operand: bit J of the lane
+// number, spread over a word.  Blocks that the network sorts descending hold complemented keys meanwhile, so the
+// roles are the same in every stage and six words serve all 21 steps.
+__device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c) {
+  const uint32_t lo = a < b ? a : b, hi = a < b ? b : a;
+  const uint32_t m = hi < c ? hi : c;
+  return lo > m ? lo : m;
+}
+template <int BIT>
+__device__ __forceinline__ uint32_t lane_bit_word(int lane) {
+  return (uint32_t)((lane << (31 - BIT)) >> 31);
+}
+template <int J>
+__device__ __forceinline__ uint32_t sort_steps_u32(uint32_t key, int lane) {
+  typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+  constexpr int BIT = J == 1 ? 0 : J == 2 ? 1 : J == 4 ? 2 : J == 8 ? 3 : J == 16 ? 4 : 5;
+  const uint32_t role = lane_bit_word<BIT>(lane);
+  if constexpr (J == 16) {
+    const u32x2 t = __builtin_amdgcn_permlane16_swap(key, key, false, false);  // in every lane: its own key and its partner's
+    key = umed3(t[0], t[1], role);
+  } else if constexpr (J == 32) {
+    const u32x2 t = __builtin_amdgcn_permlane32_swap(key, key, false, false);
+    key = umed3(t[0], t[1], role);
+  } else {
+    key = umed3(key, lane_xor_u32<J>(key, lane), role);
+  }
+  if constexpr (J > 1) key = sort_steps_u32<J / 2>(key, lane);
+  return key;
+}
+__device__ __forceinline__ uint32_t wave_sort_u32(uint32_t key, int lane) {
+  const uint32_t f1 = lane_bit_word<1>(lane), f2 = lane_bit_word<2>(lane), f3 = lane_bit_word<3>(lane);
+  const uint32_t f4 = lane_bit_word<4>(lane), f5 = lane_bit_word<5>(lane);
+  key = sort_steps_u32<1>(key ^ f1, lane);
+  key = sort_steps_u32<2>(key ^ (f1 ^ f2), lane);
+  key = sort_steps_u32<4>(key ^ (f2 ^ f3), lane);
+  key = sort_steps_u32<8>(key ^ (f3 ^ f4), lane);
+  key = sort_steps_u32<16>(key ^ (f4 ^ f5), lane);
+  return sort_steps_u32<32>(key ^ f5, lane);
+}
+
+// Sorts the `fill` (<= 64) keys of `pend` (LDS, owned by the wave), whose distances are at most t, ascending across
+// the lanes; returns the lower half (index) of the lane's key, undefined from lane `fill` on.  The 64-bit network
+// costs ~170 vector instructions, once most of the search's time, so the order is found on 32-bit words (26 leading
+// bits of distance / t, place in `pend`), ~65 instructions.  Where neighbouring words share their leading bits (equal
+// or nearly equal distances) the keys themselves are fetched in that order and every neighbouring pair is compared in
+// full: the callers queue candidates in index order, so equal distances pass; what does not (rare) goes through the
+// 64-bit network.  The result is exact either way.
+__device__ __forceinline__ uint32_t sort_queued(const key_t* pend, int fill, uint32_t t, int lane) {
+  // (a scale that overflows, from a subnormal t, only makes the words useless as an order: the check below decides;
+  // whatever the conversion makes of it, every word keeps its lane number, so the places stay a permutation)
+  const float scale = 67108000.f * __builtin_amdgcn_rcpf(__uint_as_float(t));
+  const uint32_t lead = (uint32_t)(__uint_as_float((uint32_t)(pend[lane] >> 32)) * scale);
+  const uint32_t word = lane < fill ? (lead << 6) | (uint32_t)lane : 0xffffffc0u | (uint32_t)lane;
+  const uint32_t sorted = wave_sort_u32(word, lane);
+  const uint32_t from = sorted & 63u;
+  const bool tie = (sorted ^ next_lane_u32(sorted)) < 64u;  // (lane 63 next to itself, and the pads next to each other)
+  const unsigned long long below = fill < kWave ? (1ull << fill) - 1ull : ~0ull >> 1;
+  if ((__ballot(tie) & below) != 0ull) {  // wave-uniform
+    const key_t key = lane < fill ? pend[from] : kKeyMax;
+    const uint32_t lo = (uint32_t)key, hi = (uint32_t)(key >> 32);
+    const key_t next = ((key_t)next_lane_u32(hi) << 32) | next_lane_u32(lo);
+    if (__ballot(key > next) != 0ull) {
+      // (the lane number made opaque: nothing of the rare path is worth a register throughout the caller's loop)
+      asm volatile("" : "+v"(lane));
+      return (uint32_t)wave_sort(lane < fill ? pend[lane] : kKeyMax, lane);
+    }
+  }
+  return (uint32_t)pend[from];
+}
+
+// Appends the candidates of one row at most t away to `pend` (64 keys; ROOM: they are known to fit, else those past
+// its end are dropped); returns the number queued so far.  All lanes active.
+template <bool ROOM = true>
+__device__ __forceinline__ int queue_row(key_t* pend, int fill, uint32_t d2, uint32_t id, uint32_t t) {
+  const bool in = d2 <= t;
+  const unsigned long long mask = __ballot(in);
+  const int place =
+      __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, (uint32_t)fill));
+  if (in && (ROOM || place < kWave)) pend[place] = ((key_t)d2 << 32) | id;
+  fill += __popcll(mask);
+  return ROOM ? fill : min(fill, kWave);
+}
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t x, int lane) {
+  x = min(x, lane_xor_u32<1>(x, lane));
+  x = min(x, lane_xor_u32<2>(x, lane));
+  x = min(x, lane_xor_u32<4>(x, lane));
+  x = min(x, lane_xor_u32<8>(x, lane));
+  x = min(x, lane_xor_u32<16>(x, lane));
+  x = min(x, lane_xor_u32<32>(x, lane));
+  return __builtin_amdgcn_readfirstlane(x);
+}
+
+// The K nearest of the candidates that the caller holds in `rows` rows, one per lane and row: each(f) calls f(d2, low)
+// for every row, d2 being the bit pattern of the lane's squared distance (ordered like the value, since d2 >= +0; above
+// every distance's bits where the lane has no candidate) and low the lower half of its key, ordered like the index.
+// key_at(row, lane) is any candidate's key (kKeyMax where the lane has none).  `pend`: 64 keys of LDS owned by the
+// wave.  ORDERED: low ascends with row and lane.  Returns the lower halves of the keys in ascending order of the keys
+// across the lanes (the first K are the answer).
 //
 // The wave looks for a distance threshold T with K <= #{d2 <= T} <= 64 by counting with ballots: it starts from
-// `guess` (the threshold that worked for the previous, nearby query; 0 = none), scales it by wanted / found (the
-// count grows like the area, i.e. like d2), then bisects on the bit pattern.  Everything at or below T is nearer
-// than everything above it, so the K nearest are among the counted candidates: they are compacted into one row
-// (through `pend`, 128 keys of LDS owned by the wave) and sorted once.  When no such T exists (more than
-// 64 - K + 1 candidates at one distance) the first row is sorted and later candidates that beat the current K-th
-// key are queued and merged 64 at a time.  Either way the result is exact.
-template <int ROWS>
-__device__ __forceinline__ key_t select_nearest(const uint32_t (&d2)[ROWS], const uint32_t (&id)[ROWS], int K,
-                                                uint32_t& guess, key_t* pend, int lane) {
-  const uint32_t kInfBits = 0x7f800000u;
-  auto count_le = [&](uint32_t t) -> int {
-    int n = 0;
-#pragma unroll
-    for (int row = 0; row < ROWS; ++row) n += __popcll(__ballot(d2[row] <= t));
-    return n;
-  };
+// `guess` (the threshold that worked for the previous, nearby query, or an estimate; not 0), scales it by wanted /
+// found (the count grows like the area, i.e. like d2), then alternates bisection on the bit pattern with steps to the
+// next larger distance.  Everything at or below T is nearer than everything above it, so the K nearest are among the
+// counted candidates, which are sorted once.  No such T exists when more than 64 - K + 1 candidates share a distance:
+// then the nearer ones and, in index order, as many of the equal ones as fit are sorted (candidates that are not
+// ORDERED are merged row by row into a running top 64).  Either way the result is exact.
+template <bool ORDERED, class Each, class KeyAt>
+__device__ __forceinline__ uint32_t select_nearest(int rows, int K, uint32_t& guess, key_t* pend, int lane, Each each,
+                                                   KeyAt key_at) {
   // invariant: count(lo) < K (lo = -1: nothing known), count(hi) > 64 or hi = +inf bits
-  long long lo = -1, hi = (long long)kInfBits;
-  uint32_t t = guess;
-  if (t == 0u) {  // first token of the wave: the farthest of the first 64 candidates, so the count is not 0
-    t = min(d2[0], kInfBits);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) t = max(t, (uint32_t)__shfl_xor((int)t, o));
-    t = __builtin_amdgcn_readfirstlane(t);
-  }
-  bool found = false;
-  for (int it = 0; it < 48; ++it) {
-    const int n = count_le(t);
-    if (n >= K && n <= kWave) { found = true; break; }
-    if (n < K) lo = t; else hi = t;
+  int lo = -1, hi = 0x7f800000;
+  uint32_t t = __builtin_amdgcn_readfirstlane(guess);  // (a scalar, and known to be one)
+#pragma unroll 1
+  for (int it = 0; it < 96; ++it) {  // (the bisections alone end it after 31 of them)
+    int n = 0;
+    each([&](uint32_t d2, uint32_t) { n += __popcll(__ballot(d2 <= t)); });
+    if (n >= K && n <= kWave) {
+      guess = t;
+      int fill = 0;
+      each([&](uint32_t d2, uint32_t low) { fill = queue_row(pend, fill, d2, low, t); });
+      wave_lds_sync();
+      const uint32_t id = sort_queued(pend, fill, t, lane);
+      wave_lds_sync();
+      return id;
+    }
+    if (n < K) lo = (int)t; else hi = (int)t;
     if (hi - lo <= 1) break;  // neighbouring bit patterns straddle the window
-    long long next = -1;
-    if (it < 4 && n > 0) {
-      const float scaled = __uint_as_float(t) * ((float)(K + kWave) * 0.5f / (float)n);
-      next = (long long)__float_as_uint(scaled);
+    int next = -1;
+    if (it < 4) {
+      if (n > 0)
+        next = (int)__builtin_amdgcn_readfirstlane(
+            __float_as_uint(__uint_as_float(t) * ((float)(K + kWave) * 0.5f * __builtin_amdgcn_rcpf((float)n))));
+    } else if (it & 1) {
+      uint32_t above = 0xffffffffu;
+      each([&](uint32_t d2, uint32_t) { above = min(above, (lo < 0 || d2 > (uint32_t)lo) ? d2 : 0xffffffffu); });
+      next = (int)wave_min_u32(above, lane);
+      if (next == hi) {  // nothing between: the distance hi has the surplus
+        lo = hi - 1;
+        break;
+      }
     }
     if (next <= lo || next >= hi) next = lo + (hi - lo) / 2;
     t = (uint32_t)next;
   }
-  key_t best;
-  if (found) {
-    guess = t;
+  asm volatile("" : "+v"(lane));  // rare path: see sort_queued
+  if (ORDERED) {
     int fill = 0;
-#pragma unroll
-    for (int row = 0; row < ROWS; ++row) {
-      const bool in = d2[row] <= t;
-      const unsigned long long mask = __ballot(in);
-      const int rank =
-          __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-      if (in) pend[fill + rank] = ((key_t)d2[row] << 32) | id[row];
-      fill += __popcll(mask);
-    }
+    each([&](uint32_t d2, uint32_t low) { fill = queue_row(pend, fill, lo >= 0 && d2 <= (uint32_t)lo ? d2 : 0xffffffffu, low, (uint32_t)hi); });
+    each([&](uint32_t d2, uint32_t low) { fill = queue_row<false>(pend, fill, d2 == (uint32_t)hi ? d2 : 0xffffffffu, low, (uint32_t)hi); });
     wave_lds_sync();
-    best = wave_sort((lane < fill) ? pend[lane] : kKeyMax, lane);
+    const uint32_t id = sort_queued(pend, fill, (uint32_t)hi, lane);
     wave_lds_sync();
-  } else {
-    best = wave_sort(((key_t)d2[0] << 32) | id[0], lane);
-    key_t bound = shfl_key(best, K - 1);
-    int fill = 0;
-#pragma unroll
-    for (int row = 1; row < ROWS; ++row) {
-      const key_t key = ((key_t)d2[row] << 32) | id[row];
-      const bool in = key < bound;
-      const unsigned long long mask = __ballot(in);
-      if (mask != 0ull) {
-        const int rank =
-            __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-        if (in) pend[fill + rank] = key;
-        fill += __popcll(mask);
-        if (fill >= kWave) {
-          wave_lds_sync();
-          const key_t full = pend[lane];
-          const key_t rest = pend[kWave + lane];
-          wave_lds_sync();
-          fill -= kWave;
-          if (lane < fill) pend[lane] = rest;
-          best = topk_push(best, full, lane, K - 1);
-          bound = shfl_key(best, K - 1);
-        }
-      }
-    }
-    if (fill > 0) {
-      wave_lds_sync();
-      best = topk_push(best, (lane < fill) ? pend[lane] : kKeyMax, lane, K - 1);
-    }
-    wave_lds_sync();
+    return id;
   }
-  return best;
+  key_t best = kKeyMax;
+#pragma unroll 1
+  for (int row = 0; row < rows; ++row) best = topk_push(best, key_at(row, lane), lane, K - 1);
+  return (uint32_t)best;
 }
 
 }  // namespace affmae

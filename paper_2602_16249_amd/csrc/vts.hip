@@ -101,7 +101,7 @@ constexpr int kTableRows = 16;
 constexpr int kTableRun = 16;  // grid points per wave
 __global__ __launch_bounds__(256) void vts_table_fast_kernel(const float* __restrict__ vis_xy, int B, int Nv, Grid gr,
                                                             int Kt, int32_t* __restrict__ table) {
-  __shared__ key_t pend_all[4][2 * kWave];
+  __shared__ key_t pend_all[4][kWave];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int per_image = gr.Hg * gr.Wg;
@@ -133,8 +133,19 @@ __global__ __launch_bounds__(256) void vts_table_fast_kernel(const float* __rest
 #pragma unroll
     for (int row = 0; row < kTableRows; ++row)
       d2[row] = cid[row] != 0xffffffffu ? __float_as_uint(dist2(gx, gy, cx[row], cy[row])) : 0xffffffffu;
-    const key_t best = select_nearest<kTableRows>(d2, cid, Kt, guess, pend, lane);
-    if (lane < Kt) table[((size_t)b * per_image + c) * Kt + lane] = (int32_t)(uint32_t)best;
+    // the first grid point starts from one of the distances, so that the count is not 0
+    if (guess == 0u) guess = min((uint32_t)__builtin_amdgcn_readfirstlane(d2[0]), 0x7f800000u);
+    const uint32_t best = select_nearest<true>(
+        kTableRows, Kt, guess, pend, lane,
+        [&](auto f) {
+#pragma unroll
+          for (int row = 0; row < kTableRows; ++row) f(d2[row], cid[row]);
+        },
+        [&](int row, int l) -> key_t {
+          const int i = row * kWave + l;
+          return i < Nv ? make_key(dist2(gx, gy, xy[2 * (size_t)i], xy[2 * (size_t)i + 1]), i) : kKeyMax;
+        });
+    if (lane < Kt) table[((size_t)b * per_image + c) * Kt + lane] = (int32_t)best;
   }
 }
 

@@ -127,3 +127,30 @@ def test_knn_short_last_cluster(name, B, N, S, M, K):
     rnbr_s, rnear_s = oracle.knn(coords, cid, S, M, K)
     assert np.array_equal(near_s, rnear_s)
     assert np.array_equal(nbr_s, rnbr_s)
+
+
+@pytest.mark.parametrize("explicit", [False, True])
+@pytest.mark.parametrize("S,M,K", [(20, 3, 40), (40, 4, 33), (40, 9, 48), (64, 8, 48), (64, 11, 48), (64, 16, 64),
+                                   (100, 11, 17), (128, 12, 64)])
+def test_knn_rows_and_ties(S, M, K, explicit):
+    """Every row class of the search (candidates in 1, 2, .. 16 rows of registers, or streamed) on points of which a
+    third coincide in a few places (up to 90 at one distance, more than a threshold can separate), a third sits on a
+    coarse grid (ties everywhere) and a third is free; then the same points shrunk until squared distances are
+    subnormal.  Contiguous clusters and the same clusters as an explicit, scattered assignment."""
+    rng = np.random.default_rng(S * M + K)
+    B, N = 2, 1500
+    pts = rng.uniform(0, 200, size=(B, N, 2))
+    pts[:, 0::3] = rng.uniform(0, 200, size=(B, 6, 2))[:, rng.integers(0, 6, size=(N + 2) // 3)]
+    pts[:, 1::3] = np.round(pts[:, 1::3] / 8) * 8
+    order = np.lexsort((pts[0, :, 1] // 40, pts[0, :, 0] // 40))
+    for shrink in (1.0, 1e-22):
+        coords = np.ascontiguousarray((pts[:, order] * shrink).astype(np.float32))
+        cid = None
+        if explicit:
+            perm = np.stack([rng.permutation(N) for _ in range(B)])
+            coords = np.ascontiguousarray(np.take_along_axis(coords, perm[..., None], axis=1))
+            cid = np.ascontiguousarray((perm // S).astype(np.int32))
+        nbr, near = _gpu_knn(coords, cid, S, M, K)
+        rnbr, rnear = oracle.knn(coords, cid, S, M, K)
+        assert np.array_equal(near, rnear)
+        assert np.array_equal(nbr, rnbr)
