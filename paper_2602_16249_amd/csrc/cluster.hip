@@ -5,14 +5,19 @@
 //
 // Per image the tokens are sorted by the 64-bit word (curve key << 32 | token
 // index): unique words, so the order is exact and ties go to the lower index.
-// The sort is a bitonic network over the image's words padded to a power of two
-// (pads are all ones and end up last): chunks of up to 2048 words are sorted and
-// merged in LDS by one workgroup (many workgroups per image); the compare-exchange
-// steps whose partner lies in another chunk run over global memory, up to three
-// per pass.  A last kernel writes the order and
-// each token's cluster (place along the curve / S).
+// Chunks of up to 2048 words are sorted by one workgroup each (a bitonic network
+// whose words stay in registers; many workgroups per image).  Up to 16 chunks an
+// image's order then follows in one more launch: a word's place is its place in
+// its chunk plus the number of smaller words in every other chunk (binary
+// searches).  Larger images are merged by the network's remaining steps over the
+// words padded to a power of two (pads are all ones and end up last): steps whose
+// partner lies in another chunk run over global memory, up to three per pass, the
+// others in LDS, and a last kernel writes the order and each token's cluster
+// (place along the curve / S).
+#include "cluster_common.h"
 #include "device_util.h"
 #include "launch.h"
+#include "select_util.h"
 #include "timing.h"
 
 namespace affmae {
@@ -25,6 +30,7 @@ constexpr int kSortThreads = 256;
 struct ClusterParams {
   const float* coords;  // [B,N,2]
   int N, npad, S;
+  uint32_t s_magic;  // reciprocal of S
   double x0, y0, w, h;  // frame
   word_t* words;  // [B][npad]
   int32_t* order;
@@ -101,17 +107,152 @@ __device__ __forceinline__ void lds_steps(word_t* buf, int n, int first, int k, 
   else if (j == 1) lds_pass<1>(buf, n, first, k, 1);
 }
 
-// Builds the words of one chunk and sorts it: all steps with k <= chunk size.
-__global__ __launch_bounds__(kSortThreads) void cluster_sort_chunk_kernel(ClusterParams p, int chunk) {
-  extern __shared__ word_t buf[];
-  const int chunks_per_image = p.npad / chunk;
-  const int b = blockIdx.x / chunks_per_image, c = blockIdx.x % chunks_per_image;
-  const int first = c * chunk;
-  for (int t = threadIdx.x; t < chunk; t += blockDim.x) buf[lds_place(t)] = token_word(p, b, first + t);
+// Place along the curve of a token of the image: its entry of `order`, and its cluster.
+__device__ __forceinline__ void emit(const ClusterParams& p, int b, word_t word, int place) {
+  const int tok = (int)(uint32_t)word;
+  p.order[(size_t)b * p.N + place] = tok;
+  if (p.cluster_id) p.cluster_id[(size_t)b * p.N + tok] = exact_div(place, p.S, p.s_magic);
+}
+
+// One step of the bitonic network, words W t .. W t + W - 1 of the chunk in the registers of thread t: partners W J
+// words apart are J threads apart.  Within a thread the partners are registers, within a wave the words move on the
+// vector ALU (lane_xor_key), across waves through LDS.  `k`: size of the sorted blocks that the stage makes.
+template <int W>
+__device__ __forceinline__ void keep(word_t& mine, word_t other, bool keep_min) {
+  mine = ((mine < other) == keep_min) ? mine : other;
+}
+template <int W, int J>
+__device__ __forceinline__ void lane_step(word_t (&v)[W], int t, int k) {
+  const bool keep_min = ((t * W & k) == 0) == ((t & J) == 0);  // (k > W here: all words of a thread alike)
+#pragma unroll
+  for (int m = 0; m < W; ++m) keep<W>(v[m], lane_xor_key<J>(v[m], t & (kWave - 1)), keep_min);
+}
+// (all threads of the workgroup call it, in groups of `threads` with a t and a `buf` of their own)
+template <int W>
+__device__ __forceinline__ void sort_in_registers(word_t (&v)[W], word_t* buf, int threads, int t) {
+  const int n = threads * W;
+#pragma unroll 1
+  for (int k = 2; k <= n; k <<= 1) {
+#pragma unroll 1
+    for (int j = k >> 1; j >= W * kWave; j >>= 1) {  // across waves
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < W; ++m) buf[m * threads + t] = v[m];
+      __syncthreads();
+      const bool keep_min = ((t * W & k) == 0) == ((t * W & j) == 0);
+#pragma unroll
+      for (int m = 0; m < W; ++m) keep<W>(v[m], buf[m * threads + (t ^ (j / W))], keep_min);
+    }
+    const int top = k >> 1;  // first step of the stage
+    if (top >= W * 32) lane_step<W, 32>(v, t, k);
+    if (top >= W * 16) lane_step<W, 16>(v, t, k);
+    if (top >= W * 8) lane_step<W, 8>(v, t, k);
+    if (top >= W * 4) lane_step<W, 4>(v, t, k);
+    if (top >= W * 2) lane_step<W, 2>(v, t, k);
+    if (top >= W) lane_step<W, 1>(v, t, k);
+#pragma unroll
+    for (int j = W / 2; j >= 1; j >>= 1) {
+      if (top >= j) {
+#pragma unroll
+        for (int m = 0; m < W; ++m) {
+          if (m & j) continue;
+          const bool ascending = ((t * W + m) & k) == 0;
+          const word_t a = v[m], c = v[m | j];
+          const bool swap = (a > c) == ascending;
+          v[m] = swap ? c : a;
+          v[m | j] = swap ? a : c;
+        }
+      }
+    }
+  }
+}
+
+// Number of words of the sorted run[0 .. n - 1] (n a power of two) that are smaller than `word` (or equal, if asked for).
+__device__ __forceinline__ int count_below(const word_t* run, int n, word_t word, bool or_equal) {
+  auto below = [&](word_t x) { return x < word || (or_equal && x == word); };
+  int s = 0;
+  for (int step = n >> 1; step >= 1; step >>= 1) s += below(run[s + step - 1]) ? step : 0;
+  return s + (below(run[s]) ? 1 : 0);  // (s <= n - 1 here)
+}
+
+// Builds the words of one chunk and sorts it: RUNS groups of 256 threads sort 256 W words each in registers, then a
+// word's place is its place in its run plus the counts of smaller words in the others.  WHOLE: the chunk is the image,
+// its order is written at once; otherwise the sorted words.  (2048 words by 256 threads with 8 words each, the whole
+// network in registers or through LDS: 18 - 19 us, a chain of dependent steps with one wave per SIMD; as four runs of
+// 512 by 1024 threads 12.6 us for 128 chunks.)
+template <int W, int RUNS, bool WHOLE>
+__global__ __launch_bounds__(kSortThreads* RUNS) void cluster_sort_chunk_kernel(ClusterParams p, int chunks, bool network) {
+  constexpr int kRun = W * kSortThreads, kWords = kRun * RUNS;
+  __shared__ word_t buf[kWords];
+  const int b = blockIdx.x / chunks, c = blockIdx.x - b * chunks, first = c * kWords;
+  const int g = threadIdx.x / kSortThreads, t = threadIdx.x % kSortThreads;
+  const word_t flip = network && (c & 1) ? ~0ull : 0ull;  // the network goes on from chunks in alternating order
+  word_t v[W];
+#pragma unroll
+  for (int m = 0; m < W; ++m) v[m] = token_word(p, b, first + m * kSortThreads * RUNS + threadIdx.x) ^ flip;  // (any order will do)
+  sort_in_registers<W>(v, buf + g * kRun, kSortThreads, t);
   __syncthreads();
-  for (int k = 2; k <= chunk; k <<= 1) lds_steps(buf, chunk, first, k, k >> 1);
-  word_t* out = p.words + (size_t)b * p.npad + first;
-  for (int t = threadIdx.x; t < chunk; t += blockDim.x) out[t] = buf[lds_place(t)];
+#pragma unroll
+  for (int m = 0; m < W; ++m) buf[g * kRun + t * W + m] = v[m];
+  __syncthreads();
+  int place[W];
+#pragma unroll
+  for (int m = 0; m < W; ++m) {
+    place[m] = t * W + m;
+    if (RUNS > 1) {
+#pragma unroll
+      for (int o = 1; o < RUNS; ++o) {
+        // equal words (pads, or complemented pads, only): those of the lower run come first
+        const int other = (g + o) % RUNS;
+        place[m] += count_below(buf + other * kRun, kRun, v[m], other < g);
+      }
+    }
+  }
+  if (WHOLE) {
+#pragma unroll
+    for (int m = 0; m < W; ++m)
+      if (v[m] != ~0ull) emit(p, b, v[m], place[m]);
+    return;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < W; ++m) buf[place[m]] = v[m];
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < W; ++m) {
+    const int at = m * kSortThreads * RUNS + threadIdx.x;
+    p.words[(size_t)b * p.npad + first + at] = buf[at] ^ flip;
+  }
+}
+
+// Order of an image whose `chunks` (2 .. 16) chunks are sorted: a word's place is its place in its chunk plus, for
+// every other chunk, the number of smaller words there, found by binary search: 6 steps on every 32nd word of the chunk
+// (in LDS), 5 on the words between (the lanes of a wave hold neighbouring words, so they read neighbouring places).
+// Replaces the seven further launches of the network at 8 chunks.
+constexpr int kMaxRankChunks = 16;
+__global__ __launch_bounds__(256) void cluster_rank_kernel(ClusterParams p, int chunks) {
+  __shared__ word_t split[kMaxRankChunks][64];
+  const int b = blockIdx.y;
+  const word_t* w = p.words + (size_t)b * p.npad;
+  for (int i = threadIdx.x; i < chunks * 64; i += 256) split[i >> 6][i & 63] = w[(size_t)i * (kChunk / 64)];
+  __syncthreads();
+  const int at = blockIdx.x * 256 + threadIdx.x;  // place among the chunks' words (a workgroup stays inside one chunk)
+  const int own = (blockIdx.x * 256) / kChunk;
+  const word_t word = w[at];
+  int place = at - own * kChunk;
+  for (int c = 0; c < chunks; ++c) {
+    if (c == own) continue;  // uniform
+    int s = 0;  // words of `split` below the word
+#pragma unroll
+    for (int step = 32; step >= 1; step >>= 1) s += split[c][s + step - 1] < word ? step : 0;
+    s += split[c][s] < word ? 1 : 0;  // (s <= 63 here)
+    int n = 0;  // words below it among the 31 after the last such
+    const word_t* from = w + (size_t)c * kChunk + max(s - 1, 0) * 32 + 1;
+#pragma unroll
+    for (int step = 16; step >= 1; step >>= 1) n += from[n + step - 1] < word ? step : 0;
+    place += s == 0 ? 0 : (s - 1) * 32 + 1 + n;
+  }
+  if (word != ~0ull) emit(p, b, word, place);
 }
 
 // R consecutive steps (k, J), (k, J/2), ... whose strides are all at least the chunk size: partners sit in
@@ -160,11 +301,7 @@ __global__ __launch_bounds__(kSortThreads) void cluster_merge_chunk_kernel(Clust
 
 __global__ __launch_bounds__(256) void cluster_emit_kernel(ClusterParams p) {
   const int place = blockIdx.x * blockDim.x + threadIdx.x;
-  const int b = blockIdx.y;
-  if (place >= p.N) return;
-  const int tok = (int)(uint32_t)p.words[(size_t)b * p.npad + place];  // pads sort last: the first N are tokens
-  p.order[(size_t)b * p.N + place] = tok;
-  if (p.cluster_id) p.cluster_id[(size_t)b * p.N + tok] = place / p.S;
+  if (place < p.N) emit(p, blockIdx.y, p.words[(size_t)blockIdx.y * p.npad + place], place);  // pads sort last
 }
 
 int next_pow2(int n) {
@@ -184,12 +321,28 @@ hipError_t launch_cluster(const float* coords, int B, int N, int S, double x0, d
   p.x0 = x0; p.y0 = y0; p.w = w; p.h = h;
   p.words = static_cast<word_t*>(workspace);
   p.order = order; p.cluster_id = cluster_id;
-  const int chunk = p.npad < kChunk ? p.npad : kChunk;
+  p.s_magic = div_magic(S);
+#define AFFMAE_SORT(W, RUNS, WHOLE, CHUNKS, NETWORK)                                                               \
+  AFFMAE_LAUNCH("cluster_sort_chunk_kernel", stream, (cluster_sort_chunk_kernel<W, RUNS, WHOLE>),                  \
+                dim3((unsigned)B * (CHUNKS)), dim3(kSortThreads * (RUNS)), 0, stream, p, CHUNKS, NETWORK)
+  if (N <= kChunk) {  // one chunk per image
+    if (N <= kSortThreads) AFFMAE_SORT(1, 1, true, 1, false);
+    else if (N <= 2 * kSortThreads) AFFMAE_SORT(2, 1, true, 1, false);
+    else AFFMAE_SORT(2, 4, true, 1, false);
+    return hipGetLastError();
+  }
+  const int chunks = (N + kChunk - 1) / kChunk;
+  if (chunks <= kMaxRankChunks) {
+    AFFMAE_SORT(2, 4, false, chunks, false);
+    AFFMAE_LAUNCH("cluster_rank_kernel", stream, cluster_rank_kernel, dim3(chunks * (kChunk / 256), B), dim3(256), 0, stream, p, chunks);
+    return hipGetLastError();
+  }
+  const int chunk = kChunk;
   const size_t lds = (size_t)chunk * sizeof(word_t);
-  const int threads = chunk / 2 < kSortThreads ? (chunk / 2 < 64 ? 64 : chunk / 2) : kSortThreads;
+  const int threads = kSortThreads;
   const dim3 per_chunk(B * (p.npad / chunk));
-  AFFMAE_LAUNCH("cluster_sort_chunk_kernel", stream, cluster_sort_chunk_kernel, per_chunk, dim3(threads), lds, stream, p,
-                chunk);
+  AFFMAE_SORT(2, 4, false, p.npad / chunk, true);
+#undef AFFMAE_SORT
   for (int k = chunk * 2; k <= p.npad; k <<= 1) {
     int j = k >> 1;
     while (j >= chunk) {  // up to three steps per pass over global memory

@@ -79,3 +79,16 @@ def test_cluster_full_size_configs(name):
     back = np.take_along_axis(shuffled, order2[..., None].astype(np.int64), axis=1)
     o3, _ = oracle.cluster(back, cfg.S, frame)
     assert np.array_equal(o3, ident)
+
+
+@pytest.mark.parametrize("N", [255, 256, 257, 512, 513, 1024, 1025, 2047, 2048, 2049, 4096, 4097, 32768, 32769])
+def test_cluster_sizes_at_the_edges(N):
+    """One workgroup's words per thread (1, 2, 4, 8), one chunk or several, the most chunks that are ranked (16) and the
+    first size that the network merges: points on a lattice, so that the index decides among many equal keys."""
+    rng = np.random.default_rng(N)
+    coords = rng.integers(0, 40, size=(2, N, 2)).astype(np.float32)
+    coords[1] *= 0.37
+    order, cid = _gpu_cluster(coords, 48, (0.0, 0.0, 40.0, 40.0))
+    rorder, rcid = oracle.cluster(coords, 48, (0.0, 0.0, 40.0, 40.0))
+    assert np.array_equal(order, rorder)
+    assert np.array_equal(cid, rcid)
