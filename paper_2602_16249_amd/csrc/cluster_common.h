@@ -58,7 +58,7 @@ struct PlanLayout {
   size_t sorted_pos_off;  // uint16 [strips][places]   entry values grouped by slot; kNoEntry in unused places
   size_t runs_off;        // uint16 [strips][runs_stride]
   size_t rev_count_off;   // int32  [strips]      incidences per token tile
-  size_t rev_offset_off;  // int32  [strips + 1]  exclusive prefix sum of rev_count
+  size_t rev_offset_off;  // int32  [strips + 1]  where a token tile's incidences start in rev_list
   size_t rev_cursor_off;  // int32  [strips]      build-time cursors
   size_t rev_list_off;    // uint64 [strips * max_slots]  low: (strip within image) << 8 | slot; high: run start | run length << 16
   size_t total;

@@ -36,7 +36,7 @@ struct BwdParams {
   const bf16_t *q, *k, *v, *bias, *out, *dout;
   const float* lse;
   const uint16_t *slots, *entries;
-  const int32_t* rev_offset;
+  const int32_t *rev_offset, *rev_count;
   const unsigned long long* rev_list;
   const uint16_t *sorted_pos, *runs;
   int N, H, K, strips, strips_per_image, slot_stride, max_slots, runs_stride, places;
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 4))) voi
   const int t0 = (kt - b * p.strips_per_image) * 16;  // the tile's first token, within the image
   const int nt = RAG ? min(16, p.N - t0) : 16;
   const int lo = __builtin_amdgcn_readfirstlane(p.rev_offset[kt]);
-  const int n = __builtin_amdgcn_readfirstlane(p.rev_offset[kt + 1]) - lo;
+  const int n = __builtin_amdgcn_readfirstlane(p.rev_count[kt]);
   // q / dout rows cross through LDS: a lane loads 16 contiguous bytes of a row so that a quad reads 64
   // contiguous bytes (a load straight into the operand layout puts a quad on four rows and costs four
   // times the memory-pipeline cycles); each lane then reads back the piece its operand needs.  The piece
@@ -802,6 +802,7 @@ hipError_t launch_pla_bwd_cluster(const PlaArgs& a, const void* plan, void* work
   p.slots = reinterpret_cast<const uint16_t*>(base + L.slots_off);
   p.entries = reinterpret_cast<const uint16_t*>(base + L.entries_off);
   p.rev_offset = reinterpret_cast<const int32_t*>(base + L.rev_offset_off);
+  p.rev_count = reinterpret_cast<const int32_t*>(base + L.rev_count_off);
   p.rev_list = reinterpret_cast<const unsigned long long*>(base + L.rev_list_off);
   p.sorted_pos = reinterpret_cast<const uint16_t*>(base + L.sorted_pos_off);
   p.runs = reinterpret_cast<const uint16_t*>(base + L.runs_off);

@@ -2,10 +2,13 @@
 // (paper, Sec. "Limitations": neighbourhood tables are cached per encoder stage
 // and reused by every block; the plan is such a table in the layout the tiled
 // kernels read).  Forward tables: one wave per strip of 16 queries.  Reverse
-// tables (which strips touch a token tile): count, prefix sum, fill, sort.
+// tables (which strips touch a token tile): one kernel that counts, places, files
+// and sorts in LDS and L2 (large images: count, prefix sum, fill and sort kernels).
 #include "cluster_common.h"
 #include "launch.h"
 #include "timing.h"
+
+#include <algorithm>
 
 namespace affmae {
 namespace {
@@ -25,6 +28,7 @@ struct PlanParams {
   uint16_t* sorted_pos;  // [strips][places]
   uint16_t* runs;        // [strips][runs_stride]
   int runs_stride, places;
+  bool count_tiles;       // the reverse tables are built by the count / scan / fill / sort kernels
 };
 
 __device__ __forceinline__ unsigned long long wave_or64(unsigned long long x) {
@@ -113,7 +117,7 @@ __global__ __launch_bounds__(256) void pla_plan_kernel(PlanParams p) {
     const int e = min(max(near_c[m], 0), p.G - 1);
     const int my_tile = e * tiles_per_cluster + tt;  // token tile within the image
     sl[1 + __popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)my_tile;
-    atomicAdd(p.rev_count + (size_t)b * p.strips_per_image + my_tile, 1);
+    if (p.count_tiles) atomicAdd(p.rev_count + (size_t)b * p.strips_per_image + my_tile, 1);
   }
   const int own_tile = q0 >> 4;
   if (lane == 0) sl[0] = (uint16_t)count;
@@ -221,13 +225,8 @@ __global__ __launch_bounds__(256) void plan_fill_kernel(PlanParams p) {
   }
 }
 
-// Sort every token tile's list ascending by (strip, slot): rank by counting (lists are short).
-__global__ __launch_bounds__(256) void plan_sort_kernel(PlanParams p) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int kt = blockIdx.x * (blockDim.x / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (kt >= p.strips) return;
-  const int lo = p.rev_offset[kt], n = p.rev_offset[kt + 1] - lo;
-  unsigned long long* list = p.rev_list + lo;
+// Sorts one token tile's list ascending by (strip, slot): rank by counting (lists are short).  One wave.
+__device__ __forceinline__ void sort_incidences(unsigned long long* list, int n, int lane) {
   if (n <= kWave) {
     const unsigned long long mine = lane < n ? list[lane] : ~0ull;
     const uint32_t key = (uint32_t)mine;
@@ -244,6 +243,102 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(PlanParams p) {
       }
       list[j + 1] = v;
     }
+  }
+}
+
+__global__ __launch_bounds__(256) void plan_sort_kernel(PlanParams p) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int kt = blockIdx.x * (blockDim.x / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (kt >= p.strips) return;
+  sort_incidences(p.rev_list + p.rev_offset[kt], p.rev_count[kt], lane);
+}
+
+// The reverse tables of images of at most kRevTiles token tiles, in one launch: a workgroup owns `own` consecutive tiles
+// of one image.  It reads the image's slot tables (from L2), counts every tile's incidences in LDS, prefix-sums
+// the counts (an image's lists start at a place of their own, so nothing is needed of other images), reads the tables
+// again and files the incidences of its own tiles, and sorts these lists.  Against counting with atomics in the strip
+// kernel, then zero / scan / fill / sort kernels: 24 us of launches of 5 - 6 us each at 16 x 1024 strips, this one 8 us.
+constexpr int kRevTiles = 2048;
+constexpr int kRevThreads = 1024;
+__global__ __launch_bounds__(kRevThreads) void plan_reverse_kernel(PlanParams p, int own) {
+  __shared__ int32_t count[kRevTiles];   // incidences per tile
+  __shared__ int32_t offset[kRevTiles];  // exclusive prefix, then the cursor of the own tiles
+  __shared__ int32_t part[kRevThreads / kWave];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int tiles = p.strips_per_image;
+  const int groups = (tiles + own - 1) / own;
+  const int b = blockIdx.x / groups, first = (blockIdx.x - b * groups) * own, last = min(first + own, tiles);
+  const size_t strip0 = (size_t)b * tiles;
+  for (int i = tid; i < kRevTiles; i += kRevThreads) count[i] = 0;
+  __syncthreads();
+  // a thread per strip: the first 15 slots in eight independent loads (most strips have fewer), the others one by one
+  auto each = [&](auto f) {
+    for (int strip = tid; strip < tiles; strip += kRevThreads) {
+      const uint16_t* row = p.slots + (strip0 + strip) * p.slot_stride;  // (slot_stride is even and at least 2)
+      const uint32_t* pairs = reinterpret_cast<const uint32_t*>(row);
+      const int pairs_end = p.slot_stride / 2 - 1;
+      uint32_t w[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) w[i] = pairs[min(i, pairs_end)];
+      const int n = min((int)(w[0] & 0xffffu), p.max_slots);
+#pragma unroll
+      for (int s = 0; s < 15; ++s) {
+        const int tile = (int)((w[(s + 1) >> 1] >> (16 * ((s + 1) & 1))) & 0xffffu);
+        if (s < n && tile < tiles) f(strip, s, tile);
+      }
+      for (int s = 15; s < n; ++s) {
+        const int tile = row[1 + s];
+        if (tile < tiles) f(strip, s, tile);
+      }
+    }
+  };
+  each([&](int, int, int tile) { atomicAdd(&count[tile], 1); });
+  __syncthreads();
+  // exclusive prefix: two tiles per thread
+  const int c0 = count[2 * tid], c1 = count[2 * tid + 1];
+  int incl = c0 + c1;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int v = __shfl_up(incl, o);
+    if (lane >= o) incl += v;
+  }
+  if (lane == kWave - 1) part[wave] = incl;
+  __syncthreads();
+  int before = incl - c0 - c1;
+  for (int w = 0; w < wave; ++w) before += part[w];
+  offset[2 * tid] = before;
+  offset[2 * tid + 1] = before + c0;
+  __syncthreads();
+  const size_t list0 = strip0 * p.max_slots;  // the image's lists
+  for (int i = first + tid; i < last; i += kRevThreads) {
+    p.rev_count[strip0 + i] = count[i];
+    p.rev_offset[strip0 + i] = (int32_t)(list0 + offset[i]);
+  }
+  __syncthreads();
+  each([&](int strip, int slot, int tile) {  // (strip, slot) only: the place of the run is loaded by the sort, a tile at once
+    if (tile >= first && tile < last)
+      p.rev_list[list0 + atomicAdd(&offset[tile], 1)] = ((uint32_t)strip << 8) | (uint32_t)slot;
+  });
+  __threadfence_block();
+  __syncthreads();
+  for (int tile = first + wave; tile < last; tile += kRevThreads / kWave) {
+    const int n = count[tile];
+    unsigned long long* list = p.rev_list + list0 + offset[tile] - n;
+    auto with_run = [&](unsigned long long inc) -> unsigned long long {
+      const uint16_t* runs = p.runs + (strip0 + (uint32_t)inc / 256u) * p.runs_stride + ((uint32_t)inc & 255u);
+      const uint32_t start = runs[0], len = (uint32_t)runs[1] - start;  // len may count one pad place
+      return ((unsigned long long)(start | (len << 16)) << 32) | (uint32_t)inc;
+    };
+    if (n > kWave) {
+      for (int i = lane; i < n; i += kWave) list[i] = with_run(list[i]);
+      __threadfence_block();
+      sort_incidences(list, n, lane);
+      continue;
+    }
+    const unsigned long long mine = lane < n ? with_run(list[lane]) : ~0ull;
+    int rank = 0;
+    for (int j = 0; j < n; ++j) rank += __builtin_amdgcn_readlane((uint32_t)mine, j) < (uint32_t)mine ? 1 : 0;  // keys are distinct
+    if (lane < n) list[rank] = mine;  // every lane has read its element before any write lands (one wave)
   }
 }
 
@@ -268,13 +363,24 @@ hipError_t launch_pla_plan(const int32_t* nbr_idx, const int32_t* near, int B, i
   p.runs = reinterpret_cast<uint16_t*>(base + L.runs_off);
   p.runs_stride = L.runs_stride; p.places = L.places;
   const dim3 per_strip((L.strips + 3) / 4);
-  AFFMAE_LAUNCH("plan_zero_kernel", stream, plan_zero_kernel, dim3((L.strips + 255) / 256), dim3(256), 0, stream,
-                p.rev_count, p.rev_cursor, L.strips);
+  // One workgroup per group of tiles reads its image's whole slot table: quadratic in the tiles, so only up to kRevTiles
+  // (LDS counters), and with list places that int32 can number.
+  const int tiles = p.strips_per_image;
+  p.count_tiles = tiles > kRevTiles || (long long)L.strips * L.max_slots >= (1ll << 31);
+  if (p.count_tiles)
+    AFFMAE_LAUNCH("plan_zero_kernel", stream, plan_zero_kernel, dim3((L.strips + 255) / 256), dim3(256), 0, stream,
+                  p.rev_count, p.rev_cursor, L.strips);
   const int ne = (16 * K + kWave - 1) / kWave;
   if (ne <= 4) AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<4>, per_strip, dim3(256), 0, stream, p);
   else if (ne <= 8) AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<8>, per_strip, dim3(256), 0, stream, p);
   else if (ne <= 12) AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<12>, per_strip, dim3(256), 0, stream, p);
   else AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<kMaxEntries>, per_strip, dim3(256), 0, stream, p);
+  if (!p.count_tiles) {
+    const int own = std::max(16, (tiles + 15) / 16);  // about 16 workgroups per image
+    AFFMAE_LAUNCH("plan_reverse_kernel", stream, plan_reverse_kernel, dim3(B * ((tiles + own - 1) / own)), dim3(kRevThreads), 0,
+                  stream, p, own);
+    return hipGetLastError();
+  }
   AFFMAE_LAUNCH("plan_scan_kernel", stream, plan_scan_kernel, dim3((L.strips + 1023) / 1024), dim3(256), 0, stream,
                 p.rev_count, p.rev_offset, L.strips);
   AFFMAE_LAUNCH("plan_fill_kernel", stream, plan_fill_kernel, per_strip, dim3(256), 0, stream, p);

@@ -233,3 +233,19 @@ def test_short_last_cluster_end_to_end(N, tiled):
     assert np.array_equal(nbr_d.cpu().numpy(), nbr) and np.array_equal(near_d.cpu().numpy(), near)
     assert (aff.load_library().affmae_pla_plan_bytes(cfg.B, N, K, S, M) > 0) == tiled
     check_attention(w, nbr, "bf16", 1.0 / np.sqrt(d), near=near, S=S, M=M, use_plan=tiled)
+
+
+@pytest.mark.parametrize("N,S,M,K,same", [(2048, 16, 32, 40, True),     # every strip touches the same three token tiles
+                                          (700, 32, 16, 24, True),      # the same with a short last strip
+                                          (32768, 64, 8, 16, False),    # the most token tiles of the one-launch reverse tables
+                                          (32785, 64, 8, 16, False)])   # one more: counted, scanned, filled and sorted
+def test_reverse_tables_of_the_plan(N, S, M, K, same):
+    """dk and dv walk the plan's reverse tables: lists of more than 64 strips (all points coincide, so that the index
+    decides and all queries share their neighbours) and both ways of building the tables."""
+    print(f"case reverse tables N={N} S={S} M={M} K={K}", flush=True)
+    cfg = CONFIGS["knn_scale"].scaled(B=1, N=N, C=32, H=1, K=K, S=S, M=M, dtype="bf16")
+    w = make_workload(cfg)
+    if same:
+        w["coords"] = np.full_like(w["coords"], 2.5)
+    nbr, near = oracle.knn(w["coords"], None, S, M, K)
+    check_attention(w, nbr, cfg.dtype, 1.0 / np.sqrt(32), near=near, S=S, M=M, use_plan=True)
