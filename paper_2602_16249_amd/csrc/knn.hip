@@ -3,7 +3,8 @@
 // coordinates).  Four kernels:
 //   members  (only with an explicit cluster_id): token lists per cluster
 //   centroid : double-precision mean of each cluster's coordinates -> fp32
-//   near     : per cluster the M clusters with nearest centroids
+//   near     : per cluster the M clusters with nearest centroids (up to 256 clusters
+//              per image: by the search kernel itself)
 //   knn      : per token the K nearest among the members of those M clusters
 //              (staged in LDS, selected by a counted distance threshold and one sort)
 // Selection is exact and unique: 64-bit keys (fp32 distance bits, index) compared
@@ -120,7 +121,10 @@ __global__ __launch_bounds__(256) void near_kernel(const float* __restrict__ cen
 // tests and branches per row are scalar instructions, of which a SIMD issues no more than of the others.)
 // `parts` workgroups share a cluster's tokens: with one per cluster a batch of few or large clusters leaves most of
 // the chip idle (one cluster of 256 tokens: 85 us with one workgroup, 5 us with 64).
+// Up to kNearInSearch clusters per image the workgroup finds the near clusters itself (a launch less: 4 - 9 us; more
+// clusters are searched by near_kernel, once per cluster and not once per workgroup).
 constexpr int kKnnWaves = 4;
+constexpr int kNearInSearch = kKnnWaves * kWave;
 constexpr int kFullChipWaves = 8192;  // 256 CUs x 4 SIMDs x 8 waves
 size_t knn_lds_bytes(int rows) {
   return kKnnWaves * kWave * sizeof(key_t) + (size_t)rows * kWave * (sizeof(float2) + sizeof(int32_t));
@@ -128,10 +132,12 @@ size_t knn_lds_bytes(int rows) {
 template <int ROWS, bool MEMBERS>
 __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __restrict__ coords,
                                                               const int32_t* __restrict__ members,
-                                                              const int32_t* __restrict__ near, int N, int S, int M,
-                                                              int K, int G, int rows, int parts, uint32_t s_magic,
+                                                              const float* __restrict__ centroid,
+                                                              int32_t* __restrict__ near, int N, int S, int M, int K,
+                                                              int G, int rows, int parts, uint32_t s_magic,
                                                               int32_t* __restrict__ nbr_idx) {
   extern __shared__ key_t lds[];
+  __shared__ int32_t near_lds[kWave];
   float2* cxy = reinterpret_cast<float2*>(lds + kKnnWaves * kWave);        // [rows][64]
   int32_t* ctok = reinterpret_cast<int32_t*>(cxy + (size_t)rows * kWave);  // [rows][64]
   const int gc = blockIdx.x / parts, part = blockIdx.x - gc * parts;
@@ -144,11 +150,37 @@ __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __re
   key_t* pend = lds + wave * kWave;
   // lane m: the m-th of the near clusters in index order (M <= 64; they are distinct)
   int near_sorted;
-  {
-    const int id = lane < M ? min(max(near[(size_t)gc * M + lane], 0), G - 1) : 0x7fffffff;
+  auto index_order = [&](int id) -> int {  // lane m < M: the m-th of the ids that lanes 0 .. M - 1 give
     int rank = 0;
     for (int m = 0; m < M; ++m) rank += __builtin_amdgcn_readlane(id, m) < id ? 1 : 0;
-    near_sorted = __builtin_amdgcn_ds_permute((lane < M ? rank : lane) * 4, id);
+    return __builtin_amdgcn_ds_permute((lane < M ? rank : lane) * 4, id);
+  };
+  if (G <= kNearInSearch) {
+    // the near clusters themselves, a row of 64 centroids per wave (G == 1: there is one cluster, no centroid is needed)
+    const int e = wave * kWave + lane;
+    if (G > 1) {
+      const float* cen = centroid + (size_t)b * G * 2;
+      key_t key = kKeyMax;
+      if (e < G) key = make_key(dist2(cen[2 * c], cen[2 * c + 1], cen[2 * e], cen[2 * e + 1]), e);
+      if (wave * kWave < G) pend[lane] = wave_sort(key, lane);
+      __syncthreads();
+    }
+    if (wave == 0) {
+      key_t best = 0ull;
+      if (G > 1) {
+        best = pend[lane];
+        for (int row = 1; row * kWave < G; ++row) {  // the 64 smallest of two sorted rows are bitonic
+          const key_t rev = lds[row * kWave + kWave - 1 - lane];
+          best = wave_bitonic_merge(best < rev ? best : rev, lane);
+        }
+      }
+      if (lane < M && part == 0) near[(size_t)gc * M + lane] = (int32_t)(uint32_t)best;
+      near_lds[lane] = index_order(lane < M ? (int)(uint32_t)best : 0x7fffffff);
+    }
+    __syncthreads();
+    near_sorted = near_lds[lane];
+  } else {
+    near_sorted = index_order(lane < M ? min(max(near[(size_t)gc * M + lane], 0), G - 1) : 0x7fffffff);
   }
   for (int p = threadIdx.x; p < rows * kWave; p += kKnnWaves * kWave) {  // (whole waves: all lanes take part)
     const int pp = p < Cn ? p : 0;
@@ -226,10 +258,12 @@ hipError_t launch_knn(const KnnArgs& a, hipStream_t stream) {
     members = a.members;
   }
   const int BG = a.B * a.G;
-  AFFMAE_LAUNCH("centroid_kernel", stream, centroid_kernel, dim3((BG + 3) / 4), dim3(256), 0, stream, a.coords, members, a.B, a.N,
-                     a.S, a.G, a.centroid);
-  AFFMAE_LAUNCH("near_kernel", stream, near_kernel, dim3((BG + 3) / 4), dim3(256), 0, stream, a.centroid, a.B, a.G, a.M,
-                     a.near_clusters);
+  if (a.G > 1)
+    AFFMAE_LAUNCH("centroid_kernel", stream, centroid_kernel, dim3((BG + 3) / 4), dim3(256), 0, stream, a.coords, members, a.B, a.N,
+                  a.S, a.G, a.centroid);
+  if (a.G > kNearInSearch)
+    AFFMAE_LAUNCH("near_kernel", stream, near_kernel, dim3((BG + 3) / 4), dim3(256), 0, stream, a.centroid, a.B, a.G, a.M,
+                  a.near_clusters);
   const int rows = (a.M * a.S + kWave - 1) / kWave;  // at most 64
   // enough workgroups for eight waves on every SIMD, while a wave still has a token to serve
   const int parts = std::max(1, std::min((kFullChipWaves / kKnnWaves + BG - 1) / BG, (std::min(a.S, a.N) + kKnnWaves - 1) / kKnnWaves));
@@ -238,10 +272,10 @@ hipError_t launch_knn(const KnnArgs& a, hipStream_t stream) {
   do {                                                                                                              \
     if (members)                                                                                                    \
       AFFMAE_LAUNCH("knn_kernel", stream, (knn_kernel<R, true>), grid, block, knn_lds_bytes(rows), stream, a.coords, members, \
-                    a.near_clusters, a.N, a.S, a.M, a.K, a.G, rows, parts, div_magic(a.S), a.nbr_idx);              \
+                    a.centroid, a.near_clusters, a.N, a.S, a.M, a.K, a.G, rows, parts, div_magic(a.S), a.nbr_idx);              \
     else                                                                                                            \
       AFFMAE_LAUNCH("knn_kernel", stream, (knn_kernel<R, false>), grid, block, knn_lds_bytes(rows), stream, a.coords, members, \
-                    a.near_clusters, a.N, a.S, a.M, a.K, a.G, rows, parts, div_magic(a.S), a.nbr_idx);              \
+                    a.centroid, a.near_clusters, a.N, a.S, a.M, a.K, a.G, rows, parts, div_magic(a.S), a.nbr_idx);              \
   } while (0)
   if (rows <= 2) AFFMAE_KNN(2);
   else if (rows <= 4) AFFMAE_KNN(4);
