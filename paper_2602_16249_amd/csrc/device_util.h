@@ -61,16 +61,54 @@ __device__ __forceinline__ void load_row(const bf16_t* p, float (&r)[D]) {
   }
 }
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
+// The word held by lane (lane ^ J), J a power of two, moved on the vector ALU: DPP lane
+// patterns inside a row of 16 lanes, the gfx950 row / half swaps across rows.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_mov(uint32_t x) {
+  // every pattern used here reads an existing lane, so no value is needed for lanes without a source: leaving it
+  // undefined saves the instruction that would otherwise set it before every move
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xf, 0xf, true);
+}
+template <int J>
+__device__ __forceinline__ uint32_t lane_xor_u32(uint32_t x, int lane) {
+  typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+  if constexpr (J == 1) {
+    return dpp_mov<0xB1>(x);  // quad_perm [1,0,3,2]
+  } else if constexpr (J == 2) {
+    return dpp_mov<0x4E>(x);  // quad_perm [2,3,0,1]
+  } else if constexpr (J == 4) {
+    return dpp_mov<0x1B>(dpp_mov<0x141>(x));  // reverse 8 lanes, then reverse each quad: i -> i ^ 7 ^ 3
+  } else if constexpr (J == 8) {
+    return dpp_mov<0x128>(x);  // rotate the row by 8
+  } else if constexpr (J == 16) {
+    const u32x2 t = __builtin_amdgcn_permlane16_swap(x, x, false, false);  // [0]: even rows doubled, [1]: odd rows
+    return (lane & 16) ? t[0] : t[1];
+  } else {
+    const u32x2 t = __builtin_amdgcn_permlane32_swap(x, x, false, false);  // [0]: low half doubled, [1]: high half
+    return (lane & 32) ? t[0] : t[1];
+  }
+}
+// Sum over the lanes whose numbers differ in the bits LO .. HI (powers of two), largest distance first, every lane
+// receiving it; all lanes of the wave must be active.  Through the LDS crossbar (shuffles) each step would wait for a
+// trip to LDS and back.
+template <int LO, int HI>
+__device__ __forceinline__ float lanes_sum(float x, int lane) {
+  if constexpr (LO <= HI) {
+    x += __uint_as_float(lane_xor_u32<HI>(__float_as_uint(x), lane));
+    x = lanes_sum<LO, HI / 2>(x, lane);
+  }
   return x;
 }
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+template <int LO, int HI>
+__device__ __forceinline__ float lanes_max(float x, int lane) {
+  if constexpr (LO <= HI) {
+    x = fmaxf(x, __uint_as_float(lane_xor_u32<HI>(__float_as_uint(x), lane)));
+    x = lanes_max<LO, HI / 2>(x, lane);
+  }
   return x;
 }
+__device__ __forceinline__ float wave_max(float x) { return lanes_max<1, 32>(x, threadIdx.x & (kWave - 1)); }
+__device__ __forceinline__ float wave_sum(float x) { return lanes_sum<1, 32>(x, threadIdx.x & (kWave - 1)); }
 
 // Orders LDS traffic between the lanes of one wave (no workgroup barrier).
 __device__ __forceinline__ void wave_lds_sync() {

@@ -323,44 +323,48 @@ __device__ __forceinline__ Nbr load_neighbour(const float* __restrict__ coords, 
   return r;
 }
 
-// PIECES: rows are whole 16-byte pieces and 16-byte aligned; a row takes PP lanes (the next power of two of its
-// piece count, at most 64), RW = 64 / PP rows are in flight per trip.  Otherwise lanes are channels.
-template <typename T, bool PIECES>
+// PP > 0: rows are whole 16-byte pieces and 16-byte aligned; a row takes PP lanes (the next power of two of its
+// piece count, at most 64), RW = 64 / PP rows make a trip, two trips are in flight.  PP == 0: lanes are channels.
+// (With PP a run-time number and the sums over lanes by shuffles through LDS the kernels waited on LDS round trips:
+// forward 29 us, backward 36 us at 32768 anchors, K = 48, C = 64 bf16.)
+template <typename T, int PP>
 __global__ __launch_bounds__(256) void merge_fwd_kernel(const T* __restrict__ feat, const float* __restrict__ coords,
                                                        const float* __restrict__ score,
                                                        const int32_t* __restrict__ nbr,
                                                        const int32_t* __restrict__ anchor, int B, int N, int C, int K,
-                                                       int n_keep, float p, int PP, T* __restrict__ out) {
+                                                       int n_keep, float p, T* __restrict__ out) {
   const int lane = threadIdx.x & (kWave - 1);
   const long long slot = xcd_contiguous_block() * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if (slot >= (long long)B * n_keep) return;  // wave-uniform
   const Nbr nb = load_neighbour(coords, score, nbr, anchor, slot, N, K, n_keep, p, lane);
   const T* rows = feat + (size_t)nb.b * N * C;
   T* orow = out + (size_t)slot * C;
-  if (PIECES) {
+  if constexpr (PP > 0) {
     constexpr int CH = Piece16<T>::kCh;
     const int pieces = C / CH;
-    const int RW = kWave / PP;
+    constexpr int RW = kWave / PP;
     const int pc = lane & (PP - 1), rs = lane / PP;  // piece and row of this lane inside a trip
     for (int pc0 = 0; pc0 < pieces; pc0 += PP) {      // one trip unless a row has more than 64 pieces
       const bool pon = pc0 + pc < pieces;
       const int c0 = min(pc0 + pc, pieces - 1) * CH;  // lanes past the row's end repeat its last piece (unused)
       float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      for (int j0 = 0; j0 < K; j0 += RW) {
-        const int j = j0 + rs;
-        const int jj = min(j, K - 1);
-        const float wraw = __shfl(nb.w, jj);  // (every lane takes part in the shuffles; rows past K get weight 0)
-        const int ij = __shfl(nb.idx, jj);
-        const float wj = j < K ? wraw : 0.f;
-        float f[8];
-        Piece16<T>::load(rows + (uint32_t)(ij * C + c0), f);  // (row offsets inside an image fit 32 bits on this path)
+      for (int j0 = 0; j0 < K; j0 += 2 * RW) {
+        float wj[2], f[2][8];
 #pragma unroll
-        for (int e = 0; e < CH; ++e) acc[e] = fmaf(wj, f[e], acc[e]);
-      }
-      for (int o = PP; o < kWave; o <<= 1) {  // add up the row groups
+        for (int u = 0; u < 2; ++u) {
+          const int j = j0 + u * RW + rs, jj = min(j, K - 1);
+          const float wraw = __shfl(nb.w, jj);  // (every lane takes part in the shuffles; rows past K get weight 0)
+          const int ij = __shfl(nb.idx, jj);
+          wj[u] = j < K ? wraw : 0.f;
+          Piece16<T>::load(rows + (uint32_t)(ij * C + c0), f[u]);  // (row offsets inside an image fit 32 bits on this path)
+        }
 #pragma unroll
-        for (int e = 0; e < CH; ++e) acc[e] += __shfl_xor(acc[e], o);
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int e = 0; e < CH; ++e) acc[e] = fmaf(wj[u], f[u][e], acc[e]);
       }
+#pragma unroll
+      for (int e = 0; e < CH; ++e) acc[e] = lanes_sum<PP, 32>(acc[e], lane);  // add up the row groups
       if (rs == 0 && pon) Piece16<T>::store(orow + c0, acc);
     }
   } else {
@@ -378,12 +382,12 @@ __global__ __launch_bounds__(256) void merge_fwd_kernel(const T* __restrict__ fe
   }
 }
 
-template <typename T, bool PIECES>
+template <typename T, int PP>
 __global__ __launch_bounds__(256) void merge_bwd_kernel(const T* __restrict__ feat, const float* __restrict__ coords,
                                                        const float* __restrict__ score,
                                                        const int32_t* __restrict__ nbr,
                                                        const int32_t* __restrict__ anchor, const T* __restrict__ dout,
-                                                       int B, int N, int C, int K, int n_keep, float p, int PP,
+                                                       int B, int N, int C, int K, int n_keep, float p,
                                                        float* __restrict__ wpair, float* __restrict__ dzpair,
                                                        int32_t* __restrict__ pair_token, int2* __restrict__ pair_bounds,
                                                        float* __restrict__ dp_part) {
@@ -398,23 +402,29 @@ __global__ __launch_bounds__(256) void merge_bwd_kernel(const T* __restrict__ fe
   const T* grow = dout + (size_t)slot * C;
   g[lane] = 0.f;
   wave_lds_sync();
-  if (PIECES) {
+  if constexpr (PP > 0) {
     constexpr int CH = Piece16<T>::kCh;
     const int pieces = C / CH;
-    const int RW = kWave / PP;
+    constexpr int RW = kWave / PP;
     const int pc = lane & (PP - 1), rs = lane / PP;
     for (int pc0 = 0; pc0 < pieces; pc0 += PP) {
       const bool pon = pc0 + pc < pieces;
       const int c0 = min(pc0 + pc, pieces - 1) * CH;
       const uint4 go = *reinterpret_cast<const uint4*>(grow + c0);
-      for (int j0 = 0; j0 < K; j0 += RW) {
-        const int j = j0 + rs;
-        const int ij = __shfl(nb.idx, min(j, K - 1));
-        // (row offsets inside an image fit 32 bits on this path)
-        float part = dot16(rows + (uint32_t)(ij * C + c0), go);
-        part = pon ? part : 0.f;
-        for (int o = 1; o < PP; o <<= 1) part += __shfl_xor(part, o);  // over the lanes of the row
-        if (pc == 0 && j < K) g[j] += part;                            // (one lane per j: no two lanes add to one cell)
+      for (int j0 = 0; j0 < K; j0 += 2 * RW) {
+        float part[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int ij = __shfl(nb.idx, min(j0 + u * RW + rs, K - 1));
+          // (row offsets inside an image fit 32 bits on this path)
+          part[u] = dot16(rows + (uint32_t)(ij * C + c0), go);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int j = j0 + u * RW + rs;
+          const float sum = lanes_sum<1, PP / 2>(pon ? part[u] : 0.f, lane);  // over the lanes of the row
+          if (pc == 0 && j < K) g[j] += sum;                                  // (one lane per j: no two lanes add to one cell)
+        }
       }
     }
   } else {
@@ -498,6 +508,20 @@ int lanes_per_row(const MergeArgs& a) {
 
 }  // namespace
 
+// LAUNCH(T, lanes per row) for the storage type and row shape at hand
+#define AFFMAE_MERGE_PP(LAUNCH, T)                \
+  do {                                            \
+    if (!pieces) LAUNCH(T, 0);                    \
+    else if (pp <= 4) LAUNCH(T, 4);               \
+    else if (pp == 8) LAUNCH(T, 8);               \
+    else if (pp == 16) LAUNCH(T, 16);             \
+    else if (pp == 32) LAUNCH(T, 32);             \
+    else LAUNCH(T, 64);                           \
+  } while (0)
+#define AFFMAE_MERGE_ROWS(LAUNCH)                         \
+  if (a.dtype == 1) AFFMAE_MERGE_PP(LAUNCH, bf16_t);      \
+  else AFFMAE_MERGE_PP(LAUNCH, float);
+
 hipError_t launch_merge_select(const float* score, const float* coords, int B, int N, int n_keep, int32_t* anchor_idx,
                                float* anchor_xy, hipStream_t stream) {
 #define AFFMAE_SELECT(KERNEL) \
@@ -517,11 +541,8 @@ hipError_t launch_merge_fwd(const MergeArgs& a, hipStream_t stream) {
   const int pp = lanes_per_row(a);
 #define AFFMAE_MERGE_FWD(T, P)                                                                                     \
   AFFMAE_LAUNCH("merge_fwd_kernel", stream, (merge_fwd_kernel<T, P>), grid, dim3(256), 0, stream, (const T*)a.feat, \
-                a.coords, a.score, a.nbr_idx, a.anchor_idx, a.B, a.N, a.C, a.K, a.n_keep, a.p, pp, (T*)a.out)
-  if (a.dtype == 1 && pieces) AFFMAE_MERGE_FWD(bf16_t, true);
-  else if (a.dtype == 1) AFFMAE_MERGE_FWD(bf16_t, false);
-  else if (pieces) AFFMAE_MERGE_FWD(float, true);
-  else AFFMAE_MERGE_FWD(float, false);
+                a.coords, a.score, a.nbr_idx, a.anchor_idx, a.B, a.N, a.C, a.K, a.n_keep, a.p, (T*)a.out)
+  AFFMAE_MERGE_ROWS(AFFMAE_MERGE_FWD)
 #undef AFFMAE_MERGE_FWD
   return hipGetLastError();
 }
@@ -545,12 +566,9 @@ hipError_t launch_merge_bwd(const MergeArgs& a, hipStream_t stream) {
   const int pp = lanes_per_row(a);
 #define AFFMAE_MERGE_BWD(T, P)                                                                                     \
   AFFMAE_LAUNCH("merge_bwd_kernel", stream, (merge_bwd_kernel<T, P>), grid, dim3(256), 0, stream, (const T*)a.feat, \
-                a.coords, a.score, a.nbr_idx, a.anchor_idx, (const T*)a.dout, a.B, a.N, a.C, a.K, a.n_keep, a.p, pp, \
+                a.coords, a.score, a.nbr_idx, a.anchor_idx, (const T*)a.dout, a.B, a.N, a.C, a.K, a.n_keep, a.p, \
                 wpair, dzpair, pair_token, pair_bounds, dp_part)
-  if (a.dtype == 1 && pieces) AFFMAE_MERGE_BWD(bf16_t, true);
-  else if (a.dtype == 1) AFFMAE_MERGE_BWD(bf16_t, false);
-  else if (pieces) AFFMAE_MERGE_BWD(float, true);
-  else AFFMAE_MERGE_BWD(float, false);
+  AFFMAE_MERGE_ROWS(AFFMAE_MERGE_BWD)
 #undef AFFMAE_MERGE_BWD
   if (a.dp) {
     const hipError_t e = launch_sum_parts(dp_part, anchors, dp_part2, a.dp, stream);

@@ -832,20 +832,30 @@ __global__ __launch_bounds__(kListThreads) void pair_lists_grouped_kernel(
   int whole = 0;
   auto each_pair = [&](int g0, bool count_whole, auto&& fn) {
     __syncthreads();  // the previous list has been walked (and, the first time, cnt / s_whole are set)
-    if (tid == 0) s_listed = 0;
-    __syncthreads();
-    const int g1 = min(g0 + kGroupCap, groups);
-    for (int g = g0 + tid; g < g1; g += kListThreads) {
-      const int2 bd = bounds[(size_t)b * groups + g];
-      if (bd.y < first) whole += count_whole ? 1 : 0;
-      else if (bd.x < end) glist[atomicAdd(&s_listed, 1)] = g;
+    if (count_whole || groups > kGroupCap) {  // (one list is enough for both walks when it holds all groups)
+      if (tid == 0) s_listed = 0;
+      __syncthreads();
+      const int g1 = min(g0 + kGroupCap, groups);
+      for (int g = g0 + tid; g < g1; g += kListThreads) {
+        const int2 bd = bounds[(size_t)b * groups + g];
+        if (bd.y < first) whole += count_whole ? 1 : 0;
+        else if (bd.x < end) glist[atomicAdd(&s_listed, 1)] = g;
+      }
+      __syncthreads();
     }
-    __syncthreads();
     const int items = s_listed * gs;
-    for (int i = tid; i < items; i += kListThreads) {
-      const int gi = exact_div(i, gs, gs_magic);
-      const int pair = lo + glist[gi] * gs + (i - gi * gs);
-      fn(pair_token[pair], pair);
+    for (int i0 = tid; i0 < items; i0 += 4 * kListThreads) {  // four loads in flight
+      int pair[4], tok[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = min(i0 + u * kListThreads, items - 1);
+        const int gi = exact_div(i, gs, gs_magic);
+        pair[u] = lo + glist[gi] * gs + (i - gi * gs);
+        tok[u] = pair_token[pair[u]];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (i0 + u * kListThreads < items) fn(tok[u], pair[u]);
     }
   };
   int below = 0;
@@ -897,7 +907,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void vts_dfeat16_kernel(const T* __restrict__ dout, const float* __restrict__ weights,
                                                          const int32_t* __restrict__ offset,
                                                          const int32_t* __restrict__ list, int tokens, int C, int Kt,
-                                                         T* __restrict__ dfeat, const float* __restrict__ extra,
+                                                         uint32_t kt_magic, T* __restrict__ dfeat, const float* __restrict__ extra,
                                                          float* __restrict__ extra_sum) {
   constexpr int CH = Piece<T>::kCh;
   const int lane = threadIdx.x & (kWave - 1), sub = lane & 15;
@@ -920,7 +930,7 @@ __global__ __launch_bounds__(256) void vts_dfeat16_kernel(const T* __restrict__ 
       const int mine = n > 0 ? list[lo + min(chunk + sub, n - 1)] : 0;
       const float wmine = have ? weights[mine] : 0.f;
       if (extra && base == 0 && have) xsum += extra[mine];
-      const int qmine = mine / Kt;
+      const int qmine = exact_div(mine, Kt, kt_magic);
       const int m = min(16, nmax - chunk);
       // four pairs per trip, their rows in flight together
       for (int i0 = 0; i0 < m; i0 += 4) {
@@ -960,7 +970,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void vts_dfeat_kernel(const T* __restrict__ dout, const float* __restrict__ weights,
                                                        const int32_t* __restrict__ offset,
                                                        const int32_t* __restrict__ list, int tokens, int C, int Kt,
-                                                       T* __restrict__ dfeat, const float* __restrict__ extra,
+                                                       uint32_t kt_magic, T* __restrict__ dfeat, const float* __restrict__ extra,
                                                        float* __restrict__ extra_sum) {
   const int lane = threadIdx.x & (kWave - 1);
   const long long tok = xcd_contiguous_block() * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -976,7 +986,7 @@ __global__ __launch_bounds__(256) void vts_dfeat_kernel(const T* __restrict__ do
       const int mine = lane < m ? list[lo + chunk + lane] : 0;
       float wmine = lane < m ? weights[mine] : 0.f;
       if (extra && base == 0 && lane < m) xsum += extra[mine];
-      int qmine = mine / Kt;
+      int qmine = exact_div(mine, Kt, kt_magic);
       asm volatile("" : "+v"(wmine), "+v"(qmine));  // broadcast below: computed here with every lane active
       for (int i = 0; i < m; ++i) {
         const float w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wmine), i));
@@ -1194,19 +1204,19 @@ hipError_t launch_pair_gather(const void* dout, const float* weights, const int3
     const dim3 per4(round_up8(((long long)tokens + 15) / 16));
     if (dtype == 1)
       AFFMAE_LAUNCH("vts_dfeat_kernel", stream, vts_dfeat16_kernel<bf16_t>, per4, dim3(256), 0, stream,
-                    (const bf16_t*)dout, weights, offset, list, (int)tokens, C, Kt, (bf16_t*)dfeat, extra, extra_sum);
+                    (const bf16_t*)dout, weights, offset, list, (int)tokens, C, Kt, div_magic(Kt), (bf16_t*)dfeat, extra, extra_sum);
     else
       AFFMAE_LAUNCH("vts_dfeat_kernel", stream, vts_dfeat16_kernel<float>, per4, dim3(256), 0, stream,
-                    (const float*)dout, weights, offset, list, (int)tokens, C, Kt, (float*)dfeat, extra, extra_sum);
+                    (const float*)dout, weights, offset, list, (int)tokens, C, Kt, div_magic(Kt), (float*)dfeat, extra, extra_sum);
     return hipGetLastError();
   }
   const dim3 per_token(round_up8(((long long)tokens + 3) / 4));
   if (dtype == 1)
     AFFMAE_LAUNCH("vts_dfeat_kernel", stream, vts_dfeat_kernel<bf16_t>, per_token, dim3(256), 0, stream,
-                  (const bf16_t*)dout, weights, offset, list, (int)tokens, C, Kt, (bf16_t*)dfeat, extra, extra_sum);
+                  (const bf16_t*)dout, weights, offset, list, (int)tokens, C, Kt, div_magic(Kt), (bf16_t*)dfeat, extra, extra_sum);
   else
     AFFMAE_LAUNCH("vts_dfeat_kernel", stream, vts_dfeat_kernel<float>, per_token, dim3(256), 0, stream,
-                  (const float*)dout, weights, offset, list, (int)tokens, C, Kt, (float*)dfeat, extra, extra_sum);
+                  (const float*)dout, weights, offset, list, (int)tokens, C, Kt, div_magic(Kt), (float*)dfeat, extra, extra_sum);
   return hipGetLastError();
 }
 
