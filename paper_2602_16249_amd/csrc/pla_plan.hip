@@ -257,7 +257,8 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(PlanParams p) {
 // of one image.  It reads the image's slot tables (from L2), counts every tile's incidences in LDS, prefix-sums
 // the counts (an image's lists start at a place of their own, so nothing is needed of other images), reads the tables
 // again and files the incidences of its own tiles, and sorts these lists.  Against counting with atomics in the strip
-// kernel, then zero / scan / fill / sort kernels: 24 us of launches of 5 - 6 us each at 16 x 1024 strips, this one 8 us.
+// kernel, then zero / scan / fill / sort kernels (four launches of 5 - 6 us each): 24 us at 16 x 1024 strips, this one 16.8 us
+// (8.8 us at 16 x 256).
 constexpr int kRevTiles = 2048;
 constexpr int kRevThreads = 1024;
 __global__ __launch_bounds__(kRevThreads) void plan_reverse_kernel(PlanParams p, int own) {

@@ -119,3 +119,18 @@ def test_merge_at_the_stage1_shape():
     for a, ref in ((out[:nb], r_out), (g["dfeat"][:nb], rg["dfeat"]), (g["dscore"][:nb], rg["dscore"])):
         a = a.float().cpu().numpy().astype(np.float64)
         assert np.abs(a - ref).max() / np.abs(ref).max() <= 2e-2
+
+
+@pytest.mark.parametrize("dtype,B,N,C,K,S,M,n_keep,p", [
+    ("bf16", 2, 256, 32, 16, 32, 4, 100, 0.4),     # 4 pieces per row: 16 neighbours per trip
+    ("bf16", 1, 256, 24, 33, 32, 4, 64, 0.4),      # 3 pieces, the fourth lane of each row idle
+    ("f32", 1, 256, 44, 7, 32, 4, 60, 0.4),        # 11 pieces in 16 lanes
+    ("bf16", 1, 256, 104, 64, 32, 4, 51, 0.4),     # 13 pieces, K at the limit
+    ("f32", 1, 192, 132, 17, 32, 4, 50, 0.4),      # 33 pieces: one row per trip
+    ("bf16", 1, 192, 512, 9, 32, 4, 50, 0.4),      # 64 pieces exactly
+    ("f32", 1, 192, 260, 9, 32, 4, 50, 0.4),       # 65 pieces: two trips over the pieces
+    ("f32", 1, 10000, 4, 3, 16, 2, 9000, 0.4),     # more groups per image than a workgroup of the pair lists holds
+    ("bf16", 1, 10000, 8, 3, 16, 2, 8192, 0.4),    # exactly as many
+])
+def test_merge_row_shapes_and_long_group_lists(dtype, B, N, C, K, S, M, n_keep, p):
+    test_merge_forward_backward_match_oracle(dtype, B, N, C, K, S, M, n_keep, p)
