@@ -736,7 +736,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 4))) voi
 }
 
 // dk_blank, dv_blank [H,32] = sum over the strips of their parts, in a fixed order.  One workgroup per
-// (head, which of the two): 32 groups of 32 lanes, group j adds strips j, j + 32, ...
+// (head, which of the two): 32 groups of 32 lanes, group j adds strips j, j + 32, ..., eight loads in flight (one at a
+// time the few workgroups waited for one memory round trip per strip: 7.5 us at 753 strips, 3.8 as here).
 __global__ __launch_bounds__(1024) void pla_blank_reduce_kernel(const float* __restrict__ part, int strips, int H,
                                                                float* __restrict__ dk_blank,
                                                                float* __restrict__ dv_blank) {
@@ -744,7 +745,17 @@ __global__ __launch_bounds__(1024) void pla_blank_reduce_kernel(const float* __r
   const int h = blockIdx.x >> 1, which = blockIdx.x & 1;
   const int c = threadIdx.x & 31, grp = threadIdx.x >> 5;
   float s = 0.f;
-  for (int sg = grp; sg < strips; sg += 32) s += part[(((size_t)sg * H + h) * 2 + which) * kD + c];
+  for (int sg0 = grp; sg0 < strips; sg0 += 8 * 32) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int sg = sg0 + 32 * u;
+      v[u] = part[(((size_t)min(sg, strips - 1) * H + h) * 2 + which) * kD + c];
+      if (sg >= strips) v[u] = 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
   acc[grp][c] = s;
   __syncthreads();
   if (grp == 0) {

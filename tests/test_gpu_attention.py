@@ -249,3 +249,13 @@ def test_reverse_tables_of_the_plan(N, S, M, K, same):
         w["coords"] = np.full_like(w["coords"], 2.5)
     nbr, near = oracle.knn(w["coords"], None, S, M, K)
     check_attention(w, nbr, cfg.dtype, 1.0 / np.sqrt(32), near=near, S=S, M=M, use_plan=True)
+
+
+@pytest.mark.parametrize("N", [16, 512, 528, 4080, 4112, 8192 + 16])
+def test_blank_sums_over_strips(N):
+    """dk_blank / dv_blank add one part per strip, 32 x 8 strips per trip: 1, 32, 33, 255, 257 and 513 strips."""
+    print(f"case blank sums N={N}", flush=True)
+    cfg = CONFIGS["knn_scale"].scaled(B=1, N=N, C=32, H=1, K=8, S=16, M=min(4, N // 16), dtype="bf16")
+    w = make_workload(cfg, blank=True)
+    nbr, near = oracle.knn(w["coords"], None, cfg.S, cfg.M, cfg.K)
+    check_attention(w, nbr, cfg.dtype, 1.0 / np.sqrt(32), near=near, S=cfg.S, M=cfg.M, blank=True, use_plan=True)
