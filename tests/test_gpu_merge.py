@@ -134,3 +134,21 @@ def test_merge_at_the_stage1_shape():
 ])
 def test_merge_row_shapes_and_long_group_lists(dtype, B, N, C, K, S, M, n_keep, p):
     test_merge_forward_backward_match_oracle(dtype, B, N, C, K, S, M, n_keep, p)
+
+
+@pytest.mark.parametrize("N", [3000, 16000, 20001])
+@pytest.mark.parametrize("same", [1, 2, 255, 256, 257, 600])
+@pytest.mark.parametrize("distinct", [True, False])
+def test_select_when_few_keys_share_the_leading_bits(N, same, distinct):
+    """`same` scores in one run of 1024 neighbouring fp32 values (all different, or seven values repeated), the others
+    spread widely, and the cut before, at the first of, inside, at the last of and after the run."""
+    print(f"case select N={N} same={same} distinct={distinct}", flush=True)
+    rng = np.random.default_rng(N + same)
+    offs = rng.permutation(1024)[:same] if distinct else rng.integers(0, 7, size=same)
+    run = (np.float32(1.0).view(np.int32) + offs.astype(np.int32)).view(np.float32)
+    high = rng.uniform(3.0, 9.0, size=(N - same) // 3).astype(np.float32)
+    low = -np.exp(rng.uniform(-20, 20, size=N - same - high.size)).astype(np.float32)
+    score = rng.permutation(np.concatenate([run, high, low]))[None]
+    for n_keep in sorted({high.size, high.size + 1, high.size + (same + 1) // 2, high.size + same, high.size + same + 1}):
+        idx, _ = aff.affmae_merge_select(torch.from_numpy(score).cuda(), n_keep)
+        assert np.array_equal(idx.cpu().numpy(), oracle.merge_select(score, n_keep)), n_keep
