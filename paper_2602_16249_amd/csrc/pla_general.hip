@@ -7,9 +7,14 @@
 //
 // Lane layout, all three kernels: a head's row of D channels is PP = D / E pieces of 16 bytes (E = 4 fp32 or 8
 // bf16 channels); lane (r, c) = (lane / PP, lane % PP) holds piece c of the r-th of the 64 / PP rows of a trip, so a
-// load instruction fetches whole rows, PP lanes wide, and K neighbours take ceil(K * PP / 64) trips.  A dot product
-// with the query's row is a partial sum per lane and an add over the PP lanes of the row; a weighted sum of rows
-// is accumulated per lane and added over the rows at the end.  Scores are never stored.
+// load instruction fetches whole rows, PP lanes wide, and K neighbours take ceil(K * PP / 64) <= PP trips.  A dot
+// product with the query's row is a partial sum per lane, added over the PP lanes of the row so that lane (r, c) ends
+// with the value of trip c (scatter_sum): one neighbour per lane, so bias, exp, maximum, sum and dS are done once each
+// and stored or loaded with one instruction, and a weight goes back to its row's lanes by a lane move (RowValues).  A
+// weighted sum of rows is accumulated per lane and added over the rows at the end.  Scores are never stored.
+// Bound by the vector ALU and by the latency of the row loads; so the loads of several trips are issued before the
+// first is used.  16384 tokens, K = 48, two heads of 32 fp32 channels: forward 58 us, query side 71 us, key side 42 us
+// with every lane of a row holding every score and one trip's rows in flight; 29.5, 39 and 36 us as here.
 // Backward: the query-side kernel writes dq and dbias and keeps p and dS of every (query, slot) pair; dk and dv are
 // gathered, not scattered: the pairs are filed per neighbour token (the list builder shared with the decoder's and
 // the merging backward) and a wave per token adds dS q and p dout over its list - no floating-point atomics.
@@ -20,6 +25,8 @@
 #include "timing.h"
 
 #include <hip/amd_detail/amd_hip_unsafe_atomics.h>
+
+#include <type_traits>
 
 namespace affmae {
 namespace {
@@ -32,8 +39,10 @@ struct Piece;
 template <>
 struct Piece<float> {
   static constexpr int E = 4;
-  static __device__ __forceinline__ void load(const float* p, float (&v)[8]) {
-    const float4 x = *reinterpret_cast<const float4*>(p);
+  typedef float4 Raw;
+  static __device__ __forceinline__ Raw raw(const float* p) { return *reinterpret_cast<const float4*>(p); }
+  static __device__ __forceinline__ void load(const float* p, float (&v)[8]) { unpack(raw(p), v); }
+  static __device__ __forceinline__ void unpack(const Raw& x, float (&v)[8]) {
     v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
     v[4] = v[5] = v[6] = v[7] = 0.f;
   }
@@ -44,8 +53,10 @@ struct Piece<float> {
 template <>
 struct Piece<bf16_t> {
   static constexpr int E = 8;
-  static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[8]) {
-    const uint4 x = *reinterpret_cast<const uint4*>(p);
+  typedef uint4 Raw;
+  static __device__ __forceinline__ Raw raw(const bf16_t* p) { return *reinterpret_cast<const uint4*>(p); }
+  static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[8]) { unpack(raw(p), v); }
+  static __device__ __forceinline__ void unpack(const Raw& x, float (&v)[8]) {
     const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -108,8 +119,7 @@ __device__ __forceinline__ float exp_for(float x) {
 
 // <a, b> over the 16 bytes at pa and pb: fp32 pieces by fused multiply-adds, bf16 pieces by four two-element dot
 // instructions on the packed values (no unpacking)
-__device__ __forceinline__ float dot_raw(const float* pa, const float* pb) {
-  const float4 a = *reinterpret_cast<const float4*>(pa), b = *reinterpret_cast<const float4*>(pb);
+__device__ __forceinline__ float dot_raw(const float4& a, const float4& b) {
   return fmaf(a.w, b.w, fmaf(a.z, b.z, fmaf(a.y, b.y, a.x * b.x)));
 }
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
@@ -119,24 +129,63 @@ __device__ __forceinline__ float dot_raw(const uint4& a, const uint4& b) {
   acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a.z), __builtin_bit_cast(bf16x2_t, b.z), acc, false);
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a.w), __builtin_bit_cast(bf16x2_t, b.w), acc, false);
 }
-__device__ __forceinline__ float dot_raw(const bf16_t* pa, const bf16_t* pb) {
-  return dot_raw(*reinterpret_cast<const uint4*>(pa), *reinterpret_cast<const uint4*>(pb));
+
+// fn(t) for t = 0 .. N - 1, t a compile-time constant (a DPP pattern has to be one)
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& fn) {
+  if constexpr (I < N) {
+    fn(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(fn);
+  }
 }
 
-template <int E>
-__device__ __forceinline__ float dot_piece(const float (&a)[8], const float (&b)[8]) {
-  float acc = 0.f;
+// d[t] holds this lane's part of a value of trip t; lane (r, c) receives the whole value of trip c, the sum of d[c]
+// over the PP lanes of its row.  Each step halves the values that a lane still carries: PP - 1 exchanges where the
+// sum of every trip over all lanes takes PP log2(PP), and what follows is done once per value instead of once per lane.
+template <int J, int N>
+__device__ __forceinline__ float scatter_sum(const float (&d)[N], int lane) {
+  if constexpr (N == 1) {
+    return d[0];
+  } else {
+    float half[N / 2];
+    const bool up = lane & J;
 #pragma unroll
-  for (int i = 0; i < E; ++i) acc = fmaf(a[i], b[i], acc);
-  return acc;
+    for (int i = 0; i < N / 2; ++i) {
+      const float keep = up ? d[2 * i + 1] : d[2 * i], give = up ? d[2 * i] : d[2 * i + 1];
+      half[i] = keep + lane_xor_f<J>(give, lane);
+    }
+    return scatter_sum<2 * J>(half, lane);
+  }
 }
 
-// The neighbour rows of this lane in every trip: element offset of its piece in head 0 of the row, and whether the
-// trip's row is one of the K (a row past the end repeats the last neighbour and gets weight 0).
+// The way back: get<t>() is, in every lane of a row, the value that lane t of the row held.
+template <int PP>
+struct RowValues {
+  uint32_t own, low, high;
+  __device__ __forceinline__ RowValues(uint32_t x, int lane) : own(x), low(x), high(x) {
+    if constexpr (PP == 8) {  // the row's first and second quad, in both quads
+      const uint32_t other = lane_xor_u32<4>(x, lane);
+      low = (lane & 4) ? other : x;
+      high = (lane & 4) ? x : other;
+    }
+  }
+  template <int T>
+  __device__ __forceinline__ uint32_t get() const {
+    static_assert(T < PP, "a lane of the row");
+    if constexpr (PP == 16) return dpp_mov<0x150 + T>(own);           // row_newbcast
+    else if constexpr (PP == 8) return dpp_mov<(T & 3) * 0x55>(T < 4 ? low : high);  // one lane of a quad
+    else if constexpr (PP == 4) return dpp_mov<T * 0x55>(own);
+    else return dpp_mov<T * 0x05 + (2 + T) * 0x50>(own);              // PP == 2: one lane of each pair
+  }
+  template <int T>
+  __device__ __forceinline__ float getf() const { return __uint_as_float(get<T>()); }
+};
+
+// The neighbour rows of this lane in every trip: element offset of its piece in head 0 of the row (a row past the
+// end repeats the last neighbour and gets weight 0).
 template <int TR>
 struct LaneRows {
   size_t off[TR];
-  bool valid[TR];
 };
 template <int PP, int E>
 __device__ __forceinline__ LaneRows<PP> lane_rows(int mynb, long long img_base, int C, int K, int lane) {
@@ -145,9 +194,7 @@ __device__ __forceinline__ LaneRows<PP> lane_rows(int mynb, long long img_base, 
   LaneRows<PP> r;
 #pragma unroll
   for (int t = 0; t < PP; ++t) {
-    const int j = t * RPT + rl;
-    r.valid[t] = j < K;
-    const int nbj = __shfl(mynb, min(j, K - 1));
+    const int nbj = __shfl(mynb, min(t * RPT + rl, K - 1));
     r.off[t] = (size_t)(img_base + nbj) * C + (size_t)(pc * E);
   }
   return r;
@@ -159,8 +206,10 @@ __global__ __launch_bounds__(256) void pla_fwd_general_kernel(
     const int32_t* __restrict__ nbr_idx, const T* __restrict__ k_blank, const T* __restrict__ v_blank,
     long long tokens, int N, int H, int K, float scale, T* __restrict__ out, float* __restrict__ lse) {
   constexpr int E = Piece<T>::E, PP = D / E, RPT = kWave / PP, TR = PP;  // K <= 64 = RPT * TR
+  constexpr bool kHoldV = TR <= 8;  // V rows loaded with the K rows, as far as the registers go
+  constexpr int kBatch = TR < 8 ? TR : 4;
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // token, image and their addresses: scalar
   const int rl = lane / PP, pc = lane % PP;
   const int C = H * D;
   const int trips = (K + RPT - 1) / RPT;
@@ -169,45 +218,46 @@ __global__ __launch_bounds__(256) void pla_fwd_general_kernel(
     const long long img_base = (tok / N) * N;  // first token of this image
     const int mynb = min(max(nbr_idx[tok * K + min(lane, K - 1)], 0), N - 1);
     const LaneRows<TR> rows = lane_rows<PP, E>(mynb, img_base, C, K, lane);
+    const int mine = pc * RPT + rl;  // the neighbour whose score this lane holds
+    const bool valid = mine < K;
     for (int h = 0; h < H; ++h) {
-      const T* qrow = q + (tok * H + h) * D + pc * E;
-      float s[TR], smax = -INFINITY;
+      const auto qv = Piece<T>::raw(q + (tok * H + h) * D + pc * E);
+      const float bj = (bias && valid) ? Elem<T>::load(bias + (tok * H + h) * K + mine) : 0.f;
+      typename Piece<T>::Raw vr[TR];
+      float part[TR];
 #pragma unroll
-      for (int t = 0; t < TR; ++t) {
-        s[t] = -INFINITY;
-        if (t < trips) {
-          const float dot = row_sum<PP>(dot_raw(qrow, k + rows.off[t] + (size_t)h * D), lane);
-          const float bj = (bias && rows.valid[t]) ? Elem<T>::load(bias + (tok * H + h) * K + t * RPT + rl) : 0.f;
-          s[t] = rows.valid[t] ? fmaf(scale, dot, bj) : -INFINITY;
-          smax = fmaxf(smax, s[t]);
-        }
+      for (int t0 = 0; t0 < TR; t0 += kBatch) {
+        typename Piece<T>::Raw kr[kBatch];
+#pragma unroll
+        for (int t = 0; t < kBatch; ++t)
+          if (t0 + t < trips) {
+            kr[t] = Piece<T>::raw(k + rows.off[t0 + t] + (size_t)h * D);
+            if (kHoldV) vr[t0 + t] = Piece<T>::raw(v + rows.off[t0 + t] + (size_t)h * D);
+          }
+#pragma unroll
+        for (int t = 0; t < kBatch; ++t) part[t0 + t] = t0 + t < trips ? dot_raw(qv, kr[t]) : 0.f;
       }
+      const float dot = scatter_sum<1>(part, lane);  // (by every lane: also those past K hand on parts)
+      const float s = valid ? fmaf(scale, dot, bj) : -INFINITY;
       float sb = -INFINITY, eb = 0.f;
       if (k_blank) {
-        sb = scale * row_sum<PP>(dot_raw(qrow, k_blank + (size_t)h * D + pc * E), lane);
+        sb = scale * row_sum<PP>(dot_raw(qv, Piece<T>::raw(k_blank + (size_t)h * D + pc * E)), lane);
       }
-      const float m = fmaxf(all_max(smax, lane), sb);
-      float e[TR], zl = 0.f;
-#pragma unroll
-      for (int t = 0; t < TR; ++t) {
-        e[t] = 0.f;
-        if (t < trips) {
-          e[t] = rows.valid[t] ? exp_for<T>(s[t] - m) : 0.f;
-          zl += e[t];
-        }
-      }
+      const float m = fmaxf(all_max(s, lane), sb);
+      const float e = valid ? exp_for<T>(s - m) : 0.f;
       if (k_blank) eb = exp_for<T>(sb - m);
-      const float z = all_sum(pc == 0 ? zl : 0.f, lane) + eb;  // every row once
+      const float z = all_sum(e, lane) + eb;
+      const RowValues<PP> ew(__float_as_uint(e), lane);
       float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int t = 0; t < TR; ++t) {
+      static_for<TR>([&](auto t) {
         if (t < trips) {
           float vp[8];
-          Piece<T>::load(v + rows.off[t] + (size_t)h * D, vp);
+          Piece<T>::unpack(kHoldV ? vr[t] : Piece<T>::raw(v + rows.off[t] + (size_t)h * D), vp);
+          const float et = ew.template getf<t>();
 #pragma unroll
-          for (int i = 0; i < E; ++i) acc[i] = fmaf(e[t], vp[i], acc[i]);
+          for (int i = 0; i < E; ++i) acc[i] = fmaf(et, vp[i], acc[i]);
         }
-      }
+      });
       rows_sum<PP, E>(acc, lane);
       if (v_blank) {
         float vb[8];
@@ -237,9 +287,10 @@ __global__ __launch_bounds__(256) void pla_bwd_general_kernel(
     int32_t* __restrict__ pair_tok, int2* __restrict__ bounds, float* __restrict__ dk_blank,
     float* __restrict__ dv_blank) {
   constexpr int E = Piece<T>::E, PP = D / E, RPT = kWave / PP, TR = PP;
+  constexpr bool kHoldV = TR <= 8;
   extern __shared__ float smem[];
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // token, image and their addresses: scalar
   const int rl = lane / PP, pc = lane % PP;
   const int C = H * D;
   const int trips = (K + RPT - 1) / RPT;
@@ -264,46 +315,59 @@ __global__ __launch_bounds__(256) void pla_bwd_general_kernel(
       }
       if (lane == 0) bounds[tok] = make_int2(tmin, tmax);
     }
+    const int mine = pc * RPT + rl;  // the neighbour whose p and dS this lane holds
+    const bool valid = mine < K;
     for (int h = 0; h < H; ++h) {
       const T* qrow = q + (tok * H + h) * D + pc * E;
       const T* grow = dout + (tok * H + h) * D + pc * E;
       const float l = lse[tok * H + h];
-      float kp[TR][8], p[TR], dP[TR], Dl = 0.f;
+      const auto qraw = Piece<T>::raw(qrow), graw = Piece<T>::raw(grow);
+      typename Piece<T>::Raw kr[TR], vr[TR];
+#pragma unroll
+      for (int t = 0; t < TR; ++t)
+        if (t < trips) {
+          kr[t] = Piece<T>::raw(k + rows.off[t] + (size_t)h * D);
+          if (kHoldV) vr[t] = Piece<T>::raw(v + rows.off[t] + (size_t)h * D);
+        }
+      const long long at = (tok * H + h) * K + mine;
+      const float bj = (bias && valid) ? Elem<T>::load(bias + at) : 0.f;
+      float part[TR], gpart[TR];
 #pragma unroll
       for (int t = 0; t < TR; ++t) {
-        p[t] = 0.f;
-        dP[t] = 0.f;
+        part[t] = gpart[t] = 0.f;
         if (t < trips) {
-          Piece<T>::load(k + rows.off[t] + (size_t)h * D, kp[t]);
-          const float dot = row_sum<PP>(dot_raw(qrow, k + rows.off[t] + (size_t)h * D), lane);
-          dP[t] = row_sum<PP>(dot_raw(grow, v + rows.off[t] + (size_t)h * D), lane);
-          const float bj = (bias && rows.valid[t]) ? Elem<T>::load(bias + (tok * H + h) * K + t * RPT + rl) : 0.f;
-          p[t] = rows.valid[t] ? exp_for<T>(fmaf(scale, dot, bj) - l) : 0.f;
-          Dl = fmaf(p[t], dP[t], Dl);
+          part[t] = dot_raw(qraw, kr[t]);
+          gpart[t] = dot_raw(graw, kHoldV ? vr[t] : Piece<T>::raw(v + rows.off[t] + (size_t)h * D));
         }
       }
+      const float dP = scatter_sum<1>(gpart, lane);
+      const float dot = scatter_sum<1>(part, lane);
+      const float p = valid ? exp_for<T>(fmaf(scale, dot, bj) - l) : 0.f;
       float pb = 0.f, dPb = 0.f, kb[8];
       if (k_blank) {
-        Piece<T>::load(k_blank + (size_t)h * D + pc * E, kb);
-        pb = exp_for<T>(scale * row_sum<PP>(dot_raw(qrow, k_blank + (size_t)h * D + pc * E), lane) - l);
-        dPb = row_sum<PP>(dot_raw(grow, v_blank + (size_t)h * D + pc * E), lane);
+        const auto kbraw = Piece<T>::raw(k_blank + (size_t)h * D + pc * E);
+        Piece<T>::unpack(kbraw, kb);
+        pb = exp_for<T>(scale * row_sum<PP>(dot_raw(qraw, kbraw), lane) - l);
+        dPb = row_sum<PP>(dot_raw(graw, Piece<T>::raw(v_blank + (size_t)h * D + pc * E)), lane);
       }
-      const float Dsum = all_sum(pc == 0 ? Dl : 0.f, lane) + pb * dPb;  // every row once
+      const float Dsum = all_sum(valid ? p * dP : 0.f, lane) + pb * dPb;
+      const float ds = valid ? p * (dP - Dsum) : 0.f;
+      if (valid) {
+        pw[at] = p;
+        dsw[at] = ds;
+        if (dbias) Elem<T>::store(dbias + at, ds);
+      }
+      const RowValues<PP> dsr(__float_as_uint(ds), lane);
       float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int t = 0; t < TR; ++t) {
+      static_for<TR>([&](auto t) {
         if (t < trips) {
-          const float ds = p[t] * (dP[t] - Dsum);
-          if (pc == 0 && rows.valid[t]) {
-            const long long at = (tok * H + h) * K + t * RPT + rl;
-            pw[at] = p[t];
-            dsw[at] = ds;
-            if (dbias) Elem<T>::store(dbias + at, ds);
-          }
+          float kp[8];
+          Piece<T>::unpack(kr[t], kp);
+          const float dst = dsr.template getf<t>();
 #pragma unroll
-          for (int i = 0; i < E; ++i) acc[i] = fmaf(ds, kp[t][i], acc[i]);
+          for (int i = 0; i < E; ++i) acc[i] = fmaf(dst, kp[i], acc[i]);
         }
-      }
+      });
       rows_sum<PP, E>(acc, lane);
       const float dsb = pb * (dPb - Dsum);
       if (k_blank) {
@@ -345,29 +409,48 @@ __global__ __launch_bounds__(256) void pla_bwd_general_key_kernel(
     const int32_t* __restrict__ offset, const int32_t* __restrict__ list, long long tokens, int H, int K,
     uint32_t k_magic, float scale, T* __restrict__ dk, T* __restrict__ dv) {
   constexpr int E = Piece<T>::E, PP = D / E, RPT = kWave / PP;
+  constexpr int kBatch = PP < 8 ? PP : 8;  // trips whose rows are in flight together
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // token, image and their addresses: scalar
   const int rl = lane / PP, pc = lane % PP;
   for (long long tok = (long long)blockIdx.x * kWavesPerBlock + wave; tok < tokens;
        tok += (long long)gridDim.x * kWavesPerBlock) {
     const int lo = offset[tok], n = offset[tok + 1] - lo;
     for (int h = 0; h < H; ++h) {
       float ak[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, av[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      for (int base = 0; base < n; base += RPT) {
-        const int idx = base + rl;
+      for (int base = 0; base < n; base += kWave) {
+        // lane (r, c) fetches the pair that its row handles in trip c
+        const int idx = base + pc * RPT + rl;
         const bool on = idx < n;
-        const int pair = list[lo + min(idx, n - 1)];  // a row past the end repeats the last pair with weight 0
+        const int pair = list[lo + min(idx, n - 1)];  // a place past the end repeats the last pair with weight 0
         const int i = exact_div(pair, K, k_magic), j = pair - i * K;
         const long long at = ((long long)i * H + h) * K + j;
-        const float ps = on ? pw[at] : 0.f, dss = on ? dsw[at] : 0.f;
-        float qp[8], gp[8];
-        Piece<T>::load(q + ((long long)i * H + h) * D + pc * E, qp);
-        Piece<T>::load(dout + ((long long)i * H + h) * D + pc * E, gp);
+        const RowValues<PP> qi((uint32_t)i, lane), ps(__float_as_uint(on ? pw[at] : 0.f), lane),
+            dss(__float_as_uint(on ? dsw[at] : 0.f), lane);
+        const int trips = (min(n - base, kWave) + RPT - 1) / RPT;
+        static_for<PP / kBatch>([&](auto bt) {
+          typename Piece<T>::Raw qr[kBatch], gr[kBatch];
+          static_for<kBatch>([&](auto u) {
+            if (bt * kBatch + u < trips) {
+              const long long row = ((long long)(int)qi.template get<bt * kBatch + u>() * H + h) * D + pc * E;
+              qr[u] = Piece<T>::raw(q + row);
+              gr[u] = Piece<T>::raw(dout + row);
+            }
+          });
+          static_for<kBatch>([&](auto u) {
+            if (bt * kBatch + u < trips) {
+              const float pt = ps.template getf<bt * kBatch + u>(), dst = dss.template getf<bt * kBatch + u>();
+              float qp[8], gp[8];
+              Piece<T>::unpack(qr[u], qp);
+              Piece<T>::unpack(gr[u], gp);
 #pragma unroll
-        for (int c = 0; c < E; ++c) {
-          ak[c] = fmaf(dss, qp[c], ak[c]);
-          av[c] = fmaf(ps, gp[c], av[c]);
-        }
+              for (int c = 0; c < E; ++c) {
+                ak[c] = fmaf(dst, qp[c], ak[c]);
+                av[c] = fmaf(pt, gp[c], av[c]);
+              }
+            }
+          });
+        });
       }
       rows_sum<PP, E>(ak, lane);
       rows_sum<PP, E>(av, lane);

@@ -259,3 +259,19 @@ def test_blank_sums_over_strips(N):
     w = make_workload(cfg, blank=True)
     nbr, near = oracle.knn(w["coords"], None, cfg.S, cfg.M, cfg.K)
     check_attention(w, nbr, cfg.dtype, 1.0 / np.sqrt(32), near=near, S=cfg.S, M=cfg.M, blank=True, use_plan=True)
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 16), ("f32", 32), ("f32", 64), ("bf16", 16), ("bf16", 32), ("bf16", 64)])
+@pytest.mark.parametrize("K", ["1", "trip", "trip+1", "last-1", "64"])
+def test_gather_trips(dtype, d, K):
+    """Neighbour counts at the edges of a trip (64 * 16 bytes of rows), lists of more than 64 pairs under one token,
+    and, in the longest case, more tokens than the grid with blank gradients covers in one go."""
+    trip = 64 // (d * (4 if dtype == "f32" else 2) // 16)
+    K = {"1": 1, "trip": trip, "trip+1": trip + 1, "last-1": 65 - trip, "64": 64}[K]
+    N = 4500 if K == 1 else 150
+    print(f"case trips {dtype} d={d} K={K}", flush=True)
+    rng = np.random.default_rng(K + d)
+    w = make_features(1, N, 2, d, K, dtype, rng, blank=True)
+    nbr = rng.integers(0, N, size=(1, N, K)).astype(np.int32)
+    nbr[:, :, 0] = np.where(rng.uniform(size=(1, N)) < 0.6, 3, nbr[:, :, 0])
+    check_attention(w, nbr, dtype, 1.0 / np.sqrt(d), blank=True)
