@@ -131,7 +131,8 @@ __device__ __forceinline__ uint32_t wave_sort_u32(uint32_t key, int lane) {
 }
 
 // Sorts the `fill` (<= 64) keys of `pend` (LDS, owned by the wave), whose distances are at most t, ascending across
-// the lanes; returns the lower half (index) of the lane's key, undefined from lane `fill` on.  The 64-bit network
+// the lanes; returns the lower half (index) of the lane's key, undefined from lane `fill` on (so callers queue at least
+// as many as they use).  The 64-bit network
 // costs ~170 vector instructions, once most of the search's time, so the order is found on 32-bit words (26 leading
 // bits of distance / t, place in `pend`), ~65 instructions.  Where neighbouring words share their leading bits (equal
 // or nearly equal distances) the keys themselves are fetched in that order and every neighbouring pair is compared in
@@ -194,8 +195,9 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x, int lane) {
 // found (the count grows like the area, i.e. like d2), then alternates bisection on the bit pattern with steps to the
 // next larger distance.  Everything at or below T is nearer than everything above it, so the K nearest are among the
 // counted candidates, which are sorted once.  No such T exists when more than 64 - K + 1 candidates share a distance:
-// then the nearer ones and, in index order, as many of the equal ones as fit are sorted (candidates that are not
-// ORDERED are merged row by row into a running top 64).  Either way the result is exact.
+// then the nearer ones and, in index order, as many of the equal ones as fit are sorted.  Candidates that are not
+// ORDERED, or of which fewer than K have a distance that is no NaN, are merged row by row into a running top 64 (a NaN
+// sorts by its bits, after every distance; the queue would have too few).  Either way the result is exact.
 template <bool ORDERED, class Each, class KeyAt>
 __device__ __forceinline__ uint32_t select_nearest(int rows, int K, uint32_t& guess, key_t* pend, int lane, Each each,
                                                    KeyAt key_at) {
@@ -239,10 +241,12 @@ __device__ __forceinline__ uint32_t select_nearest(int rows, int K, uint32_t& gu
     int fill = 0;
     each([&](uint32_t d2, uint32_t low) { fill = queue_row(pend, fill, lo >= 0 && d2 <= (uint32_t)lo ? d2 : 0xffffffffu, low, (uint32_t)hi); });
     each([&](uint32_t d2, uint32_t low) { fill = queue_row<false>(pend, fill, d2 == (uint32_t)hi ? d2 : 0xffffffffu, low, (uint32_t)hi); });
-    wave_lds_sync();
-    const uint32_t id = sort_queued(pend, fill, (uint32_t)hi, lane);
-    wave_lds_sync();
-    return id;
+    if (fill >= K) {  // wave-uniform
+      wave_lds_sync();
+      const uint32_t id = sort_queued(pend, fill, (uint32_t)hi, lane);
+      wave_lds_sync();
+      return id;
+    }
   }
   key_t best = kKeyMax;
 #pragma unroll 1

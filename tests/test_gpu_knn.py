@@ -154,3 +154,53 @@ def test_knn_rows_and_ties(S, M, K, explicit):
         rnbr, rnear = oracle.knn(coords, cid, S, M, K)
         assert np.array_equal(near, rnear)
         assert np.array_equal(nbr, rnbr)
+
+
+def _reference_knn_by_bits(coords, S, M, K):
+    """Near clusters and neighbours of contiguous clusters by (bits of the fp32 squared distance, index): NaN distances
+    come after every other, as the library orders them (the C oracle compares values, which NaN has no order in)."""
+    B, N, _ = coords.shape
+    G = -(-N // S)
+
+    def keys(q, x, idx):
+        with np.errstate(invalid="ignore", over="ignore"):
+            d = x - q
+            d2 = d[:, 0] * d[:, 0] + d[:, 1] * d[:, 1]  # fp32, one operation at a time
+        bits = np.where(np.isnan(d2), np.uint32(0x7fc00000), d2.view(np.uint32)).astype(np.uint64)
+        return (bits << np.uint64(32)) | idx.astype(np.uint64)
+
+    nbr = np.empty((B, N, K), dtype=np.int32)
+    near = np.empty((B, G, M), dtype=np.int32)
+    for b in range(B):
+        with np.errstate(invalid="ignore"):
+            cen = np.stack([np.cumsum(coords[b, c * S:(c + 1) * S].astype(np.float64), axis=0)[-1] /
+                            len(coords[b, c * S:(c + 1) * S]) for c in range(G)]).astype(np.float32)
+        for c in range(G):
+            near[b, c] = np.argsort(keys(cen[c], cen, np.arange(G)))[:M]
+            cand = np.concatenate([np.arange(e * S, min((e + 1) * S, N)) for e in near[b, c]])
+            for i in range(c * S, min((c + 1) * S, N)):
+                nbr[b, i] = cand[np.argsort(keys(coords[b, i], coords[b, cand], cand))[:K]]
+    return nbr, near
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, 1e30])
+@pytest.mark.parametrize("N,S,M,K", [(320, 32, 4, 24), (500, 32, 6, 64), (300, 64, 5, 40), (1100, 50, 22, 33)])
+def test_knn_without_enough_distances(N, S, M, K, bad):
+    """Tokens whose coordinates are NaN, infinite or too large to square: a few scattered ones, a whole cluster, and so
+    many that a token has fewer than K distances left.  Every index is a candidate's, ordered by the distance's bits."""
+    print(f"case bad={bad} N={N} S={S} M={M} K={K}", flush=True)
+    rng = np.random.default_rng(N + K)
+    coords = rng.uniform(0, 100, size=(4, N, 2)).astype(np.float32)
+    coords[0, rng.permutation(N)[:5], 0] = bad
+    coords[1, S:2 * S, 1] = bad
+    coords[2, rng.permutation(N)[:N - 7], 0] = bad
+    coords[3, :, :] = bad
+    nbr, near = _gpu_knn(coords, None, S, M, K)
+    rnbr, rnear = _reference_knn_by_bits(coords, S, M, K)
+    assert np.array_equal(near, rnear)
+    assert np.array_equal(nbr, rnbr)
+    # the same clusters as an explicit assignment
+    cid = np.broadcast_to((np.arange(N) // S).astype(np.int32), (4, N)).copy()
+    nbr_e, near_e = _gpu_knn(coords, cid, S, M, K)
+    assert np.array_equal(near_e, rnear)
+    assert np.array_equal(nbr_e, rnbr)

@@ -79,6 +79,29 @@ def test_table_all_tokens_coincide():
     assert np.array_equal(table, np.broadcast_to(np.arange(7, dtype=np.int32), (2, 6, 6, 7)))
 
 
+@pytest.mark.parametrize("bad", [np.nan, np.inf, 1e30])
+@pytest.mark.parametrize("Nv,Kt", [(40, 20), (200, 9), (1024, 64)])
+def test_table_without_enough_distances(Nv, Kt, bad):
+    """Visible tokens without a finite distance (a few, all but seven, all): entries are tokens, ordered by the distance's
+    bits (a NaN after every other) and then by index."""
+    print(f"case table bad={bad} Nv={Nv} Kt={Kt}", flush=True)
+    rng = np.random.default_rng(Nv)
+    vis = rng.uniform(0, 64, size=(3, Nv, 2)).astype(np.float32)
+    vis[0, rng.permutation(Nv)[:5], 0] = bad
+    vis[1, rng.permutation(Nv)[:Nv - 7], 1] = bad
+    vis[2] = bad
+    table = aff.affmae_vts_table(torch.from_numpy(vis).cuda(), (8, 8, 0.0, 0.0, 8.0), Kt).cpu().numpy()
+    centre = (np.arange(8, dtype=np.float32) + np.float32(0.5)) * np.float32(8)
+    for b in range(3):
+        for iy in range(8):
+            for ix in range(8):
+                with np.errstate(invalid="ignore", over="ignore"):
+                    dx, dy = centre[ix] - vis[b, :, 0], centre[iy] - vis[b, :, 1]
+                    d2 = dx * dx + dy * dy  # fp32, one operation at a time
+                bits = np.where(np.isnan(d2), np.uint32(0x7fc00000), d2.view(np.uint32))
+                assert np.array_equal(table[b, iy, ix], np.argsort(bits, kind="stable")[:Kt])
+
+
 SAMPLE_CASES = [
     # dtype, B, Mq, Nv, C, Hg, Wg, Kt, p
     ("f32", 1, 7, 9, 2, 3, 3, 1, 1.0),         # one candidate: a copy
