@@ -19,6 +19,7 @@
 //             gathered, not scattered: the pairs are filed per token (the list builder of the virtual-token
 //             backward) and every token adds up w * dout, respectively dz, over its own list.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_util.h"
 #include "launch.h"
@@ -383,21 +384,37 @@ __global__ __launch_bounds__(256) void merge_fwd_kernel(const T* __restrict__ fe
       const bool pon = pc0 + pc < pieces;
       const int c0 = min(pc0 + pc, pieces - 1) * CH;  // lanes past the row's end repeat its last piece (unused)
       float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      for (int j0 = 0; j0 < K; j0 += 2 * RW) {
-        float wj[2], f[2][8];
+      // U trips; FULL: all their rows are among the K, otherwise rows past K repeat the last neighbour's and are set to 0 (a
+      // weight of 0 alone would turn an infinite feature of that neighbour into a NaN)
+      auto trips = [&](int j0, auto count, auto full) {
+        constexpr int U = decltype(count)::value;
+        constexpr bool FULL = decltype(full)::value;
+        float wj[U], f[U][8];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int j = j0 + u * RW + rs, jj = min(j, K - 1);
-          const float wraw = __shfl(nb.w, jj);  // (every lane takes part in the shuffles; rows past K get weight 0)
+        for (int u = 0; u < U; ++u) {
+          const int j = j0 + u * RW + rs, jj = FULL ? j : min(j, K - 1);
+          wj[u] = __shfl(nb.w, jj);  // (every lane takes part in the shuffles)
           const int ij = __shfl(nb.idx, jj);
-          wj[u] = j < K ? wraw : 0.f;
           Piece16<T>::load(rows + (uint32_t)(ij * C + c0), f[u]);  // (row offsets inside an image fit 32 bits on this path)
+          if (!FULL) {
+#pragma unroll
+            for (int e = 0; e < CH; ++e) f[u][e] = j < K ? f[u][e] : 0.f;
+          }
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
           for (int e = 0; e < CH; ++e) acc[e] = fmaf(wj[u], f[u][e], acc[e]);
+      };
+      typedef std::integral_constant<int, 1> One;
+      typedef std::integral_constant<int, 2> Two;
+      int j0 = 0;
+      for (; j0 + 2 * RW <= K; j0 += 2 * RW) trips(j0, Two{}, std::true_type{});
+      if (j0 + RW <= K) {
+        trips(j0, One{}, std::true_type{});
+        j0 += RW;
       }
+      if (j0 < K) trips(j0, One{}, std::false_type{});
 #pragma unroll
       for (int e = 0; e < CH; ++e) acc[e] = lanes_sum<PP, 32>(acc[e], lane);  // add up the row groups
       if (rs == 0 && pon) Piece16<T>::store(orow + c0, acc);

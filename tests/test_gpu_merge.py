@@ -136,6 +136,32 @@ def test_merge_row_shapes_and_long_group_lists(dtype, B, N, C, K, S, M, n_keep, 
     test_merge_forward_backward_match_oracle(dtype, B, N, C, K, S, M, n_keep, p)
 
 
+@pytest.mark.parametrize("dtype,C,K", [
+    ("bf16", 512, 9), ("bf16", 256, 3), ("bf16", 64, 8), ("bf16", 64, 24), ("bf16", 64, 5), ("bf16", 32, 48),
+    ("f32", 256, 5), ("f32", 64, 4), ("f32", 64, 12), ("f32", 64, 13), ("f32", 8, 16), ("f32", 6, 7), ("f32", 260, 3)])
+def test_merge_of_infinite_features(dtype, C, K):
+    """One token's features are infinite.  An anchor with that token among its neighbours, in any place (the last one is
+    repeated to fill a trip of rows), has an infinite merged feature; every other anchor is what it was."""
+    print(f"case merge infinite {dtype} C={C} K={K}", flush=True)
+    rng = np.random.default_rng(C + K)
+    N, n_keep, hot = 128, 100, 77
+    coords = rng.uniform(0, 10, size=(1, N, 2)).astype(np.float32)
+    nbr = np.stack([rng.permutation(N)[:K] for _ in range(N)])[None].astype(np.int32)
+    nbr[0, :40, K - 1] = hot  # (a row may then hold it twice: its weight counts twice)
+    score = rng.normal(size=(1, N)).astype(np.float32)
+    feat = rng.normal(size=(1, N, C)).astype(np.float32)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    up = lambda x: torch.from_numpy(x).cuda()
+    args = (up(coords), up(score), up(nbr), up(np.arange(n_keep, dtype=np.int32)[None]), 0.1)
+    clean = aff.affmae_merge_fwd(up(feat).to(tdt), *args).float().cpu().numpy()
+    feat[0, hot] = np.inf
+    out = aff.affmae_merge_fwd(up(feat).to(tdt), *args).float().cpu().numpy()
+    has = (nbr[0, :n_keep] == hot).any(axis=1)
+    assert has.any() and not has.all()
+    assert np.all(out[0, has] == np.inf)
+    assert np.array_equal(out[0, ~has], clean[0, ~has])
+
+
 @pytest.mark.parametrize("N", [3000, 16000, 20001])
 @pytest.mark.parametrize("same", [1, 2, 255, 256, 257, 600])
 @pytest.mark.parametrize("distinct", [True, False])
