@@ -20,6 +20,8 @@
 #include "select_util.h"
 #include "timing.h"
 
+#include <algorithm>
+
 namespace affmae {
 namespace {
 
@@ -314,14 +316,8 @@ int next_pow2(int n) {
 
 size_t cluster_workspace_bytes(int B, int N) { return (size_t)B * next_pow2(N) * sizeof(word_t); }
 
-hipError_t launch_cluster(const float* coords, int B, int N, int S, double x0, double y0, double w, double h,
-                          int32_t* order, int32_t* cluster_id, void* workspace, hipStream_t stream) {
-  ClusterParams p;
-  p.coords = coords; p.N = N; p.npad = next_pow2(N); p.S = S;
-  p.x0 = x0; p.y0 = y0; p.w = w; p.h = h;
-  p.words = static_cast<word_t*>(workspace);
-  p.order = order; p.cluster_id = cluster_id;
-  p.s_magic = div_magic(S);
+static hipError_t launch_images(const ClusterParams& p, int B, hipStream_t stream) {
+  const int N = p.N;
 #define AFFMAE_SORT(W, RUNS, WHOLE, CHUNKS, NETWORK)                                                               \
   AFFMAE_LAUNCH("cluster_sort_chunk_kernel", stream, (cluster_sort_chunk_kernel<W, RUNS, WHOLE>),                  \
                 dim3((unsigned)B * (CHUNKS)), dim3(kSortThreads * (RUNS)), 0, stream, p, CHUNKS, NETWORK)
@@ -362,6 +358,28 @@ hipError_t launch_cluster(const float* coords, int B, int N, int S, double x0, d
   }
   AFFMAE_LAUNCH("cluster_emit_kernel", stream, cluster_emit_kernel, dim3((N + 255) / 256, B), dim3(256), 0, stream, p);
   return hipGetLastError();
+}
+
+hipError_t launch_cluster(const float* coords, int B, int N, int S, double x0, double y0, double w, double h,
+                          int32_t* order, int32_t* cluster_id, void* workspace, hipStream_t stream) {
+  ClusterParams p;
+  p.N = N; p.npad = next_pow2(N); p.S = S;
+  p.x0 = x0; p.y0 = y0; p.w = w; p.h = h;
+  p.s_magic = div_magic(S);
+  // A launch has fewer than 2^32 threads: the chunk sort gives an image at most 256 or, beyond 512 tokens, one for every
+  // two of its padded words.  (The batch is cut only where it would not be accepted: 2^24 images, 2^33 tokens.)
+  const long long threads = N <= 2 * kSortThreads ? kSortThreads : std::max(kChunk, p.npad) / 2;
+  const int most = (int)std::min((long long)B, 0xffffffffll / threads);
+  for (int b0 = 0; b0 < B; b0 += most) {
+    p.coords = coords + (size_t)b0 * N * 2;
+    p.words = static_cast<word_t*>(workspace) + (size_t)b0 * p.npad;
+    p.order = order + (size_t)b0 * N;
+    p.cluster_id = cluster_id ? cluster_id + (size_t)b0 * N : nullptr;
+    const hipError_t e = launch_images(p, std::min(most, B - b0), stream);
+    if (e != hipSuccess) return e;
+    if (B - b0 <= most) break;  // (b0 + most may pass the largest int)
+  }
+  return hipSuccess;
 }
 
 }  // namespace affmae

@@ -92,3 +92,15 @@ def test_cluster_sizes_at_the_edges(N):
     rorder, rcid = oracle.cluster(coords, 48, (0.0, 0.0, 40.0, 40.0))
     assert np.array_equal(order, rorder)
     assert np.array_equal(cid, rcid)
+
+
+def test_cluster_many_small_images():
+    """2^24 images of two tokens: with 256 threads for each, more than one launch can have."""
+    B = 1 << 24
+    x = torch.rand(B, device="cuda")
+    coords = torch.stack([torch.stack([x, x], -1), torch.stack([1 - x, 1 - x], -1)], dim=1).contiguous()
+    order, cid = aff.affmae_cluster(coords, 1, (0.0, 0.0, 1.0, 1.0))
+    q = (coords[..., 0].double() * 65536).floor().clamp(0, 65535)  # both axes alike: the curve follows it
+    first = (q[:, 1] < q[:, 0]).int()
+    assert torch.equal(order, torch.stack([first, 1 - first], dim=1))
+    assert torch.equal(cid, torch.stack([first, 1 - first], dim=1))  # (its own inverse)
