@@ -365,9 +365,11 @@ hipError_t launch_pla_plan(const int32_t* nbr_idx, const int32_t* near, int B, i
   p.runs_stride = L.runs_stride; p.places = L.places;
   const dim3 per_strip((L.strips + 3) / 4);
   // One workgroup per group of tiles reads its image's whole slot table: quadratic in the tiles, so only up to kRevTiles
-  // (LDS counters), and with list places that int32 can number.
+  // (LDS counters), with list places that int32 can number and no more threads than a launch can have (2^32 - 1).
   const int tiles = p.strips_per_image;
-  p.count_tiles = tiles > kRevTiles || (long long)L.strips * L.max_slots >= (1ll << 31);
+  const int own = std::max(16, (tiles + 15) / 16);  // about 16 workgroups per image
+  const long long groups = (long long)B * ((tiles + own - 1) / own);
+  p.count_tiles = tiles > kRevTiles || (long long)L.strips * L.max_slots >= (1ll << 31) || groups * kRevThreads >= (1ll << 32);
   if (p.count_tiles)
     AFFMAE_LAUNCH("plan_zero_kernel", stream, plan_zero_kernel, dim3((L.strips + 255) / 256), dim3(256), 0, stream,
                   p.rev_count, p.rev_cursor, L.strips);
@@ -377,9 +379,7 @@ hipError_t launch_pla_plan(const int32_t* nbr_idx, const int32_t* near, int B, i
   else if (ne <= 12) AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<12>, per_strip, dim3(256), 0, stream, p);
   else AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<kMaxEntries>, per_strip, dim3(256), 0, stream, p);
   if (!p.count_tiles) {
-    const int own = std::max(16, (tiles + 15) / 16);  // about 16 workgroups per image
-    AFFMAE_LAUNCH("plan_reverse_kernel", stream, plan_reverse_kernel, dim3(B * ((tiles + own - 1) / own)), dim3(kRevThreads), 0,
-                  stream, p, own);
+    AFFMAE_LAUNCH("plan_reverse_kernel", stream, plan_reverse_kernel, dim3((unsigned)groups), dim3(kRevThreads), 0, stream, p, own);
     return hipGetLastError();
   }
   AFFMAE_LAUNCH("plan_scan_kernel", stream, plan_scan_kernel, dim3((L.strips + 1023) / 1024), dim3(256), 0, stream,

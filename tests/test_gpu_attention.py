@@ -5,8 +5,10 @@ Tolerance (per tensor, forward and every gradient): max|gpu - ref| / max|ref|
 double precision on the same stored (already rounded) inputs."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
+import paper_2602_16249_amd as aff
 from helpers import check_attention
 from workloads import CONFIGS, make_features, make_workload, random_neighbours
 
@@ -151,7 +153,6 @@ def test_random_shapes_through_the_tiled_kernels(seed):
 def test_instrumented_library_gives_the_same_bits():
     """The bench takes its per-kernel times in the instrumented twin library (the same sources with events around
     every launch): its tiled forward and backward results are bit-equal to the product library's."""
-    import paper_2602_16249_amd as aff
     from helpers import run_gpu_attention
     cfg = CONFIGS["ft_s1_1024"].scaled(B=1)
     print("case ft_s1_1024 B=1 product against instrumented library", flush=True)
@@ -215,7 +216,6 @@ def test_short_last_cluster_end_to_end(N, tiled):
     (whole 16-token tiles, short last cluster), N = 4001 (a last strip and token tile of one token, which is also
     the whole last cluster), N = 3983 (fifteen tokens in the last tile)."""
     import torch
-    import paper_2602_16249_amd as aff
     print(f"case end to end N={N}", flush=True)
     S, M, K, H, d = 64, 8, 48, 2, 32
     cfg = CONFIGS["mae_pt_s1_1024"].scaled(B=2, N=N, C=H * d, H=H, K=K, S=S, M=M, dtype="bf16")
@@ -275,3 +275,27 @@ def test_gather_trips(dtype, d, K):
     nbr = rng.integers(0, N, size=(1, N, K)).astype(np.int32)
     nbr[:, :, 0] = np.where(rng.uniform(size=(1, N)) < 0.6, 3, nbr[:, :, 0])
     check_attention(w, nbr, dtype, 1.0 / np.sqrt(d), blank=True)
+
+
+def test_plan_of_many_small_images():
+    """2^22 images of one token each: the one-launch reverse tables would need more threads than a launch can have.  The
+    images repeat 1024 different ones, whose gradients a plan of 1024 images gives too."""
+    B, few = 1 << 22, 1024
+    print(f"case plan B={B} N=1", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(22)
+    q, k, v, dout = (torch.randn(few, 1, 1, 32, device="cuda", generator=g).bfloat16() for _ in range(4))
+    bias = torch.randn(few, 1, 1, 1, device="cuda", generator=g).bfloat16()
+    kb, vb = (torch.randn(1, 32, device="cuda", generator=g).bfloat16() for _ in range(2))
+
+    def run(n):
+        rep = lambda t: t.repeat(n // few, 1, 1, 1)
+        nbr = torch.zeros(n, 1, 1, dtype=torch.int32, device="cuda")
+        plan = aff.affmae_pla_plan(nbr, nbr, 16, 1)
+        a = (rep(q), rep(k), rep(v), rep(bias), nbr)
+        out, lse = aff.affmae_pla_fwd(*a, 0.2, nbr, 16, 1, kb, vb, plan=plan)
+        gr = aff.affmae_pla_bwd(*a, out, lse, rep(dout), 0.2, nbr, 16, 1, kb, vb, plan=plan)
+        return [out, lse] + [gr[name] for name in ("dq", "dk", "dv", "dbias")]
+
+    for big, small in zip(run(B), run(few)):
+        assert small.float().abs().max() > 0
+        assert torch.equal(big.view(B // few, *small.shape), small[None].expand(B // few, *small.shape))
