@@ -137,8 +137,12 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream() -> int:
-    # the handle alone (torch.cuda.current_stream() builds an object around it on every call)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    # the handle alone (torch.cuda.current_stream() builds an object around it on every call), by a function outside
+    # torch's public interface: the public one serves where it is missing
+    raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw_stream(torch.cuda.current_device())
 
 
 def _dev(t: torch.Tensor, name: str, dtype=None, shape=None) -> torch.Tensor:

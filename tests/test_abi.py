@@ -186,6 +186,21 @@ def test_binding_refuses_host_tensors():
         aff.affmae_knn(torch.zeros(1, 64, 2), None, 8, 2, 4)
 
 
+@pytest.mark.parametrize("missing", [False, True])
+def test_stream_handle(monkeypatch, missing):
+    """The handle of the current device's current stream, also on a torch without the internal function that gives it
+    without an object."""
+    import types
+    from paper_2602_16249_amd import binding
+    monkeypatch.setattr(binding.torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(binding.torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    if missing:
+        monkeypatch.delattr(binding.torch._C, "_cuda_getCurrentRawStream", raising=False)
+    else:
+        monkeypatch.setattr(binding.torch._C, "_cuda_getCurrentRawStream", lambda device: {3: 77}[device], raising=False)
+    assert binding._stream() == 77
+
+
 def test_relpos_rejects_bad_arguments_on_host():
     lib = aff.load_library()
     one = ctypes.c_void_p(256)  # never dereferenced: validation fails first
