@@ -111,7 +111,9 @@ __global__ __launch_bounds__(256) void near_kernel(const float* __restrict__ cen
 // The K nearest among the members of a cluster's M near clusters, for the cluster's tokens; a wave serves every
 // (4 parts)-th of them.  Coordinates and token ids of the candidates are staged in LDS once per workgroup, in rows of
 // 64; up to 1024 candidates a wave then holds all its tokens long, a lane one candidate of every row (ROWS > 0), more
-// are read from LDS as they are needed (ROWS = 0).
+// are read from LDS as they are needed (ROWS = 0): a count of 4096 of them costs several times what is left of a query,
+// so there it may be up to 128 and the steps interpolate (2 images of 4096 tokens, 64 clusters of 64 near, K = 64: 282 us
+// with the steps of the other forms, 85 us as here; 8 images, 4 clusters of 512 near, K = 48: 104 and 91 us).
 // Per token the wave looks for a distance threshold T with K <= #{candidates with d2 <= T} <= 64 by counting
 // (ballots), starting from the previous token's threshold, and sorts the counted candidates once by (d2, index): see
 // select_nearest.  The near clusters are taken in index order, so that candidates are queued in token order
@@ -126,8 +128,9 @@ __global__ __launch_bounds__(256) void near_kernel(const float* __restrict__ cen
 constexpr int kKnnWaves = 4;
 constexpr int kNearInSearch = kKnnWaves * kWave;
 constexpr int kFullChipWaves = 8192;  // 256 CUs x 4 SIMDs x 8 waves
-size_t knn_lds_bytes(int rows) {
-  return kKnnWaves * kWave * sizeof(key_t) + (size_t)rows * kWave * (sizeof(float2) + sizeof(int32_t));
+constexpr int pend_keys(int ROWS) { return ROWS ? kWave : 2 * kWave; }  // queue of a wave: see select_nearest
+size_t knn_lds_bytes(int ROWS, int rows) {
+  return kKnnWaves * pend_keys(ROWS) * sizeof(key_t) + (size_t)rows * kWave * (sizeof(float2) + sizeof(int32_t));
 }
 template <int ROWS, bool MEMBERS>
 __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __restrict__ coords,
@@ -138,7 +141,8 @@ __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __re
                                                               int32_t* __restrict__ nbr_idx) {
   extern __shared__ key_t lds[];
   __shared__ int32_t near_lds[kWave];
-  float2* cxy = reinterpret_cast<float2*>(lds + kKnnWaves * kWave);        // [rows][64]
+  constexpr int kPend = pend_keys(ROWS);
+  float2* cxy = reinterpret_cast<float2*>(lds + kKnnWaves * kPend);        // [rows][64]
   int32_t* ctok = reinterpret_cast<int32_t*>(cxy + (size_t)rows * kWave);  // [rows][64]
   const int gc = blockIdx.x / parts, part = blockIdx.x - gc * parts;
   const int b = gc / G, c = gc - b * G;
@@ -147,7 +151,7 @@ __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __re
   const int32_t* mem = MEMBERS ? members + (size_t)b * N : nullptr;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  key_t* pend = lds + wave * kWave;
+  key_t* pend = lds + wave * kPend;
   // lane m: the m-th of the near clusters in index order (M <= 64; they are distinct)
   int near_sorted;
   auto index_order = [&](int id) -> int {  // lane m < M: the m-th of the ids that lanes 0 .. M - 1 give
@@ -170,7 +174,7 @@ __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __re
       if (G > 1) {
         best = pend[lane];
         for (int row = 1; row * kWave < G; ++row) {  // the 64 smallest of two sorted rows are bitonic
-          const key_t rev = lds[row * kWave + kWave - 1 - lane];
+          const key_t rev = lds[row * kPend + kWave - 1 - lane];
           best = wave_bitonic_merge(best < rev ? best : rev, lane);
         }
       }
@@ -229,7 +233,7 @@ __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __re
       for (int row = 0; row < ROWS; ++row) d2[row] = __float_as_uint(dist2(qx, qy, cx[row], cy[row]));
       if (guess == 0u)  // no estimate: one of the distances, so that the count is not 0
         guess = min((uint32_t)__builtin_amdgcn_readlane(row_d2(0), kWave / 2), 0x7f800000u);
-      const uint32_t best = select_nearest<!MEMBERS>(
+      const uint32_t best = select_nearest<!MEMBERS, ROWS ? kOneRow : kTwoSearched, ROWS == 0>(
           rows, K, guess, pend, lane,
           [&](auto f) {
 #pragma unroll
@@ -271,10 +275,10 @@ hipError_t launch_knn(const KnnArgs& a, hipStream_t stream) {
 #define AFFMAE_KNN(R)                                                                                               \
   do {                                                                                                              \
     if (members)                                                                                                    \
-      AFFMAE_LAUNCH("knn_kernel", stream, (knn_kernel<R, true>), grid, block, knn_lds_bytes(rows), stream, a.coords, members, \
+      AFFMAE_LAUNCH("knn_kernel", stream, (knn_kernel<R, true>), grid, block, knn_lds_bytes(R, rows), stream, a.coords, members, \
                     a.centroid, a.near_clusters, a.N, a.S, a.M, a.K, a.G, rows, parts, div_magic(a.S), a.nbr_idx);              \
     else                                                                                                            \
-      AFFMAE_LAUNCH("knn_kernel", stream, (knn_kernel<R, false>), grid, block, knn_lds_bytes(rows), stream, a.coords, members, \
+      AFFMAE_LAUNCH("knn_kernel", stream, (knn_kernel<R, false>), grid, block, knn_lds_bytes(R, rows), stream, a.coords, members, \
                     a.centroid, a.near_clusters, a.N, a.S, a.M, a.K, a.G, rows, parts, div_magic(a.S), a.nbr_idx);              \
   } while (0)
   if (rows <= 2) AFFMAE_KNN(2);

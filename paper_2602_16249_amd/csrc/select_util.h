@@ -193,46 +193,78 @@ __device__ __forceinline__ key_t wave_min_key(key_t x, int lane) {
 // for every row, d2 being the bit pattern of the lane's squared distance (ordered like the value, since d2 >= +0; above
 // every distance's bits where the lane has no candidate) and low the lower half of its key, ordered like the index.
 // key_at(row, lane) is any candidate's key (kKeyMax where the lane has none).  `pend`: 64 keys of LDS owned by the
-// wave.  ORDERED: low ascends with row and lane.  Returns the lower halves of the keys in ascending order of the keys
-// across the lanes (the first K are the answer).
+// wave, 128 unless WIDE is kOneRow.  ORDERED: low ascends with row and lane.  Returns the lower halves of the keys in
+// ascending order of the keys across the lanes (the first K are the answer).
 //
-// The wave looks for a distance threshold T with K <= #{d2 <= T} <= 64 by counting with ballots: it starts from
-// `guess` (the threshold that worked for the previous, nearby query, or an estimate; not 0), scales it by wanted /
+// The wave looks for a distance threshold T with K <= #{d2 <= T} <= 64 by counting with ballots.  It starts from
+// `guess` (the threshold that worked for the previous, nearby query, or an estimate; not 0) and scales it by wanted /
 // found (the count grows like the area, i.e. like d2), then alternates bisection on the bit pattern with steps to the
-// next larger distance.  Everything at or below T is nearer than everything above it, so the K nearest are among the
-// counted candidates, which are sorted once.  No such T exists when more than 64 - K + 1 candidates share a distance:
-// then the nearer ones and, in index order, as many of the equal ones as fit are sorted (candidates that are not
-// ORDERED are merged row by row into a running top 64).  Where fewer than K candidates have a distance that is no NaN,
-// that queue would have too few: the keys are then taken one by one, NaN by its bits after every distance (merged like
-// the others they cost the search of 512 candidates two registers too many for eight waves per SIMD, 5 - 10 % of its
-// time on every input).  Either way the result is exact.
-template <bool ORDERED, class Each, class KeyAt>
+// next larger distance (which end the search where many candidates share one).  Everything at or below T is nearer than
+// everything above it, so the K nearest are among the counted candidates, which are sorted once.
+// LINEAR, for queries that may lie away from all candidates (the count then grows late and steeply) and for counts that
+// cost more than a few multiplications: once one threshold had too many, it interpolates between the closest ones with
+// too few and too many, in place of scaling and, up to the 18th step, of bisecting (grid points up to half the frame
+// away from 1024 tokens, 9 of them wanted: 3.7 steps a query without, 1.5 with it; with candidates in registers and
+// queries among them it is the slower one, 77 us without and 98 with it for 8 images of 16384 tokens in 12 blobs).
+// WIDE: where a count costs much, or the window would be next to nothing, it may be up to 128, and the K nearest of
+// these are found in the same way (kTwoSearched) or by sorting both rows (kTwoSorted: 64-bit keys, ~400 instructions and
+// registers for their lane masks).
+// No such T exists when more candidates share a distance than the window takes: then the nearer ones and, in index order,
+// as many of the equal ones as fit are sorted (candidates that are not ORDERED are merged row by row into a running top
+// 64).  Where fewer than K candidates have a distance that is no NaN, that queue would have too few: the keys are then
+// taken one by one, NaN by its bits after every distance (merged like the others they cost the search of 512 candidates
+// two registers too many for eight waves per SIMD, 5 - 10 % of its time on every input).  Either way the result is exact.
+enum { kOneRow, kTwoSearched, kTwoSorted };
+template <bool ORDERED, int WIDE, bool LINEAR, class Each, class KeyAt>
 __device__ __forceinline__ uint32_t select_nearest(int rows, int K, uint32_t& guess, key_t* pend, int lane, Each each,
                                                    KeyAt key_at) {
-  // invariant: count(lo) < K (lo = -1: nothing known), count(hi) > 64 or hi = +inf bits
-  int lo = -1, hi = 0x7f800000;
+  constexpr int most = WIDE != kOneRow ? 2 * kWave : kWave;
+  // invariant: count(lo) = at_lo < K (lo = -1: nothing known), count(hi) = at_hi > most (at_hi = -1: hi = +inf, not counted)
+  int lo = -1, hi = 0x7f800000, at_lo = 0, at_hi = -1;
   uint32_t t = __builtin_amdgcn_readfirstlane(guess);  // (a scalar, and known to be one)
 #pragma unroll 1
-  for (int it = 0; it < 96; ++it) {  // (the bisections alone end it after 31 of them)
+  for (int it = 0; it < 96; ++it) {  // (from the 19th on every other step bisects: 31 of these end it)
     int n = 0;
     each([&](uint32_t d2, uint32_t) { n += __popcll(__ballot(d2 <= t)); });
-    if (n >= K && n <= kWave) {
+    if (n >= K && n <= most) {
       guess = t;
       int fill = 0;
       each([&](uint32_t d2, uint32_t low) { fill = queue_row(pend, fill, d2, low, t); });
       wave_lds_sync();
+      if constexpr (WIDE != kOneRow) {
+        if (n > kWave) {  // wave-uniform
+          const key_t a = pend[lane], b = lane < n - kWave ? pend[kWave + lane] : kKeyMax;
+          wave_lds_sync();
+          if constexpr (WIDE == kTwoSorted) return (uint32_t)topk_push(wave_sort(a, lane), b, lane, K - 1);
+          uint32_t inner =
+              __float_as_uint(__uint_as_float(t) * ((float)(K + kWave) * 0.5f * __builtin_amdgcn_rcpf((float)n)));
+          return select_nearest<ORDERED, kOneRow, false>(
+              2, K, inner, pend, lane,
+              [&](auto f) {
+                f((uint32_t)(a >> 32), (uint32_t)a);
+                f((uint32_t)(b >> 32), (uint32_t)b);
+              },
+              [&](int row, int) -> key_t { return row ? b : a; });
+        }
+      }
       const uint32_t id = sort_queued(pend, fill, t, lane);
       wave_lds_sync();
       return id;
     }
-    if (n < K) lo = (int)t; else hi = (int)t;
+    if (n < K) {
+      lo = (int)t;
+      at_lo = n;
+    } else {
+      hi = (int)t;
+      at_hi = n;
+    }
     if (hi - lo <= 1) break;  // neighbouring bit patterns straddle the window
+    const float wanted = (float)(K + most) * 0.5f;
+    auto scaled = [&] { return __uint_as_float(t) * (wanted * __builtin_amdgcn_rcpf((float)n)); };
     int next = -1;
-    if (it < 4) {
-      if (n > 0)
-        next = (int)__builtin_amdgcn_readfirstlane(
-            __float_as_uint(__uint_as_float(t) * ((float)(K + kWave) * 0.5f * __builtin_amdgcn_rcpf((float)n))));
-    } else if (it & 1) {
+    if (!LINEAR && it < 4) {
+      if (n > 0) next = (int)__builtin_amdgcn_readfirstlane(__float_as_uint(scaled()));
+    } else if (LINEAR ? it >= 4 && !(it & 1) : it & 1) {
       uint32_t above = 0xffffffffu;
       each([&](uint32_t d2, uint32_t) { above = min(above, (lo < 0 || d2 > (uint32_t)lo) ? d2 : 0xffffffffu); });
       next = (int)wave_min_u32(above, lane);
@@ -240,6 +272,15 @@ __device__ __forceinline__ uint32_t select_nearest(int rows, int K, uint32_t& gu
         lo = hi - 1;
         break;
       }
+    } else if (LINEAR && it < 18) {
+      float x = n > 0 ? scaled() : __uint_as_float(t) * 4.f;
+      if (at_hi >= 0) {
+        const float from = lo < 0 ? 0.f : __uint_as_float((uint32_t)lo);
+        float share = (wanted - (float)at_lo) * __builtin_amdgcn_rcpf((float)(at_hi - at_lo));
+        if (lo >= 0) share = fminf(fmaxf(share, 0.0625f), 0.9375f);
+        x = fmaf(__uint_as_float((uint32_t)hi) - from, share, from);
+      }
+      next = (int)__builtin_amdgcn_readfirstlane(__float_as_uint(x));
     }
     if (next <= lo || next >= hi) next = lo + (hi - lo) / 2;
     t = (uint32_t)next;

@@ -99,9 +99,14 @@ __global__ __launch_bounds__(256) void vts_table_kernel(const float* __restrict_
 // threshold of one grid point is the first guess for the next).
 constexpr int kTableRows = 16;
 constexpr int kTableRun = 16;  // grid points per wave
+// WIDE, Kt above kTableWide: the window of 61 - 64 tokens to 64 is found late or, with tokens on the grid, never, and two
+// sorted rows cost less (8 images, 64 x 64 points, 1024 tokens, Kt = 64: on the grid 116 us with one row, 58 with two; spread
+// evenly 62 and 53; Kt = 60: 55 and 57, 39 and 53, as the second row's sort takes registers too).
+constexpr int kTableWide = 60;
+template <bool WIDE>
 __global__ __launch_bounds__(256) void vts_table_fast_kernel(const float* __restrict__ vis_xy, int B, int Nv, Grid gr,
                                                             int Kt, int32_t* __restrict__ table) {
-  __shared__ key_t pend_all[4][kWave];
+  __shared__ key_t pend_all[4][WIDE ? 2 * kWave : kWave];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int per_image = gr.Hg * gr.Wg;
@@ -113,14 +118,13 @@ __global__ __launch_bounds__(256) void vts_table_fast_kernel(const float* __rest
   const int first = (int)(grun - (long long)b * runs_per_image) * kTableRun;
   const float* xy = vis_xy + (size_t)b * Nv * 2;
   float cx[kTableRows], cy[kTableRows];
-  uint32_t cid[kTableRows];
 #pragma unroll
   for (int row = 0; row < kTableRows; ++row) {
     const int i = row * kWave + lane;
     const bool ok = i < Nv;
-    cx[row] = ok ? xy[2 * (size_t)i] : 0.f;
+    // past the last token: the distance to any point is a NaN, whose bits lie above those of every distance
+    cx[row] = ok ? xy[2 * (size_t)i] : __uint_as_float(0x7fc00000u);
     cy[row] = ok ? xy[2 * (size_t)i + 1] : 0.f;
-    cid[row] = ok ? (uint32_t)i : 0xffffffffu;
   }
   uint32_t guess = 0u;
   for (int c = first; c < min(first + kTableRun, per_image); ++c) {
@@ -131,15 +135,14 @@ __global__ __launch_bounds__(256) void vts_table_fast_kernel(const float* __rest
     const float gx = gr.x0 + sx, gy = gr.y0 + sy;
     uint32_t d2[kTableRows];
 #pragma unroll
-    for (int row = 0; row < kTableRows; ++row)
-      d2[row] = cid[row] != 0xffffffffu ? __float_as_uint(dist2(gx, gy, cx[row], cy[row])) : 0xffffffffu;
+    for (int row = 0; row < kTableRows; ++row) d2[row] = __float_as_uint(dist2(gx, gy, cx[row], cy[row]));
     // the first grid point starts from one of the distances, so that the count is not 0
     if (guess == 0u) guess = min((uint32_t)__builtin_amdgcn_readfirstlane(d2[0]), 0x7f800000u);
-    const uint32_t best = select_nearest<true>(
+    const uint32_t best = select_nearest<true, WIDE ? kTwoSorted : kOneRow, true>(
         kTableRows, Kt, guess, pend, lane,
         [&](auto f) {
 #pragma unroll
-          for (int row = 0; row < kTableRows; ++row) f(d2[row], cid[row]);
+          for (int row = 0; row < kTableRows; ++row) f(d2[row], (uint32_t)(row * kWave + lane));
         },
         [&](int row, int l) -> key_t {
           const int i = row * kWave + l;
@@ -1031,8 +1034,13 @@ hipError_t launch_vts_table(const VtsArgs& a, hipStream_t stream) {
   }
   if (a.Nv <= kTableRows * kWave) {
     const long long runs = (long long)a.B * ((a.Hg * a.Wg + kTableRun - 1) / kTableRun);
-    AFFMAE_LAUNCH("vts_table_kernel", stream, vts_table_fast_kernel, dim3((unsigned)((runs + 3) / 4)), dim3(256), 0,
-                  stream, a.vis_xy, a.B, a.Nv, gr, a.Kt, a.table_out);
+    const dim3 grid((unsigned)((runs + 3) / 4));
+    if (a.Kt > kTableWide)
+      AFFMAE_LAUNCH("vts_table_kernel", stream, vts_table_fast_kernel<true>, grid, dim3(256), 0, stream, a.vis_xy, a.B, a.Nv, gr,
+                    a.Kt, a.table_out);
+    else
+      AFFMAE_LAUNCH("vts_table_kernel", stream, vts_table_fast_kernel<false>, grid, dim3(256), 0, stream, a.vis_xy, a.B, a.Nv, gr,
+                    a.Kt, a.table_out);
     return hipGetLastError();
   }
   AFFMAE_LAUNCH("vts_table_kernel", stream, vts_table_kernel, dim3((unsigned)((cells + 3) / 4)), dim3(256), 0, stream,

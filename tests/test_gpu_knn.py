@@ -131,7 +131,7 @@ def test_knn_short_last_cluster(name, B, N, S, M, K):
 
 @pytest.mark.parametrize("explicit", [False, True])
 @pytest.mark.parametrize("S,M,K", [(20, 3, 40), (40, 4, 33), (40, 9, 48), (64, 8, 48), (64, 11, 48), (64, 16, 64),
-                                   (100, 11, 17), (128, 12, 64)])
+                                   (100, 11, 17), (128, 12, 64), (100, 11, 48), (100, 11, 49), (256, 5, 64), (32, 40, 63)])
 def test_knn_rows_and_ties(S, M, K, explicit):
     """Every row class of the search (candidates in 1, 2, .. 16 rows of registers, or streamed) on points of which a
     third coincide in a few places (up to 90 at one distance, more than a threshold can separate), a third sits on a

@@ -79,6 +79,30 @@ def test_table_all_tokens_coincide():
     assert np.array_equal(table, np.broadcast_to(np.arange(7, dtype=np.int32), (2, 6, 6, 7)))
 
 
+@pytest.mark.parametrize("kind", ["coincide", "groups", "grid", "far"])
+@pytest.mark.parametrize("Nv,Kt", [(64, 64), (200, 9), (700, 20), (1024, 49), (1000, 60), (1024, 61), (1023, 64)])
+def test_table_ties_and_far_points(Nv, Kt, kind):
+    """Up to 1024 tokens and Kt > 8, one row of counted tokens or two: all tokens at one place; groups of 65 to 200 at one
+    place (more than a threshold can separate) among free ones; every cell's centre taken; all tokens in one corner."""
+    print(f"case table ties Nv={Nv} Kt={Kt} {kind}", flush=True)
+    rng = np.random.default_rng(Nv + Kt)
+    vis = rng.uniform(0, 128, size=(2, Nv, 2)).astype(np.float32)
+    if kind == "coincide":
+        vis[:] = 41.5
+    elif kind == "groups":
+        for n in (65, 100, 200):
+            vis[:, rng.permutation(Nv)[:n]] = rng.uniform(0, 128, size=(2, 1, 2)).astype(np.float32)
+    elif kind == "grid":
+        i = np.arange(Nv)
+        vis[0] = np.stack([(i % 32 + 0.5) * 4, (i // 32 % 32 + 0.5) * 4], axis=-1)
+        vis[1] = vis[0][rng.permutation(Nv)]
+    else:
+        vis *= 0.05
+    grid = (32, 32, 0.0, 0.0, 4.0)
+    table = aff.affmae_vts_table(torch.from_numpy(vis).cuda(), grid, Kt)
+    assert np.array_equal(table.cpu().numpy(), oracle.vts_table(vis, grid, Kt))
+
+
 @pytest.mark.parametrize("bad", [np.nan, np.inf, 1e30])
 @pytest.mark.parametrize("Nv,Kt", [(40, 20), (200, 9), (1024, 64)])
 def test_table_without_enough_distances(Nv, Kt, bad):
