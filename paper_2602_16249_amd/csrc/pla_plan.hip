@@ -256,10 +256,13 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(PlanParams p) {
 // The reverse tables of images of at most kRevTiles token tiles, in one launch: a workgroup owns `own` consecutive tiles
 // of one image.  It reads the image's slot tables (from L2), counts every tile's incidences in LDS, prefix-sums
 // the counts (an image's lists start at a place of their own, so nothing is needed of other images), reads the tables
-// again and files the incidences of its own tiles, and sorts these lists.  Against counting with atomics in the strip
-// kernel, then zero / scan / fill / sort kernels (four launches of 5 - 6 us each): 24 us at 16 x 1024 strips, this one 16.8 us
-// (8.8 us at 16 x 256).
-constexpr int kRevTiles = 2048;
+// again and files the incidences of its own tiles, and sorts these lists.
+// Bound by the chain of these steps in each workgroup, which grows with the image's tiles, against counting with atomics
+// in the strip kernel and four more launches (zero, scan, fill, sort: 4 - 6 us each, of the whole batch).  Whole plan,
+// one launch and four: one image of 64 / 256 / 512 / 1024 / 2048 tiles 15 / 18 / 19 / 24 / 28 us and 18 / 20 / 19 / 21 / 23
+// us; 1024 tiles, 4 / 8 / 16 / 32 images 30 / 22 / 64 / 104 us and 29 / 25 / 66 / 112 us (at 8, K = 9); 2048 tiles, 8 /
+// 16 images 69 / 109 us and 66 / 112 us.  So: up to 512 tiles, and beyond in batches of tiles / 128 images or more.
+constexpr int kRevTiles = 2048, kRevTilesSmall = 512;
 constexpr int kRevThreads = 1024;
 __global__ __launch_bounds__(kRevThreads) void plan_reverse_kernel(PlanParams p, int own) {
   __shared__ int32_t count[kRevTiles];   // incidences per tile
@@ -364,12 +367,14 @@ hipError_t launch_pla_plan(const int32_t* nbr_idx, const int32_t* near, int B, i
   p.runs = reinterpret_cast<uint16_t*>(base + L.runs_off);
   p.runs_stride = L.runs_stride; p.places = L.places;
   const dim3 per_strip((L.strips + 3) / 4);
-  // One workgroup per group of tiles reads its image's whole slot table: quadratic in the tiles, so only up to kRevTiles
-  // (LDS counters), with list places that int32 can number and no more threads than a launch can have (2^32 - 1).
+  // One launch where it is the faster way (see plan_reverse_kernel), list places fit int32 and the threads a launch
+  // (2^32 - 1).  256 workgroups share the tiles, 16 tiles or more each (a wave sorts one list at a time); by images instead
+  // (16 workgroups for each) 27 against 24 us for one image of 1024 tiles, 74 against 69 for eight of 2048.
   const int tiles = p.strips_per_image;
-  const int own = std::max(16, (tiles + 15) / 16);  // about 16 workgroups per image
+  const int own = std::max(16, (int)((L.strips + 255ll) / 256));
   const long long groups = (long long)B * ((tiles + own - 1) / own);
-  p.count_tiles = tiles > kRevTiles || (long long)L.strips * L.max_slots >= (1ll << 31) || groups * kRevThreads >= (1ll << 32);
+  p.count_tiles = !(tiles <= kRevTilesSmall || (tiles <= kRevTiles && tiles <= 128ll * B)) ||
+                  (long long)L.strips * L.max_slots >= (1ll << 31) || groups * kRevThreads >= (1ll << 32);
   if (p.count_tiles)
     AFFMAE_LAUNCH("plan_zero_kernel", stream, plan_zero_kernel, dim3((L.strips + 255) / 256), dim3(256), 0, stream,
                   p.rev_count, p.rev_cursor, L.strips);

@@ -235,15 +235,24 @@ def test_short_last_cluster_end_to_end(N, tiled):
     check_attention(w, nbr, "bf16", 1.0 / np.sqrt(d), near=near, S=S, M=M, use_plan=tiled)
 
 
-@pytest.mark.parametrize("N,S,M,K,same", [(2048, 16, 32, 40, True),     # every strip touches the same three token tiles
-                                          (700, 32, 16, 24, True),      # the same with a short last strip
-                                          (32768, 64, 8, 16, False),    # the most token tiles of the one-launch reverse tables
-                                          (32785, 64, 8, 16, False)])   # one more: counted, scanned, filled and sorted
-def test_reverse_tables_of_the_plan(N, S, M, K, same):
+@pytest.mark.parametrize("N,S,M,K,same,B", [
+    (2048, 16, 32, 40, True, 1),     # every strip touches the same three token tiles
+    (700, 32, 16, 24, True, 1),      # the same with a short last strip
+    (32768, 64, 8, 16, False, 1),    # large images: counted, scanned, filled and sorted in launches of their own
+    (32785, 64, 8, 16, False, 1),
+    (8192, 64, 8, 16, False, 1),     # the most token tiles of the one-launch reverse tables in a small batch, and one more
+    (8200, 64, 8, 16, False, 1),
+    (16384, 64, 8, 8, False, 8),     # as many images as twice that takes, and one too few
+    (16384, 64, 8, 8, False, 7),
+    (32768, 64, 8, 4, False, 16),    # the most of all, and one tile more
+    (32769, 64, 8, 4, False, 16),
+    (64, 16, 2, 8, False, 600),      # more images than workgroups wanted: one for each
+])
+def test_reverse_tables_of_the_plan(N, S, M, K, same, B):
     """dk and dv walk the plan's reverse tables: lists of more than 64 strips (all points coincide, so that the index
     decides and all queries share their neighbours) and both ways of building the tables."""
-    print(f"case reverse tables N={N} S={S} M={M} K={K}", flush=True)
-    cfg = CONFIGS["knn_scale"].scaled(B=1, N=N, C=32, H=1, K=K, S=S, M=M, dtype="bf16")
+    print(f"case reverse tables B={B} N={N} S={S} M={M} K={K}", flush=True)
+    cfg = CONFIGS["knn_scale"].scaled(B=B, N=N, C=32, H=1, K=K, S=S, M=M, dtype="bf16")
     w = make_workload(cfg)
     if same:
         w["coords"] = np.full_like(w["coords"], 2.5)
