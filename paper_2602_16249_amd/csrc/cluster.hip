@@ -179,9 +179,10 @@ __device__ __forceinline__ int count_below(const word_t* run, int n, word_t word
 
 // Builds the words of one chunk and sorts it: RUNS groups of 256 threads sort 256 W words each in registers, then a
 // word's place is its place in its run plus the counts of smaller words in the others.  WHOLE: the chunk is the image,
-// its order is written at once; otherwise the sorted words.  (2048 words by 256 threads with 8 words each, the whole
-// network in registers or through LDS: 18 - 19 us, a chain of dependent steps with one wave per SIMD; as four runs of
-// 512 by 1024 threads 12.6 us for 128 chunks.)
+// its order is written at once; otherwise the sorted words.  Bound by a chain of dependent steps with few waves per SIMD:
+// 2048 words by 256 threads with 8 words each, the whole network in registers or through LDS, 18 - 19 us for 128 chunks,
+// as four runs of 512 by 1024 threads 12.6 us.  Images of 513 to 1024 tokens take two runs (2048 images of 600: 57 us
+// with four, half of whose words are pads; 38 as one network over 1024 words; 29 with two).
 template <int W, int RUNS, bool WHOLE>
 __global__ __launch_bounds__(kSortThreads* RUNS) void cluster_sort_chunk_kernel(ClusterParams p, int chunks, bool network) {
   constexpr int kRun = W * kSortThreads, kWords = kRun * RUNS;
@@ -324,6 +325,7 @@ static hipError_t launch_images(const ClusterParams& p, int B, hipStream_t strea
   if (N <= kChunk) {  // one chunk per image
     if (N <= kSortThreads) AFFMAE_SORT(1, 1, true, 1, false);
     else if (N <= 2 * kSortThreads) AFFMAE_SORT(2, 1, true, 1, false);
+    else if (N <= 4 * kSortThreads) AFFMAE_SORT(2, 2, true, 1, false);
     else AFFMAE_SORT(2, 4, true, 1, false);
     return hipGetLastError();
   }
