@@ -139,8 +139,8 @@ __device__ __forceinline__ void static_for(F&& fn) {
   }
 }
 
-// d[t] holds this lane's part of a value of trip t; lane (r, c) receives the whole value of trip c, the sum of d[c]
-// over the PP lanes of its row.  Each step halves the values that a lane still carries: PP - 1 exchanges where the
+// d[t] holds this lane's part of a value of trip t; lane (r, c) receives the whole value of trip c % N, the sum of d[c % N]
+// over the PP lanes of its row (row_scatter: N trips, a power of two up to PP).  Each step halves the values that a lane still carries: PP - 1 exchanges where the
 // sum of every trip over all lanes takes PP log2(PP), and what follows is done once per value instead of once per lane.
 template <int J, int N>
 __device__ __forceinline__ float scatter_sum(const float (&d)[N], int lane) {
@@ -156,6 +156,11 @@ __device__ __forceinline__ float scatter_sum(const float (&d)[N], int lane) {
     }
     return scatter_sum<2 * J>(half, lane);
   }
+}
+
+template <int PP, int N>
+__device__ __forceinline__ float row_scatter(const float (&d)[N], int lane) {
+  return sum_bits<N, PP / 2>(scatter_sum<1>(d, lane), lane);
 }
 
 // The way back: get<t>() is, in every lane of a row, the value that lane t of the row held.
@@ -187,25 +192,28 @@ template <int TR>
 struct LaneRows {
   size_t off[TR];
 };
-template <int PP, int E>
-__device__ __forceinline__ LaneRows<PP> lane_rows(int mynb, long long img_base, int C, int K, int lane) {
+template <int PP, int E, int TR>
+__device__ __forceinline__ LaneRows<TR> lane_rows(int mynb, long long img_base, int C, int K, int lane) {
   constexpr int RPT = kWave / PP;
   const int rl = lane / PP, pc = lane % PP;
-  LaneRows<PP> r;
+  LaneRows<TR> r;
 #pragma unroll
-  for (int t = 0; t < PP; ++t) {
+  for (int t = 0; t < TR; ++t) {
     const int nbj = __shfl(mynb, min(t * RPT + rl, K - 1));
     r.off[t] = (size_t)(img_base + nbj) * C + (size_t)(pc * E);
   }
   return r;
 }
 
-template <typename T, int D>
+// TR: trips that the K neighbours take at most: 1, 2 or PP.  With TR < PP the lanes c >= TR of a row repeat the values of
+// lanes c % TR and do not count.  (With PP for every K the parts of trips that K does not reach were exchanged all the same:
+// 12000 tokens, fp32, three heads of 64, K = 1: forward 37 us, 14 with one trip; eight heads, K = 8: 94 and 46 us.)
+template <typename T, int D, int TR>
 __global__ __launch_bounds__(256) void pla_fwd_general_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ bias,
     const int32_t* __restrict__ nbr_idx, const T* __restrict__ k_blank, const T* __restrict__ v_blank,
     long long tokens, int N, int H, int K, float scale, T* __restrict__ out, float* __restrict__ lse) {
-  constexpr int E = Piece<T>::E, PP = D / E, RPT = kWave / PP, TR = PP;  // K <= 64 = RPT * TR
+  constexpr int E = Piece<T>::E, PP = D / E, RPT = kWave / PP;  // K <= RPT * TR
   constexpr bool kHoldV = TR <= 8;  // V rows loaded with the K rows, as far as the registers go
   constexpr int kBatch = TR < 8 ? TR : 4;
   const int lane = threadIdx.x & (kWave - 1);
@@ -217,9 +225,9 @@ __global__ __launch_bounds__(256) void pla_fwd_general_kernel(
        tok += (long long)gridDim.x * kWavesPerBlock) {
     const long long img_base = (tok / N) * N;  // first token of this image
     const int mynb = min(max(nbr_idx[tok * K + min(lane, K - 1)], 0), N - 1);
-    const LaneRows<TR> rows = lane_rows<PP, E>(mynb, img_base, C, K, lane);
+    const LaneRows<TR> rows = lane_rows<PP, E, TR>(mynb, img_base, C, K, lane);
     const int mine = pc * RPT + rl;  // the neighbour whose score this lane holds
-    const bool valid = mine < K;
+    const bool valid = mine < K && pc < TR;
     for (int h = 0; h < H; ++h) {
       const auto qv = Piece<T>::raw(q + (tok * H + h) * D + pc * E);
       const float bj = (bias && valid) ? Elem<T>::load(bias + (tok * H + h) * K + mine) : 0.f;
@@ -237,7 +245,7 @@ __global__ __launch_bounds__(256) void pla_fwd_general_kernel(
 #pragma unroll
         for (int t = 0; t < kBatch; ++t) part[t0 + t] = t0 + t < trips ? dot_raw(qv, kr[t]) : 0.f;
       }
-      const float dot = scatter_sum<1>(part, lane);  // (by every lane: also those past K hand on parts)
+      const float dot = row_scatter<PP>(part, lane);  // (by every lane: also those past K hand on parts)
       const float s = valid ? fmaf(scale, dot, bj) : -INFINITY;
       float sb = -INFINITY, eb = 0.f;
       if (k_blank) {
@@ -278,7 +286,7 @@ __global__ __launch_bounds__(256) void pla_fwd_general_kernel(
 
 // Query side of the backward: dq, dbias, and p / dS of every (query, slot) pair for the key side; also the global
 // token of every pair and the lowest and highest of a query's K, for the list builder.
-template <typename T, int D>
+template <typename T, int D, int TR>
 __global__ __launch_bounds__(256) void pla_bwd_general_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ bias,
     const int32_t* __restrict__ nbr_idx, const T* __restrict__ k_blank, const T* __restrict__ v_blank,
@@ -286,7 +294,7 @@ __global__ __launch_bounds__(256) void pla_bwd_general_kernel(
     T* __restrict__ dq, T* __restrict__ dbias, float* __restrict__ pw, float* __restrict__ dsw,
     int32_t* __restrict__ pair_tok, int2* __restrict__ bounds, float* __restrict__ dk_blank,
     float* __restrict__ dv_blank) {
-  constexpr int E = Piece<T>::E, PP = D / E, RPT = kWave / PP, TR = PP;
+  constexpr int E = Piece<T>::E, PP = D / E, RPT = kWave / PP;
   constexpr bool kHoldV = TR <= 8;
   extern __shared__ float smem[];
   const int lane = threadIdx.x & (kWave - 1);
@@ -303,7 +311,7 @@ __global__ __launch_bounds__(256) void pla_bwd_general_kernel(
        tok += (long long)gridDim.x * kWavesPerBlock) {
     const long long img_base = (tok / N) * N;
     const int mynb = min(max(nbr_idx[tok * K + min(lane, K - 1)], 0), N - 1);
-    const LaneRows<TR> rows = lane_rows<PP, E>(mynb, img_base, C, K, lane);
+    const LaneRows<TR> rows = lane_rows<PP, E, TR>(mynb, img_base, C, K, lane);
     {
       const int gtok = (int)(img_base + mynb);  // lanes >= K repeat the last neighbour
       if (lane < K) pair_tok[tok * K + lane] = gtok;
@@ -316,7 +324,7 @@ __global__ __launch_bounds__(256) void pla_bwd_general_kernel(
       if (lane == 0) bounds[tok] = make_int2(tmin, tmax);
     }
     const int mine = pc * RPT + rl;  // the neighbour whose p and dS this lane holds
-    const bool valid = mine < K;
+    const bool valid = mine < K && pc < TR;
     for (int h = 0; h < H; ++h) {
       const T* qrow = q + (tok * H + h) * D + pc * E;
       const T* grow = dout + (tok * H + h) * D + pc * E;
@@ -340,8 +348,8 @@ __global__ __launch_bounds__(256) void pla_bwd_general_kernel(
           gpart[t] = dot_raw(graw, kHoldV ? vr[t] : Piece<T>::raw(v + rows.off[t] + (size_t)h * D));
         }
       }
-      const float dP = scatter_sum<1>(gpart, lane);
-      const float dot = scatter_sum<1>(part, lane);
+      const float dP = row_scatter<PP>(gpart, lane);
+      const float dot = row_scatter<PP>(part, lane);
       const float p = valid ? exp_for<T>(fmaf(scale, dot, bj) - l) : 0.f;
       float pb = 0.f, dPb = 0.f, kb[8];
       if (k_blank) {
@@ -497,13 +505,26 @@ GeneralBwdLayout general_bwd_layout(int B, int N, int H, int K) {
   return L;
 }
 
+// fn(TR) for the trips that K neighbours take
+template <typename T, int D, typename F>
+void by_trips(int K, F&& fn) {
+  constexpr int PP = D / Piece<T>::E, RPT = kWave / PP;
+  if (K <= RPT) return fn(std::integral_constant<int, 1>{});
+  if constexpr (PP > 2) {
+    if (K <= 2 * RPT) return fn(std::integral_constant<int, 2>{});
+  }
+  fn(std::integral_constant<int, PP>{});
+}
+
 template <typename T, int D>
 hipError_t fwd_impl(const PlaArgs& a, hipStream_t stream) {
   const long long tokens = (long long)a.B * a.N;
   const int grid = grid_for((size_t)tokens, kWavesPerBlock, 1 << 20);
-  AFFMAE_LAUNCH("pla_fwd_general_kernel", stream, (pla_fwd_general_kernel<T, D>), dim3(grid), dim3(256), 0, stream, (const T*)a.q,
-                     (const T*)a.k, (const T*)a.v, (const T*)a.bias, a.nbr_idx, (const T*)a.k_blank,
-                     (const T*)a.v_blank, tokens, a.N, a.H, a.K, a.scale, (T*)a.out, a.lse);
+  by_trips<T, D>(a.K, [&](auto trips) {
+    AFFMAE_LAUNCH("pla_fwd_general_kernel", stream, (pla_fwd_general_kernel<T, D, decltype(trips)::value>), dim3(grid), dim3(256), 0,
+                  stream, (const T*)a.q, (const T*)a.k, (const T*)a.v, (const T*)a.bias, a.nbr_idx, (const T*)a.k_blank,
+                  (const T*)a.v_blank, tokens, a.N, a.H, a.K, a.scale, (T*)a.out, a.lse);
+  });
   return hipGetLastError();
 }
 
@@ -528,10 +549,12 @@ hipError_t bwd_impl(const PlaArgs& a, hipStream_t stream) {
   // With blank gradients every workgroup adds a running sum to the same words at its end, so bound the grid: four
   // workgroups per CU.
   const int grid = grid_for((size_t)tokens, kWavesPerBlock, blank_grad ? 1024 : (1 << 20));
-  AFFMAE_LAUNCH("pla_bwd_general_kernel", stream, (pla_bwd_general_kernel<T, D>), dim3(grid), dim3(256), lds, stream, (const T*)a.q,
-                     (const T*)a.k, (const T*)a.v, (const T*)a.bias, a.nbr_idx, (const T*)a.k_blank,
-                     (const T*)a.v_blank, a.lse, (const T*)a.dout, tokens, a.N, a.H, a.K, a.scale, (T*)a.dq,
-                     (T*)a.dbias, pw, dsw, pair_tok, bounds, a.dk_blank, a.dv_blank);
+  by_trips<T, D>(a.K, [&](auto trips) {
+    AFFMAE_LAUNCH("pla_bwd_general_kernel", stream, (pla_bwd_general_kernel<T, D, decltype(trips)::value>), dim3(grid), dim3(256), lds,
+                  stream, (const T*)a.q, (const T*)a.k, (const T*)a.v, (const T*)a.bias, a.nbr_idx, (const T*)a.k_blank,
+                  (const T*)a.v_blank, a.lse, (const T*)a.dout, tokens, a.N, a.H, a.K, a.scale, (T*)a.dq, (T*)a.dbias, pw, dsw,
+                  pair_tok, bounds, a.dk_blank, a.dv_blank);
+  });
   const hipError_t e = launch_pair_lists(pair_tok, a.B, a.N, a.N * a.K, offset, list, stream,
                                          reinterpret_cast<const int32_t*>(bounds), a.K);
   if (e != hipSuccess) return e;

@@ -271,12 +271,13 @@ def test_blank_sums_over_strips(N):
 
 
 @pytest.mark.parametrize("dtype,d", [("f32", 16), ("f32", 32), ("f32", 64), ("bf16", 16), ("bf16", 32), ("bf16", 64)])
-@pytest.mark.parametrize("K", ["1", "trip", "trip+1", "last-1", "64"])
+@pytest.mark.parametrize("K", ["1", "trip", "trip+1", "trips", "trips+1", "last-1", "64"])
 def test_gather_trips(dtype, d, K):
-    """Neighbour counts at the edges of a trip (64 * 16 bytes of rows), lists of more than 64 pairs under one token,
-    and, in the longest case, more tokens than the grid with blank gradients covers in one go."""
+    """Neighbour counts at the edges of one trip (64 * 16 bytes of rows) and of two, lists of more than 64 pairs under one
+    token, and, in the longest case, more tokens than the grid with blank gradients covers in one go."""
     trip = 64 // (d * (4 if dtype == "f32" else 2) // 16)
-    K = {"1": 1, "trip": trip, "trip+1": trip + 1, "last-1": 65 - trip, "64": 64}[K]
+    K = {"1": 1, "trip": trip, "trip+1": trip + 1, "trips": 2 * trip, "trips+1": min(2 * trip + 1, 64),
+         "last-1": 65 - trip, "64": 64}[K]
     N = 4500 if K == 1 else 150
     print(f"case trips {dtype} d={d} K={K}", flush=True)
     rng = np.random.default_rng(K + d)
