@@ -136,13 +136,16 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
+# torch.cuda.current_stream() builds an object around the handle on every call; these two give the handle alone, but lie
+# outside torch's public interface
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    # the handle alone (torch.cuda.current_stream() builds an object around it on every call), by a function outside
-    # torch's public interface: the public one serves where it is missing
-    raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    if raw_stream is None:
+    if _raw_stream is None or _raw_device is None:
         return torch.cuda.current_stream().cuda_stream
-    return raw_stream(torch.cuda.current_device())
+    return _raw_stream(_raw_device())
 
 
 def _dev(t: torch.Tensor, name: str, dtype=None, shape=None) -> torch.Tensor:

@@ -186,19 +186,18 @@ def test_binding_refuses_host_tensors():
         aff.affmae_knn(torch.zeros(1, 64, 2), None, 8, 2, 4)
 
 
-@pytest.mark.parametrize("missing", [False, True])
+@pytest.mark.parametrize("missing", [None, "_raw_stream", "_raw_device"])
 def test_stream_handle(monkeypatch, missing):
-    """The handle of the current device's current stream, also on a torch without the internal function that gives it
+    """The handle of the current device's current stream, also on a torch without the internal functions that give it
     without an object."""
     import types
     from paper_2602_16249_amd import binding
-    monkeypatch.setattr(binding.torch.cuda, "current_device", lambda: 3)
-    monkeypatch.setattr(binding.torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(binding, "_raw_device", lambda: 3)
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: {3: 77}[device])
+    monkeypatch.setattr(binding.torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=78))
     if missing:
-        monkeypatch.delattr(binding.torch._C, "_cuda_getCurrentRawStream", raising=False)
-    else:
-        monkeypatch.setattr(binding.torch._C, "_cuda_getCurrentRawStream", lambda device: {3: 77}[device], raising=False)
-    assert binding._stream() == 77
+        monkeypatch.setattr(binding, missing, None)
+    assert binding._stream() == (78 if missing else 77)
 
 
 def test_relpos_rejects_bad_arguments_on_host():
