@@ -141,6 +141,7 @@ __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __re
                                                               int32_t* __restrict__ nbr_idx) {
   extern __shared__ key_t lds[];
   __shared__ int32_t near_lds[kWave];
+  __shared__ int32_t odd_lds[kKnnWaves];
   constexpr int kPend = pend_keys(ROWS);
   float2* cxy = reinterpret_cast<float2*>(lds + kKnnWaves * kPend);        // [rows][64]
   int32_t* ctok = reinterpret_cast<int32_t*>(cxy + (size_t)rows * kWave);  // [rows][64]
@@ -159,13 +160,15 @@ __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __re
     for (int m = 0; m < M; ++m) rank += __builtin_amdgcn_readlane(id, m) < id ? 1 : 0;
     return __builtin_amdgcn_ds_permute((lane < M ? rank : lane) * 4, id);
   };
+  float2 own = make_float2(0.f, 0.f);  // this cluster's centroid
+  if (G > 1) own = make_float2(centroid[2 * (size_t)gc], centroid[2 * (size_t)gc + 1]);
   if (G <= kNearInSearch) {
     // the near clusters themselves, a row of 64 centroids per wave (G == 1: there is one cluster, no centroid is needed)
     const int e = wave * kWave + lane;
     if (G > 1) {
       const float* cen = centroid + (size_t)b * G * 2;
       key_t key = kKeyMax;
-      if (e < G) key = make_key(dist2(cen[2 * c], cen[2 * c + 1], cen[2 * e], cen[2 * e + 1]), e);
+      if (e < G) key = make_key(dist2(own.x, own.y, cen[2 * e], cen[2 * e + 1]), e);
       if (wave * kWave < G) pend[lane] = wave_sort(key, lane);
       __syncthreads();
     }
@@ -186,6 +189,8 @@ __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __re
   } else {
     near_sorted = index_order(lane < M ? min(max(near[(size_t)gc * M + lane], 0), G - 1) : 0x7fffffff);
   }
+  // a coordinate that is not finite among the candidates or in this cluster (whose centroid is not finite either then)
+  bool odd = G > 1 && !finite_point(own.x, own.y);
   for (int p = threadIdx.x; p < rows * kWave; p += kKnnWaves * kWave) {  // (whole waves: all lanes take part)
     const int pp = p < Cn ? p : 0;
     const int m = fast_div(pp, s_magic), r = pp - m * S;
@@ -194,10 +199,35 @@ __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __re
     if (MEMBERS) tok = min(max(mem[tok], 0), N - 1);
     const bool real = p < Cn && r < cluster_size(e, N, S, G);  // a short last cluster fills only part of its places
     // an empty place: its distance to any point is a NaN, whose bits lie above those of every distance
-    cxy[p] = make_float2(real ? xy[2 * (size_t)tok] : __uint_as_float(0x7fc00000u), xy[2 * (size_t)tok + 1]);
+    const float x = xy[2 * (size_t)tok], y = xy[2 * (size_t)tok + 1];
+    cxy[p] = make_float2(real ? x : __uint_as_float(0x7fc00000u), y);
     ctok[p] = real ? tok : -1;
+    if (!MEMBERS) odd |= real && !finite_point(x, y);
+  }
+  if (!MEMBERS) {
+    const bool any = __ballot(odd) != 0ull;
+    if (lane == 0) odd_lds[wave] = any ? 1 : 0;
   }
   __syncthreads();
+  auto key_at = [&](float qx, float qy, int row, int l) -> key_t {
+    const float2 v = cxy[row * kWave + l];
+    const int tok = ctok[row * kWave + l];
+    return tok >= 0 ? make_key(dist2(qx, qy, v.x, v.y), MEMBERS ? tok : row * kWave + l) : kKeyMax;
+  };
+  const int my_size = cluster_size(c, N, S, G);
+  const int step = parts * kKnnWaves, first = part * kKnnWaves + wave;
+  const int served = first < my_size ? (my_size - 1 - first) / step + 1 : 0;  // tokens of this wave
+  if (!MEMBERS) {
+    if (__builtin_amdgcn_readfirstlane(odd_lds[0] | odd_lds[1] | odd_lds[2] | odd_lds[3]) != 0) {  // distances may be NaN
+      for (int i = first; i < my_size; i += step) {
+        const int qtok = c * S + i;
+        const float qx = xy[2 * (size_t)qtok], qy = xy[2 * (size_t)qtok + 1];
+        const uint32_t place = nearest_by_key(rows, K, lane, [&](int row, int l) { return key_at(qx, qy, row, l); });
+        if (lane < K) nbr_idx[((size_t)b * N + qtok) * K + lane] = ctok[place];
+      }
+      return;
+    }
+  }
   float cx[ROWS ? ROWS : 1], cy[ROWS ? ROWS : 1];
 #pragma unroll
   for (int row = 0; row < ROWS; ++row) {
@@ -205,9 +235,6 @@ __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __re
     cx[row] = row < rows ? v.x : __uint_as_float(0x7fc00000u);
     cy[row] = v.y;
   }
-  const int my_size = cluster_size(c, N, S, G);
-  const int step = parts * kKnnWaves, first = part * kKnnWaves + wave;
-  const int served = first < my_size ? (my_size - 1 - first) / step + 1 : 0;  // tokens of this wave
   uint32_t guess = 0u;  // threshold that worked for the previous token (0: none yet)
   for (int base = 0; base < served; base += kWave) {
     // lane i: token and coordinates of the i-th of the next 64
@@ -241,11 +268,7 @@ __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __re
             if (ROWS == 0)
               for (int row = 0; row < rows; ++row) f(row_d2(row), row_low(row));
           },
-          [&](int row, int l) -> key_t {
-            const float2 v = cxy[row * kWave + l];
-            const int tok = ctok[row * kWave + l];
-            return tok >= 0 ? make_key(dist2(qx, qy, v.x, v.y), MEMBERS ? tok : row * kWave + l) : kKeyMax;
-          });
+          [&](int row, int l) { return key_at(qx, qy, row, l); });
       int tok = (int)best;
       if (!MEMBERS) tok = ctok[lane < K ? tok : 0];
       if (lane < K) nbr_idx[((size_t)b * N + qtok) * K + lane] = tok;

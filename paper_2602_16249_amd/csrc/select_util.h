@@ -183,10 +183,35 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x, int lane) {
   return __builtin_amdgcn_readfirstlane(x);
 }
 
+__device__ __forceinline__ bool finite_point(float x, float y) {
+  return __builtin_isfinite(x) && __builtin_isfinite(y);
+}
+
 __device__ __forceinline__ key_t wave_min_key(key_t x, int lane) {
   const uint32_t hi = wave_min_u32((uint32_t)(x >> 32), lane);
   const uint32_t lo = wave_min_u32((uint32_t)(x >> 32) == hi ? (uint32_t)x : 0xffffffffu, lane);
   return ((key_t)hi << 32) | lo;
+}
+// The K nearest by their keys alone, each the smallest above the last one (keys are distinct), for points whose distances
+// may be NaN: these sort by their bits, after every distance.  A path of its own, decided once per workgroup or wave from
+// the coordinates (0.3 % of the search's time): inside select_nearest it cost the search of finite points 1 %, and as a
+// running top 64 two registers too many for eight waves per SIMD, 5 - 10 %.
+template <class KeyAt>
+__device__ __forceinline__ uint32_t nearest_by_key(int rows, int K, int lane, KeyAt key_at) {
+  uint32_t id = 0u;
+  key_t last = 0ull;
+#pragma unroll 1
+  for (int i = 0; i < K; ++i) {
+    key_t least = kKeyMax;
+#pragma unroll 1
+    for (int row = 0; row < rows; ++row) {
+      const key_t key = key_at(row, lane);
+      if ((i == 0 || key > last) && key < least) least = key;
+    }
+    last = wave_min_key(least, lane);
+    if (lane == i) id = (uint32_t)last;
+  }
+  return id;
 }
 
 // The K nearest of the candidates that the caller holds in `rows` rows, one per lane and row: each(f) calls f(d2, low)
@@ -211,9 +236,8 @@ __device__ __forceinline__ key_t wave_min_key(key_t x, int lane) {
 // registers for their lane masks).
 // No such T exists when more candidates share a distance than the window takes: then the nearer ones and, in index order,
 // as many of the equal ones as fit are sorted (candidates that are not ORDERED are merged row by row into a running top
-// 64).  Where fewer than K candidates have a distance that is no NaN, that queue would have too few: the keys are then
-// taken one by one, NaN by its bits after every distance (merged like the others they cost the search of 512 candidates
-// two registers too many for eight waves per SIMD, 5 - 10 % of its time on every input).  Either way the result is exact.
+// 64).  Either way the result is exact.  ORDERED: at least K candidates have a distance that is no NaN (the queue has
+// nothing else); where a coordinate is not finite the caller takes nearest_by_key.
 enum { kOneRow, kTwoSearched, kTwoSorted };
 template <bool ORDERED, int WIDE, bool LINEAR, class Each, class KeyAt>
 __device__ __forceinline__ uint32_t select_nearest(int rows, int K, uint32_t& guess, key_t* pend, int lane, Each each,
@@ -235,7 +259,10 @@ __device__ __forceinline__ uint32_t select_nearest(int rows, int K, uint32_t& gu
         if (n > kWave) {  // wave-uniform
           const key_t a = pend[lane], b = lane < n - kWave ? pend[kWave + lane] : kKeyMax;
           wave_lds_sync();
-          if constexpr (WIDE == kTwoSorted) return (uint32_t)topk_push(wave_sort(a, lane), b, lane, K - 1);
+          if constexpr (WIDE == kTwoSorted) {
+            asm volatile("" : "+v"(lane));  // its masks are made here, not held (spilled) throughout the caller's loop
+            return (uint32_t)topk_push(wave_sort(a, lane), b, lane, K - 1);
+          }
           uint32_t inner =
               __float_as_uint(__uint_as_float(t) * ((float)(K + kWave) * 0.5f * __builtin_amdgcn_rcpf((float)n)));
           return select_nearest<ORDERED, kOneRow, false>(
@@ -290,26 +317,9 @@ __device__ __forceinline__ uint32_t select_nearest(int rows, int K, uint32_t& gu
     int fill = 0;
     each([&](uint32_t d2, uint32_t low) { fill = queue_row(pend, fill, lo >= 0 && d2 <= (uint32_t)lo ? d2 : 0xffffffffu, low, (uint32_t)hi); });
     each([&](uint32_t d2, uint32_t low) { fill = queue_row<false>(pend, fill, d2 == (uint32_t)hi ? d2 : 0xffffffffu, low, (uint32_t)hi); });
-    if (fill >= K) {  // wave-uniform
-      wave_lds_sync();
-      const uint32_t id = sort_queued(pend, fill, (uint32_t)hi, lane);
-      wave_lds_sync();
-      return id;
-    }
-    // each key the smallest above the last one (keys are distinct)
-    uint32_t id = 0u;
-    key_t last = 0ull;
-#pragma unroll 1
-    for (int i = 0; i < K; ++i) {
-      key_t least = kKeyMax;
-#pragma unroll 1
-      for (int row = 0; row < rows; ++row) {
-        const key_t key = key_at(row, lane);
-        if ((i == 0 || key > last) && key < least) least = key;
-      }
-      last = wave_min_key(least, lane);
-      if (lane == i) id = (uint32_t)last;
-    }
+    wave_lds_sync();
+    const uint32_t id = sort_queued(pend, fill, (uint32_t)hi, lane);
+    wave_lds_sync();
     return id;
   }
   key_t best = kKeyMax;

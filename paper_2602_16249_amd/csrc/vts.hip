@@ -118,6 +118,7 @@ __global__ __launch_bounds__(256) void vts_table_fast_kernel(const float* __rest
   const int first = (int)(grun - (long long)b * runs_per_image) * kTableRun;
   const float* xy = vis_xy + (size_t)b * Nv * 2;
   float cx[kTableRows], cy[kTableRows];
+  bool odd = false;  // a coordinate that is not finite
 #pragma unroll
   for (int row = 0; row < kTableRows; ++row) {
     const int i = row * kWave + lane;
@@ -125,17 +126,34 @@ __global__ __launch_bounds__(256) void vts_table_fast_kernel(const float* __rest
     // past the last token: the distance to any point is a NaN, whose bits lie above those of every distance
     cx[row] = ok ? xy[2 * (size_t)i] : __uint_as_float(0x7fc00000u);
     cy[row] = ok ? xy[2 * (size_t)i + 1] : 0.f;
+    odd |= ok && !finite_point(cx[row], cy[row]);
   }
-  uint32_t guess = 0u;
-  for (int c = first; c < min(first + kTableRun, per_image); ++c) {
+  // patch centre, each operation rounded separately
+  auto centre = [&](int c) {
     const int iy = c / gr.Wg, ix = c - iy * gr.Wg;
-    // patch centre, each operation rounded separately
     const float hx = (float)ix + 0.5f, hy = (float)iy + 0.5f;
     const float sx = hx * gr.cell, sy = hy * gr.cell;
-    const float gx = gr.x0 + sx, gy = gr.y0 + sy;
+    return make_float2(gr.x0 + sx, gr.y0 + sy);
+  };
+  auto key_at = [&](const float2& g, int row, int l) -> key_t {
+    const int i = row * kWave + l;
+    return i < Nv ? make_key(dist2(g.x, g.y, xy[2 * (size_t)i], xy[2 * (size_t)i + 1]), i) : kKeyMax;
+  };
+  const int last = min(first + kTableRun, per_image);
+  if (__ballot(odd) != 0ull) {  // distances may be NaN
+    for (int c = first; c < last; ++c) {
+      const float2 g = centre(c);
+      const uint32_t id = nearest_by_key(kTableRows, Kt, lane, [&](int row, int l) { return key_at(g, row, l); });
+      if (lane < Kt) table[((size_t)b * per_image + c) * Kt + lane] = (int32_t)id;
+    }
+    return;
+  }
+  uint32_t guess = 0u;
+  for (int c = first; c < last; ++c) {
+    const float2 g = centre(c);
     uint32_t d2[kTableRows];
 #pragma unroll
-    for (int row = 0; row < kTableRows; ++row) d2[row] = __float_as_uint(dist2(gx, gy, cx[row], cy[row]));
+    for (int row = 0; row < kTableRows; ++row) d2[row] = __float_as_uint(dist2(g.x, g.y, cx[row], cy[row]));
     // the first grid point starts from one of the distances, so that the count is not 0
     if (guess == 0u) guess = min((uint32_t)__builtin_amdgcn_readfirstlane(d2[0]), 0x7f800000u);
     const uint32_t best = select_nearest<true, WIDE ? kTwoSorted : kOneRow, true>(
@@ -144,10 +162,7 @@ __global__ __launch_bounds__(256) void vts_table_fast_kernel(const float* __rest
 #pragma unroll
           for (int row = 0; row < kTableRows; ++row) f(d2[row], (uint32_t)(row * kWave + lane));
         },
-        [&](int row, int l) -> key_t {
-          const int i = row * kWave + l;
-          return i < Nv ? make_key(dist2(gx, gy, xy[2 * (size_t)i], xy[2 * (size_t)i + 1]), i) : kKeyMax;
-        });
+        [&](int row, int l) { return key_at(g, row, l); });
     if (lane < Kt) table[((size_t)b * per_image + c) * Kt + lane] = (int32_t)best;
   }
 }
