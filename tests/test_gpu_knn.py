@@ -204,3 +204,29 @@ def test_knn_without_enough_distances(N, S, M, K, bad):
     nbr_e, near_e = _gpu_knn(coords, cid, S, M, K)
     assert np.array_equal(near_e, rnear)
     assert np.array_equal(nbr_e, rnbr)
+
+
+@pytest.mark.parametrize("explicit", [False, True])
+@pytest.mark.parametrize("G,S,M,K", [(64, 8, 64, 40), (65, 8, 7, 33), (128, 8, 60, 48), (129, 8, 64, 64), (192, 8, 5, 17),
+                                     (193, 8, 63, 20), (255, 8, 64, 48), (256, 16, 3, 40), (257, 16, 64, 64), (257, 8, 2, 9),
+                                     (1023, 8, 64, 48), (1025, 16, 9, 48)])
+def test_knn_cluster_counts(G, S, M, K, explicit):
+    """Near clusters found by the search kernel (up to 256 clusters per image: one to four rows of 64 centroids, the last
+    one full or not) and by the kernel of their own beyond, with many equal centroid distances: the first image's points
+    sit on a lattice, eight per place, the second's are free.  The last cluster is short."""
+    print(f"case G={G} S={S} M={M} K={K} explicit={explicit}", flush=True)
+    rng = np.random.default_rng(G + M)
+    N = G * S - S // 2
+    coords = rng.uniform(0, 60, size=(2, N, 2)).astype(np.float32)
+    place = np.arange(N) // 8
+    coords[0] = np.stack([place % 9, place // 9 % 7], axis=-1)
+    coords[1] = coords[1][np.lexsort((coords[1, :, 1] // 8, coords[1, :, 0] // 8))]
+    cid = None
+    if explicit:
+        perm = np.stack([rng.permutation(N) for _ in range(2)])
+        coords = np.ascontiguousarray(np.take_along_axis(coords, perm[..., None], axis=1))
+        cid = np.ascontiguousarray((perm // S).astype(np.int32))
+    nbr, near = _gpu_knn(coords, cid, S, M, K)
+    rnbr, rnear = oracle.knn(coords, cid, S, M, K)
+    assert np.array_equal(near, rnear)
+    assert np.array_equal(nbr, rnbr)
