@@ -38,7 +38,7 @@ int check_knn_shape(int B, int N, int S, int M, int K) {
   const long long last = (long long)N - (long long)(G - 1) * S;
   if ((long long)K > (long long)(M - 1) * S + last) return AFFMAE_ERR_SHAPE;
   if (K > AFFMAE_MAX_K || M > AFFMAE_MAX_NEAR) return AFFMAE_ERR_UNSUPPORTED;
-  if ((long long)M * S > 4096) return AFFMAE_ERR_UNSUPPORTED;  // candidate staging: 16 B each in 64 KB of LDS
+  if ((long long)M * S > 4096) return AFFMAE_ERR_UNSUPPORTED;  // candidate staging: 12 B each and 4 KB of queues in 64 KB of LDS
   return AFFMAE_OK;
 }
 

@@ -123,8 +123,9 @@ __global__ __launch_bounds__(256) void near_kernel(const float* __restrict__ cen
 // tests and branches per row are scalar instructions, of which a SIMD issues no more than of the others.)
 // `parts` workgroups share a cluster's tokens: with one per cluster a batch of few or large clusters leaves most of
 // the chip idle (one cluster of 256 tokens: 85 us with one workgroup, 5 us with 64).
-// Up to kNearInSearch clusters per image the workgroup finds the near clusters itself (a launch less: 4 - 9 us; more
-// clusters are searched by near_kernel, once per cluster and not once per workgroup).
+// Up to kNearInSearch clusters per image (a row of 64 centroids for each wave) the workgroup finds the near clusters itself:
+// a launch less, 4 - 9 us.  More are searched by near_kernel, once per cluster: here every workgroup would sort several
+// rows per wave in turn, with `parts` workgroups per cluster each for itself.
 constexpr int kKnnWaves = 4;
 constexpr int kNearInSearch = kKnnWaves * kWave;
 constexpr int kFullChipWaves = 8192;  // 256 CUs x 4 SIMDs x 8 waves

@@ -11,7 +11,7 @@
 //   forward : one wave per anchor.  Lane j holds neighbour j of the anchor's row of the stage's neighbour table:
 //             distance to the anchor, z_j = score_j - p dist_j, w = softmax_j(z) by wave reductions.  The weighted
 //             sum of the feature rows moves 16 bytes per lane: a row takes PP lanes, 64 / PP rows are in flight per
-//             trip, and the row groups are added up with lane shuffles at the end.
+//             trip, and the row groups are added up on the vector ALU at the end.
 //   backward: the same wave forms g_j = <dout_anchor, feat_j> (partial dot per lane, reduced inside a row's
 //             lanes), dz_j = w_j (d_j - sum_i w_i d_i) with d_i = g_i - g_ref relative to the neighbour of largest
 //             weight (differences first: the form does not cancel when one weight saturates), its part of dp

@@ -77,6 +77,7 @@ struct Piece<bf16_t> {
 // Sums and maxima over lanes whose numbers differ in the bits LO .. HI (powers of two), every lane receiving the
 // result.  The exchanges run on the vector ALU (DPP patterns inside a row of 16 lanes, the row / half swaps across
 // rows): a softmax row costs some fifty of them, and through the LDS crossbar they were most of the kernel's time.
+// Nearest lanes first, unlike lanes_sum / lanes_max: with these the kernels took 0.6 % longer over 96 shapes (up to 4 %).
 // All lanes of the wave must be active.
 template <int J>
 __device__ __forceinline__ float lane_xor_f(float x, int lane) {

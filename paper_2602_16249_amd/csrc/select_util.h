@@ -132,12 +132,11 @@ __device__ __forceinline__ uint32_t wave_sort_u32(uint32_t key, int lane) {
 
 // Sorts the `fill` (<= 64) keys of `pend` (LDS, owned by the wave), whose distances are at most t, ascending across
 // the lanes; returns the lower half (index) of the lane's key, undefined from lane `fill` on (so callers queue at least
-// as many as they use).  The 64-bit network
-// costs ~170 vector instructions, once most of the search's time, so the order is found on 32-bit words (26 leading
-// bits of distance / t, place in `pend`), ~65 instructions.  Where neighbouring words share their leading bits (equal
-// or nearly equal distances) the keys themselves are fetched in that order and every neighbouring pair is compared in
-// full: the callers queue candidates in index order, so equal distances pass; what does not (rare) goes through the
-// 64-bit network.  The result is exact either way.
+// as many as they use).  The 64-bit network costs ~170 vector instructions, once most of the search's time, so the order
+// is found on 32-bit words (26 leading bits of distance / t, place in `pend`), ~65 instructions.  Where neighbouring
+// words share their leading bits (equal or nearly equal distances) the keys themselves are fetched in that order and
+// every neighbouring pair is compared in full: candidates of contiguous clusters are queued in index order, so equal
+// distances pass; what does not (rare) goes through the 64-bit network.  The result is exact either way.
 __device__ __forceinline__ uint32_t sort_queued(const key_t* pend, int fill, uint32_t t, int lane) {
   // (a scale that overflows, from a subnormal t, only makes the words useless as an order: the check below decides;
   // whatever the conversion makes of it, every word keeps its lane number, so the places stay a permutation)

@@ -22,9 +22,9 @@ CASES = [
     (2, 2, 2, (0.0, 0.0, 8.0, 8.0), "uniform"),
     (3, 100, 7, (0.0, 0.0, 64.0, 64.0), "uniform"),      # padded to 128, ragged last cluster
     (2, 4096, 64, (0.0, 0.0, 1024.0, 1024.0), "uniform"),
-    (2, 8192, 64, (0.0, 0.0, 1024.0, 1024.0), "normal"),   # exactly one LDS chunk; points outside the frame clamp
-    (2, 8193, 64, (-3.5, 7.25, 900.0, 333.0), "normal"),   # two chunks after padding to 16384
-    (1, 40000, 48, (0.0, 0.0, 512.0, 512.0), "uniform"),   # padded to 65536: several global steps
+    (2, 8192, 64, (0.0, 0.0, 1024.0, 1024.0), "normal"),   # four whole chunks; points outside the frame clamp
+    (2, 8193, 64, (-3.5, 7.25, 900.0, 333.0), "normal"),   # a fifth chunk of one token and pads
+    (1, 40000, 48, (0.0, 0.0, 512.0, 512.0), "uniform"),   # merged by the network, padded to 65536: several global steps
     (2, 5000, 16, (0.0, 0.0, 16.0, 16.0), "lattice"),      # integer lattice: many equal keys, index decides
 ]
 
@@ -83,8 +83,8 @@ def test_cluster_full_size_configs(name):
 
 @pytest.mark.parametrize("N", [255, 256, 257, 512, 513, 1024, 1025, 2047, 2048, 2049, 4096, 4097, 32768, 32769])
 def test_cluster_sizes_at_the_edges(N):
-    """One workgroup's words per thread (1, 2, 4, 8), one chunk or several, the most chunks that are ranked (16) and the
-    first size that the network merges: points on a lattice, so that the index decides among many equal keys."""
+    """One workgroup's words per thread (1 or 2) and runs (1, 2 or 4), one chunk or several, the most chunks that are ranked
+    (16) and the first size that the network merges: points on a lattice, so that the index decides among many equal keys."""
     rng = np.random.default_rng(N)
     coords = rng.integers(0, 40, size=(2, N, 2)).astype(np.float32)
     coords[1] *= 0.37

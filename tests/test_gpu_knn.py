@@ -31,7 +31,7 @@ SMALL = [
     ("knn_scale", 2, 512, 8, 3, 1),            # K = 1: every token is its own nearest
     ("knn_scale", 1, 640, 10, 64, 64),         # M at the limit, odd S
     ("knn_scale", 1, 4096, 64, 64, 64),        # the most candidates the library takes (4096)
-    ("tiny_f32", 2, 1024, 128, 8, 48),         # 1024 candidates: the general kernel
+    ("tiny_f32", 2, 1024, 128, 8, 48),         # 1024 candidates: the most that registers hold
 ]
 
 
@@ -102,7 +102,7 @@ RAGGED = [
     ("knn_scale", 2, 481, 32, 3, 20),          # a last cluster of one token
     ("knn_scale", 3, 33, 32, 2, 1),            # two clusters, the second a single token
     ("merged_stage", 2, 1001, 32, 8, 48),      # N odd: nothing is a whole tile
-    ("tiny_f32", 2, 1000, 128, 8, 48),         # 1024 candidate places (general kernel), 104 tokens in the last cluster
+    ("tiny_f32", 2, 1000, 128, 8, 48),         # 1024 candidate places, 104 tokens in the last cluster
     ("knn_scale", 1, 100, 64, 2, 100),         # M == G: exact search over 100 tokens, K = all of them... capped below
 ]
 
