@@ -262,7 +262,9 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(PlanParams p) {
 // one launch and four: one image of 64 / 256 / 512 / 1024 / 2048 tiles 15 / 18 / 19 / 24 / 28 us and 18 / 20 / 19 / 21 / 23
 // us; 1024 tiles, 4 / 8 / 16 / 32 images 30 / 22 / 64 / 104 us and 29 / 25 / 66 / 112 us (at 8, K = 9); 2048 tiles, 8 /
 // 16 images 69 / 109 us and 66 / 112 us.  So: up to 512 tiles, and beyond in batches of tiles / 128 images or more.
-constexpr int kRevTiles = 2048, kRevTilesSmall = 512;
+// Images of a few tiles take a workgroup each and give it little to do (1 tile: 16 us at 1024 images, 26 at 2048, against
+// 18; 4 tiles: 17 / 26 us at 768 / 1536 against 18 / 21; 16 tiles: 133 us at 4096 against 135): below 16 tiles, up to 768.
+constexpr int kRevTiles = 2048, kRevTilesSmall = 512, kRevTilesFew = 16, kRevImagesFew = 768;
 constexpr int kRevThreads = 1024;
 __global__ __launch_bounds__(kRevThreads) void plan_reverse_kernel(PlanParams p, int own) {
   __shared__ int32_t count[kRevTiles];   // incidences per tile
@@ -373,7 +375,9 @@ hipError_t launch_pla_plan(const int32_t* nbr_idx, const int32_t* near, int B, i
   const int tiles = p.strips_per_image;
   const int own = std::max(16, (int)((L.strips + 255ll) / 256));
   const long long groups = (long long)B * ((tiles + own - 1) / own);
-  p.count_tiles = !(tiles <= kRevTilesSmall || (tiles <= kRevTiles && tiles <= 128ll * B)) ||
+  const bool one_launch = tiles < kRevTilesFew ? B <= kRevImagesFew
+                                               : tiles <= kRevTilesSmall || (tiles <= kRevTiles && tiles <= 128ll * B);
+  p.count_tiles = !one_launch ||
                   (long long)L.strips * L.max_slots >= (1ll << 31) || groups * kRevThreads >= (1ll << 32);
   if (p.count_tiles)
     AFFMAE_LAUNCH("plan_zero_kernel", stream, plan_zero_kernel, dim3((L.strips + 255) / 256), dim3(256), 0, stream,

@@ -247,6 +247,7 @@ def test_short_last_cluster_end_to_end(N, tiled):
     (32768, 64, 8, 4, False, 16),    # the most of all, and one tile more
     (32769, 64, 8, 4, False, 16),
     (64, 16, 2, 8, False, 600),      # more images than workgroups wanted: one for each
+    (48, 16, 2, 8, False, 769),      # more images of a few tiles than one launch serves well
 ])
 def test_reverse_tables_of_the_plan(N, S, M, K, same, B):
     """dk and dv walk the plan's reverse tables: lists of more than 64 strips (all points coincide, so that the index
