@@ -177,23 +177,24 @@ __device__ __forceinline__ int count_below(const word_t* run, int n, word_t word
   return s + (below(run[s]) ? 1 : 0);  // (s <= n - 1 here)
 }
 
-// Builds the words of one chunk and sorts it: RUNS groups of 256 threads sort 256 W words each in registers, then a
+// Builds the words of one chunk and sorts it: RUNS groups of THREADS threads sort THREADS W words each in registers, then a
 // word's place is its place in its run plus the counts of smaller words in the others.  WHOLE: the chunk is the image,
 // its order is written at once; otherwise the sorted words.  Bound by a chain of dependent steps with few waves per SIMD:
 // 2048 words by 256 threads with 8 words each, the whole network in registers or through LDS, 18 - 19 us for 128 chunks,
 // as four runs of 512 by 1024 threads 12.6 us.  Images of 513 to 1024 tokens take two runs (2048 images of 600: 57 us
-// with four, half of whose words are pads; 38 as one network over 1024 words; 29 with two).
-template <int W, int RUNS, bool WHOLE>
-__global__ __launch_bounds__(kSortThreads* RUNS) void cluster_sort_chunk_kernel(ClusterParams p, int chunks, bool network) {
-  constexpr int kRun = W * kSortThreads, kWords = kRun * RUNS;
+// with four, half of whose words are pads; 38 as one network over 1024 words; 29 with two), images of up to 64 a wave
+// (THREADS; 100 000 images of 16: 192 us with 256 threads each, 40 with 64).
+template <int W, int RUNS, bool WHOLE, int THREADS = kSortThreads>
+__global__ __launch_bounds__(THREADS* RUNS) void cluster_sort_chunk_kernel(ClusterParams p, int chunks, bool network) {
+  constexpr int kRun = W * THREADS, kWords = kRun * RUNS;
   __shared__ word_t buf[kWords];
   const int b = blockIdx.x / chunks, c = blockIdx.x - b * chunks, first = c * kWords;
-  const int g = threadIdx.x / kSortThreads, t = threadIdx.x % kSortThreads;
+  const int g = threadIdx.x / THREADS, t = threadIdx.x % THREADS;
   const word_t flip = network && (c & 1) ? ~0ull : 0ull;  // the network goes on from chunks in alternating order
   word_t v[W];
 #pragma unroll
-  for (int m = 0; m < W; ++m) v[m] = token_word(p, b, first + m * kSortThreads * RUNS + threadIdx.x) ^ flip;  // (any order will do)
-  sort_in_registers<W>(v, buf + g * kRun, kSortThreads, t);
+  for (int m = 0; m < W; ++m) v[m] = token_word(p, b, first + m * THREADS * RUNS + threadIdx.x) ^ flip;  // (any order will do)
+  sort_in_registers<W>(v, buf + g * kRun, THREADS, t);
   __syncthreads();
 #pragma unroll
   for (int m = 0; m < W; ++m) buf[g * kRun + t * W + m] = v[m];
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(kSortThreads* RUNS) void cluster_sort_chunk_kernel(
   __syncthreads();
 #pragma unroll
   for (int m = 0; m < W; ++m) {
-    const int at = m * kSortThreads * RUNS + threadIdx.x;
+    const int at = m * THREADS * RUNS + threadIdx.x;
     p.words[(size_t)b * p.npad + first + at] = buf[at] ^ flip;
   }
 }
@@ -325,7 +326,10 @@ static hipError_t launch_images(const ClusterParams& p, int B, hipStream_t strea
   AFFMAE_LAUNCH("cluster_sort_chunk_kernel", stream, (cluster_sort_chunk_kernel<W, RUNS, WHOLE>),                  \
                 dim3((unsigned)B * (CHUNKS)), dim3(kSortThreads * (RUNS)), 0, stream, p, CHUNKS, NETWORK)
   if (N <= kChunk) {  // one chunk per image
-    if (N <= kSortThreads) AFFMAE_SORT(1, 1, true, 1, false);
+    if (N <= kWave)
+      AFFMAE_LAUNCH("cluster_sort_chunk_kernel", stream, (cluster_sort_chunk_kernel<1, 1, true, kWave>), dim3((unsigned)B), dim3(kWave),
+                    0, stream, p, 1, false);
+    else if (N <= kSortThreads) AFFMAE_SORT(1, 1, true, 1, false);
     else if (N <= 2 * kSortThreads) AFFMAE_SORT(2, 1, true, 1, false);
     else if (N <= 4 * kSortThreads) AFFMAE_SORT(2, 2, true, 1, false);
     else AFFMAE_SORT(2, 4, true, 1, false);

@@ -81,7 +81,7 @@ def test_cluster_full_size_configs(name):
     assert np.array_equal(o3, ident)
 
 
-@pytest.mark.parametrize("N", [255, 256, 257, 512, 513, 1024, 1025, 2047, 2048, 2049, 4096, 4097, 32768, 32769])
+@pytest.mark.parametrize("N", [63, 64, 65, 255, 256, 257, 512, 513, 1024, 1025, 2047, 2048, 2049, 4096, 4097, 32768, 32769])
 def test_cluster_sizes_at_the_edges(N):
     """One workgroup's words per thread (1 or 2) and runs (1, 2 or 4), one chunk or several, the most chunks that are ranked
     (16) and the first size that the network merges: points on a lattice, so that the index decides among many equal keys."""
@@ -95,7 +95,7 @@ def test_cluster_sizes_at_the_edges(N):
 
 
 def test_cluster_many_small_images():
-    """2^24 images of two tokens: with 256 threads for each, more than one launch can have."""
+    """2^24 images of two tokens: the batch is cut, as a launch cannot have 256 threads for each image of such a batch."""
     B = 1 << 24
     x = torch.rand(B, device="cuda")
     coords = torch.stack([torch.stack([x, x], -1), torch.stack([1 - x, 1 - x], -1)], dim=1).contiguous()
