@@ -6,9 +6,9 @@
 // Per image the tokens are sorted by the 64-bit word (curve key << 32 | token
 // index): unique words, so the order is exact and ties go to the lower index.
 // Chunks of up to 2048 words are sorted by one workgroup each (a bitonic network
-// whose words stay in registers; many workgroups per image).  Up to 16 chunks an
-// image's order then follows in one more launch: a word's place is its place in
-// its chunk plus the number of smaller words in every other chunk (binary
+// whose words stay in registers, or in LDS where there are very many chunks).  Up
+// to 16 chunks an image's order then follows in one more launch: a word's place is
+// its place in its chunk plus the number of smaller words in every other chunk (binary
 // searches).  Larger images are merged by the network's remaining steps over the
 // words padded to a power of two (pads are all ones and end up last): steps whose
 // partner lies in another chunk run over global memory, up to three per pass, the
@@ -229,6 +229,21 @@ __global__ __launch_bounds__(THREADS* RUNS) void cluster_sort_chunk_kernel(Clust
   }
 }
 
+// The same for chunks of larger images in a launch of kManyChunks or more: the whole network through LDS by 256 threads, a
+// longer chain but half the work.  1000 images of 4096 tokens (2000 chunks), whole clustering: 106 us, 120 with four runs;
+// 512 / 900 / 1024 chunks 44 / 69 / 68 us against 41 / 71 / 70.
+constexpr int kManyChunks = 1024;
+__global__ __launch_bounds__(kSortThreads) void cluster_sort_chunk_lds_kernel(ClusterParams p, int chunks, bool network) {
+  __shared__ word_t buf[kChunk];
+  const int b = blockIdx.x / chunks, c = blockIdx.x - b * chunks, first = c * kChunk;
+  const word_t flip = network && (c & 1) ? ~0ull : 0ull;
+  for (int t = threadIdx.x; t < kChunk; t += kSortThreads) buf[lds_place(t)] = token_word(p, b, first + t) ^ flip;
+  __syncthreads();
+  for (int k = 2; k <= kChunk; k <<= 1) lds_steps(buf, kChunk, 0, k, k >> 1);
+  word_t* out = p.words + (size_t)b * p.npad + first;
+  for (int t = threadIdx.x; t < kChunk; t += kSortThreads) out[t] = buf[lds_place(t)] ^ flip;
+}
+
 // Order of an image whose `chunks` (2 .. 16) chunks are sorted: a word's place is its place in its chunk plus, for
 // every other chunk, the number of smaller words there, found by binary search: 6 steps on every 32nd word of the chunk
 // (in LDS), 5 on the words between (the lanes of a wave hold neighbouring words, so they read neighbouring places).
@@ -325,6 +340,13 @@ static hipError_t launch_images(const ClusterParams& p, int B, hipStream_t strea
 #define AFFMAE_SORT(W, RUNS, WHOLE, CHUNKS, NETWORK)                                                               \
   AFFMAE_LAUNCH("cluster_sort_chunk_kernel", stream, (cluster_sort_chunk_kernel<W, RUNS, WHOLE>),                  \
                 dim3((unsigned)B * (CHUNKS)), dim3(kSortThreads * (RUNS)), 0, stream, p, CHUNKS, NETWORK)
+#define AFFMAE_SORT_CHUNKS(CHUNKS, NETWORK)                                                                        \
+  do {                                                                                                             \
+    if ((long long)B * (CHUNKS) < kManyChunks) AFFMAE_SORT(2, 4, false, CHUNKS, NETWORK);                          \
+    else                                                                                                           \
+      AFFMAE_LAUNCH("cluster_sort_chunk_kernel", stream, cluster_sort_chunk_lds_kernel,                            \
+                    dim3((unsigned)B * (CHUNKS)), dim3(kSortThreads), 0, stream, p, CHUNKS, NETWORK);              \
+  } while (0)
   if (N <= kChunk) {  // one chunk per image
     if (N <= kWave)
       AFFMAE_LAUNCH("cluster_sort_chunk_kernel", stream, (cluster_sort_chunk_kernel<1, 1, true, kWave>), dim3((unsigned)B), dim3(kWave),
@@ -337,7 +359,7 @@ static hipError_t launch_images(const ClusterParams& p, int B, hipStream_t strea
   }
   const int chunks = (N + kChunk - 1) / kChunk;
   if (chunks <= kMaxRankChunks) {
-    AFFMAE_SORT(2, 4, false, chunks, false);
+    AFFMAE_SORT_CHUNKS(chunks, false);
     AFFMAE_LAUNCH("cluster_rank_kernel", stream, cluster_rank_kernel, dim3(chunks * (kChunk / 256), B), dim3(256), 0, stream, p, chunks);
     return hipGetLastError();
   }
@@ -345,7 +367,8 @@ static hipError_t launch_images(const ClusterParams& p, int B, hipStream_t strea
   const size_t lds = (size_t)chunk * sizeof(word_t);
   const int threads = kSortThreads;
   const dim3 per_chunk(B * (p.npad / chunk));
-  AFFMAE_SORT(2, 4, false, p.npad / chunk, true);
+  AFFMAE_SORT_CHUNKS(p.npad / chunk, true);
+#undef AFFMAE_SORT_CHUNKS
 #undef AFFMAE_SORT
   for (int k = chunk * 2; k <= p.npad; k <<= 1) {
     int j = k >> 1;

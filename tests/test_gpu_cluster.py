@@ -94,6 +94,17 @@ def test_cluster_sizes_at_the_edges(N):
     assert np.array_equal(cid, rcid)
 
 
+@pytest.mark.parametrize("B,N", [(511, 2049), (512, 2049), (512, 4096), (64, 32768), (32, 33000)])
+def test_cluster_many_chunks(B, N):
+    """Chunks of large images sorted in registers or, from 1024 of them on, through LDS: ranked, and merged by the network."""
+    rng = np.random.default_rng(B + N)
+    coords = rng.integers(0, 300, size=(B, N, 2)).astype(np.float32)
+    order, cid = _gpu_cluster(coords, 64, (0.0, 0.0, 300.0, 300.0))
+    rorder, rcid = oracle.cluster(coords, 64, (0.0, 0.0, 300.0, 300.0))
+    assert np.array_equal(order, rorder)
+    assert np.array_equal(cid, rcid)
+
+
 def test_cluster_many_small_images():
     """2^24 images of two tokens: the batch is cut, as a launch cannot have 256 threads for each image of such a batch."""
     B = 1 << 24
