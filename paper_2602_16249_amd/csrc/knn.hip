@@ -219,7 +219,8 @@ __global__ __launch_bounds__(kKnnWaves* kWave) void knn_kernel(const float* __re
   const int step = parts * kKnnWaves, first = part * kKnnWaves + wave;
   const int served = first < my_size ? (my_size - 1 - first) / step + 1 : 0;  // tokens of this wave
   if (!MEMBERS) {
-    if (__builtin_amdgcn_readfirstlane(odd_lds[0] | odd_lds[1] | odd_lds[2] | odd_lds[3]) != 0) {  // distances may be NaN
+    // (distances may be NaN; "expect" puts the loop behind the others': 0.3 % of the search's time)
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(odd_lds[0] | odd_lds[1] | odd_lds[2] | odd_lds[3]) != 0, 0)) {
       for (int i = first; i < my_size; i += step) {
         const int qtok = c * S + i;
         const float qx = xy[2 * (size_t)qtok], qy = xy[2 * (size_t)qtok + 1];
