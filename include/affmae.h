@@ -277,7 +277,8 @@ int affmae_knn_static(const float* coords, const int32_t* cluster_id, int B, int
  *   nbr_idx, near_clusters  in  as produced by affmae_knn with cluster_id == NULL
  *                               (the promise described under affmae_pla_fwd).
  *   plan                    out caller-owned device buffer of affmae_pla_plan_bytes()
- *                               bytes, 256-byte aligned; opaque.
+ *                               bytes, 256-byte aligned; opaque, and readable only by
+ *                               the library build that filled it (affmae_build_id).
  * affmae_pla_plan_bytes returns 0, and affmae_pla_plan AFFMAE_ERR_UNSUPPORTED,
  * when the shapes are outside what the tiled kernels take (they need S % 16 == 0
  * - S need not divide N, nor 16: the last cluster, strip and token tile of an
@@ -383,11 +384,11 @@ int affmae_pla_bwd(const void* q, const void* k, const void* v, const void* bias
  * `bias` replaced by (coords, rel_table, R, rate) and `dbias` by drel_table.
  *
  * With the cluster promise, bf16, d = 32 and K a multiple of 8 the tiled kernels
- * compute the bias themselves (the coordinates of the token tiles a strip
- * touches are staged in LDS, a cell per (query, neighbour) pair, the value
- * through the cache): no bias or dbias tensor exists, and for tables of at most
- * 128 cells per head (R <= 5) the gradient of the table is summed inside the
- * backward kernel as well.  In every other case the bias is written into the
+ * look the bias up themselves: a small kernel writes the table cell of every
+ * (token, neighbour) pair into the workspace, 2 bytes for all heads together, and
+ * they read the head's table from LDS: no bias or dbias tensor exists, and for
+ * tables of at most 128 cells per head (R <= 5) the gradient of the table is summed
+ * inside the backward kernel as well.  In every other case the bias is written into the
  * workspace by a kernel of its own and the table's gradient is reduced from
  * dbias by another; the results are the same.
  *

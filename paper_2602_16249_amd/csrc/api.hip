@@ -489,7 +489,8 @@ bool relpos_in_kernel(int B, int N, int d, int K, int S, int M, int dtype, int c
 size_t affmae_pla_fwd_relpos_workspace_bytes(int B, int N, int H, int d, int K, int S, int M, int dtype,
                                              int clustered) {
   if (check_pla_shape(B, N, H, d, K, dtype) != AFFMAE_OK) return 0;
-  if (relpos_in_kernel(B, N, d, K, S, M, dtype, clustered)) return align_up(affmae::pla_plan_bytes(B, N, K, S, M));
+  if (relpos_in_kernel(B, N, d, K, S, M, dtype, clustered))
+    return align_up(affmae::relpos_cells_bytes(B, N, K)) + align_up(affmae::pla_plan_bytes(B, N, K, S, M));
   return bias_bytes(B, N, H, K, dtype) + align_up(affmae_pla_fwd_workspace_bytes(B, N, H, d, K, S, M, dtype, clustered));
 }
 
@@ -524,11 +525,16 @@ int affmae_pla_fwd_relpos(const void* q, const void* k, const void* v, const flo
     if (misaligned(q, 16) || misaligned(k, 16) || misaligned(v, 16) || misaligned(out, 16)) return AFFMAE_ERR_SHAPE;
     if ((k_blank && misaligned(k_blank, 16)) || (v_blank && misaligned(v_blank, 16))) return AFFMAE_ERR_SHAPE;
     if (plan && misaligned(plan, kAlign)) return AFFMAE_ERR_WORKSPACE;
-    if (!plan) {  // the workspace holds at least a plan (checked above)
-      if (affmae::launch_pla_plan(nbr_idx, near_clusters, B, N, K, S, M, ws, st) != hipSuccess)
+    const affmae::RelposArgs r = {coords, nbr_idx, rel_table, R, rate};
+    uint16_t* cells = reinterpret_cast<uint16_t*>(ws);
+    a.rel_cells = cells;
+    if (!plan) {  // the workspace holds the cells and a plan (checked above)
+      void* own = ws + align_up(affmae::relpos_cells_bytes(B, N, K));
+      if (affmae::launch_pla_plan(nbr_idx, near_clusters, B, N, K, S, M, own, st) != hipSuccess)
         return AFFMAE_ERR_DEVICE;
-      plan = ws;
+      plan = own;
     }
+    if (affmae::launch_relpos_cells(r, plan, B, N, H, K, S, M, cells, st) != hipSuccess) return AFFMAE_ERR_DEVICE;
     return affmae::launch_pla_fwd_cluster(a, plan, st) == hipSuccess ? AFFMAE_OK : AFFMAE_ERR_DEVICE;
   }
   // the bias is written into the workspace by a kernel of its own: validate the attention call before it
@@ -548,7 +554,7 @@ size_t affmae_pla_bwd_relpos_workspace_bytes(int B, int N, int H, int d, int K, 
     const size_t table = affmae::pla_bwd_cluster_rel_sums(R)
                              ? align_up(affmae::pla_bwd_cluster_rel_workspace_bytes(B, N, H, R))
                              : bias_bytes(B, N, H, K, dtype) + align_up(affmae::relpos_dtable_workspace_bytes(B, N, H, K, R));
-    return table + align_up(affmae::pla_plan_bytes(B, N, K, S, M)) +
+    return table + align_up(affmae::relpos_cells_bytes(B, N, K)) + align_up(affmae::pla_plan_bytes(B, N, K, S, M)) +
            align_up(affmae::pla_bwd_cluster_workspace_bytes(B, N, H, K, S, M));
   }
   return 2 * bias_bytes(B, N, H, K, dtype) + align_up(affmae::relpos_dtable_workspace_bytes(B, N, H, K, R)) +
@@ -607,11 +613,15 @@ int affmae_pla_bwd_relpos(const void* q, const void* k, const void* v, const flo
       parts = ws + bb;
       off += bb + tb;
     }
+    uint16_t* cells = reinterpret_cast<uint16_t*>(ws + off);
+    a.rel_cells = cells;
+    off += align_up(affmae::relpos_cells_bytes(B, N, K));
     if (!plan) {
       if (affmae::launch_pla_plan(nbr_idx, near_clusters, B, N, K, S, M, ws + off, st) != hipSuccess)
         return AFFMAE_ERR_DEVICE;
       plan = ws + off;
     }
+    if (affmae::launch_relpos_cells(r, plan, B, N, H, K, S, M, cells, st) != hipSuccess) return AFFMAE_ERR_DEVICE;
     off += align_up(affmae::pla_plan_bytes(B, N, K, S, M));
     if (affmae::launch_pla_bwd_cluster(a, plan, ws + off, st) != hipSuccess) return AFFMAE_ERR_DEVICE;
     if (!sums && affmae::launch_relpos_dtable(r, B, N, H, K, dtype, a.dbias, drel_table, parts, st) != hipSuccess)

@@ -6,8 +6,8 @@
 //
 // The plan (built by pla_plan.hip from the neighbour table) describes, per
 // strip, which token tiles hold at least one neighbour of one of its queries
-// ("slots", at most kMaxSlots) and, for every (query, neighbour slot j), where
-// that neighbour sits: entry = slot * 256 + tile_cell(query, token % 16) (see tile_cell below).
+// ("slots", at most kMaxSlots) and, for every (query, token) pair of a strip and a
+// slot, where the token stands in the query's neighbour list (see PlanLayout).
 #pragma once
 
 #include "device_util.h"
@@ -22,7 +22,6 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;  // 16 bytes on thei
 constexpr int kD = 32;                 // channels per head
 constexpr int kMaxSlots = 64;          // token tiles one strip may touch (M*S/16 <= 64)
 constexpr int kMaxEntries = 16;        // 16 queries * K (<= 64) neighbours / 64 lanes
-constexpr uint32_t kNoEntry = 0xffffu;
 
 union Frag8 {
   bf16x8 v;
@@ -40,27 +39,41 @@ union Frag4 {
   uint16_t h[4];
 };
 
-// Layout of the plan buffer.  "Incidence" = (strip, slot): a strip and one of the token tiles it touches.
-// Per strip the valid entries are also listed grouped by slot ("runs", ascending entry index inside a
-// run): sorted_pos holds the entry values in that order and runs[s] the start of slot s's run, so the
-// (p, dS) words that the backward pass leaves in run order can be read back per incidence as one
-// contiguous piece.  The reverse tables list, per token tile, the incidences that touch it (sorted, so
-// that sums formed along a list do not depend on scheduling), each with the place of its run.
+// Strips are taken in groups of kGroup consecutive ones of an image: the strips of a group touch mostly the same token
+// tiles (14.7 different ones per group on a jittered grid where each strip touches 8.6; 18.9 and 12.1 in clumps), so one
+// workgroup fetches the union once and each of its waves serves one strip from LDS.
+constexpr int kGroup = 4;
+static_assert(kGroup * kMaxSlots <= 256, "places in a group's union are bytes");
+
+// Layout of the plan buffer.
+//  uni     per group: how many token tiles its strips touch together, then these tiles, ascending.
+//  pos     per strip: how many of them it touches itself (its "slots", ascending), then each slot's place in the union.
+//  jt      per strip and slot, for every (query, token) of the 16 x 16 pairs, where the token stands in the query's
+//          neighbour list: one byte, 2 j, or 2 K for "no neighbour".  It is at the same time the byte offset of the
+//          pair's value in a row of K two-byte values with one more place behind them.  Two slots share a block of
+//          512 bytes, lane (g, q) = 16 g + q of a wave finding its four bytes for tokens 4g..4g+3 of query q at
+//          8 (16 g + q) for the first and 4 further on for the second: one 8-byte load serves a pair of slots.
+//  touch   per strip: how many groups of token tiles it touches, then per such group the group's number (high half)
+//          and the strip's slots of the group's four tiles (one byte each in the low half, 0xff: not touched).
+//  rev     the same seen from the tiles: per group of token tiles the strips that touch it, ascending (the sums
+//          formed along the list then do not depend on scheduling): strip (high half), slots of the four tiles.
+// Bytes written per strip: 256 per slot against 2 K bytes for a list of the pairs' cells, twice; in exchange no
+// kernel sorts pairs or scatters values over a tile.
 struct PlanLayout {
-  int strips;        // B * ceil(N / 16) (also the number of token tiles)
-  int max_slots;     // M * S / 16
-  int slot_stride;   // uint16 per strip in the slot table: [0] = count, [1 + s] = token tile of slot s
-  int runs_stride;   // uint16 per strip in the run table: [s] = first place of slot s, [count] = places used
-  int places;        // places per strip in run order: 16 * K entries + room to start every run at an even place
+  int strips;            // B * strips_per_image (also the number of token tiles)
+  int strips_per_image;  // ceil(N / 16)
+  int groups_per_image, groups;
+  int max_slots;         // M * S / 16
   int K;
-  size_t slots_off;       // uint16 [strips][slot_stride]
-  size_t entries_off;     // uint16 [strips][16 * K]
-  size_t sorted_pos_off;  // uint16 [strips][places]   entry values grouped by slot; kNoEntry in unused places
-  size_t runs_off;        // uint16 [strips][runs_stride]
-  size_t rev_count_off;   // int32  [strips]      incidences per token tile
-  size_t rev_offset_off;  // int32  [strips + 1]  where a token tile's incidences start in rev_list
-  size_t rev_cursor_off;  // int32  [strips]      build-time cursors
-  size_t rev_list_off;    // uint64 [strips * max_slots]  low: (strip within image) << 8 | slot; high: run start | run length << 16
+  int uni_stride;        // uint16 per group
+  int pos_stride;        // uint8 per strip
+  int jt_pairs;          // pairs of slots per strip
+  int touch_stride;      // uint64 per strip
+  size_t uni_off, pos_off, jt_off, touch_off;
+  size_t rev_count_off;   // int32  [groups]
+  size_t rev_offset_off;  // int32  [groups + 1]  where a group's list starts in rev_list
+  size_t rev_cursor_off;  // int32  [groups]      build-time cursors
+  size_t rev_list_off;    // uint64 [strips * (touch_stride - 1)]
   size_t total;
 };
 
@@ -68,47 +81,44 @@ inline size_t plan_align(size_t n) { return (n + 255) / 256 * 256; }
 
 inline PlanLayout make_plan_layout(int B, int N, int K, int S, int M) {
   PlanLayout L;
-  L.strips = (int)((long long)B * ((N + 15) / 16));  // the last strip / token tile of an image may be short
-  int max_slots = (int)((long long)M * S / 16);
-  L.max_slots = max_slots;
-  L.slot_stride = 1 + max_slots + (max_slots & 1);  // room to pad to an even number of slots
-  if (L.slot_stride & 1) L.slot_stride += 1;
+  L.strips_per_image = (N + 15) / 16;  // the last strip / token tile of an image may be short
+  L.strips = (int)((long long)B * L.strips_per_image);
+  L.groups_per_image = (L.strips_per_image + kGroup - 1) / kGroup;
+  L.groups = B * L.groups_per_image;
+  L.max_slots = (int)((long long)M * S / 16);
   L.K = K;
+  const int most = kGroup * L.max_slots < L.strips_per_image ? kGroup * L.max_slots : L.strips_per_image;
+  L.uni_stride = (1 + most + 1) / 2 * 2;
+  L.pos_stride = (1 + L.max_slots + 3) / 4 * 4;
+  L.jt_pairs = (L.max_slots + 1) / 2;
+  L.touch_stride = 1 + (L.max_slots < L.groups_per_image ? L.max_slots : L.groups_per_image);
   size_t off = 0;
-  L.slots_off = off;
-  off += plan_align((size_t)L.strips * L.slot_stride * sizeof(uint16_t));
-  L.entries_off = off;
-  off += plan_align((size_t)L.strips * 16 * K * sizeof(uint16_t));
-  L.places = 16 * K + max_slots + (max_slots & 1);  // even
-  L.sorted_pos_off = off;
-  off += plan_align((size_t)L.strips * L.places * sizeof(uint16_t));
-  L.runs_stride = max_slots + 2 + (max_slots & 1);
-  L.runs_off = off;
-  off += plan_align((size_t)L.strips * L.runs_stride * sizeof(uint16_t));
+  L.uni_off = off;
+  off += plan_align((size_t)L.groups * L.uni_stride * sizeof(uint16_t));
+  L.pos_off = off;
+  off += plan_align((size_t)L.strips * L.pos_stride);
+  L.jt_off = off;
+  off += plan_align((size_t)L.strips * L.jt_pairs * 512);
+  L.touch_off = off;
+  off += plan_align((size_t)L.strips * L.touch_stride * sizeof(uint64_t));
   L.rev_count_off = off;
-  off += plan_align((size_t)L.strips * sizeof(int32_t));
+  off += plan_align((size_t)L.groups * sizeof(int32_t));
   L.rev_offset_off = off;
-  off += plan_align(((size_t)L.strips + 1) * sizeof(int32_t));
+  off += plan_align(((size_t)L.groups + 1) * sizeof(int32_t));
   L.rev_cursor_off = off;
-  off += plan_align((size_t)L.strips * sizeof(int32_t));
+  off += plan_align((size_t)L.groups * sizeof(int32_t));
   L.rev_list_off = off;
-  off += plan_align((size_t)L.strips * max_slots * sizeof(uint64_t));
+  off += plan_align((size_t)L.strips * (L.touch_stride - 1) * sizeof(uint64_t));
   L.total = off;
   return L;
 }
 
-// Cells of a 16 x 16 (query, token) tile in LDS sit at query * 16 + (token ^ (f(query) << 2)), f(q) = (q >> 1) & 3,
-// and the plan's entries carry the cell in this form.  A lane of the MFMA layouts reads or writes the four cells of
-// tokens 4g..4g+3 of query r as one piece of 8 bytes (bf16 cells) or 16 bytes (word cells); without the XOR the
-// pieces of several queries start on the same banks (measured per 16-byte access of a wave, 16 waves per CU: write
-// 32 cycles without, 13.6 with; read 8.2 without, 5.6 with this f, 8.2 with f = ((q >> 1) & 3) ^ (q >> 3)).  The
-// XOR only permutes groups of four tokens, so a piece still holds tokens 4g'..4g'+3.
-__device__ __forceinline__ int cell_group_swizzle(int q) { return (q >> 1) & 3; }  // q in 0..15
-__device__ __forceinline__ int tile_cell(int q, int tok) { return q * 16 + (tok ^ (cell_group_swizzle(q) << 2)); }
-// token of a cell value (low byte of an entry)
-__device__ __forceinline__ uint32_t cell_token(uint32_t cell) {
-  return (cell & 15u) ^ (((cell >> 5) & 3u) << 2);
-}
+// A row of K two-byte values and the place behind them that "no neighbour" points to, rounded so that rows start on
+// words (and, for K a multiple of 8, on odd words: 16 rows spread over the LDS banks).
+__host__ __device__ __forceinline__ int row_halves(int K) { return (K & 1) ? K + 1 : K + 2; }
+
+// A launch has at most 2^32 - 1 threads: larger ones are cut into slices of workgroups of 256 (a multiple of 8 each).
+constexpr long long kMaxBlocks = (1ll << 24) - 8;
 
 // Division of a non-negative int by a small run-time constant through a 32-bit reciprocal (exact for the
 // ranges used here: n * d < 2^31).  The reciprocal of 1 does not fit 32 bits: magic 0 stands for it.

@@ -1,0 +1,235 @@
+// What the forward and the query-stationary backward kernel share: a workgroup of four waves serves a group of four
+// strips for one head; the union of the token tiles that the strips touch is fetched into LDS once, straight from
+// memory, and every wave walks the tiles of its own strip there.
+//
+// Before, every (strip, head) wave fetched its tiles itself, a pair at a time, through registers: a row crossed L1 and
+// LDS 8.6 times where 3.7 are needed, and a strip of five pairs waited for memory five times in a row.  Clocked inside
+// the kernels, such a chain, not a unit of the chip, was most of a wave's life.  Now everything that a strip needs is
+// requested at its start: the tiles, its bias rows, its q rows and the j words of all its slots.
+#pragma once
+
+#include "cluster_common.h"
+
+namespace affmae {
+
+constexpr int kSpare = 8;   // tiles beyond the places in LDS whose rows wait in registers, two per wave
+constexpr int kPairs = 12;  // pairs of slots whose j words are held in registers
+
+struct GroupTables {
+  const uint16_t* uni;
+  const uint8_t* pos;
+  const char* jt;
+  int N, H, strips_per_image, groups_per_image, groups, uni_stride, pos_stride;
+  uint32_t h_magic, gpi_magic;  // reciprocals of H and of groups_per_image
+  // products that the kernels would form again and again (each below 2^32: see pla_cluster_supported)
+  uint32_t row_bytes;  // of a token in q, k, v, out: all heads
+  uint32_t img_bytes;  // ... of an image
+  uint32_t img_pairs;  // N * H * K, values of an image in bias, dbias
+  uint32_t jt_bytes;   // of a strip in the j table
+};
+// 64-bit product of 32-bit values: two scalar instructions instead of the eight of a 64-bit product
+__device__ __forceinline__ size_t mul_u32(uint32_t a, uint32_t b) { return (size_t)a * b; }
+
+inline GroupTables group_tables(const PlanLayout& L, const void* plan, int N, int H, int K) {
+  const char* base = static_cast<const char*>(plan);
+  GroupTables t;
+  t.uni = reinterpret_cast<const uint16_t*>(base + L.uni_off);
+  t.pos = reinterpret_cast<const uint8_t*>(base + L.pos_off);
+  t.jt = base + L.jt_off;
+  t.N = N; t.H = H;
+  t.strips_per_image = L.strips_per_image; t.groups_per_image = L.groups_per_image; t.groups = L.groups;
+  t.uni_stride = L.uni_stride; t.pos_stride = L.pos_stride;
+  t.row_bytes = (uint32_t)H * kD * 2u; t.img_bytes = (uint32_t)N * t.row_bytes;
+  t.img_pairs = (uint32_t)((long long)N * H * K); t.jt_bytes = (uint32_t)L.jt_pairs * 512u;
+  t.h_magic = div_magic(H); t.gpi_magic = div_magic(L.groups_per_image);
+  return t;
+}
+
+__device__ __forceinline__ f32x4 mfma32(const Frag8& a, const Frag8& b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 mfma16(const Frag4& a, const Frag4& b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a.v, b.v, c, 0, 0, 0);
+}
+
+// Workgroups are dealt round-robin to the 8 XCDs (one L2 each); neighbouring groups share rows, so give every XCD a
+// contiguous range.  The grid is a multiple of 8.
+__device__ __forceinline__ int xcd_contiguous_block() {
+  const int per_xcd = gridDim.x >> 3;
+  return (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+}
+
+// The wave's strip, and the tiles of its group.  PL: places for tiles in LDS, RAG: N is not a multiple of 16 (only then
+// do the row clamps exist in the code).
+template <int PL, bool RAG>
+struct TileWalk {
+  const GroupTables& t;
+  int lane, wave, g, r;  // lane = 16 g + r
+  int gi, h, b, sg, q0, nq;
+  bool live;  // the image's last group may have fewer than four strips
+  uint32_t row_bytes;  // of a token, all heads
+  size_t img_off;      // bytes before the image in q, k, v, out, ...
+  const uint16_t* ul;
+  const uint8_t* pl;
+  const char* jt;
+  const char *kimg, *vimg;
+  char* tiles;  // PL x 2 KB: K rows, V rows of a tile, 16-byte pieces placed by tile_chunk
+  int U, cnt;   // tiles of the union; the strip's slots
+  int my_tile, my_pos, u_raw, cnt_raw;
+  uint32_t lane_off, lane_off_max, tile_bytes;
+  uint2 jw[kPairs];
+  u32x4 sk[kSpare / kGroup], sv[kSpare / kGroup];
+
+  __device__ __forceinline__ TileWalk(const GroupTables& tables, int gi_, int h_, char* lds_tiles) : t(tables), gi(gi_), h(h_), tiles(lds_tiles) {
+    lane = threadIdx.x & (kWave - 1);
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform: keeps per-wave indices in SGPRs
+    g = lane >> 4;
+    r = lane & 15;
+    b = exact_div(gi, t.groups_per_image, t.gpi_magic);
+    const int si_raw = (gi - b * t.groups_per_image) * kGroup + wave;
+    live = si_raw < t.strips_per_image;
+    const int si = min(si_raw, t.strips_per_image - 1);
+    sg = b * t.strips_per_image + si;
+    q0 = si * 16;
+    // An image's last strip and last token tile may be short (N % 16 != 0): rows past the end are never addressed -
+    // loads repeat the last real row (no pair refers to it, so it meets probability 0), stores are skipped.
+    nq = RAG ? min(16, t.N - q0) : 16;
+    row_bytes = t.row_bytes;
+    img_off = mul_u32(b, t.img_bytes);
+    ul = t.uni + mul_u32(gi, t.uni_stride) + 1;
+    pl = t.pos + mul_u32(sg, t.pos_stride) + 1;
+    jt = t.jt + mul_u32(sg, t.jt_bytes);
+    u_raw = (int)ul[-1];
+    cnt_raw = (int)pl[-1];
+    my_tile = (int)ul[(uint32_t)min(lane, t.uni_stride - 2)];
+    my_pos = (int)pl[(uint32_t)min(lane, t.pos_stride - 2)];
+  }
+  // first value of the strip's rows in [B,N,H,K] (the head's for `head`), in [B,N,H] and in [B,N,K] arrays
+  __device__ __forceinline__ size_t pairs0(int K, int head) const { return mul_u32(b, t.img_pairs) + ((uint32_t)q0 * t.H + head) * K; }
+  __device__ __forceinline__ size_t heads0() const { return mul_u32(b, (uint32_t)(t.N * t.H)) + (uint32_t)(q0 * t.H + h); }
+  __device__ __forceinline__ size_t slots0(int K) const { return mul_u32(b, (uint32_t)(t.N * K)) + (uint32_t)(q0 * K); }
+  // byte offset, within the image, of 16-byte piece `piece` of the head's row of query `q` of the strip
+  __device__ __forceinline__ uint32_t query_piece(int q, int piece) const {
+    return (uint32_t)(q0 + (RAG ? min(q, nq - 1) : q)) * row_bytes + (uint32_t)(h * kD * 2 + piece * 16);
+  }
+  __device__ __forceinline__ uint32_t tile_off(int tile) const {
+    const uint32_t off = lane_off + (uint32_t)tile * tile_bytes;
+    return RAG ? min(off, lane_off_max) : off;
+  }
+  // K and V rows of a tile straight into a place (16 bytes per lane, lane l's piece landing at 16 l, i.e. row l / 4,
+  // place l % 4: the lane fetches the piece whose place that is)
+  __device__ __forceinline__ void issue(int tile, int place) const {
+    typedef const __attribute__((address_space(1))) void* gptr_t;
+    typedef __attribute__((address_space(3))) void* lptr_t;
+    const uint32_t off = tile_off(tile);
+    char* dst = tiles + place * 2048;
+    __builtin_amdgcn_global_load_lds((gptr_t)(kimg + off), (lptr_t)dst, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((gptr_t)(vimg + off), (lptr_t)(dst + 1024), 16, 0, 0);
+  }
+  // everything that depends on the group's and the strip's own records
+  __device__ __forceinline__ void request(const void* k, const void* v) {
+    U = __builtin_amdgcn_readfirstlane(u_raw);
+    cnt = min(__builtin_amdgcn_readfirstlane(cnt_raw), live ? kMaxSlots : 0);
+    // the second half of an odd strip's last pair meets "no neighbour", on the rows of a tile that is there
+    const int last_pos = __builtin_amdgcn_readlane(my_pos, max(cnt - 1, 0));
+    my_pos = lane < cnt ? my_pos : last_pos;
+    kimg = static_cast<const char*>(k) + img_off;
+    vimg = static_cast<const char*>(v) + img_off;
+    const int la = lane >> 2, lc = lane & 3;
+    const uint32_t piece = (uint32_t)((lc ^ ((la >> 1) & 3)) * 16 + h * kD * 2);
+    lane_off = (uint32_t)la * row_bytes + piece;
+    lane_off_max = (uint32_t)(t.N - 1) * row_bytes + piece;
+    tile_bytes = 16u * row_bytes;
+#pragma unroll
+    for (int i = 0; i < PL / kGroup; ++i)
+      if (i * kGroup + wave < U) issue(__builtin_amdgcn_readlane(my_tile, i * kGroup + wave), i * kGroup + wave);
+    // j words of the strip's pairs, two pairs a test (the second repeats the last pair where the strip ends before it)
+    const int last_pair = (max(cnt, 1) - 1) >> 1;
+#pragma unroll
+    for (int i = 0; i < kPairs; ++i) {
+      asm volatile("" : "=v"(jw[i].x), "=v"(jw[i].y));  // any value where no slot is: no instruction
+      if (2 * (i & ~1) < cnt) jw[i] = *reinterpret_cast<const uint2*>(jt + (uint32_t)(((i & 1) ? min(i, last_pair) : i) * 512 + lane * 8));
+    }
+#pragma unroll
+    for (int i = 0; i < kSpare / kGroup; ++i)
+      if (PL + i * kGroup + wave < U) {
+        const uint32_t off = tile_off(__builtin_amdgcn_readlane(my_tile, PL + i * kGroup + wave));
+        sk[i] = *reinterpret_cast<const u32x4*>(kimg + off);
+        sv[i] = *reinterpret_cast<const u32x4*>(vimg + off);
+      }
+  }
+  // All requested rows are in LDS, and so is what the other waves wrote there.
+  __device__ __forceinline__ void arrive() const {
+    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): rows on their way to LDS count as vector loads
+    __syncthreads();
+  }
+  // The strip's slots by pairs.  fetch(frag, w0, w1, at0, at1) reads from LDS what a pair needs (j words w, tiles at byte
+  // offsets at), math(frag) uses it.  In the usual case (the union fits the places) the next pair is fetched before the
+  // present one's math: the compiler does not move loads over the branch between pairs by itself.  Unions of up to
+  // PL + kSpare tiles take two stages (the first frees places for the tiles that wait in registers), larger ones
+  // go on in eights.
+  template <class Frag, class Fetch, class Math>
+  __device__ __forceinline__ void walk(int K, Fetch fetch, Math math) {
+    if (U <= PL) {
+      const int at = min(my_pos, PL - 1) * 2048;
+      Frag f[2];
+      fetch(f[0], jw[0].x, jw[0].y, __builtin_amdgcn_readlane(at, 0), __builtin_amdgcn_readlane(at, 1));
+#pragma unroll
+      for (int i = 0; i < PL / 2; ++i) {
+        if (2 * i >= cnt) break;
+        if (i + 1 < PL / 2)
+          fetch(f[(i + 1) & 1], jw[i + 1].x, jw[i + 1].y, __builtin_amdgcn_readlane(at, 2 * i + 2), __builtin_amdgcn_readlane(at, 2 * i + 3));
+        __builtin_amdgcn_sched_barrier(0);
+        math(f[i & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      return;
+    }
+    const uint32_t none = 2u * (uint32_t)K * 0x01010101u;
+    int lo = 0, hi = min(kSpare, U - PL);
+    for (int stage = 0;; ++stage) {
+      const int s0 = (int)__popcll(__ballot(lane < cnt && my_pos < lo)), s1 = (int)__popcll(__ballot(lane < cnt && my_pos < hi));
+      const int at = (stage > 1 ? my_pos - lo : my_pos < PL ? my_pos : my_pos - PL) * 2048;
+      auto bring = [&](Frag& f, int i, uint2 w) {
+        fetch(f, 2 * i >= s0 ? w.x : none, 2 * i + 1 < s1 ? w.y : none, __builtin_amdgcn_readlane(at, max(2 * i, s0)),
+              __builtin_amdgcn_readlane(at, min(2 * i + 1, s1 - 1)));
+      };
+      Frag f;
+#pragma unroll
+      for (int i = 0; i < kPairs; ++i) {
+        if (max(2 * i, s0) >= min(2 * i + 2, s1)) continue;
+        bring(f, i, jw[i]);
+        __builtin_amdgcn_sched_barrier(0);
+        math(f);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      for (int i = max(kPairs, s0 >> 1); max(2 * i, s0) < s1; ++i) {
+        bring(f, i, *reinterpret_cast<const uint2*>(jt + (uint32_t)(i * 512 + lane * 8)));
+        math(f);
+      }
+      if (hi >= U) break;
+      __syncthreads();  // every wave is through with the tiles below hi
+      lo = hi;
+      if (stage == 0) {
+#pragma unroll
+        for (int i = 0; i < kSpare / kGroup; ++i)
+          if (PL + i * kGroup + wave < U) {
+            char* dst = tiles + (i * kGroup + wave) * 2048;
+            reinterpret_cast<u32x4*>(dst)[lane] = sk[i];
+            reinterpret_cast<u32x4*>(dst + 1024)[lane] = sv[i];
+          }
+        __syncthreads();
+        hi = min(U, PL + kSpare);
+      } else {
+        hi = min(U, lo + kSpare);
+        const int next = (int)ul[min(lo + (lane & (kSpare - 1)), U - 1)];
+#pragma unroll
+        for (int i = 0; i < kSpare / kGroup; ++i)
+          if (lo + i * kGroup + wave < U) issue(__builtin_amdgcn_readlane(next, i * kGroup + wave), i * kGroup + wave);
+        arrive();
+      }
+    }
+  }
+};
+
+}  // namespace affmae

@@ -90,6 +90,10 @@ struct RelposArgs {
 };
 hipError_t launch_relpos_bias(const RelposArgs& r, int B, int N, int H, int K, int dtype, void* bias,
                               hipStream_t stream);
+// The table cell of every (token, neighbour) pair, all heads' alike.
+size_t relpos_cells_bytes(int B, int N, int K);
+hipError_t launch_relpos_cells(const RelposArgs& r, const void* plan, int B, int N, int H, int K, int S, int M,
+                               uint16_t* cells, hipStream_t stream);
 size_t relpos_dtable_workspace_bytes(int B, int N, int H, int K, int R);
 hipError_t launch_relpos_dtable(const RelposArgs& r, int B, int N, int H, int K, int dtype, const void* dbias,
                                 float* dtable, void* workspace, hipStream_t stream);
@@ -109,6 +113,7 @@ struct PlaArgs {
   const void* rel_table;    // [H, 2R+1, 2R+1] in the storage type
   int rel_R;
   float rel_rate;
+  const uint16_t* rel_cells;  // [B,N,K] cells of the pairs (launch_relpos_cells)
   float* rel_part;    // backward: workspace of pla_bwd_cluster_rel_workspace_bytes, or null (then dbias is written)
   float* rel_dtable;  // backward, with rel_part: [H, 2R+1, 2R+1] gradient of the table
   // forward outputs / backward inputs

@@ -1,9 +1,10 @@
 // Plan of the cluster-tiled attention kernels, built from the neighbour table
 // (paper, Sec. "Limitations": neighbourhood tables are cached per encoder stage
 // and reused by every block; the plan is such a table in the layout the tiled
-// kernels read).  Forward tables: one wave per strip of 16 queries.  Reverse
-// tables (which strips touch a token tile): one kernel that counts, places, files
-// and sorts in LDS and L2 (large images: count, prefix sum, fill and sort kernels).
+// kernels read, see PlanLayout).  Forward tables: a workgroup per group of four
+// strips, a wave per strip of 16 queries.  Reverse tables (which strips touch a
+// group of token tiles): one kernel that counts, places, files and sorts in LDS
+// and L2 (large images: count, prefix sum, fill and sort kernels).
 #include "cluster_common.h"
 #include "launch.h"
 #include "timing.h"
@@ -17,18 +18,18 @@ struct PlanParams {
   const int32_t* nbr_idx;  // [B,N,K]
   const int32_t* near;     // [B,G,M]
   int N, K, S, M, G;
-  uint32_t s_magic, k_magic;
-  int strips, strips_per_image, slot_stride, max_slots;
-  uint16_t* slots;    // [strips][slot_stride]
-  uint16_t* entries;  // [strips][16*K]
+  uint32_t s_magic, k_magic, tpc_magic, gpi_magic;
+  int strips_per_image, groups_per_image, groups, uni_stride, pos_stride, jt_pairs, touch_stride;
+  uint16_t* uni;
+  uint8_t* pos;
+  uint8_t* jt;
+  unsigned long long* touch;
   int32_t* rev_count;
   int32_t* rev_offset;
   int32_t* rev_cursor;
   unsigned long long* rev_list;
-  uint16_t* sorted_pos;  // [strips][places]
-  uint16_t* runs;        // [strips][runs_stride]
-  int runs_stride, places;
-  bool count_tiles;       // the reverse tables are built by the count / scan / fill / sort kernels
+  int group0;         // first group of this launch's slice (strip kernel)
+  bool count_groups;  // the reverse tables are built by the count / scan / fill / sort kernels
 };
 
 __device__ __forceinline__ unsigned long long wave_or64(unsigned long long x) {
@@ -44,123 +45,149 @@ __global__ __launch_bounds__(256) void plan_zero_kernel(int32_t* a, int32_t* b, 
   }
 }
 
-// NE = entries per lane: 16 K / 64 rounded up to a multiple of 4 (the loops over a lane's entries are unrolled)
+// NE = entries per lane: 16 K / 64 rounded up to a multiple of 4 (the loops over a lane's entries are unrolled).
+// Bound by the chain of its steps (neighbour ids from memory, the near clusters one by one, two exchanges between the
+// group's waves); the pairs go to their bytes by plain LDS stores.
+constexpr int kJtSlots = 16;  // slots whose j tiles are assembled in LDS at a time (4 KB per strip); few strips have more
 template <int NE>
 __global__ __launch_bounds__(256) void pla_plan_kernel(PlanParams p) {
-  __shared__ uint16_t sorted_all[4][NE * kWave + kMaxSlots];
-  __shared__ int slot_count_all[4][kMaxSlots];
+  __shared__ __align__(16) uint8_t jt_all[kGroup][kJtSlots * 256];
+  __shared__ uint16_t tiles_all[kGroup][kMaxSlots];
+  __shared__ int count_all[kGroup];
+  __shared__ unsigned long long fresh_all[kGroup];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform: keeps per-wave indices in SGPRs
-  const int sg = blockIdx.x * (blockDim.x / kWave) + wave;
-  if (sg >= p.strips) return;  // wave-uniform; no workgroup barrier below
-  uint16_t* sorted = sorted_all[wave];
-  int* slot_count = slot_count_all[wave];
-  const int b = sg / p.strips_per_image;
-  const int q0 = (sg - b * p.strips_per_image) * 16;  // first query, within the image
+  const int gi = p.group0 + blockIdx.x;
+  const int b = exact_div(gi, p.groups_per_image, p.gpi_magic);
+  const int si = (gi - b * p.groups_per_image) * kGroup + wave;
+  const bool there = si < p.strips_per_image;  // the image's last group may have fewer strips
+  const int q0 = min(si, p.strips_per_image - 1) * 16;  // first query, within the image
+  const size_t sg = (size_t)b * p.strips_per_image + (q0 >> 4);
   const int c = fast_div(q0, p.s_magic);
   const int32_t* near_c = p.near + ((size_t)b * p.G + c) * p.M;
-  const int tiles_per_cluster = p.S / 16;
-  const int nent = 16 * p.K;
-  const int nent_real = min(16, p.N - q0) * p.K;  // the image's last strip may hold fewer than 16 queries
+  const int tpc = p.S / 16;  // token tiles per cluster
+  const int nent_real = there ? min(16, p.N - q0) * p.K : 0;  // the image's last strip may hold fewer than 16 queries
   const int32_t* nbr = p.nbr_idx + ((size_t)b * p.N + q0) * p.K;
 
-  // candidate-list tile of every (query, slot): m * (S/16) + (token % S) / 16
-  const int near_v = (lane < p.M) ? near_c[lane] : -1;  // lane m: the m-th near cluster (M <= 64)
-  int ct[NE], tok[NE], ecl[NE], where[NE];
+  // candidate tile of every (query, neighbour): clusters in ascending order, (token % S) / 16 inside
+  const int near_v = (lane < p.M) ? near_c[lane] : 0x7fffffff;  // lane m: the m-th near cluster (M <= 64)
+  int ecl[NE], sub[NE], ct[NE];
   bool inr[NE];
 #pragma unroll
   for (int t = 0; t < NE; ++t) {
     const int e = t * kWave + lane;
     const int n = (e < nent_real) ? nbr[e] : -1;  // queries past the end have no entries
     const int nn = min(max(n, 0), p.N - 1);
-    inr[t] = e < nent && n == nn;
-    tok[t] = nn;
+    inr[t] = n == nn;
     ecl[t] = fast_div(nn, p.s_magic);
-    where[t] = -1;
+    sub[t] = nn - ecl[t] * p.S;
+    ct[t] = -1;
   }
-  for (int m = 0; m < p.M; ++m) {  // the last match wins, as a scan of the list would have it
+  int rank = 0;  // lane m: place of the m-th near cluster among them by number
+  for (int m = 0; m < p.M; ++m) {
     const int cl = __builtin_amdgcn_readlane(near_v, m);
+    rank += (cl < near_v || (cl == near_v && m < lane)) ? 1 : 0;
+  }
+  int cl_sorted = 0;  // lane c: the cluster of candidate tile c
+  const int lane_m = fast_div(lane, p.tpc_magic);
+  for (int m = 0; m < p.M; ++m) {
+    const int cl = __builtin_amdgcn_readlane(near_v, m), rk = __builtin_amdgcn_readlane(rank, m);
+    cl_sorted = (lane_m == rk) ? cl : cl_sorted;
 #pragma unroll
-    for (int t = 0; t < NE; ++t) where[t] = (ecl[t] == cl) ? m : where[t];
+    for (int t = 0; t < NE; ++t) ct[t] = (ecl[t] == cl) ? rk * tpc : ct[t];
   }
   unsigned long long mask = 0;
 #pragma unroll
   for (int t = 0; t < NE; ++t) {
-    ct[t] = -1;
-    if (inr[t] && where[t] >= 0) {
-      ct[t] = where[t] * tiles_per_cluster + ((tok[t] - ecl[t] * p.S) >> 4);
+    if (inr[t] && ct[t] >= 0) {
+      ct[t] += sub[t] >> 4;
       mask |= 1ull << ct[t];
     } else {
-      tok[t] = 0;
+      ct[t] = -1;
     }
   }
   mask = wave_or64(mask);
-  uint16_t* ent = p.entries + (size_t)sg * nent;
-  uint32_t off[NE];
-#pragma unroll
-  for (int t = 0; t < NE; ++t) {
-    const int e = t * kWave + lane;
-    off[t] = kNoEntry;
-    if (e < nent) {
-      if (ct[t] >= 0) {
-        const int slot = __popcll(mask & ((1ull << ct[t]) - 1ull));
-        off[t] = (uint32_t)(slot * 256 + tile_cell(fast_div(e, p.k_magic), tok[t] & 15));
-      }
-      ent[e] = (uint16_t)off[t];
-    }
-  }
-  // slot table: count, then the token tile of every slot; padding repeats a valid tile
-  uint16_t* sl = p.slots + (size_t)sg * p.slot_stride;
   const int count = __popcll(mask);
-  if ((mask >> lane) & 1ull) {
-    const int m = lane / tiles_per_cluster, tt = lane - m * tiles_per_cluster;
-    const int e = min(max(near_c[m], 0), p.G - 1);
-    const int my_tile = e * tiles_per_cluster + tt;  // token tile within the image
-    sl[1 + __popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)my_tile;
-    if (p.count_tiles) atomicAdd(p.rev_count + (size_t)b * p.strips_per_image + my_tile, 1);
-  }
-  const int own_tile = q0 >> 4;
-  if (lane == 0) sl[0] = (uint16_t)count;
-  for (int s = count + lane; s < p.slot_stride - 1; s += kWave) sl[1 + s] = (uint16_t)own_tile;
-
-  // runs: the valid entries grouped by slot, every run starting at an even place; assembled in LDS and written
-  // out in rows.  Unused places hold kNoEntry.  Two sweeps over the lane's entries with LDS counters per slot:
-  // count, then claim a place (the order inside a run is the order in which the wave's LDS atomics are served;
-  // any order gives the same results downstream, where every entry is addressed by its own value).
-  for (int w = lane; w < NE * kWave + kMaxSlots; w += kWave) sorted[w] = (uint16_t)kNoEntry;
-  if (lane < kMaxSlots) slot_count[lane] = 0;
-  wave_lds_sync();
+  const int my_tile = cl_sorted * tpc + (lane - lane_m * tpc);  // of candidate `lane`, within the image
+  if ((mask >> lane) & 1ull) tiles_all[wave][__popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)my_tile;
+  if (lane == 0) count_all[wave] = count;
+  __syncthreads();
+  // lane s: slot s.  Its tile's place in every strip's list by binary search; a strip is the first of the group to have
+  // the tile if no earlier one does, and the place in the union is the number of firsts below.
+  const int T = lane < count ? (int)tiles_all[wave][lane] : 0x10000;
+  int lb[kGroup];
+  bool fresh = lane < count;
 #pragma unroll
-  for (int t = 0; t < NE; ++t)
-    if (off[t] != kNoEntry) atomicAdd(&slot_count[off[t] >> 8], 1);
-  wave_lds_sync();
-  uint16_t* runs = p.runs + (size_t)sg * p.runs_stride;
-  // exclusive prefix over the slots, every start rounded up to an even place (lane s: slot s)
-  int mine = (lane < count) ? slot_count[lane] : 0;
-  mine = (mine + 1) & ~1;
-  int incl = mine;
+  for (int v = 0; v < kGroup; ++v) {
+    const int n = count_all[v];
+    int at = 0;
 #pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int v = __shfl_up(incl, o);
-    if (lane >= o) incl += v;
+    for (int step = 32; step > 0; step >>= 1)
+      if (at + step <= n && (int)tiles_all[v][at + step - 1] < T) at += step;
+    if (at < n && (int)tiles_all[v][at] < T) ++at;  // (the steps add up to 63, a list may hold 64)
+    lb[v] = at;
+    if (v < wave && at < n && (int)tiles_all[v][at] == T) fresh = false;
   }
-  const int start = incl - mine;
-  const int last_count = __shfl((lane < count) ? slot_count[lane] : 0, max(count - 1, 0));
-  const int last_start = __shfl(start, max(count - 1, 0));
-  int place = count > 0 ? last_start + last_count : 0;  // places used: the last run is not padded
-  wave_lds_sync();
-  if (lane < count) {
-    runs[lane] = (uint16_t)start;
-    slot_count[lane] = start;  // becomes the cursor of the slot
-  }
-  wave_lds_sync();
+  const unsigned long long fm = __ballot(fresh);
+  if (lane == 0) fresh_all[wave] = fm;
+  __syncthreads();
+  int place = 0, U = 0;
 #pragma unroll
-  for (int t = 0; t < NE; ++t)
-    if (off[t] != kNoEntry) sorted[atomicAdd(&slot_count[off[t] >> 8], 1)] = (uint16_t)off[t];
-  if (lane == 0) runs[count] = (uint16_t)place;
-  wave_lds_sync();
-  uint16_t* sp = p.sorted_pos + (size_t)sg * p.places;
-  for (int w = lane; w < p.places; w += kWave) sp[w] = sorted[w];
+  for (int v = 0; v < kGroup; ++v) {
+    const unsigned long long f = fresh_all[v];
+    place += __popcll(lb[v] >= kWave ? f : (f & ((1ull << lb[v]) - 1ull)));
+    U += __popcll(f);
+  }
+  uint16_t* uni = p.uni + (size_t)gi * p.uni_stride;
+  if (fresh) uni[1 + place] = (uint16_t)T;
+  if (wave == 0 && lane == 0) {
+    uni[0] = (uint16_t)max(U, 1);  // (no tile at all only where the near clusters are not the table's: one that nobody uses)
+    if (U == 0) uni[1] = (uint16_t)(q0 >> 4);
+  }
+  if (!there) return;  // (no workgroup barrier below)
+  uint8_t* pos = p.pos + sg * p.pos_stride;
+  if (lane < count) pos[1 + lane] = (uint8_t)place;
+  if (lane == 0) pos[0] = (uint8_t)count;
+  // groups of token tiles: a slot whose group differs from the slot's before starts one
+  unsigned long long* touch = p.touch + sg * p.touch_stride;
+  const int tg = T / kGroup;
+  const int before = __shfl_up(tg, 1);
+  const bool starts = lane < count && (lane == 0 || before != tg);
+  const unsigned long long sm = __ballot(starts);
+  if (starts) {
+    uint32_t slots = 0xffffffffu;
+#pragma unroll
+    for (int d = 0; d < kGroup; ++d) {
+      const int tile = lane + d < count ? (int)tiles_all[wave][lane + d] : 0x10000;
+      if (tile / kGroup == tg) slots = (slots & ~(0xffu << (8 * (tile % kGroup)))) | ((uint32_t)(lane + d) << (8 * (tile % kGroup)));
+    }
+    touch[1 + __popcll(sm & ((1ull << lane) - 1ull))] = ((unsigned long long)(uint32_t)tg << 32) | slots;
+    if (p.count_groups) atomicAdd(p.rev_count + (size_t)b * p.groups_per_image + tg, 1);
+  }
+  if (lane == 0) touch[0] = (unsigned long long)__popcll(sm);
+  // j tiles
+  uint8_t* jt = jt_all[wave];
+  u32x4* out = reinterpret_cast<u32x4*>(p.jt + sg * p.jt_pairs * 512);
+  const uint32_t none = 2u * (uint32_t)p.K * 0x01010101u;
+  for (int s0 = 0; s0 < count; s0 += kJtSlots) {
+    const int ns = min(kJtSlots, (count - s0 + 1) & ~1);  // the second half of the last pair holds no neighbours
+    for (int i = lane; i < ns * 16; i += kWave) reinterpret_cast<u32x4*>(jt)[i] = u32x4{none, none, none, none};
+    wave_lds_sync();
+#pragma unroll
+    for (int t = 0; t < NE; ++t) {
+      if (ct[t] >= 0) {
+        const int slot = __popcll(mask & ((1ull << ct[t]) - 1ull)) - s0;
+        if (slot >= 0 && slot < kJtSlots) {
+          const int e = t * kWave + lane;
+          const int q = fast_div(e, p.k_magic), j = e - q * p.K, tok = sub[t] & 15;
+          jt[(slot >> 1) * 512 + ((tok >> 2) * 16 + q) * 8 + (slot & 1) * 4 + (tok & 3)] = (uint8_t)(2 * j);
+        }
+      }
+    }
+    wave_lds_sync();
+    for (int i = lane; i < ns * 16; i += kWave) out[s0 * 16 + i] = reinterpret_cast<const u32x4*>(jt)[i];
+    wave_lds_sync();
+  }
 }
 
 // Exclusive prefix sum of rev_count.  Workgroup j owns elements [1024 j, 1024 j + 1024): it first adds up
@@ -206,38 +233,36 @@ __global__ __launch_bounds__(256) void plan_scan_kernel(const int32_t* __restric
   if (at <= n - 1 && n - 1 < at + 4) offset[n] = run;  // the thread that owns the last element: run is the total
 }
 
-// Every strip appends itself to the list of each token tile it touches.
-__global__ __launch_bounds__(256) void plan_fill_kernel(PlanParams p) {
+// Every strip appends itself to the list of each group of token tiles it touches.
+__global__ __launch_bounds__(256) void plan_fill_kernel(PlanParams p, int strips) {
   const int lane = threadIdx.x & (kWave - 1);
   const int sg = blockIdx.x * (blockDim.x / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (sg >= p.strips) return;
+  if (sg >= strips) return;
   const int b = sg / p.strips_per_image;
-  const int strip_in_image = sg - b * p.strips_per_image;
-  const uint16_t* sl = p.slots + (size_t)sg * p.slot_stride;
-  const int count = min((int)sl[0], p.max_slots);
+  const int strip = sg - b * p.strips_per_image;
+  const unsigned long long* touch = p.touch + (size_t)sg * p.touch_stride;
+  const int count = min((int)touch[0], p.touch_stride - 1);
   if (lane < count) {
-    const size_t kt = (size_t)b * p.strips_per_image + sl[1 + lane];
-    const int at = atomicAdd(p.rev_cursor + kt, 1);
-    const uint16_t* runs = p.runs + (size_t)sg * p.runs_stride;
-    const uint32_t start = runs[lane], len = (uint32_t)runs[lane + 1] - start;  // len may count one pad place
-    p.rev_list[(size_t)p.rev_offset[kt] + at] =
-        ((unsigned long long)(start | (len << 16)) << 32) | (((uint32_t)strip_in_image << 8) | (uint32_t)lane);
+    const unsigned long long t = touch[1 + lane];
+    const size_t grp = (size_t)b * p.groups_per_image + (uint32_t)(t >> 32);
+    const int at = atomicAdd(p.rev_cursor + grp, 1);
+    p.rev_list[(size_t)p.rev_offset[grp] + at] = ((unsigned long long)(uint32_t)strip << 32) | (uint32_t)t;
   }
 }
 
-// Sorts one token tile's list ascending by (strip, slot): rank by counting (lists are short).  One wave.
-__device__ __forceinline__ void sort_incidences(unsigned long long* list, int n, int lane) {
+// Sorts one group's list ascending by strip: rank by counting (lists are short).  One wave.
+__device__ __forceinline__ void sort_list(unsigned long long* list, int n, int lane) {
   if (n <= kWave) {
     const unsigned long long mine = lane < n ? list[lane] : ~0ull;
-    const uint32_t key = (uint32_t)mine;
+    const uint32_t key = (uint32_t)(mine >> 32);
     int rank = 0;
-    for (int j = 0; j < n; ++j) rank += (__shfl(key, j) < key) ? 1 : 0;  // keys are distinct
+    for (int j = 0; j < n; ++j) rank += __builtin_amdgcn_readlane(key, j) < key ? 1 : 0;  // keys are distinct
     if (lane < n) list[rank] = mine;  // every lane has read its element before any write lands (one wave)
   } else if (lane == 0) {
     for (int i = 1; i < n; ++i) {  // insertion sort; only for unusually popular tiles
       const unsigned long long v = list[i];
       int j = i - 1;
-      while (j >= 0 && (uint32_t)list[j] > (uint32_t)v) {
+      while (j >= 0 && list[j] > v) {
         list[j + 1] = list[j];
         --j;
       }
@@ -248,61 +273,60 @@ __device__ __forceinline__ void sort_incidences(unsigned long long* list, int n,
 
 __global__ __launch_bounds__(256) void plan_sort_kernel(PlanParams p) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int kt = blockIdx.x * (blockDim.x / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (kt >= p.strips) return;
-  sort_incidences(p.rev_list + p.rev_offset[kt], p.rev_count[kt], lane);
+  const int grp = blockIdx.x * (blockDim.x / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (grp >= p.groups) return;
+  sort_list(p.rev_list + p.rev_offset[grp], p.rev_count[grp], lane);
 }
 
-// The reverse tables of images of at most kRevTiles token tiles, in one launch: a workgroup owns `own` consecutive tiles
-// of one image.  It reads the image's slot tables (from L2), counts every tile's incidences in LDS, prefix-sums
-// the counts (an image's lists start at a place of their own, so nothing is needed of other images), reads the tables
-// again and files the incidences of its own tiles, and sorts these lists.
+// The reverse tables of images of at most kRevThreads strips, in one launch: a workgroup owns `own` consecutive groups
+// of one image.  A thread reads the touch table of one of the image's strips, the workgroup counts every group's strips
+// in LDS, prefix-sums the counts (an image's lists start at a place of their own, so nothing is needed of other images),
+// files the strips of its own groups, and sorts these lists, in LDS where they fit.
 // Bound by the chain of these steps in each workgroup, which grows with the image's tiles, against counting with atomics
-// in the strip kernel and four more launches (zero, scan, fill, sort: 4 - 6 us each, of the whole batch).  Whole plan,
-// one launch and four: one image of 64 / 256 / 512 / 1024 / 2048 tiles 15 / 18 / 19 / 24 / 28 us and 18 / 20 / 19 / 21 / 23
-// us; 1024 tiles, 4 / 8 / 16 / 32 images 30 / 22 / 64 / 104 us and 29 / 25 / 66 / 112 us (at 8, K = 9); 2048 tiles, 8 /
-// 16 images 69 / 109 us and 66 / 112 us.  So: up to 512 tiles, and beyond in batches of tiles / 128 images or more.
-// Images of a few tiles take a workgroup each and give it little to do (1 tile: 16 us at 1024 images, 26 at 2048, against
-// 18; 4 tiles: 17 / 26 us at 768 / 1536 against 18 / 21; 16 tiles: 133 us at 4096 against 135): below 16 tiles, up to 768.
-constexpr int kRevTiles = 2048, kRevTilesSmall = 512, kRevTilesFew = 16, kRevImagesFew = 768;
-constexpr int kRevThreads = 1024;
+// in the strip kernel and four more launches (zero, scan, fill, sort: 4 - 6 us each, of the whole batch).  Whole plan, K =
+// 48, one launch and four: one image of 64 / 256 / 512 / 1024 tiles 14 / 15 / 16 / 17 us and 19 / 19 / 20 / 20 us; 1024
+// tiles, 4 / 8 / 16 / 32 images 24 / 34 / 50 / 85 us and 28 / 38 / 57 / 94 us.  (With the touch tables read twice and the
+// lists sorted in memory 28 / 37 / 54 / 93 us; with a list per token tile instead of per group, and the pairs of every
+// strip sorted by tile, 30 / 42 / 62 / 102 us.)  Beyond 1024 tiles a thread would serve several strips.
+// Images of a few tiles take a workgroup each and give it little to do (1 tile: 15 / 25 us at 1024 / 2048 images against
+// 16 / 18; 4 tiles: 15 / 22 us at 768 / 1536 against 17 / 20): below 16 tiles, up to 768.
+constexpr int kRevThreads = 1024, kRevGroups = kRevThreads / kGroup, kRevGroupsFew = 4, kRevImagesFew = 768;
+constexpr int kRevSorted = 1024;  // entries of a workgroup's lists that are sorted in LDS
+constexpr int kRevInline = 7;     // entries of a strip that its thread holds (most strips have fewer)
 __global__ __launch_bounds__(kRevThreads) void plan_reverse_kernel(PlanParams p, int own) {
-  __shared__ int32_t count[kRevTiles];   // incidences per tile
-  __shared__ int32_t offset[kRevTiles];  // exclusive prefix, then the cursor of the own tiles
+  __shared__ int32_t count[kRevGroups];   // strips per group
+  __shared__ int32_t offset[kRevGroups];  // exclusive prefix, then the cursor of the own groups
   __shared__ int32_t part[kRevThreads / kWave];
+  __shared__ unsigned long long sorted[kRevSorted];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int tiles = p.strips_per_image;
-  const int groups = (tiles + own - 1) / own;
-  const int b = blockIdx.x / groups, first = (blockIdx.x - b * groups) * own, last = min(first + own, tiles);
-  const size_t strip0 = (size_t)b * tiles;
-  for (int i = tid; i < kRevTiles; i += kRevThreads) count[i] = 0;
+  const int gpi = p.groups_per_image;
+  const int shares = (gpi + own - 1) / own;
+  const int b = blockIdx.x / shares, first = (blockIdx.x - b * shares) * own, last = min(first + own, gpi);
+  const size_t strip0 = (size_t)b * p.strips_per_image;
+  const unsigned long long* row = p.touch + (strip0 + min(tid, p.strips_per_image - 1)) * p.touch_stride;
+  unsigned long long w[1 + kRevInline];
+#pragma unroll
+  for (int i = 0; i <= kRevInline; ++i) w[i] = row[min(i, p.touch_stride - 1)];
+  if (tid < kRevGroups) count[tid] = 0;
   __syncthreads();
-  // a thread per strip: the first 15 slots in eight independent loads (most strips have fewer), the others one by one
+  const int n = tid < p.strips_per_image ? min((int)w[0], p.touch_stride - 1) : 0;
   auto each = [&](auto f) {
-    for (int strip = tid; strip < tiles; strip += kRevThreads) {
-      const uint16_t* row = p.slots + (strip0 + strip) * p.slot_stride;  // (slot_stride is even and at least 2)
-      const uint32_t* pairs = reinterpret_cast<const uint32_t*>(row);
-      const int pairs_end = p.slot_stride / 2 - 1;
-      uint32_t w[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) w[i] = pairs[min(i, pairs_end)];
-      const int n = min((int)(w[0] & 0xffffu), p.max_slots);
-#pragma unroll
-      for (int s = 0; s < 15; ++s) {
-        const int tile = (int)((w[(s + 1) >> 1] >> (16 * ((s + 1) & 1))) & 0xffffu);
-        if (s < n && tile < tiles) f(strip, s, tile);
-      }
-      for (int s = 15; s < n; ++s) {
-        const int tile = row[1 + s];
-        if (tile < tiles) f(strip, s, tile);
-      }
+    for (int s = 0; s < kRevInline; ++s) {
+      const int grp = (int)(w[1 + s] >> 32);
+      if (s < n && (uint32_t)grp < (uint32_t)gpi) f(grp, (uint32_t)w[1 + s]);
+    }
+    for (int s = kRevInline; s < n; ++s) {
+      const unsigned long long t = row[1 + s];
+      const int grp = (int)(t >> 32);
+      if ((uint32_t)grp < (uint32_t)gpi) f(grp, (uint32_t)t);
     }
   };
-  each([&](int, int, int tile) { atomicAdd(&count[tile], 1); });
+  each([&](int grp, uint32_t) { atomicAdd(&count[grp], 1); });
   __syncthreads();
-  // exclusive prefix: two tiles per thread
-  const int c0 = count[2 * tid], c1 = count[2 * tid + 1];
-  int incl = c0 + c1;
+  // exclusive prefix: a group per thread
+  const int mine = tid < kRevGroups ? count[tid] : 0;
+  int incl = mine;
 #pragma unroll
   for (int o = 1; o < kWave; o <<= 1) {
     const int v = __shfl_up(incl, o);
@@ -310,41 +334,40 @@ __global__ __launch_bounds__(kRevThreads) void plan_reverse_kernel(PlanParams p,
   }
   if (lane == kWave - 1) part[wave] = incl;
   __syncthreads();
-  int before = incl - c0 - c1;
-  for (int w = 0; w < wave; ++w) before += part[w];
-  offset[2 * tid] = before;
-  offset[2 * tid + 1] = before + c0;
-  __syncthreads();
-  const size_t list0 = strip0 * p.max_slots;  // the image's lists
-  for (int i = first + tid; i < last; i += kRevThreads) {
-    p.rev_count[strip0 + i] = count[i];
-    p.rev_offset[strip0 + i] = (int32_t)(list0 + offset[i]);
+  int before = incl - mine;
+  for (int i = 0; i < min(wave, kRevGroups / kWave); ++i) before += part[i];
+  if (tid < kRevGroups) offset[tid] = before;
+  const size_t list0 = strip0 * (p.touch_stride - 1);  // the image's lists
+  if (tid >= first && tid < last) {
+    p.rev_count[(size_t)b * gpi + tid] = mine;
+    p.rev_offset[(size_t)b * gpi + tid] = (int32_t)(list0 + before);
   }
   __syncthreads();
-  each([&](int strip, int slot, int tile) {  // (strip, slot) only: the place of the run is loaded by the sort, a tile at once
-    if (tile >= first && tile < last)
-      p.rev_list[list0 + atomicAdd(&offset[tile], 1)] = ((uint32_t)strip << 8) | (uint32_t)slot;
+  const int base = offset[first], total = offset[last - 1] + count[last - 1] - base;
+  const bool in_lds = total <= kRevSorted;
+  unsigned long long* list = p.rev_list + list0;
+  __syncthreads();  // (offset becomes the cursors)
+  each([&](int grp, uint32_t slots) {
+    if (grp >= first && grp < last) {
+      const int at = atomicAdd(&offset[grp], 1);
+      const unsigned long long v = ((unsigned long long)(uint32_t)tid << 32) | slots;
+      if (in_lds) sorted[at - base] = v; else list[at] = v;
+    }
   });
   __threadfence_block();
   __syncthreads();
-  for (int tile = first + wave; tile < last; tile += kRevThreads / kWave) {
-    const int n = count[tile];
-    unsigned long long* list = p.rev_list + list0 + offset[tile] - n;
-    auto with_run = [&](unsigned long long inc) -> unsigned long long {
-      const uint16_t* runs = p.runs + (strip0 + (uint32_t)inc / 256u) * p.runs_stride + ((uint32_t)inc & 255u);
-      const uint32_t start = runs[0], len = (uint32_t)runs[1] - start;  // len may count one pad place
-      return ((unsigned long long)(start | (len << 16)) << 32) | (uint32_t)inc;
-    };
-    if (n > kWave) {
-      for (int i = lane; i < n; i += kWave) list[i] = with_run(list[i]);
-      __threadfence_block();
-      sort_incidences(list, n, lane);
+  for (int grp = first + wave; grp < last; grp += kRevThreads / kWave) {
+    const int m = count[grp], at = offset[grp] - m;
+    if (!in_lds) {
+      sort_list(list + at, m, lane);
       continue;
     }
-    const unsigned long long mine = lane < n ? with_run(list[lane]) : ~0ull;
-    int rank = 0;
-    for (int j = 0; j < n; ++j) rank += __builtin_amdgcn_readlane((uint32_t)mine, j) < (uint32_t)mine ? 1 : 0;  // keys are distinct
-    if (lane < n) list[rank] = mine;  // every lane has read its element before any write lands (one wave)
+    for (int i0 = 0; i0 < m; i0 += kWave) {  // rank by counting, lists of any length
+      const unsigned long long v = i0 + lane < m ? sorted[at - base + i0 + lane] : 0ull;
+      int rank = 0;
+      for (int j = 0; j < m; ++j) rank += sorted[at - base + j] < v ? 1 : 0;  // strips are distinct
+      if (i0 + lane < m) list[at + rank] = v;
+    }
   }
 }
 
@@ -357,44 +380,44 @@ hipError_t launch_pla_plan(const int32_t* nbr_idx, const int32_t* near, int B, i
   PlanParams p;
   p.nbr_idx = nbr_idx; p.near = near;
   p.N = N; p.K = K; p.S = S; p.M = M; p.G = (N + S - 1) / S;  // the last cluster may be short
-  p.s_magic = div_magic(S); p.k_magic = div_magic(K);
-  p.strips = L.strips; p.strips_per_image = (N + 15) / 16; p.slot_stride = L.slot_stride; p.max_slots = L.max_slots;
-  p.slots = reinterpret_cast<uint16_t*>(base + L.slots_off);
-  p.entries = reinterpret_cast<uint16_t*>(base + L.entries_off);
+  p.s_magic = div_magic(S); p.k_magic = div_magic(K); p.tpc_magic = div_magic(S / 16); p.gpi_magic = div_magic(L.groups_per_image);
+  p.strips_per_image = L.strips_per_image; p.groups_per_image = L.groups_per_image; p.groups = L.groups;
+  p.uni_stride = L.uni_stride; p.pos_stride = L.pos_stride; p.jt_pairs = L.jt_pairs; p.touch_stride = L.touch_stride;
+  p.uni = reinterpret_cast<uint16_t*>(base + L.uni_off);
+  p.pos = reinterpret_cast<uint8_t*>(base + L.pos_off);
+  p.jt = reinterpret_cast<uint8_t*>(base + L.jt_off);
+  p.touch = reinterpret_cast<unsigned long long*>(base + L.touch_off);
   p.rev_count = reinterpret_cast<int32_t*>(base + L.rev_count_off);
   p.rev_offset = reinterpret_cast<int32_t*>(base + L.rev_offset_off);
   p.rev_cursor = reinterpret_cast<int32_t*>(base + L.rev_cursor_off);
   p.rev_list = reinterpret_cast<unsigned long long*>(base + L.rev_list_off);
-  p.sorted_pos = reinterpret_cast<uint16_t*>(base + L.sorted_pos_off);
-  p.runs = reinterpret_cast<uint16_t*>(base + L.runs_off);
-  p.runs_stride = L.runs_stride; p.places = L.places;
-  const dim3 per_strip((L.strips + 3) / 4);
   // One launch where it is the faster way (see plan_reverse_kernel), list places fit int32 and the threads a launch
-  // (2^32 - 1).  256 workgroups share the tiles, 16 tiles or more each (a wave sorts one list at a time); by images instead
-  // (16 workgroups for each) 27 against 24 us for one image of 1024 tiles, 74 against 69 for eight of 2048.
-  const int tiles = p.strips_per_image;
-  const int own = std::max(16, (int)((L.strips + 255ll) / 256));
-  const long long groups = (long long)B * ((tiles + own - 1) / own);
-  const bool one_launch = tiles < kRevTilesFew ? B <= kRevImagesFew
-                                               : tiles <= kRevTilesSmall || (tiles <= kRevTiles && tiles <= 128ll * B);
-  p.count_tiles = !one_launch ||
-                  (long long)L.strips * L.max_slots >= (1ll << 31) || groups * kRevThreads >= (1ll << 32);
-  if (p.count_tiles)
-    AFFMAE_LAUNCH("plan_zero_kernel", stream, plan_zero_kernel, dim3((L.strips + 255) / 256), dim3(256), 0, stream,
-                  p.rev_count, p.rev_cursor, L.strips);
+  // (2^32 - 1).  256 workgroups share the groups, four or more each.
+  const int gpi = L.groups_per_image;
+  const int own = std::max(4, (int)((L.groups + 255ll) / 256));
+  const long long shares = (long long)B * ((gpi + own - 1) / own);
+  const bool one_launch = gpi < kRevGroupsFew ? B <= kRevImagesFew : L.strips_per_image <= kRevThreads;
+  p.count_groups = !one_launch || (long long)L.strips * (L.touch_stride - 1) >= (1ll << 31) || shares * kRevThreads >= (1ll << 32);
+  if (p.count_groups)
+    AFFMAE_LAUNCH("plan_zero_kernel", stream, plan_zero_kernel, dim3((L.groups + 255) / 256), dim3(256), 0, stream,
+                  p.rev_count, p.rev_cursor, L.groups);
   const int ne = (16 * K + kWave - 1) / kWave;
-  if (ne <= 4) AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<4>, per_strip, dim3(256), 0, stream, p);
-  else if (ne <= 8) AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<8>, per_strip, dim3(256), 0, stream, p);
-  else if (ne <= 12) AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<12>, per_strip, dim3(256), 0, stream, p);
-  else AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<kMaxEntries>, per_strip, dim3(256), 0, stream, p);
-  if (!p.count_tiles) {
-    AFFMAE_LAUNCH("plan_reverse_kernel", stream, plan_reverse_kernel, dim3((unsigned)groups), dim3(kRevThreads), 0, stream, p, own);
+  for (long long g0 = 0; g0 < L.groups; g0 += kMaxBlocks) {
+    p.group0 = (int)g0;
+    const dim3 grid((unsigned)std::min((long long)L.groups - g0, kMaxBlocks));
+    if (ne <= 4) AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<4>, grid, dim3(256), 0, stream, p);
+    else if (ne <= 8) AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<8>, grid, dim3(256), 0, stream, p);
+    else if (ne <= 12) AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<12>, grid, dim3(256), 0, stream, p);
+    else AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<kMaxEntries>, grid, dim3(256), 0, stream, p);
+  }
+  if (!p.count_groups) {
+    AFFMAE_LAUNCH("plan_reverse_kernel", stream, plan_reverse_kernel, dim3((unsigned)shares), dim3(kRevThreads), 0, stream, p, own);
     return hipGetLastError();
   }
-  AFFMAE_LAUNCH("plan_scan_kernel", stream, plan_scan_kernel, dim3((L.strips + 1023) / 1024), dim3(256), 0, stream,
-                p.rev_count, p.rev_offset, L.strips);
-  AFFMAE_LAUNCH("plan_fill_kernel", stream, plan_fill_kernel, per_strip, dim3(256), 0, stream, p);
-  AFFMAE_LAUNCH("plan_sort_kernel", stream, plan_sort_kernel, per_strip, dim3(256), 0, stream, p);
+  AFFMAE_LAUNCH("plan_scan_kernel", stream, plan_scan_kernel, dim3((L.groups + 1023) / 1024), dim3(256), 0, stream,
+                p.rev_count, p.rev_offset, L.groups);
+  AFFMAE_LAUNCH("plan_fill_kernel", stream, plan_fill_kernel, dim3((L.strips + 3) / 4), dim3(256), 0, stream, p, L.strips);
+  AFFMAE_LAUNCH("plan_sort_kernel", stream, plan_sort_kernel, dim3((L.groups + 3) / 4), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 

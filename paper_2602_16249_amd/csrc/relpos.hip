@@ -3,12 +3,12 @@
 // gives no function; the reading taken here is a learned table per head over quantised offsets:
 //   bias[b,i,h,j] = table[h][by][bx],  bx = clamp(rint((x_n - x_i) * rate), -R, R) + R  (fp32, ties to even),
 //   by alike, n = nbr_idx[b,i,j].
-// This file holds the two stand-alone kernels: the bias written out as a tensor (for the gather kernels, which
-// take any neighbour table), and the gradient of the table from the bias gradients.  The tiled kernels compute
-// the same bias themselves from the coordinates of the token tiles they stage (pla_cluster_*.hip).
+// This file holds the stand-alone kernels: the bias written out as a tensor (for the gather kernels, which
+// take any neighbour table), the gradient of the table from the bias gradients, and the cell of every pair for the
+// tiled kernels, which look the bias up themselves (pla_cluster_*.hip).
 #include <algorithm>
 
-#include "device_util.h"
+#include "cluster_tiles.h"
 #include "launch.h"
 #include "timing.h"
 
@@ -65,6 +65,64 @@ __global__ __launch_bounds__(256) void relpos_bias8_kernel(const float* __restri
     o.z = (uint32_t)t[cell[4]] | ((uint32_t)t[cell[5]] << 16);
     o.w = (uint32_t)t[cell[6]] | ((uint32_t)t[cell[7]] << 16);
     *reinterpret_cast<uint4*>(bias + (tok * H + h) * K + j0) = o;
+  }
+}
+
+// The cell of every pair, for the tiled kernels (K a multiple of 8), a workgroup per group of four strips.  The neighbours
+// of the group's queries lie in the few token tiles of its union (PlanLayout): their coordinates are brought into LDS
+// and found there through a byte per token tile of the image.  Gathered from memory instead, eight 8-byte loads per
+// item kept the address units busy for the whole launch (64 cycles for a load of 64 scattered places).
+// Images of more than 65536 tokens and unions of more than 64 tiles take that way all the same.
+constexpr int kCellTiles = 4096, kCellUnion = 64;
+__global__ __launch_bounds__(256) void relpos_cells_kernel(GroupTables t, const float* __restrict__ coords,
+                                                           const int32_t* __restrict__ nbr_idx, int group0, int K,
+                                                           uint32_t cq_magic, int R, float rate,
+                                                           uint16_t* __restrict__ cells) {
+  __shared__ uint8_t place[kCellTiles];  // only the union's bytes are written, and only they are read
+  __shared__ __align__(8) float2 xy[kCellUnion * 16];
+  const int gi = group0 + blockIdx.x;
+  const int b = exact_div(gi, t.groups_per_image, t.gpi_magic);
+  const int q0 = (gi - b * t.groups_per_image) * kGroup * 16;
+  const uint16_t* ul = t.uni + mul_u32(gi, t.uni_stride);
+  const int U = ul[0];
+  const float2* cimg = reinterpret_cast<const float2*>(coords) + mul_u32(b, t.N);
+  const bool staged = t.strips_per_image <= kCellTiles && U <= kCellUnion;
+  // an item is 8 neighbours of a query: two per thread at most (K <= 64), asked for before the coordinates
+  const int chunks = K >> 3, items = min(kGroup * 16, t.N - q0) * chunks;
+  const size_t at0 = mul_u32(b, (uint32_t)(t.N * K)) + (uint32_t)(q0 * K);
+  typedef int i32x4 __attribute__((ext_vector_type(4), aligned(4)));  // (the table need not lie at a multiple of 16 bytes)
+  const i32x4* nbr = reinterpret_cast<const i32x4*>(nbr_idx + at0);
+  i32x4 n0[2], n1[2];
+  float2 ci[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = min((int)threadIdx.x + 256 * k, items - 1);
+    n0[k] = nbr[2 * i];
+    n1[k] = nbr[2 * i + 1];
+    ci[k] = cimg[q0 + fast_div(i, cq_magic)];
+  }
+  if (staged) {
+    for (int i = threadIdx.x; i < U * 16; i += 256) {
+      const int tile = ul[1 + (i >> 4)];
+      if ((i & 15) == 0) place[tile] = (uint8_t)(i >> 4);
+      xy[i] = cimg[min(tile * 16 + (i & 15), t.N - 1)];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = threadIdx.x + 256 * k;
+    if (i >= items) break;
+    const int nn[8] = {n0[k].x, n0[k].y, n0[k].z, n0[k].w, n1[k].x, n1[k].y, n1[k].z, n1[k].w};
+    uint32_t cell[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int n = min(max(nn[e], 0), t.N - 1);
+      const float2 cn = staged ? xy[min((int)place[n >> 4], kCellUnion - 1) * 16 + (n & 15)] : cimg[n];
+      cell[e] = (uint32_t)relpos_cell(cn, ci[k], rate, R);
+    }
+    reinterpret_cast<uint4*>(cells + at0)[i] = make_uint4(cell[0] | (cell[1] << 16), cell[2] | (cell[3] << 16),
+                                                          cell[4] | (cell[5] << 16), cell[6] | (cell[7] << 16));
   }
 }
 
@@ -224,6 +282,18 @@ int relpos_dtable_blocks(int B, int N, int K) {
   const long long total = (long long)B * N * K;
   return (int)((total + kDtableThreads * kDtableItems - 1) / (kDtableThreads * kDtableItems));
 }
+size_t relpos_cells_bytes(int B, int N, int K) { return (size_t)B * N * K * sizeof(uint16_t); }
+
+hipError_t launch_relpos_cells(const RelposArgs& r, const void* plan, int B, int N, int H, int K, int S, int M,
+                               uint16_t* cells, hipStream_t stream) {
+  const PlanLayout L = make_plan_layout(B, N, K, S, M);
+  const GroupTables t = group_tables(L, plan, N, H, K);
+  for (long long g0 = 0; g0 < L.groups; g0 += kMaxBlocks)
+    AFFMAE_LAUNCH("relpos_cells_kernel", stream, relpos_cells_kernel, dim3((unsigned)std::min((long long)L.groups - g0, kMaxBlocks)),
+                  dim3(256), 0, stream, t, r.coords, r.nbr_idx, (int)g0, K, div_magic(K / 8), r.R, r.rate, cells);
+  return hipGetLastError();
+}
+
 size_t relpos_dtable_workspace_bytes(int B, int N, int H, int K, int R) {
   const size_t cells = (size_t)(2 * R + 1) * (2 * R + 1);
   return (size_t)relpos_dtable_blocks(B, N, K) * H * cells * sizeof(float);

@@ -310,3 +310,56 @@ def test_plan_of_many_small_images():
     for big, small in zip(run(B), run(few)):
         assert small.float().abs().max() > 0
         assert torch.equal(big.view(B // few, *small.shape), small[None].expand(B // few, *small.shape))
+
+
+def _near_table(B, N, S, M, K, spread, rng):
+    """A table that keeps the cluster promise without coming from a search: cluster c is near to the M clusters around it
+    (spread False) or to M clusters drawn from the whole image, and a token's K distinct neighbours are drawn from them."""
+    G = N // S
+    near = np.empty((B, G, M), np.int32)
+    nbr = np.empty((B, N, K), np.int32)
+    for b in range(B):
+        for c in range(G):
+            near[b, c] = rng.choice(G, M, replace=False) if spread else (np.arange(M) + min(max(c - M // 2, 0), G - M))
+            cand = (near[b, c][:, None] * S + np.arange(S)).reshape(-1)
+            for i in range(c * S, (c + 1) * S):
+                nbr[b, i] = rng.choice(cand, K, replace=False)
+    return nbr, near
+
+
+@pytest.mark.parametrize("N,S,M,K,H,spread", [
+    (512, 64, 4, 16, 2, False),    # 16 tiles: as many as the forward kernel holds
+    (512, 32, 8, 48, 1, False),    # 16 .. 22 tiles: two stages
+    (1024, 64, 5, 48, 2, False),   # 20 tiles: as many as the narrow kernels hold and keep in registers, less 4
+    (1024, 64, 6, 56, 2, False),   # 24 tiles and rows of more than 48 values: three stages of the backward kernel
+    (1024, 64, 8, 48, 1, False),   # 32 tiles, strips of 32 slots: more pairs than are held in registers
+    (512, 16, 25, 33, 1, True),    # 32 tiles at most, an odd number of neighbours
+    (2048, 16, 64, 64, 1, True),   # unions of the whole image (128 tiles), strips of 64 slots, every list of 128 strips
+    (2096, 16, 40, 40, 2, True),   # the same with a last group of three strips
+])
+def test_unions_of_many_tiles(N, S, M, K, H, spread):
+    """Groups of strips that touch from 16 to 131 token tiles together, at the sizes where the tiled kernels change the way
+    they hold them: all in LDS, a second stage from registers, further stages from memory."""
+    print(f"case unions N={N} S={S} M={M} K={K} H={H}", flush=True)
+    rng = np.random.default_rng(N + M + K)
+    nbr, near = _near_table(1, N, S, M, K, spread, rng)
+    w = make_features(1, N, H, 32, K, "bf16", rng, blank=True)
+    check_attention(w, nbr, "bf16", 1.0 / np.sqrt(32), near=near, S=S, M=M, blank=True, use_plan=True)
+
+
+# (no blank column where it would leave the neighbours probabilities below fp32's range: the gradients would be compared with
+# values that are not representable)
+@pytest.mark.parametrize("low,high,blank", [(-3.0e4, -3.0e4, False), (-500.0, -500.0, False), (3.0e4, 3.0e4, False), (3.0e4, 3.0e4, True),
+                                            (-60.0, 90.0, False), (-60.0, 90.0, True), (-200.0, 3.0, False)])
+@pytest.mark.parametrize("N,S,M,K", [(256, 32, 4, 20), (1024, 64, 6, 48), (1001, 32, 4, 24)])
+def test_scores_far_from_the_reference(N, S, M, K, low, high, blank):
+    """The forward kernel takes its exponentials relative to the first pair of tiles and sums again, from memory, where that
+    does not hold: all scores far below or above 0, and scores that rise by 150 to 200 with the neighbour's token number
+    (bias rounded to bf16 beforehand; what is left of a large bias is exact in the oracle as well)."""
+    print(f"case far scores N={N} low={low} high={high} blank={blank}", flush=True)
+    cfg = CONFIGS["mae_pt_s1_1024"].scaled(B=1, N=N, C=64, H=2, K=K, S=S, M=M, dtype="bf16")
+    w = make_workload(cfg, blank=blank)
+    nbr, near = oracle.knn(w["coords"], None, S, M, K)
+    ramp = low + (high - low) * nbr[:, :, None, :] / (N - 1.0)
+    w["bias"] = torch.from_numpy((w["bias"] + ramp).astype(np.float32)).bfloat16().float().numpy()
+    check_attention(w, nbr, "bf16", 1.0 / np.sqrt(32), near=near, S=S, M=M, blank=blank, use_plan=True)

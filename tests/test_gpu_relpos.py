@@ -77,3 +77,22 @@ def test_relpos_clustered(name, B, N, S, M, K, H, R, rate, blank, use_plan):
     nbr, near = oracle.knn(w["coords"], None, S, M, K)
     _check(w, w["coords"], nbr, _table(rng, H, R, "bf16"), R, rate, "bf16", 1.0 / np.sqrt(32.0), near, S, M, blank,
            use_plan)
+
+
+@pytest.mark.parametrize("N,S,M,K", [(2048, 16, 64, 64), (65536 + 64, 64, 4, 8)])
+def test_relpos_cells_from_memory(N, S, M, K):
+    """Cells of pairs whose coordinates are not brought into LDS first: unions of more than 64 token tiles, and images of
+    more than 4096 of them."""
+    print(f"case relpos cells N={N} S={S} M={M} K={K}", flush=True)
+    rng = np.random.default_rng(N)
+    G = N // S
+    near = np.stack([rng.choice(G, M, replace=False) if N < 4096 else (np.arange(M) + min(max(c - 1, 0), G - M))
+                     for c in range(G)]).astype(np.int32)
+    cand = (near[:, :, None] * S + np.arange(S)).reshape(G, M * S)
+    pick = np.argsort(rng.random((N, M * S), dtype=np.float32), axis=1)[:, :K]
+    nbr = np.take_along_axis(np.repeat(cand, S, axis=0), pick, axis=1).astype(np.int32)[None]
+    cfg = CONFIGS["knn_scale"].scaled(B=1, N=256, C=32, H=1, K=K, S=16, M=4, dtype="bf16")
+    w = make_workload(cfg, blank=False)
+    w = {n: np.ascontiguousarray(np.resize(w[n], (1, N) + w[n].shape[2:])) for n in ("q", "k", "v", "dout")}
+    coords = rng.uniform(0, 100, size=(1, N, 2)).astype(np.float32)
+    _check(w, coords, nbr, _table(rng, 1, 4, "bf16"), 4, 0.1, "bf16", 1.0 / np.sqrt(32.0), near[None], S, M, False, True)
