@@ -30,6 +30,13 @@ struct GroupTables {
 // 64-bit product of 32-bit values: two scalar instructions instead of the eight of a 64-bit product
 __device__ __forceinline__ size_t mul_u32(uint32_t a, uint32_t b) { return (size_t)a * b; }
 
+// Values that a lane moves at a time between the bias (or dbias) rows in memory and those in LDS: 16 bytes where every row
+// of K values starts at a multiple of them, else 4, else one value.
+inline int bias_item(int K, const void* bias, const void* dbias) {
+  const uintptr_t at = reinterpret_cast<uintptr_t>(bias) | reinterpret_cast<uintptr_t>(dbias);
+  return K % 8 == 0 && at % 16 == 0 ? 8 : K % 2 == 0 && at % 4 == 0 ? 2 : 1;
+}
+
 inline GroupTables group_tables(const PlanLayout& L, const void* plan, int N, int H, int K) {
   const char* base = static_cast<const char*>(plan);
   GroupTables t;
@@ -141,8 +148,8 @@ struct TileWalk {
     lane_off_max = (uint32_t)(t.N - 1) * row_bytes + piece;
     tile_bytes = 16u * row_bytes;
 #pragma unroll
-    for (int i = 0; i < PL / kGroup; ++i)
-      if (i * kGroup + wave < U) issue(__builtin_amdgcn_readlane(my_tile, i * kGroup + wave), i * kGroup + wave);
+    for (int i = 0; i < (PL + kGroup - 1) / kGroup; ++i)
+      if (i * kGroup + wave < min(U, PL)) issue(__builtin_amdgcn_readlane(my_tile, i * kGroup + wave), i * kGroup + wave);
     // j words of the strip's pairs, two pairs a test (the second repeats the last pair where the strip ends before it)
     const int last_pair = (max(cnt, 1) - 1) >> 1;
 #pragma unroll
@@ -175,9 +182,9 @@ struct TileWalk {
       Frag f[2];
       fetch(f[0], jw[0].x, jw[0].y, __builtin_amdgcn_readlane(at, 0), __builtin_amdgcn_readlane(at, 1));
 #pragma unroll
-      for (int i = 0; i < PL / 2; ++i) {
+      for (int i = 0; i < (PL + 1) / 2; ++i) {
         if (2 * i >= cnt) break;
-        if (i + 1 < PL / 2)
+        if (i + 1 < (PL + 1) / 2)
           fetch(f[(i + 1) & 1], jw[i + 1].x, jw[i + 1].y, __builtin_amdgcn_readlane(at, 2 * i + 2), __builtin_amdgcn_readlane(at, 2 * i + 3));
         __builtin_amdgcn_sched_barrier(0);
         math(f[i & 1]);

@@ -41,7 +41,7 @@ struct BwdParams {
   const unsigned long long* rev_list;
   int K, block_bytes;           // block_bytes: of a (strip, head) in `hand`
   int block0;                   // first workgroup of this launch's slice
-  uint32_t k_magic, cq_magic;   // reciprocals of K and of K / 8
+  uint32_t item_magic;          // reciprocal of K / W, the items of a query
   float scale;
   bf16_t *dq, *dk, *dv;
   bf16_t* ds;    // [B,N,H,K] dS = dbias, or nullptr when the caller does not want it
@@ -65,24 +65,25 @@ struct BwdPair {
   uint16_t at[8];      // their places
 };
 
-// Bytes of one of a wave's three row arrays (bias, dS, p): K up to 48 or 64.  Three workgroups per CU either way: 16 tiles
-// and 51 KB, 12 tiles and 49 KB.
-template <bool WIDE>
+// Classes of K: up to 48, 60, 64.  Bytes of a wave's bias rows (the words of dS and p take twice that; the key-stationary
+// kernel holds one such array a strip), and the token tiles that fit beside them with three workgroups per CU.  LDS is
+// given out in pieces of 1280 bytes: three have 53760 bytes each (with 17 tiles, 54016 bytes, two ran: 135 us for 115).
+template <int CL>
 struct RowArray {
-  static constexpr int bytes = WIDE ? 16 * 66 * 2 : 16 * 50 * 2;
-  static constexpr int places = WIDE ? 12 : 16;
+  static constexpr int bytes = CL == 0 ? 25 * 64 : CL == 1 ? 31 * 64 : 33 * 64;
+  static constexpr int places = CL == 0 ? 16 : CL == 1 ? 14 : 13;
 };
 
-// Items per lane as in the forward kernel: NT chunks of 8 slots (K % 8 == 0) or NT single entries.
+// Items per lane as in the forward kernel: NT of W slots each (W = 8, 2, 1).
 // REL: the bias comes from the head's relative-position table, and the table's gradient is summed per
 // workgroup (SUMS): each pair's dS is added to its bin in an fp64 table in LDS (ds_add_f64 runs at the speed of an integer
 // LDS atomic on this chip; the fp32 form is several times slower) and the workgroup writes its table out at the end.
 // RAG: N is not a multiple of 16 (only then do the row clamps and store tests below exist in the code).
-template <int NT, bool WIDE, bool VEC, bool REL, bool SUMS, bool RAG>
+template <int NT, int W, int CL, bool REL, bool SUMS, bool RAG>
 __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
   static_assert(!SUMS || REL, "the table's gradient belongs to the table form");
-  static_assert(!REL || VEC, "the table form is built for 16-byte items");
-  constexpr int PL = RowArray<WIDE>::places, RB = RowArray<WIDE>::bytes;
+  static_assert(!REL || W == 8, "the table form is built for 16-byte items");
+  constexpr int PL = RowArray<CL>::places, RB = RowArray<CL>::bytes;
   __shared__ __align__(16) char tiles[PL * 2048];
   __shared__ __align__(16) char rows_all[kGroup][3 * RB];
   __shared__ __align__(16) double sums[SUMS ? kRelCells : 1];  // (one table for the four waves: with one each, two workgroups per CU)
@@ -103,35 +104,41 @@ __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
     of.x4 = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(p.out) + at);
   }
   const float lse = (p.lse + w.heads0())[(uint32_t)((RAG ? min(r, w.nq - 1) : r) * p.t.H)];
-  constexpr int EW = VEC ? 4 : 1;  // 32-bit words per item
-  const int items = VEC ? 2 * K : 16 * K;
+  constexpr int EW = W == 8 ? 4 : 1;  // 32-bit words per item
+  const int per = K / W, items = 16 * per;
+  // Place of an item: byte offset in the bias rows, and element offset of its first value within the strip's
+  // [token, head, :] rows, head 0.  Single values and pairs: worked out again at the end, not held (16 items of one value
+  // took 177 registers, two wavefronts a SIMD).
+  auto item_place = [&](int t, int ln, int& row_at, uint32_t& item_off, bool& live) {
+    const int i = t * kWave + ln, ii = i < items ? i : 0;
+    const int qi = fast_div(ii, p.item_magic);
+    const int j0 = (ii - qi * per) * W;
+    row_at = (qi * RH + j0) * 2;
+    item_off = (uint32_t)(RAG ? min(qi, w.nq - 1) : qi) * p.t.H * K + j0;
+    live = i < items && (!RAG || qi < w.nq);  // items of queries past the image's end: no dbias is written
+  };
   uint32_t bw[NT][EW];
-  int row_at[NT];
-  uint32_t item_off[NT];  // element offset of the item's first value within the strip's [token, head, :] rows, head 0
-  bool item_live[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    const int i = t * kWave + lane, ii = i < items ? i : 0;
-    const int qi = fast_div(ii, VEC ? p.cq_magic : p.k_magic);
-    const int j0 = VEC ? (ii - qi * (K >> 3)) * 8 : ii - qi * K;
-    const int qc = RAG ? min(qi, w.nq - 1) : qi;
-    row_at[t] = (qi * RH + j0) * 2;
-    item_off[t] = (uint32_t)qc * p.t.H * K + j0;
-    item_live[t] = i < items && (!RAG || qi < w.nq);  // items of queries past the image's end: no dbias is written
+    int row_at;
+    uint32_t item_off;
+    bool item_live;
+    item_place(t, lane, row_at, item_off, item_live);
 #pragma unroll
     for (int e = 0; e < EW; ++e) bw[t][e] = 0u;
     if (REL) {  // the cells instead
-      const u32x4 x = *reinterpret_cast<const u32x4*>(p.cells + w.slots0(K) + (uint32_t)(qc * K + j0));
+      const int ii = t * kWave + lane < items ? t * kWave + lane : 0;
+      const u32x4 x = reinterpret_cast<const u32x4*>(p.cells + w.slots0(K))[RAG ? min(ii, w.nq * per - 1) : ii];
 #pragma unroll
       for (int e = 0; e < EW; ++e) bw[t][e] = x[e];
     } else if (p.bias) {
-      const bf16_t* src = p.bias + w.pairs0(K, h) + item_off[t];
-      if (VEC) {
+      const bf16_t* src = p.bias + w.pairs0(K, h) + item_off;
+      if (W == 8) {
         const u32x4 x = *reinterpret_cast<const u32x4*>(src);
 #pragma unroll
         for (int e = 0; e < EW; ++e) bw[t][e] = x[e];
       } else {
-        bw[t][0] = *src;
+        bw[t][0] = W == 2 ? *reinterpret_cast<const uint32_t*>(src) : *src;
       }
     }
   }
@@ -144,20 +151,27 @@ __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     if (t * kWave + lane < items) {
-      if (VEC) {
+      int row_at;
+      uint32_t item_off;
+      bool item_live;
+      item_place(t, lane, row_at, item_off, item_live);
+      if (W == 1) {
+        *reinterpret_cast<bf16_t*>(rows + row_at) = (bf16_t)bw[t][0];
+      } else {
 #pragma unroll
         for (int e = 0; e < EW; ++e) {
           uint32_t x = bw[t][e];
           if (REL) x = *reinterpret_cast<const bf16_t*>(table + (x & 0xffffu) * 2u) | ((uint32_t)*reinterpret_cast<const bf16_t*>(table + (x >> 16) * 2u) << 16);
-          reinterpret_cast<uint32_t*>(rows + row_at[t])[e] = x;
+          reinterpret_cast<uint32_t*>(rows + row_at)[e] = x;
         }
-      } else {
-        *reinterpret_cast<bf16_t*>(rows + row_at[t]) = (bf16_t)bw[t][0];
       }
     }
   }
   if (lane < 16) reinterpret_cast<bf16_t*>(rows)[lane * RH + K] = 0xff80u;  // -inf where "no neighbour" points
-  char* row = rows + r * RH * 2;
+  const char* row = rows + r * RH * 2;
+  // dS (low half) and p (high half) of a pair in one word, laid out as the bias rows: half the writes of two arrays
+  char* words = rows + RB;
+  char* word_row = words + r * RH * 4;
   const int rd_off = tile_chunk(r, g) * 16;
   const int tr_off0 = tile_tr_offset(g, r, 0), tr_off1 = tile_tr_offset(g, r, 1);
   const float scale = p.scale;
@@ -242,18 +256,15 @@ __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
       pv[i] = __builtin_amdgcn_exp2f(fmaf(fmaf(st[i >> 2][i & 3], scale, __uint_as_float((uint32_t)f.tb[i] << 16)), kLog2e, nl2));
       dsv[i] = pv[i] * dp[i >> 2][i & 3];
     }
+    uint32_t both[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {  // ("no neighbour": zeros, behind the rows' ends)
+      both[i] = pack_bf16x2(dsv[i], pv[i]);
+      *reinterpret_cast<uint32_t*>(word_row + 2 * (int)f.at[i]) = both[i];
+    }
     Frag8 dsf;  // dS^T operand: k-slots 0..3 = first tile's tokens 4g..4g+3, 4..7 = second tile's
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      dsf.u[i] = pack_bf16x2(dsv[2 * i], dsv[2 * i + 1]);
-      const uint32_t pp = pack_bf16x2(pv[2 * i], pv[2 * i + 1]);
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {  // ("no neighbour": zeros, behind the rows' ends)
-        char* at = row + f.at[2 * i + e];
-        *reinterpret_cast<uint16_t*>(at + RB) = (uint16_t)(dsf.u[i] >> (16 * e));
-        *reinterpret_cast<uint16_t*>(at + 2 * RB) = (uint16_t)(pp >> (16 * e));
-      }
-    }
+    for (int i = 0; i < 4; ++i) dsf.u[i] = __builtin_amdgcn_perm(both[2 * i + 1], both[2 * i], 0x05040100u);
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt) acc[dt] = mfma32(f.kt[dt], dsf, acc[dt]);  // dq^T[channel 16dt + 4g+i][query r]
   };
@@ -263,17 +274,31 @@ __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
     wave_lds_sync();
     // rows of p and -D to the other kernel
     char* hand = p.hand + mul_u32(unit, p.block_bytes);
-    for (int i = lane; i < 2 * RH; i += kWave) reinterpret_cast<u32x4*>(hand)[i] = reinterpret_cast<const u32x4*>(rows + 2 * RB)[i];
+    // two words' halves of one kind in one word
+    auto halves = [](uint2 x, bool high) { return __builtin_amdgcn_perm(x.y, x.x, high ? 0x07060302u : 0x05040100u); };
+    for (int i = lane; i < 2 * RH; i += kWave) {
+      u32x4 x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = halves(reinterpret_cast<const uint2*>(words)[4 * i + e], true);
+      reinterpret_cast<u32x4*>(hand)[i] = x;
+    }
     if (g == 0) reinterpret_cast<float*>(hand + 32 * RH)[r] = -Dq;
     // dbias [token, head, slot]; whole 16-byte pieces when K is a multiple of 8
     if (SUMS || p.ds) {
+      int ln = lane;
+      if (W != 8) asm volatile("" : "+v"(ln));  // (the places are not held from above)
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        if (VEC) {
+        int row_at;
+        uint32_t item_off;
+        bool item_live;
+        item_place(t, ln, row_at, item_off, item_live);
+        const char* src = words + 2 * row_at;
+        if (W == 8) {
           u32x4 x;
 #pragma unroll
-          for (int e = 0; e < EW; ++e) x[e] = reinterpret_cast<const uint32_t*>(rows + RB + row_at[t])[e];
-          if (item_live[t]) {
+          for (int e = 0; e < EW; ++e) x[e] = halves(reinterpret_cast<const uint2*>(src)[e], false);
+          if (item_live) {
             if (SUMS) {
 #pragma unroll
               for (int e = 0; e < EW; ++e) {
@@ -281,11 +306,13 @@ __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
                 atomicAdd(&sums[SUMS ? (bw[t][e] >> 16) : 0], (double)__uint_as_float(x[e] & 0xffff0000u));
               }
             } else {
-              *reinterpret_cast<u32x4*>(p.ds + w.pairs0(K, h) + item_off[t]) = x;
+              *reinterpret_cast<u32x4*>(p.ds + w.pairs0(K, h) + item_off) = x;
             }
           }
-        } else if (item_live[t]) {
-          (p.ds + w.pairs0(K, h))[item_off[t]] = *reinterpret_cast<const bf16_t*>(rows + RB + row_at[t]);
+        } else if (item_live) {
+          bf16_t* dst = p.ds + w.pairs0(K, h) + item_off;
+          if (W == 2) *reinterpret_cast<uint32_t*>(dst) = halves(*reinterpret_cast<const uint2*>(src), false);
+          else *dst = *reinterpret_cast<const bf16_t*>(src);
         }
       }
     }
@@ -309,30 +336,34 @@ __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
   }
 }
 
-template <int NT, bool WIDE, bool RAG>
+template <int NT, int CL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pla_bwd_query_kernel(BwdParams p) {
-  pla_bwd_query_body<NT, WIDE, true, false, false, RAG>(p);
+  pla_bwd_query_body<NT, 8, CL, false, false, RAG>(p);
 }
-template <int NT, bool WIDE, bool RAG>
+template <int NT, int CL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pla_bwd_query_rel_kernel(BwdParams p) {
-  pla_bwd_query_body<NT, WIDE, true, true, true, RAG>(p);
+  pla_bwd_query_body<NT, 8, CL, true, true, RAG>(p);
 }
-template <int NT, bool WIDE, bool RAG>
+template <int NT, int CL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3))) void pla_bwd_query_rel_ds_kernel(BwdParams p) {
-  pla_bwd_query_body<NT, WIDE, true, true, false, RAG>(p);
+  pla_bwd_query_body<NT, 8, CL, true, false, RAG>(p);
 }
-template <int NT, bool WIDE, bool RAG>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3))) void pla_bwd_query_scalar_kernel(BwdParams p) {
-  pla_bwd_query_body<NT, WIDE, false, false, false, RAG>(p);
+template <int NT, int CL, bool RAG>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pla_bwd_query_even_kernel(BwdParams p) {
+  pla_bwd_query_body<NT, 2, CL, false, false, RAG>(p);
+}
+template <int NT, int CL, bool RAG>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pla_bwd_query_scalar_kernel(BwdParams p) {
+  pla_bwd_query_body<NT, 1, CL, false, false, RAG>(p);
 }
 
 // ------------------------------------------------------------------------------------------------
 // key-stationary kernel
 constexpr int kChunk = 4;  // strips in LDS at a time, one per wave to fetch; twice: the next chunk's rows fly during the math
 
-template <bool WIDE, bool RAG>
+template <int CL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pla_bwd_key_kernel(BwdParams p) {
-  constexpr int kRows = RowArray<WIDE>::bytes;
+  constexpr int kRows = RowArray<CL>::bytes;
   constexpr int kStrip = 2048 + kRows + 64;  // q rows, dout rows, the strip's block of `hand`
   __shared__ __align__(16) char strips[2][kChunk][kStrip];
   __shared__ __align__(16) char jb_all[2][kGroup][kChunk][256];  // j bytes of (strip, own tile), 16 (token / 4) + query words
@@ -403,9 +434,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         dma16(dst, qimg, off);
         dma16(dst + 1024u, gimg, off);
         const char* hand = p.hand + mul_u32((strip0 + (uint32_t)__builtin_amdgcn_readlane(my_strip, e)) * p.t.H + h, p.block_bytes);
-        dma16(dst + 2048u, hand, (uint32_t)lane * 16u);  // (a block has at least 68 pieces)
 #pragma unroll
-        for (int i = 1; i < (WIDE ? 3 : 2); ++i)
+        for (int i = 0; i < (CL == 2 ? 3 : 2); ++i)
           if (lane + i * kWave < hand_pieces) dma16(dst + 2048u + i * 1024u, hand, (uint32_t)(lane + i * kWave) * 16u);
       }
       const uint32_t on = (uint32_t)(mask >> (c * kChunk));
@@ -582,49 +612,61 @@ hipError_t launch_pla_bwd_cluster(const PlaArgs& a, const void* plan, void* work
                      : nullptr;
   p.rel_table = (const bf16_t*)a.rel_table; p.cells = a.rel_cells; p.ncells = (2 * a.rel_R + 1) * (2 * a.rel_R + 1);
   p.rel_part = a.rel_part;
-  p.k_magic = div_magic(a.K);
-  p.cq_magic = div_magic(a.K >= 8 ? a.K / 8 : 1);
-  const bool vec = a.K % 8 == 0 && (!a.bias || reinterpret_cast<uintptr_t>(a.bias) % 16 == 0) &&
-                   (!p.ds || reinterpret_cast<uintptr_t>(p.ds) % 16 == 0);
+  const int W = bias_item(a.K, a.bias, p.ds);
+  p.item_magic = div_magic(a.K / W);
   const bool rag = a.N % 16 != 0;  // a short last strip / token tile per image: the variants with row clamps
-  const bool wide = a.K > 48;
+  const int cl = a.K <= 48 ? 0 : a.K <= 60 ? 1 : 2;
   const size_t shared = a.rel_table ? (size_t)p.ncells * 2 : 0;
   const long long blocks = (long long)L.groups * a.H;
   // the XCD-contiguous mapping needs a grid that is a multiple of 8; surplus workgroups exit at once
   for (long long b0 = 0; b0 < blocks; b0 += kMaxBlocks) {
     p.block0 = (int)b0;
     const dim3 grid((unsigned)((std::min(blocks - b0, kMaxBlocks) + 7) / 8 * 8));
-#define AFFMAE_BWDQ(KERNEL, NT, WIDE)                                                                                             \
+#define AFFMAE_BWDQ(KERNEL, NT, CL)                                                                                               \
   do {                                                                                                                            \
-    if (rag) AFFMAE_LAUNCH("pla_bwd_query_kernel", stream, (KERNEL<NT, WIDE, true>), grid, dim3(256), shared, stream, p);         \
-    else AFFMAE_LAUNCH("pla_bwd_query_kernel", stream, (KERNEL<NT, WIDE, false>), grid, dim3(256), shared, stream, p);            \
+    if (rag) AFFMAE_LAUNCH("pla_bwd_query_kernel", stream, (KERNEL<NT, CL, true>), grid, dim3(256), shared, stream, p);           \
+    else AFFMAE_LAUNCH("pla_bwd_query_kernel", stream, (KERNEL<NT, CL, false>), grid, dim3(256), shared, stream, p);              \
   } while (0)
-    // (an item per lane covers K <= 32; two cover the rest)
-#define AFFMAE_BWDQ_VEC(KERNEL)                           \
-  do {                                                    \
-    if (2 * a.K <= kWave) AFFMAE_BWDQ(KERNEL, 1, false);  \
-    else if (!wide) AFFMAE_BWDQ(KERNEL, 2, false);        \
-    else AFFMAE_BWDQ(KERNEL, 2, true);                    \
+#define AFFMAE_BWDQ_LAST(KERNEL, NT)               \
+  do {                                             \
+    if (cl == 1) AFFMAE_BWDQ(KERNEL, NT, 1);       \
+    else AFFMAE_BWDQ(KERNEL, NT, 2);               \
+  } while (0)
+    // (an item of 8 per lane covers K <= 32; two cover the rest)
+#define AFFMAE_BWDQ_VEC(KERNEL)                       \
+  do {                                                \
+    if (2 * a.K <= kWave) AFFMAE_BWDQ(KERNEL, 1, 0);  \
+    else if (cl == 0) AFFMAE_BWDQ(KERNEL, 2, 0);      \
+    else AFFMAE_BWDQ_LAST(KERNEL, 2);                 \
   } while (0)
     if (a.rel_table && a.rel_part) AFFMAE_BWDQ_VEC(pla_bwd_query_rel_kernel);  // callers check pla_cluster_relpos_supported first
     else if (a.rel_table) AFFMAE_BWDQ_VEC(pla_bwd_query_rel_ds_kernel);
-    else if (vec) AFFMAE_BWDQ_VEC(pla_bwd_query_kernel);
-    else {
+    else if (W == 8) AFFMAE_BWDQ_VEC(pla_bwd_query_kernel);
+    else if (W == 2) {
+      if (a.K <= 16) AFFMAE_BWDQ(pla_bwd_query_even_kernel, 2, 0);
+      else if (a.K <= 32) AFFMAE_BWDQ(pla_bwd_query_even_kernel, 4, 0);
+      else if (cl == 0) AFFMAE_BWDQ(pla_bwd_query_even_kernel, 6, 0);
+      else AFFMAE_BWDQ_LAST(pla_bwd_query_even_kernel, 8);
+    } else {
       const int ent = (16 * a.K + kWave - 1) / kWave;
-      if (ent <= 4) AFFMAE_BWDQ(pla_bwd_query_scalar_kernel, 4, false);
-      else if (ent <= 8) AFFMAE_BWDQ(pla_bwd_query_scalar_kernel, 8, false);
-      else if (ent <= 12) AFFMAE_BWDQ(pla_bwd_query_scalar_kernel, 12, false);
-      else AFFMAE_BWDQ(pla_bwd_query_scalar_kernel, 16, true);
+      if (ent <= 4) AFFMAE_BWDQ(pla_bwd_query_scalar_kernel, 4, 0);
+      else if (ent <= 8) AFFMAE_BWDQ(pla_bwd_query_scalar_kernel, 8, 0);
+      else if (cl == 0) AFFMAE_BWDQ(pla_bwd_query_scalar_kernel, 12, 0);
+      else AFFMAE_BWDQ_LAST(pla_bwd_query_scalar_kernel, 16);
     }
 #undef AFFMAE_BWDQ_VEC
+#undef AFFMAE_BWDQ_LAST
 #undef AFFMAE_BWDQ
   }
   for (long long b0 = 0; b0 < blocks; b0 += kMaxBlocks) {
     p.block0 = (int)b0;
     const dim3 grid((unsigned)((std::min(blocks - b0, kMaxBlocks) + 7) / 8 * 8));
-#define AFFMAE_BWDK(WIDE, RAG) AFFMAE_LAUNCH("pla_bwd_key_kernel", stream, (pla_bwd_key_kernel<WIDE, RAG>), grid, dim3(256), 0, stream, p)
-    if (wide) { if (rag) AFFMAE_BWDK(true, true); else AFFMAE_BWDK(true, false); }
-    else { if (rag) AFFMAE_BWDK(false, true); else AFFMAE_BWDK(false, false); }
+#define AFFMAE_BWDK(CL)                                                                                                            \
+  do {                                                                                                                            \
+    if (rag) AFFMAE_LAUNCH("pla_bwd_key_kernel", stream, (pla_bwd_key_kernel<CL, true>), grid, dim3(256), 0, stream, p);          \
+    else AFFMAE_LAUNCH("pla_bwd_key_kernel", stream, (pla_bwd_key_kernel<CL, false>), grid, dim3(256), 0, stream, p);             \
+  } while (0)
+    if (cl == 0) AFFMAE_BWDK(0); else if (cl == 1) AFFMAE_BWDK(1); else AFFMAE_BWDK(2);
 #undef AFFMAE_BWDK
   }
   if (a.rel_table && a.rel_part) {

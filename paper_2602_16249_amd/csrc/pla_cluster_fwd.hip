@@ -30,14 +30,17 @@ namespace affmae {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kPlaces = 16;  // token tiles held in LDS
+// Token tiles held in LDS: as many as leave room for four workgroups per CU beside the rows of K values (K > 60: 33 words a
+// row; with 16 places and three workgroups 40.1 us against 36.3 before the tiles were shared, K = 64, B = 8, N = 4096, H = 8).
+constexpr int kMostPlaces = 16;
+inline int places(int K) { return K <= 60 ? kMostPlaces : kMostPlaces - 1; }
 
 struct FwdParams {
   GroupTables t;
   const bf16_t *q, *k, *v, *bias, *k_blank, *v_blank;
   int K, wave_bytes;
   int block0;                   // first workgroup of this launch's slice
-  uint32_t k_magic, cq_magic;   // reciprocals of K and of K / 8
+  uint32_t item_magic;          // reciprocal of K / W, the items of a query
   float scale;
   // bias from a relative-position table (REL kernels): table [H][cells], cell of every (token, neighbour) [B,N,K]
   const bf16_t* rel_table;
@@ -54,32 +57,32 @@ struct FwdPair {
   uint16_t tb[8];   // bias of query r and these tokens
 };
 
-// Bias rows [query][row_halves] of the strip: with K a multiple of 8 (VEC) a lane brings NT chunks of 8 values, otherwise
-// NT single ones.  REL: the values are looked up in the head's table, which the workgroup holds in LDS.
+// Bias rows [query][row_halves] of the strip: a lane brings NT items of W values each, 8 when K is a multiple of 8, 2 when
+// it is even, otherwise 1 (see bias_item).  REL: the values are looked up in the head's table, which the workgroup holds in LDS.
 // RAG: N is not a multiple of 16.
-template <int NT, bool VEC, bool REL, bool RAG>
+template <int NT, int W, int PL, bool REL, bool RAG>
 __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
-  static_assert(!REL || VEC, "the table form is built for 16-byte items");
+  static_assert(!REL || W == 8, "the table form is built for 16-byte items");
   extern __shared__ __align__(16) char lds[];  // tiles, per wave bias rows, REL: the head's table
   const int blk = p.block0 + xcd_contiguous_block();
   const int gi = exact_div(blk, p.t.H, p.t.h_magic);
   if (gi >= p.t.groups) return;  // the whole workgroup
-  TileWalk<kPlaces, RAG> w(p.t, gi, blk - gi * p.t.H, lds);
+  TileWalk<PL, RAG> w(p.t, gi, blk - gi * p.t.H, lds);
   const int lane = w.lane, g = w.g, r = w.r, h = w.h, K = p.K;
   const int RH = row_halves(K);
-  char* rows = lds + kPlaces * 2048 + w.wave * p.wave_bytes;
-  const char* table = lds + kPlaces * 2048 + kGroup * p.wave_bytes;
+  char* rows = lds + PL * 2048 + w.wave * p.wave_bytes;
+  const char* table = lds + PL * 2048 + kGroup * p.wave_bytes;
   Frag8 qf;  // Q^T operand: lane (query r, channels 8g..8g+7)
   qf.x4 = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(p.q) + w.img_off + w.query_piece(r, g));
-  constexpr int EW = VEC ? 4 : 1;  // 32-bit words per item
-  const int items = VEC ? 2 * K : 16 * K;
+  constexpr int EW = W == 8 ? 4 : 1;  // 32-bit words per item
+  const int per = K / W, items = 16 * per;
   uint32_t bw[NT][EW];
   int row_at[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     const int i = t * kWave + lane, ii = i < items ? i : 0;
-    const int qi = fast_div(ii, VEC ? p.cq_magic : p.k_magic);
-    const int j0 = VEC ? (ii - qi * (K >> 3)) * 8 : ii - qi * K;
+    const int qi = fast_div(ii, p.item_magic);
+    const int j0 = (ii - qi * per) * W;
     const int qc = RAG ? min(qi, w.nq - 1) : qi;
     row_at[t] = (qi * RH + j0) * 2;
 #pragma unroll
@@ -90,24 +93,26 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
       for (int e = 0; e < EW; ++e) bw[t][e] = x[e];
     } else if (p.bias) {
       const bf16_t* src = p.bias + w.pairs0(K, h) + (uint32_t)qc * p.t.H * K + j0;
-      if (VEC) {
+      if (W == 8) {
         const u32x4 x = *reinterpret_cast<const u32x4*>(src);
 #pragma unroll
         for (int e = 0; e < EW; ++e) bw[t][e] = x[e];
       } else {
-        bw[t][0] = *src;
+        bw[t][0] = W == 2 ? *reinterpret_cast<const uint32_t*>(src) : *src;
       }
     }
   }
   w.request(p.k, p.v);
   if (REL) {
-    for (int i = threadIdx.x; i < p.ncells; i += 256) reinterpret_cast<bf16_t*>(lds + kPlaces * 2048 + kGroup * p.wave_bytes)[i] = p.rel_table[h * p.ncells + i];
+    for (int i = threadIdx.x; i < p.ncells; i += 256) reinterpret_cast<bf16_t*>(lds + PL * 2048 + kGroup * p.wave_bytes)[i] = p.rel_table[h * p.ncells + i];
     __syncthreads();
   }
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     if (t * kWave + lane < items) {
-      if (VEC) {
+      if (W == 1) {
+        *reinterpret_cast<bf16_t*>(rows + row_at[t]) = (bf16_t)bw[t][0];
+      } else {
 #pragma unroll
         for (int e = 0; e < EW; ++e) {
           if (REL) {
@@ -117,8 +122,6 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
           }
           reinterpret_cast<uint32_t*>(rows + row_at[t])[e] = bw[t][e];
         }
-      } else {
-        *reinterpret_cast<bf16_t*>(rows + row_at[t]) = (bf16_t)bw[t][0];
       }
     }
   }
@@ -279,17 +282,21 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
     (p.lse + w.heads0())[(uint32_t)(r * p.t.H)] = (m2 + __builtin_amdgcn_logf(l_tot)) * 0.69314718055994531f;
 }
 
-template <int NT, bool RAG>
+template <int NT, int PL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pla_fwd_cluster_kernel(FwdParams p) {
-  pla_fwd_body<NT, true, false, RAG>(p);
+  pla_fwd_body<NT, 8, PL, false, RAG>(p);
 }
-template <int NT, bool RAG>
+template <int NT, int PL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pla_fwd_cluster_rel_kernel(FwdParams p) {
-  pla_fwd_body<NT, true, true, RAG>(p);
+  pla_fwd_body<NT, 8, PL, true, RAG>(p);
 }
-template <int NT, bool RAG>
+template <int NT, int PL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pla_fwd_cluster_scalar_kernel(FwdParams p) {
-  pla_fwd_body<NT, false, false, RAG>(p);
+  pla_fwd_body<NT, 1, PL, false, RAG>(p);
+}
+template <int NT, int PL, bool RAG>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pla_fwd_cluster_even_kernel(FwdParams p) {
+  pla_fwd_body<NT, 2, PL, false, RAG>(p);
 }
 
 }  // namespace
@@ -323,34 +330,47 @@ hipError_t launch_pla_fwd_cluster(const PlaArgs& a, const void* plan, hipStream_
   p.scale = a.scale;
   p.out = (bf16_t*)a.out; p.lse = a.lse;
   p.rel_table = (const bf16_t*)a.rel_table; p.cells = a.rel_cells; p.ncells = (2 * a.rel_R + 1) * (2 * a.rel_R + 1);
-  p.k_magic = div_magic(a.K);
-  p.cq_magic = div_magic(a.K >= 8 ? a.K / 8 : 1);
+  const int W = bias_item(a.K, a.bias, nullptr);
+  p.item_magic = div_magic(a.K / W);
   p.wave_bytes = std::max(1024, (16 * row_halves(a.K) * 2 + 15) / 16 * 16);  // (out rows cross there: 1 KB)
-  const size_t shared = kPlaces * 2048 + kGroup * p.wave_bytes + (a.rel_table ? (size_t)p.ncells * 2 : 0);
-  const bool vec = a.K % 8 == 0 && (!a.bias || reinterpret_cast<uintptr_t>(a.bias) % 16 == 0);
+  const bool full = places(a.K) == kMostPlaces;
+  const size_t shared = places(a.K) * 2048 + kGroup * p.wave_bytes + (a.rel_table ? (size_t)p.ncells * 2 : 0);
   const bool rag = a.N % 16 != 0;  // a short last strip / token tile per image: the variants with row clamps
   const long long blocks = (long long)L.groups * a.H;
   for (long long b0 = 0; b0 < blocks; b0 += kMaxBlocks) {
     // the XCD-contiguous mapping needs a grid that is a multiple of 8; surplus workgroups exit at once
     p.block0 = (int)b0;
     const dim3 grid((unsigned)((std::min(blocks - b0, kMaxBlocks) + 7) / 8 * 8));
-#define AFFMAE_FWD(KERNEL, NT)                                                                                                  \
-  do {                                                                                                                          \
-    if (rag) AFFMAE_LAUNCH("pla_fwd_cluster_kernel", stream, (KERNEL<NT, true>), grid, dim3(256), shared, stream, p);           \
-    else AFFMAE_LAUNCH("pla_fwd_cluster_kernel", stream, (KERNEL<NT, false>), grid, dim3(256), shared, stream, p);              \
+#define AFFMAE_FWD_PL(KERNEL, NT, PL)                                                                                         \
+  do {                                                                                                                         \
+    if (rag) AFFMAE_LAUNCH("pla_fwd_cluster_kernel", stream, (KERNEL<NT, PL, true>), grid, dim3(256), shared, stream, p);      \
+    else AFFMAE_LAUNCH("pla_fwd_cluster_kernel", stream, (KERNEL<NT, PL, false>), grid, dim3(256), shared, stream, p);         \
+  } while (0)
+#define AFFMAE_FWD(KERNEL, NT) AFFMAE_FWD_PL(KERNEL, NT, kMostPlaces)
+#define AFFMAE_FWD_LAST(KERNEL, NT)  /* K > 48 among others */         \
+  do {                                                                 \
+    if (full) AFFMAE_FWD(KERNEL, NT);                                  \
+    else AFFMAE_FWD_PL(KERNEL, NT, kMostPlaces - 1);                   \
   } while (0)
     if (a.rel_table) {  // callers check pla_cluster_relpos_supported first
-      if (2 * a.K <= kWave) AFFMAE_FWD(pla_fwd_cluster_rel_kernel, 1); else AFFMAE_FWD(pla_fwd_cluster_rel_kernel, 2);
-    } else if (vec) {
-      if (2 * a.K <= kWave) AFFMAE_FWD(pla_fwd_cluster_kernel, 1); else AFFMAE_FWD(pla_fwd_cluster_kernel, 2);
+      if (2 * a.K <= kWave) AFFMAE_FWD(pla_fwd_cluster_rel_kernel, 1); else AFFMAE_FWD_LAST(pla_fwd_cluster_rel_kernel, 2);
+    } else if (W == 8) {
+      if (2 * a.K <= kWave) AFFMAE_FWD(pla_fwd_cluster_kernel, 1); else AFFMAE_FWD_LAST(pla_fwd_cluster_kernel, 2);
+    } else if (W == 2) {
+      if (a.K <= 16) AFFMAE_FWD(pla_fwd_cluster_even_kernel, 2);
+      else if (a.K <= 32) AFFMAE_FWD(pla_fwd_cluster_even_kernel, 4);
+      else if (a.K <= 48) AFFMAE_FWD(pla_fwd_cluster_even_kernel, 6);
+      else AFFMAE_FWD_LAST(pla_fwd_cluster_even_kernel, 8);
     } else {
       const int ent = (16 * a.K + kWave - 1) / kWave;
       if (ent <= 4) AFFMAE_FWD(pla_fwd_cluster_scalar_kernel, 4);
       else if (ent <= 8) AFFMAE_FWD(pla_fwd_cluster_scalar_kernel, 8);
       else if (ent <= 12) AFFMAE_FWD(pla_fwd_cluster_scalar_kernel, 12);
-      else AFFMAE_FWD(pla_fwd_cluster_scalar_kernel, 16);
+      else AFFMAE_FWD_LAST(pla_fwd_cluster_scalar_kernel, 16);
     }
+#undef AFFMAE_FWD_LAST
 #undef AFFMAE_FWD
+#undef AFFMAE_FWD_PL
   }
   return hipGetLastError();
 }

@@ -9,7 +9,7 @@ import torch
 
 import oracle
 import paper_2602_16249_amd as aff
-from helpers import check_attention
+from helpers import check_attention, to_dev
 from workloads import CONFIGS, make_features, make_workload, random_neighbours
 
 pytestmark = pytest.mark.gpu
@@ -363,3 +363,27 @@ def test_scores_far_from_the_reference(N, S, M, K, low, high, blank):
     ramp = low + (high - low) * nbr[:, :, None, :] / (N - 1.0)
     w["bias"] = torch.from_numpy((w["bias"] + ramp).astype(np.float32)).bfloat16().float().numpy()
     check_attention(w, nbr, "bf16", 1.0 / np.sqrt(32), near=near, S=S, M=M, blank=blank, use_plan=True)
+
+
+@pytest.mark.parametrize("K", [15, 16, 17, 32, 46, 47, 48, 50, 56, 59, 60, 61, 62, 63, 64])
+@pytest.mark.parametrize("N", [512, 493])
+def test_rows_of_every_length(N, K):
+    """Row lengths round the edges of the tiled kernels' classes (48, 60 and 64 values; 8, 2 or 1 of them moved at a time),
+    and a bias that starts 2, 4 or 8 bytes off: the way its values reach LDS differs, the results may not in any bit."""
+    print(f"case rows N={N} K={K}", flush=True)
+    S, M = 32, 5
+    w = make_workload(CONFIGS["knn_scale"].scaled(B=1, N=N, C=64, H=2, K=K, S=S, M=M, dtype="bf16"), blank=True)
+    nbr, near = oracle.knn(w["coords"], None, S, M, K)
+    scale = 1.0 / np.sqrt(32)
+    check_attention(w, nbr, "bf16", scale, near=near, S=S, M=M, blank=True, use_plan=True)
+    q, k, v, dout, bias = (to_dev(w[n], "bf16") for n in ("q", "k", "v", "dout", "bias"))
+    nbr, near = (torch.from_numpy(np.ascontiguousarray(x, dtype=np.int32)).cuda() for x in (nbr, near))
+    results = []
+    for off in (0, 1, 2, 4):
+        moved = torch.empty(bias.numel() + 8, dtype=bias.dtype, device="cuda")[off:off + bias.numel()].view(bias.shape)
+        moved.copy_(bias)
+        out, lse = aff.affmae_pla_fwd(q, k, v, moved, nbr, scale, near, S, M)
+        g = aff.affmae_pla_bwd(q, k, v, moved, nbr, out, lse, dout, scale, near, S, M)
+        results.append([out, lse] + [g[n] for n in sorted(g) if g[n] is not None])
+    for other in results[1:]:
+        assert all(torch_equal(a, b) for a, b in zip(results[0], other))
