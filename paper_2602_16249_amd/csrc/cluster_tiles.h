@@ -154,7 +154,8 @@ struct TileWalk {
     const int last_pair = (max(cnt, 1) - 1) >> 1;
 #pragma unroll
     for (int i = 0; i < kPairs; ++i) {
-      asm volatile("" : "=v"(jw[i].x), "=v"(jw[i].y));  // any value where no slot is: no instruction
+      if (i & 1) asm volatile("" : "=v"(jw[i].x), "=v"(jw[i].y));  // any value where no slot is: no instruction
+      else jw[i] = make_uint2(0u, 0u);  // the pair behind the last may be fetched: bytes as they come are odd addresses, and slow
       if (2 * (i & ~1) < cnt) jw[i] = *reinterpret_cast<const uint2*>(jt + (uint32_t)(((i & 1) ? min(i, last_pair) : i) * 512 + lane * 8));
     }
 #pragma unroll
