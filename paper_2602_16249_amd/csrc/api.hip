@@ -527,14 +527,14 @@ int affmae_pla_fwd_relpos(const void* q, const void* k, const void* v, const flo
     if (plan && misaligned(plan, kAlign)) return AFFMAE_ERR_WORKSPACE;
     const affmae::RelposArgs r = {coords, nbr_idx, rel_table, R, rate};
     uint16_t* cells = reinterpret_cast<uint16_t*>(ws);
-    a.rel_cells = cells;
+    if (!affmae::pla_cluster_relpos_direct(a)) a.rel_cells = cells;
     if (!plan) {  // the workspace holds the cells and a plan (checked above)
       void* own = ws + align_up(affmae::relpos_cells_bytes(B, N, K));
       if (affmae::launch_pla_plan(nbr_idx, near_clusters, B, N, K, S, M, own, st) != hipSuccess)
         return AFFMAE_ERR_DEVICE;
       plan = own;
     }
-    if (affmae::launch_relpos_cells(r, plan, B, N, H, K, S, M, cells, st) != hipSuccess) return AFFMAE_ERR_DEVICE;
+    if (a.rel_cells && affmae::launch_relpos_cells(r, plan, B, N, H, K, S, M, cells, st) != hipSuccess) return AFFMAE_ERR_DEVICE;
     return affmae::launch_pla_fwd_cluster(a, plan, st) == hipSuccess ? AFFMAE_OK : AFFMAE_ERR_DEVICE;
   }
   // the bias is written into the workspace by a kernel of its own: validate the attention call before it
@@ -614,14 +614,14 @@ int affmae_pla_bwd_relpos(const void* q, const void* k, const void* v, const flo
       off += bb + tb;
     }
     uint16_t* cells = reinterpret_cast<uint16_t*>(ws + off);
-    a.rel_cells = cells;
+    if (!affmae::pla_cluster_relpos_direct(a)) a.rel_cells = cells;
     off += align_up(affmae::relpos_cells_bytes(B, N, K));
     if (!plan) {
       if (affmae::launch_pla_plan(nbr_idx, near_clusters, B, N, K, S, M, ws + off, st) != hipSuccess)
         return AFFMAE_ERR_DEVICE;
       plan = ws + off;
     }
-    if (affmae::launch_relpos_cells(r, plan, B, N, H, K, S, M, cells, st) != hipSuccess) return AFFMAE_ERR_DEVICE;
+    if (a.rel_cells && affmae::launch_relpos_cells(r, plan, B, N, H, K, S, M, cells, st) != hipSuccess) return AFFMAE_ERR_DEVICE;
     off += align_up(affmae::pla_plan_bytes(B, N, K, S, M));
     if (affmae::launch_pla_bwd_cluster(a, plan, ws + off, st) != hipSuccess) return AFFMAE_ERR_DEVICE;
     if (!sums && affmae::launch_relpos_dtable(r, B, N, H, K, dtype, a.dbias, drel_table, parts, st) != hipSuccess)

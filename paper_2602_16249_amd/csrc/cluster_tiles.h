@@ -9,6 +9,7 @@
 #pragma once
 
 #include "cluster_common.h"
+#include "launch.h"
 
 namespace affmae {
 
@@ -36,6 +37,24 @@ inline int bias_item(int K, const void* bias, const void* dbias) {
   const uintptr_t at = reinterpret_cast<uintptr_t>(bias) | reinterpret_cast<uintptr_t>(dbias);
   return K % 8 == 0 && at % 16 == 0 ? 8 : K % 2 == 0 && at % 4 == 0 ? 2 : 1;
 }
+
+// Bias from a relative-position table (REL of the kernels): kRelCells, the cells of the pairs come from memory, written by
+// a kernel of their own; kRelDirect, every (strip, head) works its own out from the coordinates.
+enum { kNoRel = 0, kRelCells = 1, kRelDirect = 2 };
+struct RelSource {
+  const bf16_t* table;    // [H][ncells]
+  int ncells;
+  const uint16_t* cells;  // [B,N,K] (kRelCells)
+  const float2* coords;   // [B,N], nbr [B,N,K] (kRelDirect)
+  const int32_t* nbr;
+  float rate;
+  int R;
+};
+// Calls of up to this many (token, head, neighbour) triples work their cells out directly: two launches less, and the extra
+// round trip to memory is hidden or the launch is short.  us forward + backward, cells from memory / directly: 47 / 41 up to
+// 1 M triples, 64 / 56 at 2.1 M (one head), 90.2 / 85.5 at 6.3 M, 143 / 143 at 12.6 M, 263 / 265 at 16.8 M, 277 / 283 at 25 M
+// (8 heads: the cells of a pair are worked out 8 times, and 24 bytes are gathered for 2 bytes read).
+constexpr long long kRelDirectTriples = 10ll << 20;
 
 inline GroupTables group_tables(const PlanLayout& L, const void* plan, int N, int H, int K) {
   const char* base = static_cast<const char*>(plan);
@@ -239,5 +258,41 @@ struct TileWalk {
     }
   }
 };
+
+// Eight neighbours of a query (an item of the kernels, K a multiple of 8) on their way to cells (kRelDirect).
+struct RelItem {
+  typedef int i32x4 __attribute__((ext_vector_type(4), aligned(4)));  // (the table need not lie at a multiple of 16 bytes)
+  i32x4 n0, n1;
+  float2 ci;
+  template <class Walk>
+  __device__ __forceinline__ void request(const RelSource& s, const Walk& w, int K, int qc, int j0) {
+    const i32x4* src = reinterpret_cast<const i32x4*>(s.nbr + w.slots0(K) + (uint32_t)(qc * K + j0));
+    n0 = src[0];
+    n1 = src[1];
+    ci = (s.coords + mul_u32(w.b, w.t.N))[(uint32_t)(w.q0 + qc)];
+  }
+  template <class Walk>
+  __device__ __forceinline__ void cells(const RelSource& s, const Walk& w, uint32_t (&out)[4]) const {
+    const float2* cimg = s.coords + mul_u32(w.b, w.t.N);
+    const int nn[8] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
+    float2 cn[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) cn[e] = cimg[(uint32_t)min(max(nn[e], 0), w.t.N - 1)];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      out[e] = (uint32_t)relpos_cell(cn[2 * e], ci, s.rate, s.R) | ((uint32_t)relpos_cell(cn[2 * e + 1], ci, s.rate, s.R) << 16);
+  }
+};
+inline RelSource rel_source(const PlaArgs& a) {
+  RelSource s;
+  s.table = (const bf16_t*)a.rel_table;
+  s.ncells = (2 * a.rel_R + 1) * (2 * a.rel_R + 1);
+  s.cells = a.rel_cells;
+  s.coords = (const float2*)a.rel_coords;
+  s.nbr = a.nbr_idx;
+  s.rate = a.rel_rate;
+  s.R = a.rel_R;
+  return s;
+}
 
 }  // namespace affmae

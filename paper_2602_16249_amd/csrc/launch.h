@@ -113,7 +113,7 @@ struct PlaArgs {
   const void* rel_table;    // [H, 2R+1, 2R+1] in the storage type
   int rel_R;
   float rel_rate;
-  const uint16_t* rel_cells;  // [B,N,K] cells of the pairs (launch_relpos_cells)
+  const uint16_t* rel_cells;  // [B,N,K] cells of the pairs (launch_relpos_cells), or null: worked out from the coordinates
   float* rel_part;    // backward: workspace of pla_bwd_cluster_rel_workspace_bytes, or null (then dbias is written)
   float* rel_dtable;  // backward, with rel_part: [H, 2R+1, 2R+1] gradient of the table
   // forward outputs / backward inputs
@@ -137,6 +137,7 @@ hipError_t launch_pla_plan(const int32_t* nbr_idx, const int32_t* near, int B, i
                            hipStream_t stream);
 hipError_t launch_pla_fwd_cluster(const PlaArgs& a, const void* plan, hipStream_t stream);
 size_t pla_bwd_cluster_workspace_bytes(int B, int N, int H, int K, int S, int M);
+bool pla_cluster_relpos_direct(const PlaArgs& a);     // ... without cells in memory: the call is small
 bool pla_bwd_cluster_rel_sums(int R);  // the table is small enough for the backward kernel to sum its gradient itself
 size_t pla_bwd_cluster_rel_workspace_bytes(int B, int N, int H, int R);
 hipError_t launch_pla_bwd_cluster(const PlaArgs& a, const void* plan, void* workspace, hipStream_t stream);

@@ -31,7 +31,7 @@ namespace affmae {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kRelCells = 128;  // bins of a workgroup's fp64 table
+constexpr int kRelBins = 128;  // bins of a workgroup's fp64 table
 
 struct BwdParams {
   GroupTables t;
@@ -48,11 +48,8 @@ struct BwdParams {
   char* hand;    // workspace [strips][H]: rows of p [16][row_halves] bf16, then -D [16] fp32
   const bf16_t *k_blank, *v_blank;  // [H,32] or nullptr
   float* blank_part;                // workspace [strips][H][2][32]: the strip's parts of dk_blank, dv_blank; or nullptr
-  // bias from a relative-position table (REL kernels): table [H][ncells], cell of every (token, neighbour) [B,N,K]
-  const bf16_t* rel_table;
-  const uint16_t* cells;
-  int ncells;
-  float* rel_part;  // workspace [groups][H][ncells]: every workgroup's sums of dS per bin (needs ncells <= kRelCells),
+  RelSource rel;    // REL kernels
+  float* rel_part;  // workspace [groups][H][ncells]: every workgroup's sums of dS per bin (needs ncells <= kRelBins),
                     // or nullptr: then dS goes out through `ds` for the stand-alone table-gradient kernel
 };
 
@@ -79,14 +76,14 @@ struct RowArray {
 // workgroup (SUMS): each pair's dS is added to its bin in an fp64 table in LDS (ds_add_f64 runs at the speed of an integer
 // LDS atomic on this chip; the fp32 form is several times slower) and the workgroup writes its table out at the end.
 // RAG: N is not a multiple of 16 (only then do the row clamps and store tests below exist in the code).
-template <int NT, int W, int CL, bool REL, bool SUMS, bool RAG>
+template <int NT, int W, int CL, int REL, bool SUMS, bool RAG>
 __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
   static_assert(!SUMS || REL, "the table's gradient belongs to the table form");
   static_assert(!REL || W == 8, "the table form is built for 16-byte items");
   constexpr int PL = RowArray<CL>::places, RB = RowArray<CL>::bytes;
   __shared__ __align__(16) char tiles[PL * 2048];
   __shared__ __align__(16) char rows_all[kGroup][3 * RB];
-  __shared__ __align__(16) double sums[SUMS ? kRelCells : 1];  // (one table for the four waves: with one each, two workgroups per CU)
+  __shared__ __align__(16) double sums[SUMS ? kRelBins : 1];  // (one table for the four waves: with one each, two workgroups per CU)
   extern __shared__ __align__(16) char table[];  // REL: the head's table
   const int blk = p.block0 + xcd_contiguous_block();
   const int gi = exact_div(blk, p.t.H, p.t.h_magic);
@@ -118,6 +115,7 @@ __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
     live = i < items && (!RAG || qi < w.nq);  // items of queries past the image's end: no dbias is written
   };
   uint32_t bw[NT][EW];
+  RelItem item[REL == kRelDirect ? NT : 1];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     int row_at;
@@ -126,9 +124,12 @@ __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
     item_place(t, lane, row_at, item_off, item_live);
 #pragma unroll
     for (int e = 0; e < EW; ++e) bw[t][e] = 0u;
-    if (REL) {  // the cells instead
+    if constexpr (REL == kRelDirect) {
+      const int ii = t * kWave + lane < items ? t * kWave + lane : 0, qi = fast_div(ii, p.item_magic);
+      item[REL == kRelDirect ? t : 0].request(p.rel, w, K, RAG ? min(qi, w.nq - 1) : qi, (ii - qi * per) * W);
+    } else if (REL) {  // the cells instead
       const int ii = t * kWave + lane < items ? t * kWave + lane : 0;
-      const u32x4 x = reinterpret_cast<const u32x4*>(p.cells + w.slots0(K))[RAG ? min(ii, w.nq * per - 1) : ii];
+      const u32x4 x = reinterpret_cast<const u32x4*>(p.rel.cells + w.slots0(K))[RAG ? min(ii, w.nq * per - 1) : ii];
 #pragma unroll
       for (int e = 0; e < EW; ++e) bw[t][e] = x[e];
     } else if (p.bias) {
@@ -144,8 +145,12 @@ __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
   }
   w.request(p.k, p.v);
   if (REL) {
-    for (int i = threadIdx.x; i < p.ncells; i += 256) reinterpret_cast<bf16_t*>(table)[i] = p.rel_table[h * p.ncells + i];
-    if (SUMS && threadIdx.x < kRelCells) sums[SUMS ? threadIdx.x : 0] = 0.;
+    if constexpr (REL == kRelDirect) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) item[REL == kRelDirect ? t : 0].cells(p.rel, w, bw[t]);
+    }
+    for (int i = threadIdx.x; i < p.rel.ncells; i += 256) reinterpret_cast<bf16_t*>(table)[i] = p.rel.table[h * p.rel.ncells + i];
+    if (SUMS && threadIdx.x < kRelBins) sums[SUMS ? threadIdx.x : 0] = 0.;
     __syncthreads();
   }
 #pragma unroll
@@ -332,29 +337,37 @@ __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
   }
   if (SUMS) {
     __syncthreads();
-    if (threadIdx.x < (unsigned)p.ncells) (p.rel_part + mul_u32((uint32_t)gi * p.t.H + h, p.ncells))[threadIdx.x] = (float)sums[SUMS ? threadIdx.x : 0];
+    if (threadIdx.x < (unsigned)p.rel.ncells) (p.rel_part + mul_u32((uint32_t)gi * p.t.H + h, p.rel.ncells))[threadIdx.x] = (float)sums[SUMS ? threadIdx.x : 0];
   }
 }
 
 template <int NT, int CL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pla_bwd_query_kernel(BwdParams p) {
-  pla_bwd_query_body<NT, 8, CL, false, false, RAG>(p);
+  pla_bwd_query_body<NT, 8, CL, kNoRel, false, RAG>(p);
 }
 template <int NT, int CL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pla_bwd_query_rel_kernel(BwdParams p) {
-  pla_bwd_query_body<NT, 8, CL, true, true, RAG>(p);
+  pla_bwd_query_body<NT, 8, CL, kRelCells, true, RAG>(p);
+}
+template <int NT, int CL, bool RAG>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pla_bwd_query_rel_direct_kernel(BwdParams p) {
+  pla_bwd_query_body<NT, 8, CL, kRelDirect, true, RAG>(p);
 }
 template <int NT, int CL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3))) void pla_bwd_query_rel_ds_kernel(BwdParams p) {
-  pla_bwd_query_body<NT, 8, CL, true, false, RAG>(p);
+  pla_bwd_query_body<NT, 8, CL, kRelCells, false, RAG>(p);
+}
+template <int NT, int CL, bool RAG>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3))) void pla_bwd_query_rel_ds_direct_kernel(BwdParams p) {
+  pla_bwd_query_body<NT, 8, CL, kRelDirect, false, RAG>(p);
 }
 template <int NT, int CL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pla_bwd_query_even_kernel(BwdParams p) {
-  pla_bwd_query_body<NT, 2, CL, false, false, RAG>(p);
+  pla_bwd_query_body<NT, 2, CL, kNoRel, false, RAG>(p);
 }
 template <int NT, int CL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pla_bwd_query_scalar_kernel(BwdParams p) {
-  pla_bwd_query_body<NT, 1, CL, false, false, RAG>(p);
+  pla_bwd_query_body<NT, 1, CL, kNoRel, false, RAG>(p);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -580,7 +593,7 @@ size_t pla_bwd_cluster_rel_workspace_bytes(int B, int N, int H, int R) {
   const size_t groups = (size_t)B * ((N + 16 * kGroup - 1) / (16 * kGroup));
   return plan_align(groups * H * cells * sizeof(float)) + plan_align((size_t)kRelParts * H * cells * sizeof(float));
 }
-bool pla_bwd_cluster_rel_sums(int R) { return (2 * R + 1) * (2 * R + 1) <= kRelCells; }
+bool pla_bwd_cluster_rel_sums(int R) { return (2 * R + 1) * (2 * R + 1) <= kRelBins; }
 
 // bytes of a (strip, head) in the hand-over: rows of p, -D
 static size_t hand_bytes(int K) { return (size_t)32 * row_halves(K) + 64; }
@@ -610,13 +623,13 @@ hipError_t launch_pla_bwd_cluster(const PlaArgs& a, const void* plan, void* work
   p.blank_part = (a.k_blank && a.dk_blank)
                      ? reinterpret_cast<float*>(p.hand + plan_align((size_t)L.strips * a.H * hand_bytes(a.K)))
                      : nullptr;
-  p.rel_table = (const bf16_t*)a.rel_table; p.cells = a.rel_cells; p.ncells = (2 * a.rel_R + 1) * (2 * a.rel_R + 1);
+  p.rel = rel_source(a);
   p.rel_part = a.rel_part;
   const int W = bias_item(a.K, a.bias, p.ds);
   p.item_magic = div_magic(a.K / W);
   const bool rag = a.N % 16 != 0;  // a short last strip / token tile per image: the variants with row clamps
   const int cl = a.K <= 48 ? 0 : a.K <= 60 ? 1 : 2;
-  const size_t shared = a.rel_table ? (size_t)p.ncells * 2 : 0;
+  const size_t shared = a.rel_table ? (size_t)p.rel.ncells * 2 : 0;
   const long long blocks = (long long)L.groups * a.H;
   // the XCD-contiguous mapping needs a grid that is a multiple of 8; surplus workgroups exit at once
   for (long long b0 = 0; b0 < blocks; b0 += kMaxBlocks) {
@@ -639,7 +652,10 @@ hipError_t launch_pla_bwd_cluster(const PlaArgs& a, const void* plan, void* work
     else if (cl == 0) AFFMAE_BWDQ(KERNEL, 2, 0);      \
     else AFFMAE_BWDQ_LAST(KERNEL, 2);                 \
   } while (0)
-    if (a.rel_table && a.rel_part) AFFMAE_BWDQ_VEC(pla_bwd_query_rel_kernel);  // callers check pla_cluster_relpos_supported first
+    // callers check pla_cluster_relpos_supported first
+    if (a.rel_table && !a.rel_cells && a.rel_part) AFFMAE_BWDQ_VEC(pla_bwd_query_rel_direct_kernel);
+    else if (a.rel_table && !a.rel_cells) AFFMAE_BWDQ_VEC(pla_bwd_query_rel_ds_direct_kernel);
+    else if (a.rel_table && a.rel_part) AFFMAE_BWDQ_VEC(pla_bwd_query_rel_kernel);
     else if (a.rel_table) AFFMAE_BWDQ_VEC(pla_bwd_query_rel_ds_kernel);
     else if (W == 8) AFFMAE_BWDQ_VEC(pla_bwd_query_kernel);
     else if (W == 2) {

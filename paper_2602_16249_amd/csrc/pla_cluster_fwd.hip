@@ -42,10 +42,7 @@ struct FwdParams {
   int block0;                   // first workgroup of this launch's slice
   uint32_t item_magic;          // reciprocal of K / W, the items of a query
   float scale;
-  // bias from a relative-position table (REL kernels): table [H][cells], cell of every (token, neighbour) [B,N,K]
-  const bf16_t* rel_table;
-  const uint16_t* cells;
-  int ncells;
+  RelSource rel;
   bf16_t* out;
   float* lse;
 };
@@ -60,7 +57,7 @@ struct FwdPair {
 // Bias rows [query][row_halves] of the strip: a lane brings NT items of W values each, 8 when K is a multiple of 8, 2 when
 // it is even, otherwise 1 (see bias_item).  REL: the values are looked up in the head's table, which the workgroup holds in LDS.
 // RAG: N is not a multiple of 16.
-template <int NT, int W, int PL, bool REL, bool RAG>
+template <int NT, int W, int PL, int REL, bool RAG>
 __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
   static_assert(!REL || W == 8, "the table form is built for 16-byte items");
   extern __shared__ __align__(16) char lds[];  // tiles, per wave bias rows, REL: the head's table
@@ -78,6 +75,7 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
   const int per = K / W, items = 16 * per;
   uint32_t bw[NT][EW];
   int row_at[NT];
+  RelItem item[REL == kRelDirect ? NT : 1];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     const int i = t * kWave + lane, ii = i < items ? i : 0;
@@ -87,8 +85,10 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
     row_at[t] = (qi * RH + j0) * 2;
 #pragma unroll
     for (int e = 0; e < EW; ++e) bw[t][e] = 0u;
-    if (REL) {  // the cells instead
-      const u32x4 x = *reinterpret_cast<const u32x4*>(p.cells + w.slots0(K) + (uint32_t)(qc * K + j0));
+    if constexpr (REL == kRelDirect) {
+      item[REL == kRelDirect ? t : 0].request(p.rel, w, K, qc, j0);
+    } else if (REL) {  // the cells instead
+      const u32x4 x = *reinterpret_cast<const u32x4*>(p.rel.cells + w.slots0(K) + (uint32_t)(qc * K + j0));
 #pragma unroll
       for (int e = 0; e < EW; ++e) bw[t][e] = x[e];
     } else if (p.bias) {
@@ -104,7 +104,11 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
   }
   w.request(p.k, p.v);
   if (REL) {
-    for (int i = threadIdx.x; i < p.ncells; i += 256) reinterpret_cast<bf16_t*>(lds + PL * 2048 + kGroup * p.wave_bytes)[i] = p.rel_table[h * p.ncells + i];
+    if constexpr (REL == kRelDirect) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) item[REL == kRelDirect ? t : 0].cells(p.rel, w, bw[t]);
+    }
+    for (int i = threadIdx.x; i < p.rel.ncells; i += 256) reinterpret_cast<bf16_t*>(lds + PL * 2048 + kGroup * p.wave_bytes)[i] = p.rel.table[h * p.rel.ncells + i];
     __syncthreads();
   }
 #pragma unroll
@@ -284,19 +288,23 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
 
 template <int NT, int PL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pla_fwd_cluster_kernel(FwdParams p) {
-  pla_fwd_body<NT, 8, PL, false, RAG>(p);
+  pla_fwd_body<NT, 8, PL, kNoRel, RAG>(p);
 }
 template <int NT, int PL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pla_fwd_cluster_rel_kernel(FwdParams p) {
-  pla_fwd_body<NT, 8, PL, true, RAG>(p);
+  pla_fwd_body<NT, 8, PL, kRelCells, RAG>(p);
+}
+template <int NT, int PL, bool RAG>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pla_fwd_cluster_rel_direct_kernel(FwdParams p) {
+  pla_fwd_body<NT, 8, PL, kRelDirect, RAG>(p);
 }
 template <int NT, int PL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pla_fwd_cluster_scalar_kernel(FwdParams p) {
-  pla_fwd_body<NT, 1, PL, false, RAG>(p);
+  pla_fwd_body<NT, 1, PL, kNoRel, RAG>(p);
 }
 template <int NT, int PL, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pla_fwd_cluster_even_kernel(FwdParams p) {
-  pla_fwd_body<NT, 2, PL, false, RAG>(p);
+  pla_fwd_body<NT, 2, PL, kNoRel, RAG>(p);
 }
 
 }  // namespace
@@ -306,6 +314,8 @@ bool pla_cluster_relpos_supported(const PlaArgs& a) {
   return pla_cluster_supported(a) && a.K % 8 == 0 && a.rel_coords && a.rel_table &&
          reinterpret_cast<uintptr_t>(a.rel_coords) % 8 == 0;
 }
+
+bool pla_cluster_relpos_direct(const PlaArgs& a) { return (long long)a.B * a.N * a.H * a.K <= kRelDirectTriples; }
 
 bool pla_cluster_supported(const PlaArgs& a) {
   if (!a.near_clusters || a.dtype != 1 || a.d != kD) return false;
@@ -329,12 +339,12 @@ hipError_t launch_pla_fwd_cluster(const PlaArgs& a, const void* plan, hipStream_
   p.K = a.K;
   p.scale = a.scale;
   p.out = (bf16_t*)a.out; p.lse = a.lse;
-  p.rel_table = (const bf16_t*)a.rel_table; p.cells = a.rel_cells; p.ncells = (2 * a.rel_R + 1) * (2 * a.rel_R + 1);
+  p.rel = rel_source(a);
   const int W = bias_item(a.K, a.bias, nullptr);
   p.item_magic = div_magic(a.K / W);
   p.wave_bytes = std::max(1024, (16 * row_halves(a.K) * 2 + 15) / 16 * 16);  // (out rows cross there: 1 KB)
   const bool full = places(a.K) == kMostPlaces;
-  const size_t shared = places(a.K) * 2048 + kGroup * p.wave_bytes + (a.rel_table ? (size_t)p.ncells * 2 : 0);
+  const size_t shared = places(a.K) * 2048 + kGroup * p.wave_bytes + (a.rel_table ? (size_t)p.rel.ncells * 2 : 0);
   const bool rag = a.N % 16 != 0;  // a short last strip / token tile per image: the variants with row clamps
   const long long blocks = (long long)L.groups * a.H;
   for (long long b0 = 0; b0 < blocks; b0 += kMaxBlocks) {
@@ -352,7 +362,9 @@ hipError_t launch_pla_fwd_cluster(const PlaArgs& a, const void* plan, hipStream_
     if (full) AFFMAE_FWD(KERNEL, NT);                                  \
     else AFFMAE_FWD_PL(KERNEL, NT, kMostPlaces - 1);                   \
   } while (0)
-    if (a.rel_table) {  // callers check pla_cluster_relpos_supported first
+    if (a.rel_table && !a.rel_cells) {  // callers check pla_cluster_relpos_supported first
+      if (2 * a.K <= kWave) AFFMAE_FWD(pla_fwd_cluster_rel_direct_kernel, 1); else AFFMAE_FWD_LAST(pla_fwd_cluster_rel_direct_kernel, 2);
+    } else if (a.rel_table) {
       if (2 * a.K <= kWave) AFFMAE_FWD(pla_fwd_cluster_rel_kernel, 1); else AFFMAE_FWD_LAST(pla_fwd_cluster_rel_kernel, 2);
     } else if (W == 8) {
       if (2 * a.K <= kWave) AFFMAE_FWD(pla_fwd_cluster_kernel, 1); else AFFMAE_FWD_LAST(pla_fwd_cluster_kernel, 2);

@@ -79,20 +79,42 @@ def test_relpos_clustered(name, B, N, S, M, K, H, R, rate, blank, use_plan):
            use_plan)
 
 
-@pytest.mark.parametrize("N,S,M,K", [(2048, 16, 64, 64), (65536 + 64, 64, 4, 8)])
-def test_relpos_cells_from_memory(N, S, M, K):
-    """Cells of pairs whose coordinates are not brought into LDS first: unions of more than 64 token tiles, and images of
-    more than 4096 of them."""
-    print(f"case relpos cells N={N} S={S} M={M} K={K}", flush=True)
+@pytest.mark.parametrize("N,S,M,K,H,B,R", [
+    (2000, 32, 6, 48, 16, 7, 3),       # coordinates found in LDS
+    (2000, 32, 6, 56, 16, 7, 7),       # the same, table gradient by the stand-alone kernel
+    (2048, 16, 64, 64, 16, 6, 5),      # unions of more than 64 token tiles: coordinates from memory
+    (65536 + 64, 64, 4, 8, 8, 3, 4),   # images of more than 4096 of them: likewise
+])
+def test_relpos_cells_of_large_calls(N, S, M, K, H, B, R):
+    """Large calls read the pairs' cells from memory, small ones work them out in the attention kernels: B copies of an
+    image in one call give the bits of the image by itself."""
+    print(f"case relpos cells N={N} S={S} M={M} K={K} H={H} B={B}", flush=True)
+    assert N * H * K <= 10 << 20 < B * N * H * K
     rng = np.random.default_rng(N)
-    G = N // S
-    near = np.stack([rng.choice(G, M, replace=False) if N < 4096 else (np.arange(M) + min(max(c - 1, 0), G - M))
+    G = -(-N // S)
+    near = np.stack([rng.choice(G, M, replace=False) if M == 64 else (np.arange(M) + min(max(c - 1, 0), G - M))
                      for c in range(G)]).astype(np.int32)
     cand = (near[:, :, None] * S + np.arange(S)).reshape(G, M * S)
-    pick = np.argsort(rng.random((N, M * S), dtype=np.float32), axis=1)[:, :K]
-    nbr = np.take_along_axis(np.repeat(cand, S, axis=0), pick, axis=1).astype(np.int32)[None]
-    cfg = CONFIGS["knn_scale"].scaled(B=1, N=256, C=32, H=1, K=K, S=16, M=4, dtype="bf16")
-    w = make_workload(cfg, blank=False)
-    w = {n: np.ascontiguousarray(np.resize(w[n], (1, N) + w[n].shape[2:])) for n in ("q", "k", "v", "dout")}
-    coords = rng.uniform(0, 100, size=(1, N, 2)).astype(np.float32)
-    _check(w, coords, nbr, _table(rng, 1, 4, "bf16"), 4, 0.1, "bf16", 1.0 / np.sqrt(32.0), near[None], S, M, False, True)
+    order = rng.random((N, M * S), dtype=np.float32)
+    cand = np.repeat(cand, S, axis=0)[:N]
+    order[cand >= N] = 2.0  # (the last cluster may be short)
+    nbr = np.take_along_axis(cand, np.argsort(order, axis=1)[:, :K], axis=1).astype(np.int32)
+    gen = torch.Generator().manual_seed(N)
+    image = {n: torch.randn(1, N, H, 32, generator=gen).bfloat16().cuda() for n in ("q", "k", "v", "dout")}
+    table = torch.randn(H, 2 * R + 1, 2 * R + 1, generator=gen).bfloat16().cuda()
+    coords = torch.from_numpy(rng.uniform(0, 100, size=(1, N, 2)).astype(np.float32)).cuda()
+    tables = [torch.from_numpy(x[None]).cuda() for x in (nbr, near)]
+    def run(copies):
+        many = lambda t: t.repeat((copies,) + (1,) * (t.dim() - 1)).contiguous()
+        q, k, v, dout = (many(image[n]) for n in ("q", "k", "v", "dout"))
+        c, nb, nr = many(coords), many(tables[0]), many(tables[1])
+        out, lse = aff.affmae_pla_fwd_relpos(q, k, v, c, table, nb, 0.18, 0.1, nr, S, M)
+        g = aff.affmae_pla_bwd_relpos(q, k, v, c, table, nb, out, lse, dout, 0.18, 0.1, nr, S, M)
+        return [out, lse, g["dq"], g["dk"], g["dv"]], g["drel_table"]
+    alone, dtable = run(1)
+    together, dtables = run(B)
+    for a, b in zip(alone, together):
+        assert all(torch.equal(a[0], b[i]) for i in range(B))
+    # sums of the same N * K values of dS per head, in other orders: fp64 in LDS, fp32 between workgroups (2^-24 each)
+    err = (dtables.double() - B * dtable.double()).abs().max() / (B * dtable.double().abs().max())
+    assert err <= 1e-4
