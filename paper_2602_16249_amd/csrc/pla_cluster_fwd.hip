@@ -19,7 +19,10 @@
 // writes per pass.)
 //
 // Bound by instruction issue and the two memory round trips at a wave's start; four
-// workgroups per CU (39 KB of LDS at K = 48).
+// workgroups per CU (39 KB of LDS at K = 48).  us, tiles fetched per (strip, head) / shared:
+// B64 N1024 H8 K48 89 / 76, B8 N65536 blobs H2 K48 172 / 149, B8 N16384 H2 K48 34 / 34.  Where
+// four strips touch more than 16 tiles together (two stages) and share few of them, S = 16 and
+// M of 8 and more, it is 3 - 15 % slower than before; 22 tiles and three workgroups were not better.
 #include "cluster_tiles.h"
 #include "launch.h"
 #include "timing.h"
