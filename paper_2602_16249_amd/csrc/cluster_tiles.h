@@ -50,10 +50,12 @@ struct RelSource {
   float rate;
   int R;
 };
-// Calls of up to this many (token, head, neighbour) triples work their cells out directly: two launches less, and the extra
-// round trip to memory is hidden or the launch is short.  us forward + backward, cells from memory / directly: 47 / 41 up to
-// 1 M triples, 64 / 56 at 2.1 M (one head), 90.2 / 85.5 at 6.3 M, 143 / 143 at 12.6 M, 263 / 265 at 16.8 M, 277 / 283 at 25 M
-// (8 heads: the cells of a pair are worked out 8 times, and 24 bytes are gathered for 2 bytes read).
+// Calls of few heads, or of up to this many (token, head, neighbour) triples, work their cells out directly: two launches
+// less in a step.  us forward + backward, cells from memory / directly: 47 / 41 up to 1 M triples, 90.2 / 85.5 at 6.3 M, 143 / 143 at
+// 12.6 M and 277 / 283 at 25 M (8 heads: the cells of a pair are worked out 8 times, and 24 bytes are gathered for 2 bytes
+// read).  With few heads the cells' own kernel costs more at every size: 148 / 124 (one head, 12.6 M), 285 / 268 (two, 25 M),
+// 174 / 171 (three, 19 M), 238 / 237 (four, 25 M).
+constexpr int kRelDirectHeads = 3;
 constexpr long long kRelDirectTriples = 10ll << 20;
 
 inline GroupTables group_tables(const PlanLayout& L, const void* plan, int N, int H, int K) {

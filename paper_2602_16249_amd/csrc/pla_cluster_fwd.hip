@@ -318,7 +318,9 @@ bool pla_cluster_relpos_supported(const PlaArgs& a) {
          reinterpret_cast<uintptr_t>(a.rel_coords) % 8 == 0;
 }
 
-bool pla_cluster_relpos_direct(const PlaArgs& a) { return (long long)a.B * a.N * a.H * a.K <= kRelDirectTriples; }
+bool pla_cluster_relpos_direct(const PlaArgs& a) {
+  return a.H <= kRelDirectHeads || (long long)a.B * a.N * a.H * a.K <= kRelDirectTriples;
+}
 
 bool pla_cluster_supported(const PlaArgs& a) {
   if (!a.near_clusters || a.dtype != 1 || a.d != kD) return false;
