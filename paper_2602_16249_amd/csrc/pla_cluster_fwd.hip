@@ -199,7 +199,8 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
   // then add up to 1: a query with one neighbour gets its V row unchanged), lse takes the sum of the unrounded ones.
   float l_tot = group_sum(l_run);
   float m2 = -shift;  // reference of the exponentials, in powers of two
-  if (__ballot(!(l_tot > 0x1p-40f && l_tot < 0x1p60f)) != 0ull) {
+  // (the rows past the image's end have no neighbours and a sum of 0: they have no say)
+  if (__ballot((!RAG || r < w.nq) && !(l_tot > 0x1p-40f && l_tot < 0x1p60f)) != 0ull) {
     // scores too far from 0 for some query (rare): the row maxima first, then the sums again, rows from memory
     auto tile_row = [&](int s) { return 16u * (uint32_t)w.ul[w.pl[s]]; };
     auto scores = [&](int s, uint32_t row0) {

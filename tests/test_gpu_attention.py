@@ -387,3 +387,28 @@ def test_rows_of_every_length(N, K):
         results.append([out, lse] + [g[n] for n in sorted(g) if g[n] is not None])
     for other in results[1:]:
         assert all(torch_equal(a, b) for a, b in zip(results[0], other))
+
+
+@pytest.mark.parametrize("short", [1, 5, 15])
+@pytest.mark.parametrize("K,blank", [(24, False), (37, True), (48, True)])
+def test_short_strip_as_a_full_one(short, K, blank):
+    """The rows of an image's short last strip have the bits that they have in a full strip: the rows past its end, which have
+    no neighbours, do not send it down another path (the second sum, for scores far from 0, rounds differently).  The full
+    image's further queries repeat the neighbours of the last real one, so both calls touch the same token tiles."""
+    print(f"case short strip by {short} K={K} blank={blank}", flush=True)
+    N, S, M, H = 512, 32, 4, 3
+    G, Nr = N // S, N - short
+    rng = np.random.default_rng(100 * K + short)
+    near = np.stack([np.arange(M) + min(max(c - 1, 0), G - M) for c in range(G)]).astype(np.int32)[None]
+    nbr = np.empty((1, N, K), np.int32)
+    for i in range(N):
+        cand = (near[0, i // S][:, None] * S + np.arange(S)).reshape(-1)
+        nbr[0, i] = rng.choice(cand[cand < Nr], K, replace=False) if i < Nr else nbr[0, Nr - 1]
+    w = make_features(1, N, H, 32, K, "bf16", rng, blank=blank)
+    q, k, v, bias = (to_dev(w[n], "bf16") for n in ("q", "k", "v", "bias"))
+    kb, vb = (to_dev(w[n], "bf16") if blank else None for n in ("k_blank", "v_blank"))
+    nbr, near = (torch.from_numpy(x).cuda() for x in (nbr, near))
+    full = aff.affmae_pla_fwd(q, k, v, bias, nbr, 0.2, near, S, M, kb, vb)
+    cut = aff.affmae_pla_fwd(*(x[:, :Nr].contiguous() for x in (q, k, v, bias, nbr)), 0.2, near, S, M, kb, vb)
+    for a, b in zip(full, cut):
+        assert torch.equal(a[:, :Nr], b)
