@@ -32,7 +32,7 @@
 namespace affmae {
 namespace {
 
-constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.69314718055994531f;
 // Token tiles held in LDS: as many as leave room for four workgroups per CU beside the rows of K values (K > 60: 33 words a
 // row; with 16 places and three workgroups 40.1 us against 36.3 before the tiles were shared, K = 64, B = 8, N = 4096, H = 8).
 constexpr int kMostPlaces = 16;
@@ -165,7 +165,7 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
   // in that range, and so do their sums.  (Any reference would do; with 0 the error of out against 64 bits was 1 - 2 %
   // larger, because no probability is exactly 1 then.)
   bool has_ref = false;
-  float shift = 0.f;
+  float ref = 0.f, shift = 0.f;  // shift = -ref log2 e, rounded
   auto math = [&](const FwdPair& f) {
     f32x4 st[2];
 #pragma unroll
@@ -178,7 +178,8 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
     for (int i = 0; i < 8; ++i) pr[i] = fmaf(st[i >> 2][i & 3], scale, __uint_as_float((uint32_t)f.tb[i] << 16));
     if (!has_ref) {
       const float mx = group_max(fmaxf(fmaxf(fmaxf(pr[0], pr[1]), fmaxf(pr[2], pr[3])), fmaxf(fmaxf(pr[4], pr[5]), fmaxf(pr[6], pr[7]))));
-      shift = mx == -INFINITY ? 0.f : -mx * kLog2e;
+      ref = mx == -INFINITY ? 0.f : mx;
+      shift = -ref * kLog2e;
       has_ref = true;
     }
 #pragma unroll
@@ -198,7 +199,11 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
   // The probabilities that entered the MFMAs were rounded to bf16.  out divides by the sum of the rounded ones (the weights
   // then add up to 1: a query with one neighbour gets its V row unchanged), lse takes the sum of the unrounded ones.
   float l_tot = group_sum(l_run);
-  float m2 = -shift;  // reference of the exponentials, in powers of two
+  // The exponentials are 2^(s log2 e + shift) = 2^((s - ref) log2 e + rest), rest what the rounding of shift left (exact in
+  // fp32).  So lse = ref + ln 2 (log2 of the sum - rest), the logarithm taken of the sum's mantissa (of the whole sum it is
+  // off by a unit of a value of 6 or 7, as much as lse's own rounding).  From shift instead, lse was up to 10 % further from
+  // 64 bits than with a reference in natural units throughout (5.9e-8 for 5.3e-8; B3 N4001 H3 K37).
+  float rest = fmaf(ref, kLog2e, shift);
   // (the rows past the image's end have no neighbours and a sum of 0: they have no say)
   if (__ballot((!RAG || r < w.nq) && !(l_tot > 0x1p-40f && l_tot < 0x1p60f)) != 0ull) {
     // scores too far from 0 for some query (rare): the row maxima first, then the sums again, rows from memory
@@ -211,7 +216,7 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
       const uint32_t wd = *reinterpret_cast<const uint32_t*>(w.jt + (s >> 1) * 512 + lane * 8 + (s & 1) * 4);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        st[i] = fmaf(st[i], scale, bf16_to_f32(*reinterpret_cast<const uint16_t*>(row + ((wd >> (8 * i)) & 0xffu)))) * kLog2e;
+        st[i] = fmaf(st[i], scale, bf16_to_f32(*reinterpret_cast<const uint16_t*>(row + ((wd >> (8 * i)) & 0xffu))));
       return st;
     };
     float mx = -INFINITY;
@@ -220,7 +225,8 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
       mx = fmaxf(mx, fmaxf(fmaxf(st[0], st[1]), fmaxf(st[2], st[3])));
     }
     mx = group_max(mx);
-    m2 = mx == -INFINITY ? 0.f : mx;
+    ref = mx == -INFINITY ? 0.f : mx;
+    rest = 0.f;
     l_run = 0.f;
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -231,7 +237,7 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
       float pr[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        pr[i] = __builtin_amdgcn_exp2f(st[i] - m2);
+        pr[i] = __builtin_amdgcn_exp2f((st[i] - ref) * kLog2e);
         l_run += pr[i];
       }
       Frag4 pf;
@@ -258,13 +264,14 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
     float part = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) part = fmaf(bf16_to_f32(qf.h[i]), bf16_to_f32(kb.h[i]), part);
-    const float sb = scale * group_sum(part) * kLog2e;
-    const float m_fin = fmaxf(m2, sb);
-    const float alpha = __builtin_amdgcn_exp2f(m2 - m_fin);
-    const float pb = __builtin_amdgcn_exp2f(sb - m_fin);
+    const float sb = scale * group_sum(part);
+    const float m_fin = fmaxf(ref, sb);
+    const float alpha = __builtin_amdgcn_exp2f(fmaf(ref - m_fin, kLog2e, -rest));
+    const float pb = __builtin_amdgcn_exp2f((sb - m_fin) * kLog2e);
     l_tot = l_tot * alpha + pb;
     w_tot = w_tot * alpha + pb;
-    m2 = m_fin;
+    ref = m_fin;
+    rest = 0.f;
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
@@ -287,7 +294,7 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
   if (!RAG || la < w.nq)
     *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(p.out) + w.img_off + w.query_piece(la, lc)) = reinterpret_cast<const u32x4*>(rows)[tile_chunk(la, lc)];
   if (g == 0 && (!RAG || r < w.nq))
-    (p.lse + w.heads0())[(uint32_t)(r * p.t.H)] = (m2 + __builtin_amdgcn_logf(l_tot)) * 0.69314718055994531f;
+    (p.lse + w.heads0())[(uint32_t)(r * p.t.H)] = ref + fmaf((float)__builtin_amdgcn_frexp_expf(l_tot), kLn2, (__builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(l_tot)) - rest) * kLn2);
 }
 
 template <int NT, int PL, bool RAG>

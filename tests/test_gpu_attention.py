@@ -412,3 +412,25 @@ def test_short_strip_as_a_full_one(short, K, blank):
     cut = aff.affmae_pla_fwd(*(x[:, :Nr].contiguous() for x in (q, k, v, bias, nbr)), 0.2, near, S, M, kb, vb)
     for a, b in zip(full, cut):
         assert torch.equal(a[:, :Nr], b)
+
+
+@pytest.mark.parametrize("around", [96.0, -96.0, 3.0])
+@pytest.mark.parametrize("N,K", [(512, 48), (505, 37)])
+def test_lse_to_half_a_unit(N, K, around):
+    """With q = 0 the scores are the bias and exact, so all that lse = log sum exp(bias) can be off by is its own rounding (half
+    a unit in the last place) and the errors of the exponentials and of the logarithm: each term 2^-22 relative at most, the
+    logarithm one unit of a value below 8 (times ln 2)."""
+    print(f"case lse N={N} K={K} around {around}", flush=True)
+    S, M = 32, 4
+    rng = np.random.default_rng(K)
+    nbr, near = oracle.knn(rng.uniform(0, 100, size=(1, N, 2)).astype(np.float32), None, S, M, K)
+    w = make_features(1, N, 2, 32, K, "bf16", rng)
+    w["q"] = np.zeros_like(w["q"])
+    w["bias"] = (around + 0.5 * rng.integers(-4, 5, size=w["bias"].shape)).astype(np.float32)  # (exact in bf16)
+    args = [to_dev(w[n], "bf16") for n in ("q", "k", "v", "bias")]
+    nbr, near = (torch.from_numpy(np.ascontiguousarray(x, dtype=np.int32)).cuda() for x in (nbr, near))
+    _, lse = aff.affmae_pla_fwd(*args, nbr, 0.2, near, S, M)
+    b = w["bias"].astype(np.float64)
+    exact = b.max(-1) + np.log(np.exp(b - b.max(-1, keepdims=True)).sum(-1))
+    err = np.abs(lse.cpu().numpy().astype(np.float64) - exact)
+    assert (err <= 0.5 * np.spacing(np.abs(exact).astype(np.float32)) + 2.0 ** -22 + 2.0 ** -21 * np.log(2.0)).all()
