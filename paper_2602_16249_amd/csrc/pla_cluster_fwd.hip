@@ -159,13 +159,15 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
       f.vt[1].u2[tt] = lds_read_tr(t[tt] + vt_off1);
     }
   };
-  // Exponentials relative to the query's largest score among its first pair of tiles (or 0 where it has no neighbour
-  // there): no running maximum, no rescaling.  Scores that rise or stay far away are caught at the end (a sum outside
-  // [2^-40, 2^60]): in fp32 and in bf16 operands, which have its exponents, probabilities keep their relative precision
-  // in that range, and so do their sums.  (Any reference would do; with 0 the error of out against 64 bits was 1 - 2 %
-  // larger, because no probability is exactly 1 then.)
-  bool has_ref = false;
-  float ref = 0.f, shift = 0.f;  // shift = -ref log2 e, rounded
+  // Exponentials relative to the query's largest score in the first of the strip's first two pairs of tiles that holds a
+  // neighbour of it (or 0 where neither does): no running maximum, no rescaling.  Scores that rise or stay far away are caught
+  // at the end (a sum outside [2^-40, 2^60]): in fp32 and in bf16 operands, which have its exponents, probabilities keep their
+  // relative precision in that range, and so do their sums.  Any reference would do but for the last digit: the largest
+  // probability is exactly 1 then, which a bf16 operand holds without error.  Error of out against 64 bits with the first pair
+  // alone / the first two / all pairs looked at: K9 S64 M4 2.057e-3 / 1.976e-3 / -, K48 S32 M8 2.217e-3 / 2.202e-3 / 2.191e-3;
+  // us, B64 N1024 H8 K48 60.5 / 61.9 / 62.1, B8 N16384 H2 K48 27.9 / 28.2 / 28.6.
+  int looks = 2;
+  float ref = -INFINITY, shift = 0.f;  // shift = -ref log2 e, rounded
   auto math = [&](const FwdPair& f) {
     f32x4 st[2];
 #pragma unroll
@@ -176,11 +178,11 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
     float pr[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) pr[i] = fmaf(st[i >> 2][i & 3], scale, __uint_as_float((uint32_t)f.tb[i] << 16));
-    if (!has_ref) {
+    if (looks > 0) {
       const float mx = group_max(fmaxf(fmaxf(fmaxf(pr[0], pr[1]), fmaxf(pr[2], pr[3])), fmaxf(fmaxf(pr[4], pr[5]), fmaxf(pr[6], pr[7]))));
-      ref = mx == -INFINITY ? 0.f : mx;
-      shift = -ref * kLog2e;
-      has_ref = true;
+      ref = ref == -INFINITY ? mx : ref;
+      shift = ref == -INFINITY ? 0.f : -ref * kLog2e;
+      --looks;
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) pr[i] = __builtin_amdgcn_exp2f(fmaf(pr[i], kLog2e, shift));
@@ -194,6 +196,7 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
   };
   w.arrive();
   w.template walk<FwdPair>(K, fetch, math);
+  ref = ref == -INFINITY ? 0.f : ref;
   if (!w.live) return;  // (no workgroup barrier below)
 
   // The probabilities that entered the MFMAs were rounded to bf16.  out divides by the sum of the rounded ones (the weights

@@ -434,3 +434,26 @@ def test_lse_to_half_a_unit(N, K, around):
     exact = b.max(-1) + np.log(np.exp(b - b.max(-1, keepdims=True)).sum(-1))
     err = np.abs(lse.cpu().numpy().astype(np.float64) - exact)
     assert (err <= 0.5 * np.spacing(np.abs(exact).astype(np.float32)) + 2.0 ** -22 + 2.0 ** -21 * np.log(2.0)).all()
+
+
+def test_largest_probability_is_exact():
+    """Two neighbours of values 1 and -1 and exact scores: out = w1 - w2, and an error d of one of the two probabilities changes
+    it by 2 w1 w2 d.  Relative to the larger score one of them is 1, and only the other is rounded to bf16 (by 2^-8 at most).
+    Half of a strip's queries have no neighbour in its first pair of tiles."""
+    print("case largest probability", flush=True)
+    N, H, rng = 64, 16, np.random.default_rng(9)
+    nbr = np.empty((1, N, 2), np.int32)
+    for i in range(N):
+        tile = 2 * (i % 16 // 8) + i % 2  # queries 8..15 of a strip: tiles 2 and 3
+        nbr[0, i] = 16 * tile + 2 * rng.integers(0, 8) + np.arange(2)
+    w = make_features(1, N, H, 32, 2, "bf16", rng)
+    q, k = (to_dev(w[n], "bf16") for n in ("q", "k"))
+    v = torch.ones_like(q)
+    v[:, 1::2] = -1
+    bias = torch.from_numpy(rng.uniform(0.25, 1.0, size=(1, N, H, 2)).astype(np.float32)).bfloat16().cuda()
+    near = torch.zeros(1, 1, 1, dtype=torch.int32, device="cuda")
+    out, _ = aff.affmae_pla_fwd(torch.zeros_like(q), k, v, bias, torch.from_numpy(nbr).cuda(), 0.2, near, N, 1)
+    p = bias.double().softmax(-1)
+    exact = (p[..., 0] - p[..., 1])[..., None]
+    bound = 2.0 ** -8 * (2 * p.prod(-1)[..., None] + exact.abs()) * (1 + 2.0 ** -7) + 2.0 ** -21  # rounding of p, of out; fp32
+    assert ((out.double() - exact).abs() <= bound).all()
