@@ -228,7 +228,8 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
       mx = fmaxf(mx, fmaxf(fmaxf(st[0], st[1]), fmaxf(st[2], st[3])));
     }
     mx = group_max(mx);
-    ref = mx == -INFINITY ? 0.f : mx;
+    const float from = mx == -INFINITY ? 0.f : mx;
+    ref = mx;  // (-inf where every neighbour is masked: a blank column takes it all then, however low its score)
     rest = 0.f;
     l_run = 0.f;
 #pragma unroll
@@ -240,7 +241,7 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
       float pr[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        pr[i] = __builtin_amdgcn_exp2f((st[i] - ref) * kLog2e);
+        pr[i] = __builtin_amdgcn_exp2f((st[i] - from) * kLog2e);
         l_run += pr[i];
       }
       Frag4 pf;

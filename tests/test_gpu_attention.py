@@ -9,7 +9,7 @@ import torch
 
 import oracle
 import paper_2602_16249_amd as aff
-from helpers import check_attention, to_dev
+from helpers import LSE_TOL, TOL, check_attention, rel_err, run_gpu_attention, run_oracle_attention, to_dev
 from workloads import CONFIGS, make_features, make_workload, random_neighbours
 
 pytestmark = pytest.mark.gpu
@@ -457,3 +457,29 @@ def test_largest_probability_is_exact():
     exact = (p[..., 0] - p[..., 1])[..., None]
     bound = 2.0 ** -8 * (2 * p.prod(-1)[..., None] + exact.abs()) * (1 + 2.0 ** -7) + 2.0 ** -21  # rounding of p, of out; fp32
     assert ((out.double() - exact).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("N,K", [(512, 48), (505, 21)])
+def test_masked_neighbours_and_a_low_blank_score(N, K):
+    """A bias of the storage type's lowest value on all neighbours of some queries and on half of those of others, beside a blank
+    column of score -200: it takes the whole weight of the former, and none of the latter's."""
+    print(f"case masked neighbours N={N} K={K}", flush=True)
+    S, M = 32, 4
+    rng = np.random.default_rng(N)
+    nbr, near = oracle.knn(rng.uniform(0, 100, size=(1, N, 2)).astype(np.float32), None, S, M, K)
+    w = make_features(1, N, 2, 32, K, "bf16", rng, blank=True)
+    w["q"][..., 0] = 4.0
+    w["k_blank"][:] = 0.0
+    w["k_blank"][:, 0] = -50.0
+    w["k"][..., 0] = 0.0
+    lowest = float(torch.finfo(torch.bfloat16).min)
+    w["bias"][:, ::3] = lowest
+    w["bias"][:, 1::3, :, ::2] = lowest
+    out, lse, g = run_gpu_attention(w, nbr, "bf16", 1.0, near, S, M, True, True)
+    rout, rlse, rg = run_oracle_attention(w, nbr, 1.0, True)
+    assert rel_err(lse, rlse) <= LSE_TOL
+    for name, got, ref in [("out", out, rout)] + [(n, g[n], rg[n]) for n in rg if n != "dk_blank"]:
+        assert rel_err(got, ref) <= TOL["bf16"], name
+    # dk_blank is 0 but for roundings: dS = <dout, v_blank> - <dout, out> with out = v_blank, two fp32 sums of 32 products
+    terms = np.abs(w["dout"] * w["v_blank"]).sum(-1) * np.abs(w["q"]).max(-1)
+    assert np.abs(g["dk_blank"].cpu().numpy()).max() <= 64 * 2.0 ** -24 * terms.sum(1).max()
