@@ -180,6 +180,10 @@ __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
   // dS (low half) and p (high half) of a pair in one word, laid out as the bias rows: half the writes of two arrays
   char* words = rows + RB;
   char* word_row = words + r * RH * 4;
+  // (a slot whose token the plan does not hold - a table that breaks the promise - is not written below: its dS is 0)
+#pragma unroll
+  for (int i = 0; i < (2 * RB / 16 + kWave - 1) / kWave; ++i)
+    if (i * kWave + lane < 2 * RB / 16) reinterpret_cast<u32x4*>(words)[i * kWave + lane] = u32x4{0u, 0u, 0u, 0u};
   const int rd_off = tile_chunk(r, g) * 16;
   const int tr_off0 = tile_tr_offset(g, r, 0), tr_off1 = tile_tr_offset(g, r, 1);
   const float scale = p.scale;

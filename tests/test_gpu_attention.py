@@ -483,3 +483,49 @@ def test_masked_neighbours_and_a_low_blank_score(N, K):
     # dk_blank is 0 but for roundings: dS = <dout, v_blank> - <dout, out> with out = v_blank, two fp32 sums of 32 products
     terms = np.abs(w["dout"] * w["v_blank"]).sum(-1) * np.abs(w["q"]).max(-1)
     assert np.abs(g["dk_blank"].cpu().numpy()).max() <= 64 * 2.0 ** -24 * terms.sum(1).max()
+
+
+@pytest.mark.parametrize("N,K", [(1024, 48), (1001, 24), (1024, 62), (1024, 37)])
+def test_slots_that_the_plan_does_not_hold(N, K):
+    """Neighbours outside the near clusters break the promise; the tiled kernels leave them out, and their slots of dbias are 0
+    (and add nothing to a relative-position table), not what LDS held from the launch before."""
+    print(f"case foreign neighbours N={N} K={K}", flush=True)
+    S, M, H = 64, 3, 2
+    G = -(-N // S)
+    rng = np.random.default_rng(K)
+    near = np.stack([np.arange(M) + min(max(c - 1, 0), G - M) for c in range(G)]).astype(np.int32)[None]
+    nbr = np.empty((1, N, K), np.int32)
+    for i in range(N):
+        cand = (near[0, i // S][:, None] * S + np.arange(S)).reshape(-1)
+        nbr[0, i] = rng.choice(cand[cand < N], K, replace=False)
+    foreign = np.zeros((1, N, K), bool)
+    foreign[0, ::2, 1::5] = True
+    far = np.where(np.arange(N) < N // 2, N - 1 - rng.integers(0, S, size=N) % 32, rng.integers(0, S, size=N))
+    broken = np.where(foreign, far[None, :, None], nbr).astype(np.int32)
+    w = make_features(1, N, H, 32, K, "bf16", rng)
+    q, k, v, dout = (to_dev(w[n], "bf16") for n in ("q", "k", "v", "dout"))
+    R, rate = 2, 0.1
+    coords = torch.from_numpy(rng.uniform(0, 100, size=(1, N, 2)).astype(np.float32)).cuda()
+    table = torch.from_numpy(rng.normal(size=(H, 5, 5)).astype(np.float32)).bfloat16().cuda()
+    nbr, broken, near = (torch.from_numpy(x).cuda() for x in (nbr, broken, near))
+    diff = coords[0][broken[0].long()] - coords[0][:, None]
+    cell = ((diff * rate).round().clamp(-R, R).long() + R)
+    cell = cell[..., 1] * 5 + cell[..., 0]
+    bias = table.reshape(H, 25)[:, cell].permute(1, 0, 2)[None].contiguous()
+    foreign = torch.from_numpy(foreign).cuda()[:, :, None].expand(1, N, H, K)
+
+    def run(n):
+        out, lse = aff.affmae_pla_fwd(q, k, v, bias, n, 0.2, near, S, M)
+        return aff.affmae_pla_bwd(q, k, v, bias, n, out, lse, dout, 0.2, near, S, M)["dbias"]
+
+    run(nbr)
+    dbias = run(broken)
+    assert (dbias[foreign] == 0).all() and (dbias[~foreign] != 0).float().mean() > 0.9
+    if K % 8 == 0:
+        out, lse = aff.affmae_pla_fwd_relpos(q, k, v, coords, table, broken, 0.2, rate, near, S, M)
+        got = aff.affmae_pla_bwd_relpos(q, k, v, coords, table, broken, out, lse, dout, 0.2, rate, near, S, M)["drel_table"]
+        sums = torch.zeros(H, 25, dtype=torch.float64, device="cuda")
+        for h in range(H):
+            sums[h].index_add_(0, cell.reshape(-1), dbias[0, :, h].double().reshape(-1))
+        # the same bf16 values of dS, added up in fp64 and rounded to fp32 per workgroup
+        assert (got.double().view(H, 25) - sums).abs().max() <= 2.0 ** -20 * dbias.double().abs().sum()
