@@ -430,12 +430,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   for (int dt = 0; dt < 2; ++dt) dk[dt] = dv[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   // The rows come straight from memory into LDS.  By hand: for the compiler every LDS read might read what such a load
   // still writes, and it would wait for the next chunk before it reads this one.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"  // (m0 is reserved: written only for the next instruction, never held)
   auto dma16 = [](uint32_t dst, const char* base, uint32_t off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(base) : "m0", "memory");
   };
   auto dma4 = [](uint32_t dst, const char* base, uint32_t off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(dst), "v"(off), "s"(base) : "m0", "memory");
   };
+#pragma clang diagnostic pop
   for (int base = 0; base < n; base += kWave) {
     const int nb = min(kWave, n - base);
     const unsigned long long mine = lane < nb ? list[base + lane] : ~0ull;
