@@ -484,13 +484,17 @@ size_t bias_bytes(int B, int N, int H, int K, int dtype) {
 bool relpos_in_kernel(int B, int N, int d, int K, int S, int M, int dtype, int clustered) {
   return clustered && dtype == AFFMAE_BF16 && d == 32 && K % 8 == 0 && tiled_shape_ok(B, N, K, S, M);
 }
+// Workspace for the cells of the pairs, where that form reads them from memory.
+size_t cells_bytes(int B, int N, int H, int K) {
+  return affmae::pla_cluster_relpos_direct(B, N, H, K) ? 0 : align_up(affmae::relpos_cells_bytes(B, N, K));
+}
 }  // namespace
 
 size_t affmae_pla_fwd_relpos_workspace_bytes(int B, int N, int H, int d, int K, int S, int M, int dtype,
                                              int clustered) {
   if (check_pla_shape(B, N, H, d, K, dtype) != AFFMAE_OK) return 0;
   if (relpos_in_kernel(B, N, d, K, S, M, dtype, clustered))
-    return align_up(affmae::relpos_cells_bytes(B, N, K)) + align_up(affmae::pla_plan_bytes(B, N, K, S, M));
+    return cells_bytes(B, N, H, K) + align_up(affmae::pla_plan_bytes(B, N, K, S, M));
   return bias_bytes(B, N, H, K, dtype) + align_up(affmae_pla_fwd_workspace_bytes(B, N, H, d, K, S, M, dtype, clustered));
 }
 
@@ -527,9 +531,10 @@ int affmae_pla_fwd_relpos(const void* q, const void* k, const void* v, const flo
     if (plan && misaligned(plan, kAlign)) return AFFMAE_ERR_WORKSPACE;
     const affmae::RelposArgs r = {coords, nbr_idx, rel_table, R, rate};
     uint16_t* cells = reinterpret_cast<uint16_t*>(ws);
-    if (!affmae::pla_cluster_relpos_direct(a)) a.rel_cells = cells;
-    if (!plan) {  // the workspace holds the cells and a plan (checked above)
-      void* own = ws + align_up(affmae::relpos_cells_bytes(B, N, K));
+    const size_t cb = cells_bytes(B, N, H, K);
+    if (cb) a.rel_cells = cells;
+    if (!plan) {  // the workspace holds the cells, if any, and a plan (checked above)
+      void* own = ws + cb;
       if (affmae::launch_pla_plan(nbr_idx, near_clusters, B, N, K, S, M, own, st) != hipSuccess)
         return AFFMAE_ERR_DEVICE;
       plan = own;
@@ -554,7 +559,7 @@ size_t affmae_pla_bwd_relpos_workspace_bytes(int B, int N, int H, int d, int K, 
     const size_t table = affmae::pla_bwd_cluster_rel_sums(R)
                              ? align_up(affmae::pla_bwd_cluster_rel_workspace_bytes(B, N, H, R))
                              : bias_bytes(B, N, H, K, dtype) + align_up(affmae::relpos_dtable_workspace_bytes(B, N, H, K, R));
-    return table + align_up(affmae::relpos_cells_bytes(B, N, K)) + align_up(affmae::pla_plan_bytes(B, N, K, S, M)) +
+    return table + cells_bytes(B, N, H, K) + align_up(affmae::pla_plan_bytes(B, N, K, S, M)) +
            align_up(affmae::pla_bwd_cluster_workspace_bytes(B, N, H, K, S, M));
   }
   return 2 * bias_bytes(B, N, H, K, dtype) + align_up(affmae::relpos_dtable_workspace_bytes(B, N, H, K, R)) +
@@ -614,8 +619,9 @@ int affmae_pla_bwd_relpos(const void* q, const void* k, const void* v, const flo
       off += bb + tb;
     }
     uint16_t* cells = reinterpret_cast<uint16_t*>(ws + off);
-    if (!affmae::pla_cluster_relpos_direct(a)) a.rel_cells = cells;
-    off += align_up(affmae::relpos_cells_bytes(B, N, K));
+    const size_t cb = cells_bytes(B, N, H, K);
+    if (cb) a.rel_cells = cells;
+    off += cb;
     if (!plan) {
       if (affmae::launch_pla_plan(nbr_idx, near_clusters, B, N, K, S, M, ws + off, st) != hipSuccess)
         return AFFMAE_ERR_DEVICE;

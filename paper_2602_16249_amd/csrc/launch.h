@@ -137,7 +137,7 @@ hipError_t launch_pla_plan(const int32_t* nbr_idx, const int32_t* near, int B, i
                            hipStream_t stream);
 hipError_t launch_pla_fwd_cluster(const PlaArgs& a, const void* plan, hipStream_t stream);
 size_t pla_bwd_cluster_workspace_bytes(int B, int N, int H, int K, int S, int M);
-bool pla_cluster_relpos_direct(const PlaArgs& a);     // ... without cells in memory: few heads, or a small call
+bool pla_cluster_relpos_direct(int B, int N, int H, int K);  // ... without cells in memory: few heads, or a small call
 bool pla_bwd_cluster_rel_sums(int R);  // the table is small enough for the backward kernel to sum its gradient itself
 size_t pla_bwd_cluster_rel_workspace_bytes(int B, int N, int H, int R);
 hipError_t launch_pla_bwd_cluster(const PlaArgs& a, const void* plan, void* workspace, hipStream_t stream);

@@ -330,8 +330,8 @@ bool pla_cluster_relpos_supported(const PlaArgs& a) {
          reinterpret_cast<uintptr_t>(a.rel_coords) % 8 == 0;
 }
 
-bool pla_cluster_relpos_direct(const PlaArgs& a) {
-  return a.H <= kRelDirectHeads || (long long)a.B * a.N * a.H * a.K <= kRelDirectTriples;
+bool pla_cluster_relpos_direct(int B, int N, int H, int K) {
+  return H <= kRelDirectHeads || (long long)B * N * H * K <= kRelDirectTriples;
 }
 
 bool pla_cluster_supported(const PlaArgs& a) {

@@ -255,3 +255,17 @@ def test_knn_static_rejects_on_host():
     assert lib.affmae_knn_static(one, None, B, N, S, M, K, one, None, None) == -4   # beyond the fixed scratch
     assert lib.affmae_knn_static(None, None, 1, 64, 8, 2, 4, one, None, None) == -1
     assert lib.affmae_knn_static(one, None, 1, 65, 8, 2, 10, one, None, None) == -2
+
+
+def test_relpos_workspace_holds_cells_only_where_they_are_written():
+    """The relative-position calls put the pairs' table cells (2 bytes each) into the workspace only in the form that reads them
+    from there: more than three heads and more than 10 << 20 (token, head, neighbour) triples."""
+    lib = aff.load_library()
+    N, K, S, M, R = 16384, 48, 64, 8, 4
+    for B, H, cells in ((8, 2, False), (64, 3, False), (2, 6, False), (8, 8, True)):
+        plan = lib.affmae_pla_plan_bytes(B, N, K, S, M)
+        assert lib.affmae_pla_fwd_relpos_workspace_bytes(B, N, H, 32, K, S, M, 1, 1) == plan + (2 * B * N * K if cells else 0)
+        # backward: a plan, the cells, and parts that grow with the number of heads (each rounded up to 256 bytes)
+        bwd = {h: lib.affmae_pla_bwd_relpos_workspace_bytes(B, N, h, 32, K, S, M, R, 1, 1) for h in (1, 2, H)}
+        rest = bwd[H] - plan - H * (bwd[2] - bwd[1])
+        assert abs(rest - (2 * B * N * K if cells else 0)) <= 256 * 8 * H
