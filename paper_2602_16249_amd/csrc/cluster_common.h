@@ -63,7 +63,7 @@ struct PlanLayout {
   int strips;            // B * strips_per_image (also the number of token tiles)
   int strips_per_image;  // ceil(N / 16)
   int groups_per_image, groups;
-  int max_slots;         // M * S / 16
+  int max_slots;         // at most M * S / 16
   int K;
   int uni_stride;        // uint16 per group
   int pos_stride;        // uint8 per strip
@@ -85,7 +85,10 @@ inline PlanLayout make_plan_layout(int B, int N, int K, int S, int M) {
   L.strips = (int)((long long)B * L.strips_per_image);
   L.groups_per_image = (L.strips_per_image + kGroup - 1) / kGroup;
   L.groups = B * L.groups_per_image;
+  // a strip touches no more token tiles than its near clusters have, than the image has, and than it has neighbours
   L.max_slots = (int)((long long)M * S / 16);
+  if (L.max_slots > L.strips_per_image) L.max_slots = L.strips_per_image;
+  if (L.max_slots > 16 * K) L.max_slots = 16 * K;
   L.K = K;
   const int most = kGroup * L.max_slots < L.strips_per_image ? kGroup * L.max_slots : L.strips_per_image;
   L.uni_stride = (1 + most + 1) / 2 * 2;

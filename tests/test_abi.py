@@ -269,3 +269,13 @@ def test_relpos_workspace_holds_cells_only_where_they_are_written():
         bwd = {h: lib.affmae_pla_bwd_relpos_workspace_bytes(B, N, h, 32, K, S, M, R, 1, 1) for h in (1, 2, H)}
         rest = bwd[H] - plan - H * (bwd[2] - bwd[1])
         assert abs(rest - (2 * B * N * K if cells else 0)) <= 256 * 8 * H
+
+
+@pytest.mark.parametrize("B,N,K,S,M", [(8, 16384, 16, 64, 16), (2, 16384, 1, 64, 16), (3, 1000, 3, 64, 16), (4, 100, 48, 64, 2),
+                                       (64, 10, 8, 64, 1), (1, 1, 1, 1024, 1), (16, 16384, 48, 64, 8)])
+def test_plan_bytes(B, N, K, S, M):
+    """256 bytes per token tile that a strip can touch: of its near clusters, of the image, and no more than it has neighbours;
+    and the smaller tables (2 bytes a tile and group of four strips, 1 + 8 + 8 a tile and strip)."""
+    strips, slots = -(-N // 16), min(M * S // 16, -(-N // 16), 16 * K)
+    size = aff.load_library().affmae_pla_plan_bytes(B, N, K, S, M)
+    assert 256 * slots * B * strips <= size <= B * strips * (256 * (slots + 1) + 8 * (slots + 2) + 17 * slots + 60) + 8 * 256

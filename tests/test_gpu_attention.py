@@ -529,3 +529,21 @@ def test_slots_that_the_plan_does_not_hold(N, K):
             sums[h].index_add_(0, cell.reshape(-1), dbias[0, :, h].double().reshape(-1))
         # the same bf16 values of dS, added up in fp64 and rounded to fp32 per workgroup
         assert (got.double().view(H, 25) - sums).abs().max() <= 2.0 ** -20 * dbias.double().abs().sum()
+
+
+@pytest.mark.parametrize("B,N,K,S,M", [(2, 1000, 1, 64, 16), (2, 1000, 3, 64, 16), (3, 70, 24, 64, 2), (5, 10, 8, 64, 1),
+                                       (2, 130, 33, 48, 3)])
+def test_plans_with_room_for_less_than_the_near_clusters(B, N, K, S, M):
+    """A plan has room for as many token tiles a strip as it has neighbours, or as the image has, where its near clusters hold
+    more: neighbours drawn from all of them, so that the room is used up."""
+    print(f"case plan room B={B} N={N} K={K} S={S} M={M}", flush=True)
+    rng = np.random.default_rng(N + K)
+    G = -(-N // S)
+    near = np.stack([np.stack([rng.choice(G, M, replace=False) for _ in range(G)]) for _ in range(B)]).astype(np.int32)
+    nbr = np.empty((B, N, K), np.int32)
+    for b in range(B):
+        for i in range(N):
+            cand = (near[b, i // S][:, None] * S + np.arange(S)).reshape(-1)
+            nbr[b, i] = rng.choice(cand[cand < N], K, replace=False)
+    w = make_features(B, N, 2, 32, K, "bf16", rng, blank=True)
+    check_attention(w, nbr, "bf16", 0.2, near=near, S=S, M=M, blank=True, use_plan=True)
