@@ -4,7 +4,7 @@
 // kernels read, see PlanLayout).  Forward tables: a workgroup per group of four
 // strips, a wave per strip of 16 queries.  Reverse tables (which strips touch a
 // group of token tiles): one kernel that counts, places, files and sorts in LDS
-// and L2 (large images: count, prefix sum, fill and sort kernels).
+// (large images: count, prefix sum, fill and sort kernels).
 #include "cluster_common.h"
 #include "launch.h"
 #include "timing.h"
@@ -250,24 +250,34 @@ __global__ __launch_bounds__(256) void plan_fill_kernel(PlanParams p, int strips
   }
 }
 
-// Sorts one group's list ascending by strip: rank by counting (lists are short).  One wave.
-__device__ __forceinline__ void sort_list(unsigned long long* list, int n, int lane) {
+// How many of a list's n entries (at least one; in memory or in LDS) belong to a strip below `key`: a list is sorted by
+// putting every entry at that place (its strips are distinct).  One wave, every lane its own key.
+__device__ __forceinline__ int entries_below(const unsigned long long* list, int n, uint32_t key, int lane) {
+  int rank = 0;
+  for (int j0 = 0; j0 < n; j0 += kWave) {
+    const uint32_t other = j0 + lane < n ? (uint32_t)(list[j0 + lane] >> 32) : ~0u;  // (behind the list: below no key)
+    for (int j1 = 0; j1 < min(kWave, n - j0); j1 += 16)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) rank += __builtin_amdgcn_readlane(other, j1 + j) < key ? 1 : 0;
+  }
+  return rank;
+}
+
+// Sorts one group's list ascending by strip.  One wave; lists of more than 64 entries (popular groups) by way of a copy.
+// (One lane's insertion sort of a list of 96 held up the whole plan: 241 us for 27 now, B2 N20480 K16 S64 M8.)
+__device__ __forceinline__ void sort_list(unsigned long long* list, unsigned long long* copy, int n, int lane) {
   if (n <= kWave) {
     const unsigned long long mine = lane < n ? list[lane] : ~0ull;
-    const uint32_t key = (uint32_t)(mine >> 32);
-    int rank = 0;
-    for (int j = 0; j < n; ++j) rank += __builtin_amdgcn_readlane(key, j) < key ? 1 : 0;  // keys are distinct
+    const int rank = entries_below(list, n, (uint32_t)(mine >> 32), lane);
     if (lane < n) list[rank] = mine;  // every lane has read its element before any write lands (one wave)
-  } else if (lane == 0) {
-    for (int i = 1; i < n; ++i) {  // insertion sort; only for unusually popular tiles
-      const unsigned long long v = list[i];
-      int j = i - 1;
-      while (j >= 0 && list[j] > v) {
-        list[j + 1] = list[j];
-        --j;
-      }
-      list[j + 1] = v;
-    }
+    return;
+  }
+  for (int i = lane; i < n; i += kWave) copy[i] = list[i];
+  __threadfence_block();  // (every lane reads what the others have written)
+  for (int i0 = 0; i0 < n; i0 += kWave) {
+    const unsigned long long mine = copy[min(i0 + lane, n - 1)];
+    const int rank = entries_below(copy, n, (uint32_t)(mine >> 32), lane);
+    if (i0 + lane < n) list[rank] = mine;
   }
 }
 
@@ -275,13 +285,15 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(PlanParams p) {
   const int lane = threadIdx.x & (kWave - 1);
   const int grp = blockIdx.x * (blockDim.x / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if (grp >= p.groups) return;
-  sort_list(p.rev_list + p.rev_offset[grp], p.rev_count[grp], lane);
+  // (the touch tables have been filed: their place, an entry per strip larger than the lists', takes the copies)
+  const int at = __builtin_amdgcn_readfirstlane(p.rev_offset[grp]), n = __builtin_amdgcn_readfirstlane(p.rev_count[grp]);
+  sort_list(p.rev_list + at, p.touch + at, n, lane);
 }
 
 // The reverse tables of images of at most kRevThreads strips, in one launch: a workgroup owns `own` consecutive groups
 // of one image.  A thread reads the touch table of one of the image's strips, the workgroup counts every group's strips
 // in LDS, prefix-sums the counts (an image's lists start at a place of their own, so nothing is needed of other images),
-// files the strips of its own groups, and sorts these lists, in LDS where they fit.
+// files the strips of its own groups, and sorts these lists in LDS.
 // Bound by the chain of these steps in each workgroup, which grows with the image's tiles, against counting with atomics
 // in the strip kernel and four more launches (zero, scan, fill, sort: 4 - 6 us each, of the whole batch).  Whole plan, K =
 // 48, one launch and four: one image of 64 / 256 / 512 / 1024 tiles 14 / 15 / 16 / 17 us and 19 / 19 / 20 / 20 us; 1024
@@ -291,7 +303,8 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(PlanParams p) {
 // Images of a few tiles take a workgroup each and give it little to do (1 tile: 15 / 25 us at 1024 / 2048 images against
 // 16 / 18; 4 tiles: 15 / 22 us at 768 / 1536 against 17 / 20): below 16 tiles, up to 768.
 constexpr int kRevThreads = 1024, kRevGroups = kRevThreads / kGroup, kRevGroupsFew = 4, kRevImagesFew = 768;
-constexpr int kRevSorted = 1024;  // entries of a workgroup's lists that are sorted in LDS
+constexpr int kRevSorted = 1024;  // entries of a workgroup's lists that are in LDS at a time
+static_assert(kRevSorted >= kRevThreads, "room for a group's list of all the image's strips");
 constexpr int kRevInline = 7;     // entries of a strip that its thread holds (most strips have fewer)
 __global__ __launch_bounds__(kRevThreads) void plan_reverse_kernel(PlanParams p, int own) {
   __shared__ int32_t count[kRevGroups];   // strips per group
@@ -343,31 +356,29 @@ __global__ __launch_bounds__(kRevThreads) void plan_reverse_kernel(PlanParams p,
     p.rev_offset[(size_t)b * gpi + tid] = (int32_t)(list0 + before);
   }
   __syncthreads();
-  const int base = offset[first], total = offset[last - 1] + count[last - 1] - base;
-  const bool in_lds = total <= kRevSorted;
   unsigned long long* list = p.rev_list + list0;
-  __syncthreads();  // (offset becomes the cursors)
-  each([&](int grp, uint32_t slots) {
-    if (grp >= first && grp < last) {
-      const int at = atomicAdd(&offset[grp], 1);
-      const unsigned long long v = ((unsigned long long)(uint32_t)tid << 32) | slots;
-      if (in_lds) sorted[at - base] = v; else list[at] = v;
+  // as many of the own groups at a time as have room for their lists in LDS (one has: it lists a strip once)
+  for (int g0 = first, g1; g0 < last; g0 = g1) {
+    const int base = offset[g0];
+    g1 = last;
+    if (offset[last - 1] + count[last - 1] - base > kRevSorted) {
+      int total = count[g0];
+      for (g1 = g0 + 1; g1 < last && total + count[g1] <= kRevSorted; ++g1) total += count[g1];
     }
-  });
-  __threadfence_block();
-  __syncthreads();
-  for (int grp = first + wave; grp < last; grp += kRevThreads / kWave) {
-    const int m = count[grp], at = offset[grp] - m;
-    if (!in_lds) {
-      sort_list(list + at, m, lane);
-      continue;
+    __syncthreads();  // (offset becomes the cursors)
+    each([&](int grp, uint32_t slots) {
+      if (grp >= g0 && grp < g1) sorted[atomicAdd(&offset[grp], 1) - base] = ((unsigned long long)(uint32_t)tid << 32) | slots;
+    });
+    __syncthreads();
+    for (int grp = g0 + wave; grp < g1; grp += kRevThreads / kWave) {
+      const int m = __builtin_amdgcn_readfirstlane(count[grp]), at = __builtin_amdgcn_readfirstlane(offset[grp]) - m;
+      for (int i0 = 0; i0 < m; i0 += kWave) {
+        const unsigned long long v = sorted[at - base + min(i0 + lane, m - 1)];
+        const int rank = entries_below(sorted + (at - base), m, (uint32_t)(v >> 32), lane);
+        if (i0 + lane < m) list[at + rank] = v;
+      }
     }
-    for (int i0 = 0; i0 < m; i0 += kWave) {  // rank by counting, lists of any length
-      const unsigned long long v = i0 + lane < m ? sorted[at - base + i0 + lane] : 0ull;
-      int rank = 0;
-      for (int j = 0; j < m; ++j) rank += sorted[at - base + j] < v ? 1 : 0;  // strips are distinct
-      if (i0 + lane < m) list[at + rank] = v;
-    }
+    __syncthreads();
   }
 }
 

@@ -240,12 +240,13 @@ def test_short_last_cluster_end_to_end(N, tiled):
     (700, 32, 16, 24, True, 1),      # the same with a short last strip
     (32768, 64, 8, 16, False, 1),    # large images: counted, scanned, filled and sorted in launches of their own
     (32785, 64, 8, 16, False, 1),
-    (8192, 64, 8, 16, False, 1),     # the most token tiles of the one-launch reverse tables in a small batch, and one more
-    (8200, 64, 8, 16, False, 1),
-    (16384, 64, 8, 8, False, 8),     # as many images as twice that takes, and one too few
-    (16384, 64, 8, 8, False, 7),
-    (32768, 64, 8, 4, False, 16),    # the most of all, and one tile more
+    (16384, 64, 8, 16, False, 1),    # the most token tiles of the one-launch reverse tables, and one more
+    (16385, 64, 8, 16, False, 1),
+    (16384, 64, 8, 8, False, 8),     # more groups than workgroups: eight a workgroup, a last one with fewer
+    (16304, 64, 8, 8, False, 7),
+    (32768, 64, 8, 4, False, 16),
     (32769, 64, 8, 4, False, 16),
+    (48, 16, 2, 8, False, 768),      # the most images of a few tiles in one launch
     (64, 16, 2, 8, False, 600),      # more images than workgroups wanted: one for each
     (48, 16, 2, 8, False, 769),      # more images of a few tiles than one launch serves well
 ])
@@ -259,6 +260,33 @@ def test_reverse_tables_of_the_plan(N, S, M, K, same, B):
         w["coords"] = np.full_like(w["coords"], 2.5)
     nbr, near = oracle.knn(w["coords"], None, S, M, K)
     check_attention(w, nbr, cfg.dtype, 1.0 / np.sqrt(32), near=near, S=S, M=M, use_plan=True)
+
+
+@pytest.mark.parametrize("N,B,strips", [
+    (4096, 1, 60), (4096, 1, 100),     # one group that 65 or more strips touch beside the usual lists
+    (16384, 1, 1000),                  # more entries than a workgroup of the one launch has room for at a time: in two steps
+    (16384, 8, 1000), (8192, 3, 500),  # the same with several groups a workgroup
+    (16400, 1, 60), (16400, 2, 300), (20480, 1, 1270),  # large images: lists of a group sorted by one wave each
+])
+def test_popular_groups_of_tiles(N, B, strips):
+    """`strips` strips in a row have, beside their own surroundings, neighbours in the first cluster: lists of the reverse tables
+    on both sides of 64 and of 1024 entries."""
+    print(f"case popular groups B={B} N={N} strips={strips}", flush=True)
+    S, M, K = 64, 5, 8
+    rng = np.random.default_rng(strips)
+    G = -(-N // S)
+    near = np.stack([np.arange(M) + min(max(c - 1, 0), G - M) for c in range(G)]).astype(np.int32)
+    first = (G - strips * 16 // S) // 2 + 3 if strips < G * S // 16 - 40 else 4
+    far = (np.arange(G) >= max(first, M)) & (np.arange(G) < first + -(-strips * 16 // S))
+    near[far, M - 1] = 0
+    cand = (near[:, :, None] * S + np.arange(S)).reshape(G, M * S)
+    nbr = np.empty((N, K), np.int32)
+    for i in range(N):
+        c = cand[i // S]
+        nbr[i] = rng.choice(c[c < N], K, replace=False)
+    w = make_features(B, N, 1, 32, K, "bf16", rng)
+    many = lambda t: np.repeat(t[None], B, axis=0)
+    check_attention(w, many(nbr), "bf16", 0.2, near=many(near), S=S, M=M, use_plan=True)
 
 
 @pytest.mark.parametrize("N", [16, 512, 528, 4080, 4112, 8192 + 16])
