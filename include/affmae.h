@@ -279,6 +279,9 @@ int affmae_knn_static(const float* coords, const int32_t* cluster_id, int B, int
  *   plan                    out caller-owned device buffer of affmae_pla_plan_bytes()
  *                               bytes, 256-byte aligned; opaque, and readable only by
  *                               the library build that filled it (affmae_build_id).
+ *                               Mostly 256 bytes for each of the token tiles of 16 that
+ *                               a strip of 16 queries can touch, min(M*S/16, ceil(N/16),
+ *                               16 K): B N min(M S, N) bytes as a rule.
  * affmae_pla_plan_bytes returns 0, and affmae_pla_plan AFFMAE_ERR_UNSUPPORTED,
  * when the shapes are outside what the tiled kernels take (they need S % 16 == 0
  * - S need not divide N, nor 16: the last cluster, strip and token tile of an
@@ -384,13 +387,14 @@ int affmae_pla_bwd(const void* q, const void* k, const void* v, const void* bias
  * `bias` replaced by (coords, rel_table, R, rate) and `dbias` by drel_table.
  *
  * With the cluster promise, bf16, d = 32 and K a multiple of 8 the tiled kernels
- * look the bias up themselves: a small kernel writes the table cell of every
- * (token, neighbour) pair into the workspace, 2 bytes for all heads together, and
- * they read the head's table from LDS: no bias or dbias tensor exists, and for
- * tables of at most 128 cells per head (R <= 5) the gradient of the table is summed
- * inside the backward kernel as well.  In every other case the bias is written into the
- * workspace by a kernel of its own and the table's gradient is reduced from
- * dbias by another; the results are the same.
+ * look the bias up themselves, in the head's table in LDS: no bias tensor exists.
+ * The table cell of a (token, neighbour) pair is worked out from the coordinates
+ * where it is needed if H <= 3 or B*N*H*K <= 10 << 20; in larger calls a small kernel
+ * first writes every pair's cell into the workspace, 2 bytes for all heads together.
+ * For tables of at most 128 cells per head (R <= 5) the gradient of the table is summed
+ * inside the backward kernel as well, without a dbias tensor.  In every other case the
+ * bias is written into the workspace by a kernel of its own and the table's gradient is
+ * reduced from dbias by another; the results are the same.
  *
  *   coords      in  [B,N,2] fp32, 8-byte aligned
  *   rel_table   in  [H, 2R+1, 2R+1] in the storage type (row = y bin)

@@ -57,8 +57,8 @@ static_assert(kGroup * kMaxSlots <= 256, "places in a group's union are bytes");
 //          and the strip's slots of the group's four tiles (one byte each in the low half, 0xff: not touched).
 //  rev     the same seen from the tiles: per group of token tiles the strips that touch it, ascending (the sums
 //          formed along the list then do not depend on scheduling): strip (high half), slots of the four tiles.
-// Bytes written per strip: 256 per slot against 2 K bytes for a list of the pairs' cells, twice; in exchange no
-// kernel sorts pairs or scatters values over a tile.
+// Bytes written per strip: 256 per slot (8 to 12 of them as a rule) against 32 K for a list of the pairs' cells, twice; in
+// exchange no kernel sorts pairs or scatters values over a tile.  Room is kept for every slot that there may be.
 struct PlanLayout {
   int strips;            // B * strips_per_image (also the number of token tiles)
   int strips_per_image;  // ceil(N / 16)

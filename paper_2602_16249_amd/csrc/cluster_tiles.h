@@ -51,10 +51,11 @@ struct RelSource {
   int R;
 };
 // Calls of few heads, or of up to this many (token, head, neighbour) triples, work their cells out directly: two launches
-// less in a step.  us forward + backward, cells from memory / directly: 47 / 41 up to 1 M triples, 90.2 / 85.5 at 6.3 M, 143 / 143 at
-// 12.6 M and 277 / 283 at 25 M (8 heads: the cells of a pair are worked out 8 times, and 24 bytes are gathered for 2 bytes
-// read).  With few heads the cells' own kernel costs more at every size: 148 / 124 (one head, 12.6 M), 285 / 268 (two, 25 M),
-// 174 / 171 (three, 19 M), 238 / 237 (four, 25 M).
+// less in a step.  us forward + backward, cells from memory / directly: 47 / 41 up to 1 M triples, 90.2 / 85.5 at 6.3 M; with
+// eight heads (the cells of a pair are worked out 8 times, and 24 bytes are gathered for 2 bytes read) 113 / 116 at 12.6 M, 220 /
+// 232 at 25 M.  With few heads the cells' own kernel costs more at every size, R = 3 (R = 7 alike): one head 3 / 13 / 38 M
+// 56 / 147 / 444 and 47 / 126 / 393, two heads 6 / 13 / 25 / 50 M 77 / 126 / 283 / 547 and 71 / 119 / 265 / 533; three heads
+// 9 / 19 / 38 M 96 / 174 / 386 and 93 / 171 / 385, four heads 13 / 25 / 50 M 116 / 235 / 494 and 116 / 237 / 504.
 constexpr int kRelDirectHeads = 3;
 constexpr long long kRelDirectTriples = 10ll << 20;
 

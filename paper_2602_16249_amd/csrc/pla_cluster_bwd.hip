@@ -22,8 +22,8 @@
 //    dK^T = Q^T dS and dV^T = dO^T P in registers, so dk and dv are written once, without
 //    atomics and in a fixed summation order.
 //
-// Bound by instruction issue, three (query) and four (key) workgroups per CU.  us, rows fetched per (strip, head) and
-// (tile, head) / shared: query 132 / 115, key 91 / 82 (B64 N1024 H8 K48); 263 / 229, 185 / 169 (B8 N65536 blobs H2 K48).
+// Bound by instruction issue, three (query) and four (key; above K = 60 three) workgroups per CU.  us, rows fetched per (strip, head) and
+// (tile, head) / shared: query 127 / 114, key 88 / 82 (B64 N1024 H8 K48); 265 / 235, 187 / 173 (B16 N16384 blobs H4 K48).
 #include "cluster_tiles.h"
 #include "launch.h"
 #include "timing.h"

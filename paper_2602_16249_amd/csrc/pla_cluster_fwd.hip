@@ -20,9 +20,11 @@
 //
 // Bound by instruction issue and the two memory round trips at a wave's start; four
 // workgroups per CU (39 KB of LDS at K = 48).  us, tiles fetched per (strip, head) / shared:
-// B64 N1024 H8 K48 89 / 76, B8 N65536 blobs H2 K48 172 / 149, B8 N16384 H2 K48 34 / 34.  Where
-// four strips touch more than 16 tiles together (two stages) and share few of them, S = 16 and
-// M of 8 and more, it is 3 - 15 % slower than before; 22 tiles and three workgroups were not better.
+// B64 N1024 H8 K48 87 / 77, B16 N16384 blobs H4 K48 174 / 154, B8 N16384 H2 K48 40 / 39.  Where
+// four strips touch more than 16 tiles together (two stages) and share few of them, it is slower
+// than before: S = 16 and M of 8 and more by 4 - 16 % (B6 N4096 H8 K32 19.5 / 20.9), masked grids
+// by up to 7 % (B3 N4001 H3 K37 11.8 / 12.5).  Not better: 22 tiles and three workgroups; the stages
+// walked with the next pair fetched ahead, j words from memory (20.9 -> 23.5, blobs 145 -> 193).
 #include "cluster_tiles.h"
 #include "launch.h"
 #include "timing.h"

@@ -242,9 +242,12 @@ def test_short_last_cluster_end_to_end(N, tiled):
     (32785, 64, 8, 16, False, 1),
     (16384, 64, 8, 16, False, 1),    # the most token tiles of the one-launch reverse tables, and one more
     (16385, 64, 8, 16, False, 1),
-    (16384, 64, 8, 8, False, 8),     # more groups than workgroups: eight a workgroup, a last one with fewer
+    (8192, 64, 8, 16, False, 1),     # half of that
+    (8200, 64, 8, 16, False, 1),
+    (16384, 64, 8, 8, False, 8),     # more groups than workgroups: eight a workgroup, or seven and a last one with fewer
+    (16384, 64, 8, 8, False, 7),
     (16304, 64, 8, 8, False, 7),
-    (32768, 64, 8, 4, False, 16),
+    (32768, 64, 8, 4, False, 16),    # large batches of large images, whole tiles and not
     (32769, 64, 8, 4, False, 16),
     (48, 16, 2, 8, False, 768),      # the most images of a few tiles in one launch
     (64, 16, 2, 8, False, 600),      # more images than workgroups wanted: one for each
