@@ -194,69 +194,91 @@ struct TileWalk {
     __syncthreads();
   }
   // The strip's slots by pairs.  fetch(frag, w0, w1, at0, at1) reads from LDS what a pair needs (j words w, tiles at byte
-  // offsets at), math(frag) uses it.  In the usual case (the union fits the places) the next pair is fetched before the
-  // present one's math: the compiler does not move loads over the branch between pairs by itself.  Unions of up to
-  // PL + kSpare tiles take two stages (the first frees places for the tiles that wait in registers), larger ones
-  // go on in eights.
+  // offsets at), math(frag, early) uses it (early: among the first pairs, see the forward kernel).  The next pair is fetched
+  // before the present one's math: the compiler does not move loads over the branch between pairs by itself.
+  // Unions of more than PL tiles go in stages: the first, of a pair or two as a rule, frees places for the tiles that wait in
+  // registers; the rest is walked like a union that fits, the j words of the pairs that are done shifted out of the way.
+  // (With every pair of both stages fetched only when the one before was done, the forward kernel was slower than with tiles
+  // fetched per strip wherever unions are large and shared little: masked grids by up to 7 %, S = 16 by up to 16 %.  us, B6
+  // N4096 H8 S16: K32 M8 20.9 -> 20.3, K64 M10 27.2 -> 26.0; B8 N16384 H4 K64 M10 blobs 57.8 -> 55.2; B64 N1024 H8 K48 S32 M8
+  // 61.7 -> 59.2; B16 N16384 H4 K48 S64 M8 blobs 147 -> 142; what fits is as fast as before.)  Unions of more than PL + kSpare
+  // tiles go on in eights.
   template <class Frag, class Fetch, class Math>
   __device__ __forceinline__ void walk(int K, Fetch fetch, Math math) {
-    if (U <= PL) {
-      const int at = min(my_pos, PL - 1) * 2048;
-      Frag f[2];
-      fetch(f[0], jw[0].x, jw[0].y, __builtin_amdgcn_readlane(at, 0), __builtin_amdgcn_readlane(at, 1));
-#pragma unroll
-      for (int i = 0; i < (PL + 1) / 2; ++i) {
-        if (2 * i >= cnt) break;
-        if (i + 1 < (PL + 1) / 2)
-          fetch(f[(i + 1) & 1], jw[i + 1].x, jw[i + 1].y, __builtin_amdgcn_readlane(at, 2 * i + 2), __builtin_amdgcn_readlane(at, 2 * i + 3));
-        __builtin_amdgcn_sched_barrier(0);
-        math(f[i & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      return;
-    }
     const uint32_t none = 2u * (uint32_t)K * 0x01010101u;
-    int lo = 0, hi = min(kSpare, U - PL);
-    for (int stage = 0;; ++stage) {
-      const int s0 = (int)__popcll(__ballot(lane < cnt && my_pos < lo)), s1 = (int)__popcll(__ballot(lane < cnt && my_pos < hi));
-      const int at = (stage > 1 ? my_pos - lo : my_pos < PL ? my_pos : my_pos - PL) * 2048;
-      auto bring = [&](Frag& f, int i, uint2 w) {
-        fetch(f, 2 * i >= s0 ? w.x : none, 2 * i + 1 < s1 ? w.y : none, __builtin_amdgcn_readlane(at, max(2 * i, s0)),
+    int at = min(my_pos, PL - 1) * 2048;
+    int a = 0, end = cnt;  // first pair and last slot of the main part
+    if (U > PL) {
+      const int done = (int)__popcll(__ballot(lane < cnt && my_pos < min(kSpare, U - PL)));  // slots of the places to be freed
+#pragma unroll
+      for (int i = 0; i < kSpare / 2; ++i) {
+        if (2 * i >= done) break;
+        Frag f;
+        fetch(f, jw[i].x, 2 * i + 1 < done ? jw[i].y : none, __builtin_amdgcn_readlane(at, 2 * i),
+              __builtin_amdgcn_readlane(at, min(2 * i + 1, done - 1)));
+        __builtin_amdgcn_sched_barrier(0);
+        math(f, true);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __syncthreads();  // every wave is through with these places
+#pragma unroll
+      for (int i = 0; i < kSpare / kGroup; ++i)
+        if (PL + i * kGroup + wave < U) {
+          char* dst = tiles + (i * kGroup + wave) * 2048;
+          reinterpret_cast<u32x4*>(dst)[lane] = sk[i];
+          reinterpret_cast<u32x4*>(dst + 1024)[lane] = sv[i];
+        }
+      __syncthreads();
+      a = done >> 1;
+#pragma unroll
+      for (int step = kSpare / 2; step > 0; step >>= 1)
+        if (a & step) {
+#pragma unroll
+          for (int i = 0; i < kPairs; ++i) jw[i] = i + step < kPairs ? jw[i + step] : make_uint2(0u, 0u);
+        }
+      if (done & 1) jw[0].x = none;  // (its tile's place holds another tile now, whose rows meet probability 0)
+      end = (int)__popcll(__ballot(lane < cnt && my_pos < PL + kSpare));
+      if (end < cnt && (end & 1)) {
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i)
+          if (2 * (a + i) + 1 == end) jw[i].y = none;
+      }
+      at = min(my_pos < PL ? my_pos : my_pos - PL, PL - 1) * 2048;
+    }
+    Frag f[2];
+    fetch(f[0], jw[0].x, jw[0].y, __builtin_amdgcn_readlane(at, 2 * a), __builtin_amdgcn_readlane(at, 2 * a + 1));
+#pragma unroll
+    for (int i = 0; i < kPairs; ++i) {
+      if (2 * (a + i) >= end) break;
+      if (i + 1 < kPairs)
+        fetch(f[(i + 1) & 1], jw[i + 1].x, jw[i + 1].y, __builtin_amdgcn_readlane(at, 2 * (a + i) + 2), __builtin_amdgcn_readlane(at, 2 * (a + i) + 3));
+      __builtin_amdgcn_sched_barrier(0);
+      math(f[i & 1], i < 2);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (U <= PL + kSpare) return;
+    const int last_pair = (max(cnt, 1) - 1) >> 1;
+    auto words = [&](int i) { return *reinterpret_cast<const uint2*>(jt + (uint32_t)(min(i, last_pair) * 512 + lane * 8)); };
+    for (int lo = PL + kSpare; lo < U; lo += kSpare) {
+      const int hi = min(U, lo + kSpare);
+      const int s0 = end, s1 = (int)__popcll(__ballot(lane < cnt && my_pos < hi));
+      end = s1;
+      const int next = (int)ul[min(lo + (lane & (kSpare - 1)), U - 1)];
+      int i = s0 >> 1;
+      uint2 w = words(i);
+      __syncthreads();  // every wave is through with the tiles below lo
+#pragma unroll
+      for (int t = 0; t < kSpare / kGroup; ++t)
+        if (lo + t * kGroup + wave < U) issue(__builtin_amdgcn_readlane(next, t * kGroup + wave), t * kGroup + wave);
+      arrive();
+      at = min(max(my_pos - lo, 0), PL - 1) * 2048;
+      for (; max(2 * i, s0) < s1; ++i) {
+        const uint2 after = words(i + 1);
+        fetch(f[0], 2 * i >= s0 ? w.x : none, 2 * i + 1 < s1 ? w.y : none, __builtin_amdgcn_readlane(at, max(2 * i, s0)),
               __builtin_amdgcn_readlane(at, min(2 * i + 1, s1 - 1)));
-      };
-      Frag f;
-#pragma unroll
-      for (int i = 0; i < kPairs; ++i) {
-        if (max(2 * i, s0) >= min(2 * i + 2, s1)) continue;
-        bring(f, i, jw[i]);
         __builtin_amdgcn_sched_barrier(0);
-        math(f);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      for (int i = max(kPairs, s0 >> 1); max(2 * i, s0) < s1; ++i) {
-        bring(f, i, *reinterpret_cast<const uint2*>(jt + (uint32_t)(i * 512 + lane * 8)));
-        math(f);
-      }
-      if (hi >= U) break;
-      __syncthreads();  // every wave is through with the tiles below hi
-      lo = hi;
-      if (stage == 0) {
-#pragma unroll
-        for (int i = 0; i < kSpare / kGroup; ++i)
-          if (PL + i * kGroup + wave < U) {
-            char* dst = tiles + (i * kGroup + wave) * 2048;
-            reinterpret_cast<u32x4*>(dst)[lane] = sk[i];
-            reinterpret_cast<u32x4*>(dst + 1024)[lane] = sv[i];
-          }
-        __syncthreads();
-        hi = min(U, PL + kSpare);
-      } else {
-        hi = min(U, lo + kSpare);
-        const int next = (int)ul[min(lo + (lane & (kSpare - 1)), U - 1)];
-#pragma unroll
-        for (int i = 0; i < kSpare / kGroup; ++i)
-          if (lo + i * kGroup + wave < U) issue(__builtin_amdgcn_readlane(next, i * kGroup + wave), i * kGroup + wave);
-        arrive();
+        math(f[0], false);
+        w = after;
       }
     }
   }

@@ -254,7 +254,7 @@ __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
     }
   };
   const f32x4 nd = {-Dq, -Dq, -Dq, -Dq};
-  auto math = [&](const BwdPair& f) {
+  auto math = [&](const BwdPair& f, bool) {
     f32x4 st[2], dp[2];
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {

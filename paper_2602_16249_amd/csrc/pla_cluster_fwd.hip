@@ -20,11 +20,10 @@
 //
 // Bound by instruction issue and the two memory round trips at a wave's start; four
 // workgroups per CU (39 KB of LDS at K = 48).  us, tiles fetched per (strip, head) / shared:
-// B64 N1024 H8 K48 87 / 77, B16 N16384 blobs H4 K48 174 / 154, B8 N16384 H2 K48 40 / 39.  Where
-// four strips touch more than 16 tiles together (two stages) and share few of them, it is slower
-// than before: S = 16 and M of 8 and more by 4 - 16 % (B6 N4096 H8 K32 19.5 / 20.9), masked grids
-// by up to 7 % (B3 N4001 H3 K37 11.8 / 12.5).  Not better: 22 tiles and three workgroups; the stages
-// walked with the next pair fetched ahead, j words from memory (20.9 -> 23.5, blobs 145 -> 193).
+// B64 N1024 H8 K48 88 / 75, B16 N16384 blobs H4 K48 175 / 151, B8 N16384 H2 K48 40 / 39.  Where
+// four strips of small clusters share few tiles it is slower than before: S = 16, M of 8 and more by
+// 2 - 12 % (B6 N4096 H8, K32 M8 19.5 / 20.3, K64 M10 23.4 / 26.0; with the second stage's pairs
+// fetched only when the one before was done 20.9 and 27.2).  22 tiles and three workgroups were not better.
 #include "cluster_tiles.h"
 #include "launch.h"
 #include "timing.h"
@@ -168,9 +167,8 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
   // probability is exactly 1 then, which a bf16 operand holds without error.  Error of out against 64 bits with the first pair
   // alone / the first two / all pairs looked at: K9 S64 M4 2.057e-3 / 1.976e-3 / -, K48 S32 M8 2.217e-3 / 2.202e-3 / 2.191e-3;
   // us, B64 N1024 H8 K48 60.5 / 61.9 / 62.1, B8 N16384 H2 K48 27.9 / 28.2 / 28.6.
-  int looks = 2;
   float ref = -INFINITY, shift = 0.f;  // shift = -ref log2 e, rounded
-  auto math = [&](const FwdPair& f) {
+  auto math = [&](const FwdPair& f, bool early) {
     f32x4 st[2];
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
@@ -180,11 +178,10 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
     float pr[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) pr[i] = fmaf(st[i >> 2][i & 3], scale, __uint_as_float((uint32_t)f.tb[i] << 16));
-    if (looks > 0) {
+    if (early) {
       const float mx = group_max(fmaxf(fmaxf(fmaxf(pr[0], pr[1]), fmaxf(pr[2], pr[3])), fmaxf(fmaxf(pr[4], pr[5]), fmaxf(pr[6], pr[7]))));
       ref = ref == -INFINITY ? mx : ref;
       shift = ref == -INFINITY ? 0.f : -ref * kLog2e;
-      --looks;
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) pr[i] = __builtin_amdgcn_exp2f(fmaf(pr[i], kLog2e, shift));

@@ -378,6 +378,22 @@ def test_unions_of_many_tiles(N, S, M, K, H, spread):
     check_attention(w, nbr, "bf16", 1.0 / np.sqrt(32), near=near, S=S, M=M, blank=True, use_plan=True)
 
 
+@pytest.mark.parametrize("K", [16, 15, 62])
+@pytest.mark.parametrize("few", [1, 2, 3, 5, 8])
+def test_strips_of_few_tiles_in_large_unions(few, K):
+    """One strip of every group has neighbours in the image's first tiles only, the other three all over it: the first stage of
+    the walk, which frees places for tiles still to come, is all that there is for the one."""
+    print(f"case few tiles {few} K={K}", flush=True)
+    N, S, H = 400, 16, 2
+    few = max(few, -(-K // 16))
+    G = N // S
+    rng = np.random.default_rng(10 * K + few)
+    near = np.broadcast_to(np.arange(G, dtype=np.int32), (1, G, G)).copy()
+    nbr = np.stack([rng.choice(16 * few if i // 16 % 4 == 1 else N, K, replace=False) for i in range(N)]).astype(np.int32)[None]
+    w = make_features(1, N, H, 32, K, "bf16", rng, blank=True)
+    check_attention(w, nbr, "bf16", 0.2, near=near, S=S, M=G, blank=True, use_plan=True)
+
+
 # (no blank column where it would leave the neighbours probabilities below fp32's range: the gradients would be compared with
 # values that are not representable)
 @pytest.mark.parametrize("low,high,blank", [(-3.0e4, -3.0e4, False), (-500.0, -500.0, False), (3.0e4, 3.0e4, False), (3.0e4, 3.0e4, True),
