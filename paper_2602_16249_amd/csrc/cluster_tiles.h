@@ -11,6 +11,8 @@
 #include "cluster_common.h"
 #include "launch.h"
 
+#include <type_traits>
+
 namespace affmae {
 
 constexpr int kSpare = 8;   // tiles beyond the places in LDS whose rows wait in registers, two per wave
@@ -193,6 +195,21 @@ struct TileWalk {
     __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): rows on their way to LDS count as vector loads
     __syncthreads();
   }
+  // Up to P pairs, from the a-th on, of the slots below `end`.  (Compiled apart for unions that fit: one loop for both took
+  // them 1 - 2 % longer.)
+  template <int P, class Frag, class Fetch, class Math>
+  __device__ __forceinline__ void pairs(std::integral_constant<int, P>, Frag (&f)[2], int a, int end, int at, Fetch& fetch, Math& math) {
+    fetch(f[0], jw[0].x, jw[0].y, __builtin_amdgcn_readlane(at, 2 * a), __builtin_amdgcn_readlane(at, 2 * a + 1));
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      if (2 * (a + i) >= end) break;
+      if (i + 1 < P)
+        fetch(f[(i + 1) & 1], jw[i + 1].x, jw[i + 1].y, __builtin_amdgcn_readlane(at, 2 * (a + i) + 2), __builtin_amdgcn_readlane(at, 2 * (a + i) + 3));
+      __builtin_amdgcn_sched_barrier(0);
+      math(f[i & 1], i < 2);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
   // The strip's slots by pairs.  fetch(frag, w0, w1, at0, at1) reads from LDS what a pair needs (j words w, tiles at byte
   // offsets at), math(frag, early) uses it (early: among the first pairs, see the forward kernel).  The next pair is fetched
   // before the present one's math: the compiler does not move loads over the branch between pairs by itself.
@@ -207,8 +224,13 @@ struct TileWalk {
   __device__ __forceinline__ void walk(int K, Fetch fetch, Math math) {
     const uint32_t none = 2u * (uint32_t)K * 0x01010101u;
     int at = min(my_pos, PL - 1) * 2048;
-    int a = 0, end = cnt;  // first pair and last slot of the main part
-    if (U > PL) {
+    if (U <= PL) {
+      Frag f[2];
+      pairs(std::integral_constant<int, (PL + 1) / 2>{}, f, 0, cnt, at, fetch, math);
+      return;
+    }
+    int a, end;  // first pair and last slot of the main part
+    {
       const int done = (int)__popcll(__ballot(lane < cnt && my_pos < min(kSpare, U - PL)));  // slots of the places to be freed
 #pragma unroll
       for (int i = 0; i < kSpare / 2; ++i) {
@@ -246,16 +268,7 @@ struct TileWalk {
       at = min(my_pos < PL ? my_pos : my_pos - PL, PL - 1) * 2048;
     }
     Frag f[2];
-    fetch(f[0], jw[0].x, jw[0].y, __builtin_amdgcn_readlane(at, 2 * a), __builtin_amdgcn_readlane(at, 2 * a + 1));
-#pragma unroll
-    for (int i = 0; i < kPairs; ++i) {
-      if (2 * (a + i) >= end) break;
-      if (i + 1 < kPairs)
-        fetch(f[(i + 1) & 1], jw[i + 1].x, jw[i + 1].y, __builtin_amdgcn_readlane(at, 2 * (a + i) + 2), __builtin_amdgcn_readlane(at, 2 * (a + i) + 3));
-      __builtin_amdgcn_sched_barrier(0);
-      math(f[i & 1], i < 2);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    pairs(std::integral_constant<int, kPairs>{}, f, a, end, at, fetch, math);
     if (U <= PL + kSpare) return;
     const int last_pair = (max(cnt, 1) - 1) >> 1;
     auto words = [&](int i) { return *reinterpret_cast<const uint2*>(jt + (uint32_t)(min(i, last_pair) * 512 + lane * 8)); };
