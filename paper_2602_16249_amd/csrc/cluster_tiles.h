@@ -195,8 +195,7 @@ struct TileWalk {
     __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): rows on their way to LDS count as vector loads
     __syncthreads();
   }
-  // Up to P pairs, from the a-th on, of the slots below `end`.  (Compiled apart for unions that fit: one loop for both took
-  // them 1 - 2 % longer.)
+  // Up to P pairs, from the a-th on, of the slots below `end`.
   template <int P, class Frag, class Fetch, class Math>
   __device__ __forceinline__ void pairs(std::integral_constant<int, P>, Frag (&f)[2], int a, int end, int at, Fetch& fetch, Math& math) {
     fetch(f[0], jw[0].x, jw[0].y, __builtin_amdgcn_readlane(at, 2 * a), __builtin_amdgcn_readlane(at, 2 * a + 1));
@@ -220,17 +219,19 @@ struct TileWalk {
   // N4096 H8 S16: K32 M8 20.9 -> 20.3, K64 M10 27.2 -> 26.0; B8 N16384 H4 K64 M10 blobs 57.8 -> 55.2; B64 N1024 H8 K48 S32 M8
   // 61.7 -> 59.2; B16 N16384 H4 K48 S64 M8 blobs 147 -> 142; what fits is as fast as before.)  Unions of more than PL + kSpare
   // tiles go on in eights.
-  template <class Frag, class Fetch, class Math>
+  // APART: unions that fit have a loop of their own, without the pairs that only others have (the forward kernel is 1 - 2 %
+  // faster with it; the query-stationary one is not, and with a relative-position table it has no registers left for two).
+  template <bool APART, class Frag, class Fetch, class Math>
   __device__ __forceinline__ void walk(int K, Fetch fetch, Math math) {
     const uint32_t none = 2u * (uint32_t)K * 0x01010101u;
     int at = min(my_pos, PL - 1) * 2048;
-    if (U <= PL) {
+    if (APART && U <= PL) {
       Frag f[2];
       pairs(std::integral_constant<int, (PL + 1) / 2>{}, f, 0, cnt, at, fetch, math);
       return;
     }
-    int a, end;  // first pair and last slot of the main part
-    {
+    int a = 0, end = cnt;  // first pair and last slot of the main part
+    if (APART || U > PL) {
       const int done = (int)__popcll(__ballot(lane < cnt && my_pos < min(kSpare, U - PL)));  // slots of the places to be freed
 #pragma unroll
       for (int i = 0; i < kSpare / 2; ++i) {

@@ -281,7 +281,7 @@ __device__ __forceinline__ void pla_bwd_query_body(const BwdParams& p) {
     for (int dt = 0; dt < 2; ++dt) acc[dt] = mfma32(f.kt[dt], dsf, acc[dt]);  // dq^T[channel 16dt + 4g+i][query r]
   };
   w.arrive();
-  w.template walk<BwdPair>(K, fetch, math);
+  w.template walk<false, BwdPair>(K, fetch, math);
   if (w.live) {
     wave_lds_sync();
     // rows of p and -D to the other kernel

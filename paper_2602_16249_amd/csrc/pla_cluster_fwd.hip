@@ -194,7 +194,7 @@ __device__ __forceinline__ void pla_fwd_body(const FwdParams& p) {
     accw = mfma32(ones, pf, accw);
   };
   w.arrive();
-  w.template walk<FwdPair>(K, fetch, math);
+  w.template walk<true, FwdPair>(K, fetch, math);
   ref = ref == -INFINITY ? 0.f : ref;
   if (!w.live) return;  // (no workgroup barrier below)
 
