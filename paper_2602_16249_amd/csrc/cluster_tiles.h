@@ -223,6 +223,8 @@ struct TileWalk {
   // faster with it; the query-stationary one is not, and with a relative-position table it has no registers left for two).
   template <bool APART, class Frag, class Fetch, class Math>
   __device__ __forceinline__ void walk(int K, Fetch fetch, Math math) {
+    static_assert(2 * kPairs >= PL + kSpare, "the j words of two stages' slots are in registers");
+    static_assert(kSpare % kGroup == 0 && (kSpare & (kSpare - 1)) == 0 && kSpare <= PL, "");
     const uint32_t none = 2u * (uint32_t)K * 0x01010101u;
     int at = min(my_pos, PL - 1) * 2048;
     if (APART && U <= PL) {

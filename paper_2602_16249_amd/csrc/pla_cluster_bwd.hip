@@ -382,7 +382,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 constexpr int kChunk = 4;  // strips in LDS at a time, one per wave to fetch; twice: the next chunk's rows fly during the math
 
 template <int CL, bool RAG>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void pla_bwd_key_kernel(BwdParams p) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CL == 2 ? 3 : 4, CL == 2 ? 3 : 4))) void pla_bwd_key_kernel(BwdParams p) {
   constexpr int kRows = RowArray<CL>::bytes;
   constexpr int kStrip = 2048 + kRows + 64;  // q rows, dout rows, the strip's block of `hand`
   __shared__ __align__(16) char strips[2][kChunk][kStrip];
