@@ -58,6 +58,29 @@ hipError_t launch_pair_gather(const void* dout, const float* weights, const int3
                               size_t tokens, int C, int Kt, int dtype, void* dfeat, bool pieces, hipStream_t stream,
                               const float* extra = nullptr, float* extra_sum = nullptr);
 
+// Filing and summing in one launch (pair_sum.hip), where pair_sum_takes it: dfeat and extra_sum as launch_pair_lists and
+// launch_pair_gather would give them, and dp as the sum of dp_part[0 .. dp_n), dp_n <= kPairSumMostParts, if dp_part is given.
+struct PairSumArgs {
+  const int32_t* pair_token;
+  int B, Nv, pairs_per_image, row_pairs;  // row_pairs consecutive pairs belong to a row of dout
+  // every group_size consecutive pairs: bit i is set where one names a token of the image's i-th part of pair_part(Nv) tokens
+  const unsigned long long* group_parts;
+  int group_size;
+  const void* dout;
+  const float *weights, *extra;
+  int C, dtype;
+  void* dfeat;
+  float* extra_sum;
+  int32_t* list;  // workspace [B * pairs_per_image]
+  const float* dp_part;
+  int dp_n;
+  float* dp;
+};
+inline int pair_part(int Nv) { return (Nv + 63) / 64; }
+bool pair_sum_takes(const PairSumArgs& a);
+hipError_t launch_pair_sum(const PairSumArgs& a, hipStream_t stream);
+constexpr size_t kPairSumMostParts = 131072;  // (128 values a thread; more parts of dp take two launches of their own)
+
 // Neighbourhood merging (merge.hip): anchor selection, location-aware aggregation, backward.
 struct MergeArgs {
   const void* feat;           // [B,N,C]

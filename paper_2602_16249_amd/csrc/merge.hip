@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "cluster_common.h"
 #include "device_util.h"
 #include "launch.h"
 #include "timing.h"
@@ -442,6 +443,7 @@ __global__ __launch_bounds__(256) void merge_bwd_kernel(const T* __restrict__ fe
                                                        int B, int N, int C, int K, int n_keep, float p,
                                                        float* __restrict__ wpair, float* __restrict__ dzpair,
                                                        int32_t* __restrict__ pair_token, int2* __restrict__ pair_bounds,
+                                                       int part, uint32_t part_magic,
                                                        float* __restrict__ dp_part) {
   __shared__ float g_all[4][kWave];
   const int lane = threadIdx.x & (kWave - 1);
@@ -513,6 +515,15 @@ __global__ __launch_bounds__(256) void merge_bwd_kernel(const T* __restrict__ fe
     pair_token[pair] = nb.b * N + nb.idx;
   }
   if (lane == 0 && dp_part) dp_part[slot] = dpv;
+  if (part) {  // which of the image's 64 parts of `part` tokens the anchor's pairs name (lanes >= K hold the anchor's token)
+    const int at = exact_div(nb.idx, part, part_magic);
+    const uint32_t bit = 1u << (at & 31);
+    uint32_t lo = at < 32 ? bit : 0u, hi = at < 32 ? 0u : bit;
+    lo = wave_or32(lo);
+    hi = wave_or32(hi);
+    if (lane == 0) pair_bounds[slot] = make_int2((int)lo, (int)hi);
+    return;
+  }
   // the lowest and highest token of the anchor's pairs, for the list builder (lanes >= K hold the anchor's token)
   int tmin = nb.b * N + nb.idx, tmax = tmin;
 #pragma unroll
@@ -616,16 +627,25 @@ hipError_t launch_merge_bwd(const MergeArgs& a, hipStream_t stream) {
   const dim3 grid(round_up8(((long long)anchors + 3) / 4));
   const bool pieces = merge_pieces(a, a.feat, a.dout);
   const int pp = lanes_per_row(a);
+  PairSumArgs s = {};
+  s.pair_token = pair_token; s.B = a.B; s.Nv = a.N; s.pairs_per_image = a.n_keep * a.K; s.row_pairs = a.K;
+  s.group_parts = reinterpret_cast<const unsigned long long*>(pair_bounds); s.group_size = a.K;
+  s.dout = a.dout; s.weights = wpair; s.extra = dzpair; s.C = a.C; s.dtype = a.dtype;
+  s.dfeat = a.dfeat; s.extra_sum = a.dscore; s.list = list;
+  const bool one = pair_sum_takes(s);
 #define AFFMAE_MERGE_BWD(T, P)                                                                                     \
   AFFMAE_LAUNCH("merge_bwd_kernel", stream, (merge_bwd_kernel<T, P>), grid, dim3(256), 0, stream, (const T*)a.feat, \
                 a.coords, a.score, a.nbr_idx, a.anchor_idx, (const T*)a.dout, a.B, a.N, a.C, a.K, a.n_keep, a.p, \
-                wpair, dzpair, pair_token, pair_bounds, dp_part)
+                wpair, dzpair, pair_token, pair_bounds, one ? pair_part(a.N) : 0, div_magic(pair_part(a.N)), dp_part)
   AFFMAE_MERGE_ROWS(AFFMAE_MERGE_BWD)
 #undef AFFMAE_MERGE_BWD
-  if (a.dp) {
+  if (a.dp && one && anchors <= kPairSumMostParts) {
+    s.dp_part = dp_part; s.dp_n = (int)anchors; s.dp = a.dp;
+  } else if (a.dp) {
     const hipError_t e = launch_sum_parts(dp_part, anchors, dp_part2, a.dp, stream);
     if (e != hipSuccess) return e;
   }
+  if (one) return launch_pair_sum(s, stream);
   hipError_t e = launch_pair_lists(pair_token, a.B, a.N, a.n_keep * a.K, offset, list, stream,
                                    reinterpret_cast<const int32_t*>(pair_bounds), a.K);
   if (e != hipSuccess) return e;

@@ -1,0 +1,342 @@
+// The gathered half of the merging backward (paper, Sec. "AutoFocusFormer"): for every token
+//   dfeat[token] = sum over the (anchor, neighbour) pairs that name it of weight[pair] * dout[anchor of the pair]
+//   extra_sum[token] = sum of extra[pair] over the same pairs
+// without floating-point atomics.
+//
+// One workgroup owns a range of an image's tokens: it picks the pairs that name one of them out of the image's, sorts
+// them by token in LDS (counted, prefix-summed, placed), with the place of the pair's row in dout and its weight, and
+// its waves add the rows up from there, G lanes of 16 bytes per row.  Neighbouring tokens are named by the same anchors,
+// whose rows then come from the CU's own cache.  Before, one launch wrote every token's list to memory and a second one
+// read, per 16 pairs of a token, the list, then the weights it named, then the rows; at C = 64 (bf16) half of the 16
+// lanes that a token got had no channels.  8 images, 16384 tokens, 4096 anchors, K = 48, C = 64: 20.4 + 29.1 us and 4.6 for
+// dp (which one workgroup of this launch adds up now); 26.5 us as here.
+// Bound by the chain of the sort (12 of its 16 us a workgroup: the anchors' masks, the pairs they point to, their weights:
+// each step waits for memory) and then by the rows.  Two workgroups of 1024 threads per CU: 36.8 us with one (71
+// registers).  Which anchors to look at is told by a bit for each 64th of the image: 43.7 us with the lowest and highest
+// token, which along a space-filling curve often lie far apart (of 4096 anchors 282 for 121 that do have a pair in 256 tokens).
+// (The virtual tokens' backward, whose queries lie anywhere, would look at all pairs in every workgroup: 64.7 us for 17.3 +
+// 39.0 + 4.7, 48 images of 8192 queries with 4 candidates.)
+#include <algorithm>
+#include <type_traits>
+
+#include "cluster_common.h"
+#include "device_util.h"
+#include "launch.h"
+#include "timing.h"
+
+namespace affmae {
+namespace {
+
+constexpr int kSumThreads = 1024, kSumWaves = kSumThreads / kWave;
+constexpr int kSumCap = 4096;       // pairs of a workgroup's tokens that have a place in LDS
+constexpr int kSumRange = 1024;     // most tokens of a workgroup
+constexpr int kSumGroups = 8192;    // groups of pairs that a workgroup lists at a time
+
+struct SumParams {
+  const int32_t* pair_token;  // [B * ppi]: the pair's token, b * Nv + t
+  const unsigned long long* parts;  // which of the 64 parts of the image (of `part` tokens) every `gs` consecutive pairs name
+  const uint4* dout;          // [B * ppi / row_pairs] rows of `pieces` 16-byte pieces
+  const float *weights, *extra;
+  uint4* dfeat;
+  float* extra_sum;
+  int32_t* list;              // room for all pairs: the lists that do not fit LDS
+  int B, Nv, ppi, groups, gs, part, range, ranges, pieces, row_pairs;
+  uint32_t gs_magic, row_magic;
+  const float* dp_part;       // dp = their sum, by the workgroup behind the last range's, or nullptr
+  int dp_n;
+  float* dp;
+};
+
+template <typename T>
+__device__ __forceinline__ void add_piece(const uint4& x, float w, float (&acc)[8]) {
+  const uint32_t v[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (sizeof(T) == 2) {
+      acc[2 * e] = fmaf(w, __uint_as_float(v[e] << 16), acc[2 * e]);
+      acc[2 * e + 1] = fmaf(w, __uint_as_float(v[e] & 0xffff0000u), acc[2 * e + 1]);
+    } else {
+      acc[e] = fmaf(w, __uint_as_float(v[e]), acc[e]);
+    }
+  }
+}
+template <typename T>
+__device__ __forceinline__ uint4 pack_piece(const float (&a)[8]) {
+  if constexpr (sizeof(T) == 2) return make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]), pack_bf16x2(a[6], a[7]));
+  else return make_uint4(__float_as_uint(a[0]), __float_as_uint(a[1]), __float_as_uint(a[2]), __float_as_uint(a[3]));
+}
+
+// Sum of the parts in the order of launch_sum_parts (one workgroup).
+__device__ __forceinline__ void sum_parts(const float* part, int n, float* out, float* wave_sums) {
+  float s = 0.f;
+  const int n4 = n / 4;
+  for (int i = threadIdx.x; i < n4; i += kSumThreads) {
+    const float4 v = reinterpret_cast<const float4*>(part)[i];
+    s += (v.x + v.y) + (v.z + v.w);
+  }
+  for (int i = n4 * 4 + threadIdx.x; i < n; i += kSumThreads) s += part[i];
+  s = wave_sum(s);
+  if ((threadIdx.x & (kWave - 1)) == 0) wave_sums[threadIdx.x / kWave] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float t = 0.f;
+    for (int w = 0; w < kSumWaves; ++w) t += wave_sums[w];
+    *out = t;
+  }
+}
+
+// G: lanes per row (4, 8 or 16).  SPLIT: a wave per token, its 64 / G groups of lanes taking the token's pairs in turn
+// (ranges of so few tokens that a group of lanes per token would leave lanes idle); otherwise G lanes per token.
+template <typename T, int G, bool SPLIT>
+__global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void pair_sum_kernel(SumParams p) {
+  __shared__ uint2 entry[kSumCap];  // row (its first piece in the image's dout), weight; before that: the listed groups
+  __shared__ float entry_extra[kSumCap];
+  __shared__ uint32_t hit_pair[kSumCap];  // pairs of the own tokens as they are found
+  __shared__ uint16_t hit_token[kSumCap];
+  __shared__ int32_t cnt[kSumRange];  // pairs per token; then the next free place of each; then where its list ends
+  __shared__ int32_t wave_total[kSumWaves], wave_below[kSumWaves];
+  __shared__ int32_t s_listed, s_hits;
+  static_assert(kSumGroups * 4 <= kSumCap * 8, "the listed groups lie in the entries' place");
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  if ((int)blockIdx.x == p.B * p.ranges) {  // (only there with dp_part)
+    sum_parts(p.dp_part, p.dp_n, p.dp, reinterpret_cast<float*>(wave_total));
+    return;
+  }
+  const int b = blockIdx.x / p.ranges, rg = blockIdx.x - b * p.ranges;
+  const int t0 = rg * p.range, span = min(p.range, p.Nv - t0);  // >= 1
+  const int first = b * p.Nv + t0;
+  const int lo = b * p.ppi, hi = lo + p.ppi;  // the image's pairs
+  cnt[tid] = 0;
+  if (tid == 0) s_hits = 0;
+
+  // fn(tokens, pairs, in) for four pairs at a time, all lanes of a wave together, of the groups that name a token of the range's
+  // parts of the image
+  int32_t* glist = reinterpret_cast<int32_t*>(entry);
+  const int part_lo = t0 / p.part, part_hi = (t0 + span - 1) / p.part;
+  const unsigned long long own_parts = (part_hi - part_lo >= 63 ? ~0ull : (2ull << (part_hi - part_lo)) - 1ull) << part_lo;
+  auto each_pair = [&](auto&& fn) {
+    for (int g0 = 0; g0 < p.groups; g0 += kSumGroups) {
+      __syncthreads();  // the list before has been walked (and, the first time, the counters are set)
+      if (tid == 0) s_listed = 0;
+      __syncthreads();
+      const int g1 = min(g0 + kSumGroups, p.groups);
+      for (int gw = g0 + wave * kWave; gw < g1; gw += kSumThreads) {
+        const int g = gw + lane;
+        const bool in = g < g1 && (p.parts[(size_t)b * p.groups + min(g, g1 - 1)] & own_parts) != 0ull;
+        const unsigned long long mask = __ballot(in);
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&s_listed, (int)__popcll(mask));
+        at = __builtin_amdgcn_readfirstlane(at);
+        const int place = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, (uint32_t)at));
+        if (in) glist[place] = g;
+      }
+      __syncthreads();
+      const int items = s_listed * p.gs;
+      for (int i0 = 0; i0 < items; i0 += 4 * kSumThreads) {
+        int pair[4], tok[4];
+        bool in[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int at = i0 + u * kSumThreads + tid, i = min(at, items - 1);
+          const int gi = exact_div(i, p.gs, p.gs_magic);
+          in[u] = at < items;
+          pair[u] = lo + glist[gi] * p.gs + (i - gi * p.gs);
+          tok[u] = p.pair_token[pair[u]];
+        }
+        fn(tok, pair, in);
+      }
+    }
+  };
+
+  // the own tokens' pairs: counted and noted
+  each_pair([&](const int (&tok)[4], const int (&pair)[4], const bool (&in)[4]) {
+    unsigned long long mask[4];
+    int found = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int rel = tok[u] - first;
+      const bool own = in[u] && (unsigned)rel < (unsigned)span;
+      mask[u] = __ballot(own);
+      found += __popcll(mask[u]);
+      if (own) atomicAdd(&cnt[rel], 1);
+    }
+    if (found == 0) return;  // wave-uniform
+    int at = 0;
+    if (lane == 0) at = atomicAdd(&s_hits, found);
+    at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int place = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask[u], (uint32_t)at));
+      if (((mask[u] >> lane) & 1ull) && place < kSumCap) {
+        hit_pair[place] = (uint32_t)pair[u];
+        hit_token[place] = (uint16_t)(tok[u] - first);
+      }
+      at += __popcll(mask[u]);
+    }
+  });
+  __syncthreads();
+  // where each token's list starts
+  const int mine = cnt[tid];
+  int incl = mine;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int v = __shfl_up(incl, o);
+    if (lane >= o) incl += v;
+  }
+  if (lane == kWave - 1) wave_total[wave] = incl;
+  __syncthreads();
+  int run = incl - mine, total = 0;
+#pragma unroll
+  for (int w = 0; w < kSumWaves; ++w) {
+    const int t = wave_total[w];
+    run += w < wave ? t : 0;
+    total += t;
+  }
+  const bool fits = total <= kSumCap;
+  cnt[tid] = run;
+  // (lists that do not fit, where many pairs name few tokens, go to memory, behind those of all earlier tokens)
+  int32_t* far = p.list;
+  if (!fits) {
+    int below = 0;
+    for (int i = lo + tid; i < hi; i += kSumThreads) below += p.pair_token[i] < first ? 1 : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o);
+    if (lane == 0) wave_below[wave] = below;
+    __syncthreads();
+    int start = lo;
+    for (int w = 0; w < kSumWaves; ++w) start += wave_below[w];
+    far += start;
+  }
+  __syncthreads();
+  auto row_of = [&](int pair) { return (uint32_t)exact_div(pair - lo, p.row_pairs, p.row_magic) * (uint32_t)p.pieces; };
+  if (fits) {
+    for (int i = tid; i < total; i += kSumThreads) {
+      const int pair = (int)hit_pair[i];
+      const int at = atomicAdd(&cnt[hit_token[i]], 1);
+      entry[at] = make_uint2(row_of(pair), __float_as_uint(p.weights[pair]));
+      if (p.extra) entry_extra[at] = p.extra[pair];
+    }
+  } else {
+    each_pair([&](const int (&tok)[4], const int (&pair)[4], const bool (&in)[4]) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int rel = tok[u] - first;
+        if (in[u] && (unsigned)rel < (unsigned)span) far[atomicAdd(&cnt[rel], 1)] = pair[u];
+      }
+    });
+    __threadfence_block();
+  }
+  __syncthreads();
+
+  // the sums: N consumers of a token's list, this one the n-th, rows in flight four at a time
+  constexpr int kGroupsOfLanes = kWave / G, kStep = SPLIT ? kGroupsOfLanes : 1;
+  const int sub = lane & (G - 1), grp = lane / G;
+  const uint4* rows = p.dout + (size_t)b * (p.ppi / p.row_pairs) * p.pieces;
+  auto sums = [&](auto in_lds) {
+  const int per_turn = SPLIT ? kSumWaves : kSumThreads / G;  // tokens at a time
+  for (int r0 = 0; r0 < span; r0 += per_turn) {  // (workgroup-uniform)
+    const int rel = r0 + (SPLIT ? wave : tid / G);
+    const bool live = rel < span;
+    const int l0 = live && rel > 0 ? cnt[rel - 1] : 0, l1 = live ? cnt[rel] : 0;
+    const int from = l0 + (SPLIT ? grp : 0);
+    auto at = [&](int i) -> uint2 {
+      if constexpr (decltype(in_lds)::value) return entry[i];
+      const int pair = far[i];
+      return make_uint2(row_of(pair), __float_as_uint(p.weights[pair]));
+    };
+    for (int c0 = 0; c0 < p.pieces; c0 += G) {
+      const int c = min(c0 + sub, p.pieces - 1);  // lanes past the row's end repeat its last piece (unused)
+      float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      int i = from;
+      for (; i + 3 * kStep < l1; i += 4 * kStep) {
+        uint2 e[4];
+        uint4 x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) e[u] = at(i + u * kStep);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = rows[(size_t)(e[u].x + (uint32_t)c)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) add_piece<T>(x[u], __uint_as_float(e[u].y), acc);
+      }
+      if (i < l1) {  // up to three more: past the end the last one again, as zeros
+        uint2 e[3];
+        uint4 x[3];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) e[u] = at(min(i + u * kStep, l1 - 1));
+#pragma unroll
+        for (int u = 0; u < 3; ++u) x[u] = rows[(size_t)(e[u].x + (uint32_t)c)];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+          if (u > 0 && i + u * kStep >= l1) x[u] = make_uint4(0u, 0u, 0u, 0u);
+          add_piece<T>(x[u], __uint_as_float(e[u].y), acc);
+        }
+      }
+      if constexpr (SPLIT) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] = lanes_sum<G, 32>(acc[e], lane);
+      }
+      if (live && c0 + sub < p.pieces && (!SPLIT || grp == 0)) p.dfeat[(size_t)(first + rel) * p.pieces + c] = pack_piece<T>(acc);
+    }
+    if (p.extra) {
+      float x = 0.f;
+      for (int i = l0 + (SPLIT ? lane : sub); i < l1; i += SPLIT ? kWave : G) x += decltype(in_lds)::value ? entry_extra[i] : p.extra[far[i]];
+      x = lanes_sum<1, SPLIT ? 32 : G / 2>(x, lane);
+      if (live && (SPLIT ? lane : sub) == 0) p.extra_sum[first + rel] = x;
+    }
+  }
+  };
+  if (fits) sums(std::true_type{}); else sums(std::false_type{});
+}
+
+}  // namespace
+
+// Pairs per token up to which this is the way (on average): beyond, too few tokens' lists fit a workgroup.
+constexpr int kSumMostPairs = kSumCap / 16 * 5 / 8;
+
+bool pair_sum_takes(const PairSumArgs& a) {
+  auto al = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
+  const size_t row = (size_t)a.C * (a.dtype == 1 ? 2 : 4);
+  if (row % 16 || !al(a.dout) || !al(a.dfeat)) return false;
+  if ((long long)(a.pairs_per_image / a.row_pairs) * (long long)(row / 16) >= (1ll << 32)) return false;  // places of an image's rows
+  if ((long long)a.pairs_per_image > (long long)kSumMostPairs * a.Nv) return false;
+  return true;
+}
+
+hipError_t launch_pair_sum(const PairSumArgs& a, hipStream_t stream) {
+  SumParams p;
+  p.pair_token = a.pair_token; p.parts = a.group_parts; p.part = pair_part(a.Nv);
+  p.dout = static_cast<const uint4*>(a.dout); p.weights = a.weights; p.extra = a.extra;
+  p.dfeat = static_cast<uint4*>(a.dfeat); p.extra_sum = a.extra_sum; p.list = a.list;
+  p.B = a.B; p.Nv = a.Nv; p.ppi = a.pairs_per_image; p.row_pairs = a.row_pairs; p.row_magic = div_magic(a.row_pairs);
+  p.gs = a.group_size; p.groups = a.pairs_per_image / p.gs; p.gs_magic = div_magic(p.gs);
+  p.pieces = (int)((size_t)a.C * (a.dtype == 1 ? 2 : 4) / 16);
+  p.dp_part = a.dp_part; p.dp_n = a.dp_n; p.dp = a.dp;
+  const int g = p.pieces <= 4 ? 4 : p.pieces <= 8 ? 8 : 16;
+  // tokens of a workgroup: two workgroups per CU, but no more pairs than fit with a quarter to spare
+  const int want = std::max(1, (512 + a.B - 1) / a.B);
+  const long long fit = std::max(1ll, (long long)kSumCap * 3 / 4 * a.Nv / std::max(1, a.pairs_per_image));
+  p.range = (int)std::min({std::max(64ll, ((long long)a.Nv + want - 1) / want), fit, (long long)kSumRange});
+  const int turn = kSumThreads / g;  // tokens at a time, with G lanes each: whole turns
+  if (p.range > turn) p.range = p.range / turn * turn;
+  p.ranges = (a.Nv + p.range - 1) / p.range;
+  const bool split = p.range * g < kSumThreads / 2;
+  const dim3 grid((unsigned)(a.B * p.ranges + (a.dp_part ? 1 : 0)));
+#define AFFMAE_SUM(T, G, SPLIT) \
+  AFFMAE_LAUNCH("pair_sum_kernel", stream, (pair_sum_kernel<T, G, SPLIT>), grid, dim3(kSumThreads), 0, stream, p)
+#define AFFMAE_SUM_G(T, SPLIT)             \
+  do {                                     \
+    if (g == 4) AFFMAE_SUM(T, 4, SPLIT);   \
+    else if (g == 8) AFFMAE_SUM(T, 8, SPLIT); \
+    else AFFMAE_SUM(T, 16, SPLIT);         \
+  } while (0)
+  if (a.dtype == 1) {
+    if (split) AFFMAE_SUM_G(bf16_t, true); else AFFMAE_SUM_G(bf16_t, false);
+  } else {
+    if (split) AFFMAE_SUM_G(float, true); else AFFMAE_SUM_G(float, false);
+  }
+#undef AFFMAE_SUM_G
+#undef AFFMAE_SUM
+  return hipGetLastError();
+}
+
+}  // namespace affmae

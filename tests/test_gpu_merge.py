@@ -178,3 +178,38 @@ def test_select_when_few_keys_share_the_leading_bits(N, same, distinct):
     for n_keep in sorted({high.size, high.size + 1, high.size + (same + 1) // 2, high.size + same, high.size + same + 1}):
         idx, _ = aff.affmae_merge_select(torch.from_numpy(score).cuda(), n_keep)
         assert np.array_equal(idx.cpu().numpy(), oracle.merge_select(score, n_keep)), n_keep
+
+
+@pytest.mark.parametrize("dtype,B,N,C,K,n_keep,few", [
+    ("bf16", 1, 1500, 64, 48, 1100, 3),    # nearly all pairs name three tokens: lists that do not fit a workgroup's LDS
+    ("f32", 2, 700, 16, 32, 500, 1),       # ... one token, and the second image's lists behind the first's
+    ("bf16", 1, 40, 8, 24, 40, 0),         # fewer tokens than parts of an image
+    ("bf16", 1, 64, 40, 5, 64, 0),         # as many; 5 pieces in 8 lanes
+    ("f32", 1, 65, 4, 16, 30, 0),          # one more: parts of two tokens, the last half full
+    ("bf16", 2, 4161, 64, 64, 4161, 0),    # 64 pairs a token: the fewest tokens a workgroup takes, a wave for each
+    ("f32", 1, 1025, 96, 3, 1000, 0),      # 24 pieces: two trips of 16 lanes
+    ("bf16", 300, 70, 16, 9, 20, 0),       # many small images
+])
+def test_merge_sums_per_token(dtype, B, N, C, K, n_keep, few):
+    """dfeat, dscore and dp for neighbour tables of any kind (tokens named by nobody, by few, by all anchors)."""
+    print(f"case merge sums {dtype} B={B} N={N} C={C} K={K} n_keep={n_keep} few={few}", flush=True)
+    rng = np.random.default_rng(N + C + K)
+    coords = rng.uniform(0, 30, size=(B, N, 2)).astype(np.float32)
+    nbr = np.stack([[rng.permutation(N)[:K] for _ in range(N)] for _ in range(B)]).astype(np.int32)
+    if few:
+        nbr[:, :, : K - 2] = rng.integers(N - few, N, size=(B, N, K - 2))
+    feat, dout = (rng.normal(size=(B, n, C)).astype(np.float32) for n in (N, n_keep))
+    score = rng.normal(size=(B, N)).astype(np.float32)
+    tdt = torch.float32
+    if dtype == "bf16":
+        feat, dout, tdt = bf16_round(feat), bf16_round(dout), torch.bfloat16
+    anchors = oracle.merge_select(score, n_keep)
+    up = lambda x: torch.from_numpy(x).cuda()
+    g = aff.affmae_merge_bwd(up(feat).to(tdt), up(coords), up(score), up(nbr), up(anchors), up(dout).to(tdt), 0.3)
+    torch.cuda.synchronize()
+    rg = oracle.merge_bwd(coords, feat, score, nbr, anchors, dout, 0.3)
+    for name in ("dfeat", "dscore"):
+        got = g[name].float().cpu().numpy().astype(np.float64)
+        # fp32 sums of up to n_keep K terms (here at most 5e4, of both signs): 1e-5 of the largest holds as elsewhere
+        assert np.abs(got - rg[name]).max() <= TOL[dtype] * np.abs(rg[name]).max(), name
+    assert abs(float(g["dp"].cpu()) - rg["dp"]) <= TOL[dtype] * rg["dp_abs"]
