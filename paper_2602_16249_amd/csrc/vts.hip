@@ -708,10 +708,8 @@ __global__ __launch_bounds__(256) void vts_bwdg_kernel(const float* __restrict__
 // dp = sum of the per-query parts in a fixed order, in two steps: workgroup j adds up parts [j per, (j + 1) per)
 // into out[j]; a second launch with one workgroup adds up those sums.
 constexpr int kDpPer = 16384;
-__global__ __launch_bounds__(1024) void vts_dp_kernel(const float* __restrict__ part, size_t n, size_t per,
-                                                      float* __restrict__ out) {
-  __shared__ float acc[16];
-  const size_t lo = (size_t)blockIdx.x * per, hi = min(n, lo + per);  // per is a multiple of 4 or the only block's n
+constexpr size_t kDpInLists = 8 * (size_t)kDpPer;  // up to so many, the sum is one workgroup's, behind those of the lists' launch
+__device__ __forceinline__ void sum_parts(const float* __restrict__ part, size_t lo, size_t hi, float* acc, float* out) {
   float s = 0.f;
   const size_t n4 = (hi - lo) / 4;  // the workspace slots are 256-byte aligned: whole 16-byte pieces first
   for (size_t i = threadIdx.x; i < n4; i += blockDim.x) {
@@ -725,8 +723,14 @@ __global__ __launch_bounds__(1024) void vts_dp_kernel(const float* __restrict__ 
   if (threadIdx.x == 0) {
     float t = 0.f;
     for (int w = 0; w < 16; ++w) t += acc[w];
-    out[blockIdx.x] = t;
+    *out = t;
   }
+}
+__global__ __launch_bounds__(1024) void vts_dp_kernel(const float* __restrict__ part, size_t n, size_t per,
+                                                      float* __restrict__ out) {
+  __shared__ float acc[16];
+  const size_t lo = (size_t)blockIdx.x * per;  // per is a multiple of 4 or the only block's n
+  sum_parts(part, lo, min(n, lo + per), acc, out + blockIdx.x);
 }
 
 // Files every (query, candidate) pair in the list of its token, with no atomic on global memory.  A
@@ -742,9 +746,15 @@ template <int NP>
 __global__ __launch_bounds__(kListThreads) void vts_lists_kernel(const int32_t* __restrict__ pair_token, int B, int Nv,
                                                                  int pairs_per_image, int range, int ranges,
                                                                  int32_t* __restrict__ offset,
-                                                                 int32_t* __restrict__ list) {
+                                                                 int32_t* __restrict__ list,
+                                                                 const float* __restrict__ dp_part, int dp_n,
+                                                                 float* __restrict__ dp) {
   __shared__ int32_t cnt[kListRange];
   __shared__ int32_t wave_total[kListThreads / kWave], wave_below[kListThreads / kWave];
+  if ((int)blockIdx.x == B * ranges) {  // (only there with dp_part)
+    sum_parts(dp_part, 0, (size_t)dp_n, reinterpret_cast<float*>(wave_total), dp);
+    return;
+  }
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int b = blockIdx.x / ranges, rg = blockIdx.x - b * ranges;
   const int t0 = rg * range;
@@ -814,7 +824,7 @@ __global__ __launch_bounds__(kListThreads) void vts_lists_kernel(const int32_t* 
     cnt[4 * tid + i] = run;  // from here on: the next free place of the token's list
     run += c[i];
   }
-  if (blockIdx.x == gridDim.x - 1 && tid == 0) offset[(size_t)B * Nv] = B * pairs_per_image;
+  if ((int)blockIdx.x == B * ranges - 1 && tid == 0) offset[(size_t)B * Nv] = B * pairs_per_image;
   __syncthreads();
   each_pair([&](int tok, int pair) {
     const int rel = tok - first;
@@ -1156,13 +1166,15 @@ hipError_t launch_vts_bwd(const VtsArgs& a, hipStream_t stream) {
     AFFMAE_LAUNCH("vts_bwd_kernel", stream, vts_bwd_kernel<float>, grid, dim3(256), 0, stream, a.query_xy, a.vis_xy,
                   (const float*)a.feat, a.table, (const float*)a.dout, a.B, a.Mq, a.Nv, a.C, gr, a.Kt, a.p, a.eps,
                   weights, pair_token, a.dquery, dp_part);
-  if (a.dp) {
-    // parts: one per wave of the grouped kernels, one per query otherwise
-    const size_t n = grouped ? (size_t)gridg.x * 4 : (size_t)a.B * a.Mq;
+  // parts: one per wave of the grouped kernels, one per query otherwise
+  const size_t n = grouped ? (size_t)gridg.x * 4 : (size_t)a.B * a.Mq;
+  const bool in_lists = a.dp && n <= kDpInLists;  // (more are added up by launches of their own)
+  if (a.dp && !in_lists) {
     const hipError_t e = launch_sum_parts(dp_part, n, dp_part2, a.dp, stream);
     if (e != hipSuccess) return e;
   }
-  const hipError_t e = launch_pair_lists(pair_token, a.B, a.Nv, a.Mq * a.Kt, offset, list, stream);
+  const hipError_t e = launch_pair_lists(pair_token, a.B, a.Nv, a.Mq * a.Kt, offset, list, stream, nullptr, 0,
+                                         in_lists ? dp_part : nullptr, (int)n, a.dp);
   if (e != hipSuccess) return e;
   const bool pieces = vts_grouped(a, a.dout, a.dfeat, nullptr);  // (Kt <= 16 is not needed here, only the row shape)
   return launch_pair_gather(a.dout, weights, offset, list, tokens, a.C, a.Kt, a.dtype, a.dfeat, pieces, stream);
@@ -1185,10 +1197,12 @@ hipError_t launch_sum_parts(const float* part, size_t n, float* part2, float* ou
 // Files pairs per token: pair_token[b * pairs_per_image + i] = the (global, b * Nv + t) token of pair i of image b
 // -> offset [B * Nv + 1] (start of every token's list) and list [B * pairs_per_image] (pair ids grouped by token).
 // group_bounds (optional): [B * pairs_per_image / group_size][2], the lowest and highest token of every run of
-// group_size consecutive pairs.
+// group_size consecutive pairs.  dp_part (without group_bounds): *dp = dp_part[0] + ... + dp_part[dp_n - 1] as well, in the
+// order of launch_sum_parts, by one more workgroup (a launch of its own took 4.7 us of the decoder's backward).
 hipError_t launch_pair_lists(const int32_t* pair_token, int B, int Nv, int pairs_per_image, int32_t* offset,
-                             int32_t* list, hipStream_t stream, const int32_t* group_bounds, int group_size) {
-  if (group_bounds && group_size >= 1 && pairs_per_image % group_size == 0) {
+                             int32_t* list, hipStream_t stream, const int32_t* group_bounds, int group_size,
+                             const float* dp_part, int dp_n, float* dp) {
+  if (group_bounds && !dp_part && group_size >= 1 && pairs_per_image % group_size == 0) {
     // a range walks only the groups that reach into it: many small ranges cost little
     const int groups = pairs_per_image / group_size;
     const int want = (512 + B - 1) / B;
@@ -1205,11 +1219,11 @@ hipError_t launch_pair_lists(const int32_t* pair_token, int B, int Nv, int pairs
   int range = std::max(64, (Nv + want - 1) / want);
   range = std::min(range, kListRange);
   const int ranges = (Nv + range - 1) / range;
-  const dim3 lgrid((unsigned)(B * ranges));
+  const dim3 lgrid((unsigned)(B * ranges + (dp_part ? 1 : 0)));
   const int ppi = pairs_per_image, pieces_max = (ppi + 3) / 4 + 1;  // + 1: an image may start inside a piece
 #define AFFMAE_VTS_LISTS(NP)                                                                                         \
   AFFMAE_LAUNCH("vts_lists_kernel", stream, vts_lists_kernel<NP>, lgrid, dim3(kListThreads), 0, stream, pair_token, \
-                B, Nv, ppi, range, ranges, offset, list)
+                B, Nv, ppi, range, ranges, offset, list, dp_part, dp_n, dp)
   if (pieces_max <= 4 * kListThreads) AFFMAE_VTS_LISTS(4);
   else if (pieces_max <= 9 * kListThreads) AFFMAE_VTS_LISTS(9);
   else AFFMAE_VTS_LISTS(0);
