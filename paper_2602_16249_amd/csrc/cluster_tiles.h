@@ -85,10 +85,11 @@ __device__ __forceinline__ f32x4 mfma16(const Frag4& a, const Frag4& b, f32x4 c)
 
 // Workgroups are dealt round-robin to the 8 XCDs (one L2 each); neighbouring groups share rows, so give every XCD a
 // contiguous range.  The grid is a multiple of 8.
-__device__ __forceinline__ int xcd_contiguous_block() {
-  const int per_xcd = gridDim.x >> 3;
-  return (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+__device__ __forceinline__ int xcd_contiguous_block(unsigned block, unsigned blocks) {
+  const int per_xcd = blocks >> 3;
+  return (block & 7) * per_xcd + (block >> 3);
 }
+__device__ __forceinline__ int xcd_contiguous_block() { return xcd_contiguous_block(blockIdx.x, gridDim.x); }
 
 // The wave's strip, and the tiles of its group.  PL: places for tiles in LDS, RAG: N is not a multiple of 16 (only then
 // do the row clamps exist in the code).

@@ -12,7 +12,7 @@
 //    rows of p are handed to the other kernel as they are, with D of every query.  With blank
 //    tokens the blank column joins every query's softmax: its dS feeds dq, and the strip's sums
 //    for dk_blank / dv_blank go to the workspace, to be added up over the strips in a fixed
-//    order by a last kernel;
+//    order beside the other kernel;
 //
 //  key-stationary (one wave per tile of 16 tokens and head, four tiles a workgroup): the workgroup
 //    walks the strips that touch any of its tiles, four at a time, their q, dout and p rows
@@ -54,6 +54,10 @@ struct BwdParams {
   RelSource rel;    // REL kernels
   float* rel_part;  // workspace [groups][H][ncells]: every workgroup's sums of dS per bin (needs ncells <= kRelBins),
                     // or nullptr: then dS goes out through `ds` for the stand-alone table-gradient kernel
+  // Sums over what the query-stationary kernel left in the workspace, by workgroups in front of the key-stationary ones (`front`
+  // of them, a multiple of 8): see side_sums.
+  int front, rel_entries, blank_blocks, strips;
+  float *rel_dtable, *dk_blank, *dv_blank;
 };
 
 // ------------------------------------------------------------------------------------------------
@@ -378,10 +382,55 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 }
 
 // ------------------------------------------------------------------------------------------------
+// What is left to add up behind the query-stationary kernel, each in a fixed order, `i` being the workgroup:
+//  rel_dtable[i] = sum over the groups of rel_part[group][i]  (i < rel_entries)
+//  dk_blank, dv_blank [H,32] = sums over the strips of blank_part: four workgroups per (head, which of the two), 8 channels
+//  each, 32 groups of 8 lanes; group j adds strips j, j + 32, ..., eight loads in flight (one at a time the few workgroups
+//  waited for one memory round trip per strip: 7.5 us at 753 strips).
+// As launches of their own, behind the key-stationary kernel, they took 5.0 us (2048 tables of 162 bins) and 3.5 us (753
+// strips, 3 heads) and the gap before them, at the end of a step; here they run beside it.
+__device__ __forceinline__ void side_sums(const BwdParams& p, int i, float* lds) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  if (i < p.rel_entries) {
+    float s = 0.f;
+    for (int t = threadIdx.x; t < p.t.groups; t += 256) s += p.rel_part[(size_t)t * p.rel_entries + i];
+    s = wave_sum(s);
+    if (lane == 0) lds[wave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) p.rel_dtable[i] = (lds[0] + lds[1]) + (lds[2] + lds[3]);
+    return;
+  }
+  i -= p.rel_entries;
+  if (i >= p.blank_blocks) return;
+  const int h = i >> 3, which = (i >> 2) & 1;
+  const int c = (i & 3) * 8 + (threadIdx.x & 7), grp = threadIdx.x >> 3;
+  float s = 0.f;
+  for (int sg0 = grp; sg0 < p.strips; sg0 += 8 * 32) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int sg = sg0 + 32 * u;
+      v[u] = p.blank_part[(((size_t)min(sg, p.strips - 1) * p.t.H + h) * 2 + which) * kD + c];
+      if (sg >= p.strips) v[u] = 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
+  lds[threadIdx.x] = s;
+  __syncthreads();
+  if (grp == 0) {
+    float t = 0.f;
+    for (int j = 0; j < 32; ++j) t += lds[j * 8 + threadIdx.x];
+    (which ? p.dv_blank : p.dk_blank)[h * kD + c] = t;
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
 // key-stationary kernel
 constexpr int kChunk = 4;  // strips in LDS at a time, one per wave to fetch; twice: the next chunk's rows fly during the math
 
-template <int CL, bool RAG>
+// FRONT: workgroups of side_sums stand in front (the test alone cost calls without them 0.7 %)
+template <int CL, bool RAG, bool FRONT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CL == 2 ? 3 : 4, CL == 2 ? 3 : 4))) void pla_bwd_key_kernel(BwdParams p) {
   constexpr int kRows = RowArray<CL>::bytes;
   constexpr int kStrip = 2048 + kRows + 64;  // q rows, dout rows, the strip's block of `hand`
@@ -390,7 +439,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CL == 2 ? 3
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform: keeps per-wave indices in SGPRs
   const int g = lane >> 4, r = lane & 15;
-  const int blk = p.block0 + xcd_contiguous_block();
+  if (FRONT && (int)blockIdx.x < p.front) {  // the whole workgroup
+    side_sums(p, blockIdx.x, reinterpret_cast<float*>(strips));
+    return;
+  }
+  const int blk = p.block0 + (FRONT ? xcd_contiguous_block(blockIdx.x - p.front, gridDim.x - p.front) : xcd_contiguous_block());
   const int gi = exact_div(blk, p.t.H, p.t.h_magic);
   if (gi >= p.t.groups) return;  // the whole workgroup
   const int h = blk - gi * p.t.H;
@@ -542,36 +595,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CL == 2 ? 3
   }
 }
 
-// dk_blank, dv_blank [H,32] = sum over the strips of their parts, in a fixed order.  One workgroup per
-// (head, which of the two): 32 groups of 32 lanes, group j adds strips j, j + 32, ..., eight loads in flight (one at a
-// time the few workgroups waited for one memory round trip per strip: 7.5 us at 753 strips, 3.8 as here).
-__global__ __launch_bounds__(1024) void pla_blank_reduce_kernel(const float* __restrict__ part, int strips, int H,
-                                                               float* __restrict__ dk_blank,
-                                                               float* __restrict__ dv_blank) {
-  __shared__ float acc[32][kD + 1];
-  const int h = blockIdx.x >> 1, which = blockIdx.x & 1;
-  const int c = threadIdx.x & 31, grp = threadIdx.x >> 5;
-  float s = 0.f;
-  for (int sg0 = grp; sg0 < strips; sg0 += 8 * 32) {
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int sg = sg0 + 32 * u;
-      v[u] = part[(((size_t)min(sg, strips - 1) * H + h) * 2 + which) * kD + c];
-      if (sg >= strips) v[u] = 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s += v[u];
-  }
-  acc[grp][c] = s;
-  __syncthreads();
-  if (grp == 0) {
-    float t = 0.f;
-    for (int j = 0; j < 32; ++j) t += acc[j][c];
-    (which ? dv_blank : dk_blank)[h * kD + c] = t;
-  }
-}
-
 // First step of the sum of the workgroups' relative-position tables [groups][H][cells]: workgroup (head, part) adds
 // its share of them, thread = (bin, one of the groups that fit 256 threads), and writes one table.
 constexpr int kRelParts = 64;
@@ -684,36 +707,42 @@ hipError_t launch_pla_bwd_cluster(const PlaArgs& a, const void* plan, void* work
 #undef AFFMAE_BWDQ_LAST
 #undef AFFMAE_BWDQ
   }
-  for (long long b0 = 0; b0 < blocks; b0 += kMaxBlocks) {
+  // up to 4096 tables of relative-position sums are added up beside the key-stationary kernel, a workgroup per bin; more take
+  // two launches of their own
+  const int cells = (2 * a.rel_R + 1) * (2 * a.rel_R + 1);
+  const bool rel_sums = a.rel_table && a.rel_part, rel_beside = rel_sums && L.groups <= 4096;
+  p.rel_entries = rel_beside ? a.H * cells : 0;
+  p.rel_dtable = a.rel_dtable;
+  p.blank_blocks = p.blank_part ? 8 * a.H : 0;
+  p.strips = L.strips;
+  p.dk_blank = a.dk_blank; p.dv_blank = a.dv_blank;
+  const int front = (p.rel_entries + p.blank_blocks + 7) / 8 * 8;
+  const long long slice = kMaxBlocks - front;
+  for (long long b0 = 0; b0 < blocks; b0 += slice) {
     p.block0 = (int)b0;
-    const dim3 grid((unsigned)((std::min(blocks - b0, kMaxBlocks) + 7) / 8 * 8));
-#define AFFMAE_BWDK(CL)                                                                                                            \
-  do {                                                                                                                            \
-    if (rag) AFFMAE_LAUNCH("pla_bwd_key_kernel", stream, (pla_bwd_key_kernel<CL, true>), grid, dim3(256), 0, stream, p);          \
-    else AFFMAE_LAUNCH("pla_bwd_key_kernel", stream, (pla_bwd_key_kernel<CL, false>), grid, dim3(256), 0, stream, p);             \
+    p.front = b0 == 0 ? front : 0;
+    const dim3 grid((unsigned)(p.front + (std::min(blocks - b0, slice) + 7) / 8 * 8));
+#define AFFMAE_BWDK_RAG(CL, RAG)                                                                                                      \
+  do {                                                                                                                                \
+    if (p.front) AFFMAE_LAUNCH("pla_bwd_key_kernel", stream, (pla_bwd_key_kernel<CL, RAG, true>), grid, dim3(256), 0, stream, p);     \
+    else AFFMAE_LAUNCH("pla_bwd_key_kernel", stream, (pla_bwd_key_kernel<CL, RAG, false>), grid, dim3(256), 0, stream, p);            \
+  } while (0)
+#define AFFMAE_BWDK(CL)                                                         \
+  do {                                                                          \
+    if (rag) AFFMAE_BWDK_RAG(CL, true); else AFFMAE_BWDK_RAG(CL, false);        \
   } while (0)
     if (cl == 0) AFFMAE_BWDK(0); else if (cl == 1) AFFMAE_BWDK(1); else AFFMAE_BWDK(2);
 #undef AFFMAE_BWDK
+#undef AFFMAE_BWDK_RAG
   }
-  if (a.rel_table && a.rel_part) {
-    const int cells = (2 * a.rel_R + 1) * (2 * a.rel_R + 1);
-    // up to 4096 tables are added up by one launch, a workgroup per bin (its reads are scattered, but the second launch of
-    // the other way costs 4.8 us whatever it does; 2048 tables of 162 bins: 5.1 us against 4.9 + 4.6)
-    hipError_t e;
-    if (L.groups <= 4096) {
-      e = launch_relpos_table_sum(a.rel_part, L.groups, a.H * cells, a.rel_dtable, stream);
-    } else {
-      float* second = reinterpret_cast<float*>(reinterpret_cast<char*>(a.rel_part) +
-                                               plan_align((size_t)L.groups * a.H * cells * sizeof(float)));
-      AFFMAE_LAUNCH("pla_rel_reduce_kernel", stream, pla_rel_reduce_kernel, dim3(a.H * kRelParts), dim3(256), 0, stream,
-                    a.rel_part, L.groups, a.H, cells, second);
-      e = launch_relpos_table_sum(second, kRelParts, a.H * cells, a.rel_dtable, stream);
-    }
+  if (rel_sums && !rel_beside) {
+    float* second = reinterpret_cast<float*>(reinterpret_cast<char*>(a.rel_part) +
+                                             plan_align((size_t)L.groups * a.H * cells * sizeof(float)));
+    AFFMAE_LAUNCH("pla_rel_reduce_kernel", stream, pla_rel_reduce_kernel, dim3(a.H * kRelParts), dim3(256), 0, stream,
+                  a.rel_part, L.groups, a.H, cells, second);
+    const hipError_t e = launch_relpos_table_sum(second, kRelParts, a.H * cells, a.rel_dtable, stream);
     if (e != hipSuccess) return e;
   }
-  if (p.blank_part)
-    AFFMAE_LAUNCH("pla_blank_reduce_kernel", stream, pla_blank_reduce_kernel, dim3(2 * a.H), dim3(1024), 0, stream,
-                  p.blank_part, L.strips, a.H, a.dk_blank, a.dv_blank);
   return hipGetLastError();
 }
 
