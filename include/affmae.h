@@ -317,10 +317,13 @@ int affmae_pla_plan(const int32_t* nbr_idx, const int32_t* near_clusters, int B,
  *                     of near_clusters[b,c,:], and that a token's neighbours
  *                     are pairwise distinct - what affmae_knn produces with
  *                     cluster_id == NULL.  It allows the cluster-tiled kernels
- *                     (bf16 storage, d == 32, S % 16 == 0, any N,
- *                     M*S <= 1024; other shapes, head sizes 16 and 64 among them,
- *                     are served by the slower gather kernels, same results);
- *                     inputs must then be finite.  With NULL, S and M are ignored.
+ *                     (S % 16 == 0, any N, M*S <= 1024): those for bf16 storage
+ *                     and d == 32 always, those for fp32 storage and for head sizes
+ *                     16 and 64, whose products are fp32 throughout, in calls that
+ *                     bring a plan and are large enough (B * ceil(N/64) * H >= 256;
+ *                     fp32, d >= 32: K >= 16).  Other calls are served by the
+ *                     slower gather kernels, same results.
+ *                     Inputs must then be finite.  With NULL, S and M are ignored.
  *   plan          in  NULL, or the buffer affmae_pla_plan filled for this
  *                     nbr_idx / near_clusters and these B,N,K,S,M.
  *   k_blank,v_blank in [H,d] of `dtype`, or both NULL.
@@ -350,8 +353,9 @@ int affmae_pla_fwd(const void* q, const void* k, const void* v, const void* bias
  *
  *   inputs as affmae_pla_fwd, plus
  *   out           in  [B,N,H,d] of `dtype`: forward output.  Required by the
- *                     cluster-tiled kernels (they take D = <dout, out>); the
- *                     gather kernels rebuild D from p and dP and accept NULL.
+ *                     cluster-tiled kernels for bf16 and d == 32 (they take
+ *                     D = <dout, out>); with NULL other calls are served by the
+ *                     gather kernels, which rebuild D from p and dP.
  *   lse           in  [B,N,H] fp32 from the forward call.
  *   dout          in  [B,N,H,d] of `dtype`.
  *   dq,dk,dv      out [B,N,H,d] of `dtype`; sums are formed in fp32.  The order

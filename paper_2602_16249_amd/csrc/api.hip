@@ -366,7 +366,8 @@ int pla_fwd_run(const void* q, const void* k, const void* v, const void* bias, c
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (!affmae::pla_cluster_supported(a)) {
     if (!launch) return AFFMAE_OK;
-    return affmae::launch_pla_fwd_general(a, st) == hipSuccess ? AFFMAE_OK : AFFMAE_ERR_DEVICE;
+    const hipError_t e = affmae::pla_fwd_wide_supported(a, plan) ? affmae::launch_pla_fwd_wide(a, plan, st) : affmae::launch_pla_fwd_general(a, st);
+    return e == hipSuccess ? AFFMAE_OK : AFFMAE_ERR_DEVICE;
   }
   if (plan && misaligned(plan, kAlign)) return AFFMAE_ERR_WORKSPACE;
   if (!plan) {  // no cached plan: rebuild it in the workspace
@@ -452,7 +453,8 @@ int pla_bwd_run(const void* q, const void* k, const void* v, const void* bias, c
   const size_t need = align_up(affmae::pla_bwd_general_workspace_bytes(B, N, H, K));
   if (!workspace || workspace_bytes < need) return AFFMAE_ERR_WORKSPACE;
   if (!launch) return AFFMAE_OK;
-  return affmae::launch_pla_bwd_general(a, st) == hipSuccess ? AFFMAE_OK : AFFMAE_ERR_DEVICE;
+  const hipError_t e = affmae::pla_bwd_wide_supported(a, plan) ? affmae::launch_pla_bwd_wide(a, plan, st) : affmae::launch_pla_bwd_general(a, st);
+  return e == hipSuccess ? AFFMAE_OK : AFFMAE_ERR_DEVICE;
 }
 }  // namespace
 

@@ -165,4 +165,10 @@ bool pla_bwd_cluster_rel_sums(int R);  // the table is small enough for the back
 size_t pla_bwd_cluster_rel_workspace_bytes(int B, int N, int H, int R);
 hipError_t launch_pla_bwd_cluster(const PlaArgs& a, const void* plan, void* workspace, hipStream_t stream);
 
+// The same on fp32 operands (fp32 storage; bf16 with d = 16, 64), where a plan is given and the call is large enough.
+bool pla_fwd_wide_supported(const PlaArgs& a, const void* plan);
+bool pla_bwd_wide_supported(const PlaArgs& a, const void* plan);
+hipError_t launch_pla_fwd_wide(const PlaArgs& a, const void* plan, hipStream_t stream);
+hipError_t launch_pla_bwd_wide(const PlaArgs& a, const void* plan, hipStream_t stream);
+
 }  // namespace affmae

@@ -594,3 +594,27 @@ def test_plans_with_room_for_less_than_the_near_clusters(B, N, K, S, M):
             nbr[b, i] = rng.choice(cand[cand < N], K, replace=False)
     w = make_features(B, N, 2, 32, K, "bf16", rng, blank=True)
     check_attention(w, nbr, "bf16", 0.2, near=near, S=S, M=M, blank=True, use_plan=True)
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 16), ("f32", 32), ("f32", 64), ("bf16", 16), ("bf16", 64)])
+@pytest.mark.parametrize("B,N,H,K,S,M,blank", [  # (at least 256 workgroups: below, the gather kernels serve these calls)
+    (8, 1024, 2, 48, 64, 8, False),
+    (6, 1000, 3, 37, 64, 8, True),    # a short last strip and token tile, odd K and H
+    (32, 512, 1, 64, 16, 32, True),   # the longest rows; unions of many stages
+    (64, 90, 2, 16, 48, 2, False),    # a group of two strips, the last one short
+    (4, 4099, 1, 24, 32, 6, True),
+    (2, 2064, 5, 33, 64, 5, False),   # the last group of one strip
+    (2, 2051, 4, 1, 64, 2, True),     # K = 1: the shortest rows (fp32: the gather kernels from d = 32 on)
+    (2, 2051, 4, 16, 64, 3, True),    # the fewest neighbours that fp32 takes here
+])
+def test_plans_for_other_types_and_heads(dtype, d, B, N, H, K, S, M, blank):
+    """fp32 storage, and bf16 with head sizes other than 32, on a plan: products on fp32 operands.  The bar of the gather
+    kernels (1e-5 and 2e-2 of the largest value), and scores spread so widely that the reference has to move."""
+    print(f"case wide {dtype} d={d} B={B} N={N} H={H} K={K} S={S} M={M} blank={blank}", flush=True)
+    cfg = CONFIGS["knn_scale" if N % 16 else "mae_pt_s1_1024"].scaled(B=B, N=N, C=H * d, H=H, K=K, S=S, M=M, dtype=dtype)
+    w = make_workload(cfg, blank=blank)
+    nbr, near = oracle.knn(w["coords"], None, S, M, K)
+    check_attention(w, nbr, dtype, 1.0 / np.sqrt(d), near=near, S=S, M=M, blank=blank, use_plan=True)
+    # logits with a standard deviation of 8: scores below 64, whose products and sum round to 2^-19 a few times over, as does lse, so
+    # that p = exp(s - lse) is off by up to 1e-5; p (dP - D) and its sums over terms of both signs by a few times that
+    check_attention(w, nbr, dtype, 8.0 / np.sqrt(d), near=near, S=S, M=M, blank=blank, use_plan=True, tol=4e-5 if dtype == "f32" else None)
