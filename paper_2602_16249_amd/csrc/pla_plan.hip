@@ -10,6 +10,7 @@
 #include "timing.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace affmae {
 namespace {
@@ -45,14 +46,43 @@ __global__ __launch_bounds__(256) void plan_zero_kernel(int32_t* a, int32_t* b, 
   }
 }
 
-// NE = entries per lane: 16 K / 64 rounded up to a multiple of 4 (the loops over a lane's entries are unrolled).
-// Bound by the chain of its steps (neighbour ids from memory, the near clusters one by one, two exchanges between the
-// group's waves); the pairs go to their bytes by plain LDS stores.
+// inclusive prefix sum over the wave (all lanes active)
+__device__ __forceinline__ int wave_prefix(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+// A strip's candidate tiles are those of its near clusters, numbered by cluster and place (at most 64).  NE = entries per
+// lane: 16 K / 64 rounded up to a multiple of 4 (the loops over a lane's entries are unrolled); the four lanes of a query
+// share its list.  The pairs go to their bytes by plain LDS stores.
+// Bound by the vector ALU, so whatever can be looked up in LDS is: TABLE, for images of at most kTableTiles token tiles,
+// finds an entry's candidate by its tile in a table of bytes, the candidates in use by marks, an entry's slot in a table
+// by candidate, and the places in the group's union by the prefix sum of a bit map of the image's tiles.  Without it an
+// entry's cluster is compared with every near one, and a tile's place is searched in the lists of the group's strips.
+// Whole plan, K = 48, S = 64, M = 8, with comparisons and searches throughout and now: 16 images of 16384 tokens 51.5 and
+// 31.2 us (the kernel itself 42 and 21.5, 1230 and 480 vector instructions a strip), 16 of 4096 22.0 and 15.2, one of 1024
+// 13.7 and 10.6; 4 images of 57344, the most that the table's place in LDS allows, 53.7 and 37.3, of 57360 54.1 and 48.2.
 constexpr int kJtSlots = 16;  // slots whose j tiles are assembled in LDS at a time (4 KB per strip); few strips have more
-template <int NE>
+constexpr int kTableTiles = 3584;
+constexpr uint32_t kNoCandidate = 64, kNoPlace = 0xffff;
+struct StripTables {            // in LDS, where the j tiles are assembled afterwards
+  uint8_t candidate[kTableTiles];  // by token tile of the image
+  uint8_t mark[128];               // by candidate
+  uint16_t at[128];                // by candidate: where its slot's bytes start among the j tiles
+};
+static_assert(sizeof(StripTables) <= kJtSlots * 256 && kTableTiles % 16 == 0 && kTableTiles <= 64 * kWave, "");
+__device__ __forceinline__ uint32_t slot_start(int slot) { return (uint32_t)((slot >> 1) * 512 + (slot & 1) * 4); }
+
+template <int NE, bool TABLE>
 __global__ __launch_bounds__(256) void pla_plan_kernel(PlanParams p) {
   __shared__ __align__(16) uint8_t jt_all[kGroup][kJtSlots * 256];
   __shared__ uint16_t tiles_all[kGroup][kMaxSlots];
+  __shared__ __align__(8) uint32_t map_all[TABLE ? kGroup : 1][2 * kWave];  // TABLE: a strip's tiles, a bit each
   __shared__ int count_all[kGroup];
   __shared__ unsigned long long fresh_all[kGroup];
   const int lane = threadIdx.x & (kWave - 1);
@@ -66,80 +96,135 @@ __global__ __launch_bounds__(256) void pla_plan_kernel(PlanParams p) {
   const int c = fast_div(q0, p.s_magic);
   const int32_t* near_c = p.near + ((size_t)b * p.G + c) * p.M;
   const int tpc = p.S / 16;  // token tiles per cluster
-  const int nent_real = there ? min(16, p.N - q0) * p.K : 0;  // the image's last strip may hold fewer than 16 queries
+  const int queries = there ? min(16, p.N - q0) : 0;  // the image's last strip may hold fewer than 16
+  const int q = lane >> 2, j0 = lane & 3;  // this lane: places j0, j0 + 4, ... of the list of query q
   const int32_t* nbr = p.nbr_idx + ((size_t)b * p.N + q0) * p.K;
+  const uint32_t row = (uint32_t)(min(q, max(queries, 1) - 1) * p.K);
+  uint8_t* jt = jt_all[wave];
+  StripTables& table = *reinterpret_cast<StripTables*>(jt);
 
-  // candidate tile of every (query, neighbour): clusters in ascending order, (token % S) / 16 inside
   const int near_v = (lane < p.M) ? near_c[lane] : 0x7fffffff;  // lane m: the m-th near cluster (M <= 64)
-  int ecl[NE], sub[NE], ct[NE];
+  int tok[NE];
   bool inr[NE];
 #pragma unroll
+  for (int t = 0; t < NE; ++t) tok[t] = nbr[row + (uint32_t)min(4 * t + j0, p.K - 1)];
+#pragma unroll
   for (int t = 0; t < NE; ++t) {
-    const int e = t * kWave + lane;
-    const int n = (e < nent_real) ? nbr[e] : -1;  // queries past the end have no entries
-    const int nn = min(max(n, 0), p.N - 1);
-    inr[t] = n == nn;
-    ecl[t] = fast_div(nn, p.s_magic);
-    sub[t] = nn - ecl[t] * p.S;
-    ct[t] = -1;
+    const int n = tok[t];
+    tok[t] = min(max(n, 0), p.N - 1);
+    inr[t] = n == tok[t] && 4 * t + j0 < p.K && q < queries;  // queries past the end have no entries
   }
-  int rank = 0;  // lane m: place of the m-th near cluster among them by number
-  for (int m = 0; m < p.M; ++m) {
-    const int cl = __builtin_amdgcn_readlane(near_v, m);
-    rank += (cl < near_v || (cl == near_v && m < lane)) ? 1 : 0;
-  }
-  int cl_sorted = 0;  // lane c: the cluster of candidate tile c
+  // candidate tile of every (query, neighbour): clusters in ascending order, (token % S) / 16 inside
   const int lane_m = fast_div(lane, p.tpc_magic);
-  for (int m = 0; m < p.M; ++m) {
-    const int cl = __builtin_amdgcn_readlane(near_v, m), rk = __builtin_amdgcn_readlane(rank, m);
-    cl_sorted = (lane_m == rk) ? cl : cl_sorted;
+  int rank = 0;  // lane m: near clusters below the m-th one
+  for (int m = 0; m < p.M; ++m) rank += __builtin_amdgcn_readlane(near_v, m) < near_v ? 1 : 0;
+  const bool known = (uint32_t)near_v < (uint32_t)p.G;
+  // lane c: the cluster of candidate c (one that is there twice goes to one place; -1: none)
+  const int cl_by_rank = __builtin_amdgcn_ds_permute(rank << 2, known ? near_v + 1 : 0) - 1;
+  const int cl = __builtin_amdgcn_ds_bpermute(lane_m << 2, cl_by_rank);
+  const int my_tile = cl * tpc + (lane - lane_m * tpc);  // of candidate `lane`, within the image
+  uint32_t at[NE];  // where an entry's byte lies among the j tiles
+  unsigned long long mask;  // candidates in use
+  if constexpr (TABLE) {
+    for (int i = lane; i < (p.strips_per_image + 15) / 16; i += kWave)
+      reinterpret_cast<u32x4*>(table.candidate)[i] = (u32x4)(kNoCandidate * 0x01010101u);
+    table.mark[lane] = 0;
+    *reinterpret_cast<unsigned long long*>(&map_all[wave][2 * lane]) = 0ull;
+    wave_lds_sync();
+    if (lane < p.M * tpc && cl >= 0 && my_tile < p.strips_per_image) table.candidate[my_tile] = (uint8_t)lane;
+    wave_lds_sync();
 #pragma unroll
-    for (int t = 0; t < NE; ++t) ct[t] = (ecl[t] == cl) ? rk * tpc : ct[t];
-  }
-  unsigned long long mask = 0;
+    for (int t = 0; t < NE; ++t) {
+      at[t] = table.candidate[tok[t] >> 4];
+      at[t] = inr[t] ? at[t] : kNoCandidate;
+    }
 #pragma unroll
-  for (int t = 0; t < NE; ++t) {
-    if (inr[t] && ct[t] >= 0) {
-      ct[t] += sub[t] >> 4;
-      mask |= 1ull << ct[t];
-    } else {
+    for (int t = 0; t < NE; ++t) table.mark[at[t]] = 1;
+    wave_lds_sync();
+    mask = __builtin_amdgcn_ballot_w64(table.mark[lane] != 0);
+  } else {
+    int ecl[NE], ct[NE];
+#pragma unroll
+    for (int t = 0; t < NE; ++t) {
+      ecl[t] = fast_div(tok[t], p.s_magic);
       ct[t] = -1;
     }
+    for (int m = 0; m < p.M; ++m) {
+      const int near_m = __builtin_amdgcn_readlane(near_v, m), rk = __builtin_amdgcn_readlane(rank, m);
+#pragma unroll
+      for (int t = 0; t < NE; ++t) ct[t] = (ecl[t] == near_m) ? rk * tpc : ct[t];
+    }
+    mask = 0;
+#pragma unroll
+    for (int t = 0; t < NE; ++t) {
+      const int cand = ct[t] + ((tok[t] - ecl[t] * p.S) >> 4);
+      const bool there_t = inr[t] && ct[t] >= 0;
+      mask |= there_t ? 1ull << cand : 0ull;
+      at[t] = there_t ? (uint32_t)cand : kNoCandidate;
+    }
+    mask = wave_or64(mask);
   }
-  mask = wave_or64(mask);
   const int count = __popcll(mask);
-  const int my_tile = cl_sorted * tpc + (lane - lane_m * tpc);  // of candidate `lane`, within the image
-  if ((mask >> lane) & 1ull) tiles_all[wave][__popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)my_tile;
-  if (lane == 0) count_all[wave] = count;
+  const bool used = (mask >> lane) & 1ull;
+  const int my_slot = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+  if (used) tiles_all[wave][my_slot] = (uint16_t)my_tile;
+  if constexpr (TABLE) {
+    if (used) atomicOr(&map_all[wave][my_tile >> 5], 1u << (my_tile & 31));
+    table.at[lane] = (uint16_t)slot_start(my_slot);
+    if (lane == 0) table.at[kNoCandidate] = (uint16_t)kNoPlace;
+    wave_lds_sync();
+#pragma unroll
+    for (int t = 0; t < NE; ++t) at[t] = table.at[at[t]];
+  } else {
+#pragma unroll
+    for (int t = 0; t < NE; ++t)
+      at[t] = at[t] == kNoCandidate ? kNoPlace : slot_start(__popcll(mask & ((1ull << at[t]) - 1ull)));
+    if (lane == 0) count_all[wave] = count;
+  }
   __syncthreads();
-  // lane s: slot s.  Its tile's place in every strip's list by binary search; a strip is the first of the group to have
-  // the tile if no earlier one does, and the place in the union is the number of firsts below.
+  // lane s: slot s, and its tile's place in the union of the group's strips
   const int T = lane < count ? (int)tiles_all[wave][lane] : 0x10000;
-  int lb[kGroup];
-  bool fresh = lane < count;
-#pragma unroll
-  for (int v = 0; v < kGroup; ++v) {
-    const int n = count_all[v];
-    int at = 0;
-#pragma unroll
-    for (int step = 32; step > 0; step >>= 1)
-      if (at + step <= n && (int)tiles_all[v][at + step - 1] < T) at += step;
-    if (at < n && (int)tiles_all[v][at] < T) ++at;  // (the steps add up to 63, a list may hold 64)
-    lb[v] = at;
-    if (v < wave && at < n && (int)tiles_all[v][at] == T) fresh = false;
-  }
-  const unsigned long long fm = __ballot(fresh);
-  if (lane == 0) fresh_all[wave] = fm;
-  __syncthreads();
-  int place = 0, U = 0;
-#pragma unroll
-  for (int v = 0; v < kGroup; ++v) {
-    const unsigned long long f = fresh_all[v];
-    place += __popcll(lb[v] >= kWave ? f : (f & ((1ull << lb[v]) - 1ull)));
-    U += __popcll(f);
-  }
+  int place, U;
   uint16_t* uni = p.uni + (size_t)gi * p.uni_stride;
-  if (fresh) uni[1 + place] = (uint16_t)T;
+  if constexpr (TABLE) {
+    unsigned long long all = 0ull;  // lane i: tiles 64 i .. 64 i + 63
+#pragma unroll
+    for (int v = 0; v < kGroup; ++v) all |= *reinterpret_cast<const unsigned long long*>(&map_all[v][2 * lane]);
+    const int n = __popcll(all), upto = wave_prefix(n);
+    U = __builtin_amdgcn_readlane(upto, kWave - 1);
+    const int from = (T >> 6) << 2;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)all);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(all >> 32));
+    place = __builtin_amdgcn_ds_bpermute(from, upto - n) + __popcll((((unsigned long long)hi << 32) | lo) & ((1ull << (T & 63)) - 1ull));
+    if (lane < count) uni[1 + place] = (uint16_t)T;  // (from every strip that touches it)
+  } else {
+    // a tile's place in every strip's list by binary search; a strip is the first of the group to have the tile if no
+    // earlier one does, and the place in the union is the number of firsts below
+    int lb[kGroup];
+    bool fresh = lane < count;
+#pragma unroll
+    for (int v = 0; v < kGroup; ++v) {
+      const int n = count_all[v];
+      int low = 0;
+#pragma unroll
+      for (int step = 32; step > 0; step >>= 1)
+        if (low + step <= n && (int)tiles_all[v][low + step - 1] < T) low += step;
+      if (low < n && (int)tiles_all[v][low] < T) ++low;  // (the steps add up to 63, a list may hold 64)
+      lb[v] = low;
+      if (v < wave && low < n && (int)tiles_all[v][low] == T) fresh = false;
+    }
+    const unsigned long long fm = __ballot(fresh);
+    if (lane == 0) fresh_all[wave] = fm;
+    __syncthreads();
+    place = 0, U = 0;
+#pragma unroll
+    for (int v = 0; v < kGroup; ++v) {
+      const unsigned long long f = fresh_all[v];
+      place += __popcll(lb[v] >= kWave ? f : (f & ((1ull << lb[v]) - 1ull)));
+      U += __popcll(f);
+    }
+    if (fresh) uni[1 + place] = (uint16_t)T;
+  }
   if (wave == 0 && lane == 0) {
     uni[0] = (uint16_t)max(U, 1);  // (no tile at all only where the near clusters are not the table's: one that nobody uses)
     if (U == 0) uni[1] = (uint16_t)(q0 >> 4);
@@ -166,23 +251,18 @@ __global__ __launch_bounds__(256) void pla_plan_kernel(PlanParams p) {
   }
   if (lane == 0) touch[0] = (unsigned long long)__popcll(sm);
   // j tiles
-  uint8_t* jt = jt_all[wave];
   u32x4* out = reinterpret_cast<u32x4*>(p.jt + sg * p.jt_pairs * 512);
   const uint32_t none = 2u * (uint32_t)p.K * 0x01010101u;
+#pragma unroll
+  for (int t = 0; t < NE; ++t) at[t] += (uint32_t)(((tok[t] & 12) << 5) | (tok[t] & 3)) + (uint32_t)q * 8u;
   for (int s0 = 0; s0 < count; s0 += kJtSlots) {
     const int ns = min(kJtSlots, (count - s0 + 1) & ~1);  // the second half of the last pair holds no neighbours
     for (int i = lane; i < ns * 16; i += kWave) reinterpret_cast<u32x4*>(jt)[i] = u32x4{none, none, none, none};
     wave_lds_sync();
 #pragma unroll
     for (int t = 0; t < NE; ++t) {
-      if (ct[t] >= 0) {
-        const int slot = __popcll(mask & ((1ull << ct[t]) - 1ull)) - s0;
-        if (slot >= 0 && slot < kJtSlots) {
-          const int e = t * kWave + lane;
-          const int q = fast_div(e, p.k_magic), j = e - q * p.K, tok = sub[t] & 15;
-          jt[(slot >> 1) * 512 + ((tok >> 2) * 16 + q) * 8 + (slot & 1) * 4 + (tok & 3)] = (uint8_t)(2 * j);
-        }
-      }
+      const uint32_t here = at[t] - (uint32_t)s0 * 256u;
+      if (here < kJtSlots * 256u) jt[here] = (uint8_t)(2 * (4 * t + j0));
     }
     wave_lds_sync();
     for (int i = lane; i < ns * 16; i += kWave) out[s0 * 16 + i] = reinterpret_cast<const u32x4*>(jt)[i];
@@ -297,7 +377,8 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(PlanParams p) {
 // Bound by the chain of these steps in each workgroup, which grows with the image's tiles, against counting with atomics
 // in the strip kernel and four more launches (zero, scan, fill, sort: 4 - 6 us each, of the whole batch).  Whole plan, K =
 // 48, one launch and four: one image of 64 / 256 / 512 / 1024 tiles 14 / 15 / 16 / 17 us and 19 / 19 / 20 / 20 us; 1024
-// tiles, 4 / 8 / 16 / 32 images 24 / 34 / 50 / 85 us and 28 / 38 / 57 / 94 us.  (With the touch tables read twice and the
+// tiles, 4 / 8 / 16 / 32 images 24 / 34 / 50 / 85 us and 28 / 38 / 57 / 94 us, both with a strip kernel that took 3 to 40 us
+// longer.  (With the touch tables read twice and the
 // lists sorted in memory 28 / 37 / 54 / 93 us; with a list per token tile instead of per group, and the pairs of every
 // strip sorted by tile, 30 / 42 / 62 / 102 us; with a list's places from broadcast lanes instead of LDS reads, as now, 0.5 -
 // 0.8 us less than the figures above.)  Beyond 1024 tiles a thread would serve several strips.
@@ -417,10 +498,12 @@ hipError_t launch_pla_plan(const int32_t* nbr_idx, const int32_t* near, int B, i
   for (long long g0 = 0; g0 < L.groups; g0 += kMaxBlocks) {
     p.group0 = (int)g0;
     const dim3 grid((unsigned)std::min((long long)L.groups - g0, kMaxBlocks));
-    if (ne <= 4) AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<4>, grid, dim3(256), 0, stream, p);
-    else if (ne <= 8) AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<8>, grid, dim3(256), 0, stream, p);
-    else if (ne <= 12) AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<12>, grid, dim3(256), 0, stream, p);
-    else AFFMAE_LAUNCH("pla_plan_kernel", stream, pla_plan_kernel<kMaxEntries>, grid, dim3(256), 0, stream, p);
+    auto kernel = [&](auto table) {
+      return ne <= 4 ? pla_plan_kernel<4, table.value> : ne <= 8 ? pla_plan_kernel<8, table.value>
+             : ne <= 12 ? pla_plan_kernel<12, table.value> : pla_plan_kernel<kMaxEntries, table.value>;
+    };
+    AFFMAE_LAUNCH("pla_plan_kernel", stream, (L.strips_per_image <= kTableTiles ? kernel(std::true_type{}) : kernel(std::false_type{})),
+                  grid, dim3(256), 0, stream, p);
   }
   if (!p.count_groups) {
     AFFMAE_LAUNCH("plan_reverse_kernel", stream, plan_reverse_kernel, dim3((unsigned)shares), dim3(kRevThreads), 0, stream, p, own);

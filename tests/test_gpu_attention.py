@@ -596,6 +596,24 @@ def test_plans_with_room_for_less_than_the_near_clusters(B, N, K, S, M):
     check_attention(w, nbr, "bf16", 0.2, near=near, S=S, M=M, blank=True, use_plan=True)
 
 
+@pytest.mark.parametrize("N", [57344, 57349, 57327])
+@pytest.mark.parametrize("K,S,M", [(13, 64, 16), (3, 16, 1)])
+def test_plans_on_both_sides_of_the_tile_table(N, K, S, M):
+    """Images of 3584 token tiles, the most whose tiles the plan kernel looks up in LDS, of one more, and with a short last tile:
+    as many candidate tiles as there may be, in distant clusters, and one; lists that are no multiple of a query's four lanes."""
+    print(f"case tile table N={N} K={K} S={S} M={M}", flush=True)
+    rng = np.random.default_rng(N + K)
+    G = -(-N // S)
+    own = np.arange(G)
+    near = np.stack([own] + [(own + 1 + i * (G // M)) % G for i in range(M - 1)], axis=1).astype(np.int32)
+    near = rng.permuted(near, axis=1)
+    cand = (near[:, :, None] * S + np.arange(S)).reshape(G, M * S)
+    pick = np.argsort(rng.random((N, M * S), dtype=np.float32) + 2.0 * (cand[np.arange(N) // S] >= N), axis=1)[:, :K]
+    nbr = np.take_along_axis(cand[np.arange(N) // S], pick, axis=1).astype(np.int32)[None]
+    w = make_features(1, N, 1, 32, K, "bf16", rng)
+    check_attention(w, nbr, "bf16", 0.2, near=near[None], S=S, M=M, use_plan=True)
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 16), ("f32", 32), ("f32", 64), ("bf16", 16), ("bf16", 64)])
 @pytest.mark.parametrize("B,N,H,K,S,M,blank", [  # (at least 256 workgroups: below, the gather kernels serve these calls)
     (8, 1024, 2, 48, 64, 8, False),
