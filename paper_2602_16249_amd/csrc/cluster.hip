@@ -244,35 +244,67 @@ __global__ __launch_bounds__(kSortThreads) void cluster_sort_chunk_lds_kernel(Cl
   for (int t = threadIdx.x; t < kChunk; t += kSortThreads) out[t] = buf[lds_place(t)] ^ flip;
 }
 
-// Order of an image whose `chunks` (2 .. 16) chunks are sorted: a word's place is its place in its chunk plus, for
-// every other chunk, the number of smaller words there, found by binary search: 6 steps on every 32nd word of the chunk
-// (in LDS), 5 on the words between (the lanes of a wave hold neighbouring words, so they read neighbouring places).
-// Replaces the seven further launches of the network at 8 chunks (16 images of 16384 tokens: 26 us with both kernels, 49 us
-// with the network; one image of 32768 tokens, 16 chunks, 27 us against 53; of 32769 by the network 80).  The line at 16
-// keeps the workgroup's samples at 8 KB of LDS; the ranks would still be the faster way a little beyond.
+// Number of words below `word` in each of the chunks first .. first + U - 1 behind chunk `own` (cyclically; those from
+// `others` + 1 on are not counted), added up: by binary search, 6 steps on every 32nd word of a chunk (in LDS), 5 on the
+// words between (the lanes of a wave hold neighbouring words, so they read neighbouring places).  The steps of the U
+// searches alternate: each is a chain of reads.
 constexpr int kMaxRankChunks = 16;
+template <int U>
+__device__ __forceinline__ int count_in_chunks(const word_t (&split)[kMaxRankChunks][64], const word_t* w, int chunks, int own,
+                                               int first, word_t word) {
+  int c[U], s[U], n[U];
+  const word_t* from[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    c[u] = own + min(first + u, chunks - 1);
+    c[u] -= c[u] >= chunks ? chunks : 0;
+    s[u] = n[u] = 0;
+  }
+#pragma unroll
+  for (int step = 32; step >= 1; step >>= 1)
+#pragma unroll
+    for (int u = 0; u < U; ++u) s[u] += split[c[u]][s[u] + step - 1] < word ? step : 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    s[u] += split[c[u]][s[u]] < word ? 1 : 0;  // (s <= 63 here)
+    from[u] = w + (size_t)c[u] * kChunk + max(s[u] - 1, 0) * 32 + 1;
+  }
+  // words below it among the 31 after the last such
+#pragma unroll
+  for (int step = 16; step >= 1; step >>= 1)
+#pragma unroll
+    for (int u = 0; u < U; ++u) n[u] += from[u][n[u] + step - 1] < word ? step : 0;
+  int count = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) count += s[u] == 0 || first + u >= chunks ? 0 : (s[u] - 1) * 32 + 1 + n[u];
+  return count;
+}
+
+// Order of an image whose `chunks` (2 .. 16) chunks are sorted: a word's place is its place in its chunk plus, for
+// every other chunk, the number of smaller words there.
+// Replaces the seven further launches of the network at 8 chunks (16 images of 16384 tokens: 23 us with both kernels, 49 us
+// with the network; one image of 32768 tokens, 16 chunks, 21 us against 53; of 32769 by the network 80).  The line at 16
+// keeps the workgroup's samples at 8 KB of LDS; the ranks would still be the faster way a little beyond.
+// Bound by the chains of reads and by the scattered writes of the order and the clusters: 16 images of 8 chunks 13.8 us with
+// one search after the other, 11.9 with seven at a time, 10.0 with an image's workgroups on one XCD, whose L2 then joins the
+// writes to a line (and reads the words once).  (Comparing 32-bit keys, as earlier chunks have the lower numbers: 10 - 10.6.)
 __global__ __launch_bounds__(256) void cluster_rank_kernel(ClusterParams p, int chunks) {
   __shared__ word_t split[kMaxRankChunks][64];
-  const int b = blockIdx.y;
+  // (an image has 8 workgroups per chunk)
+  const unsigned block = (unsigned)xcd_contiguous_block(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+  const int b = block / gridDim.x, part = block - b * gridDim.x;
   const word_t* w = p.words + (size_t)b * p.npad;
+  const int at = part * 256 + threadIdx.x;  // place among the chunks' words (a workgroup stays inside one chunk)
+  const int own = part / (kChunk / 256);
+  const word_t word = w[at];
   for (int i = threadIdx.x; i < chunks * 64; i += 256) split[i >> 6][i & 63] = w[(size_t)i * (kChunk / 64)];
   __syncthreads();
-  const int at = blockIdx.x * 256 + threadIdx.x;  // place among the chunks' words (a workgroup stays inside one chunk)
-  const int own = (blockIdx.x * 256) / kChunk;
-  const word_t word = w[at];
   int place = at - own * kChunk;
-  for (int c = 0; c < chunks; ++c) {
-    if (c == own) continue;  // uniform
-    int s = 0;  // words of `split` below the word
-#pragma unroll
-    for (int step = 32; step >= 1; step >>= 1) s += split[c][s + step - 1] < word ? step : 0;
-    s += split[c][s] < word ? 1 : 0;  // (s <= 63 here)
-    int n = 0;  // words below it among the 31 after the last such
-    const word_t* from = w + (size_t)c * kChunk + max(s - 1, 0) * 32 + 1;
-#pragma unroll
-    for (int step = 16; step >= 1; step >>= 1) n += from[n + step - 1] < word ? step : 0;
-    place += s == 0 ? 0 : (s - 1) * 32 + 1 + n;
-  }
+  if (chunks == 2) place += count_in_chunks<1>(split, w, chunks, own, 1, word);
+  else if (chunks <= 5) place += count_in_chunks<4>(split, w, chunks, own, 1, word);
+  else if (chunks <= 8) place += count_in_chunks<7>(split, w, chunks, own, 1, word);
+  else
+    for (int o = 1; o < chunks; o += 8) place += count_in_chunks<8>(split, w, chunks, own, o, word);
   if (word != ~0ull) emit(p, b, word, place);
 }
 

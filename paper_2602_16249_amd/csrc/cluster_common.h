@@ -139,6 +139,13 @@ __device__ __forceinline__ int exact_div(int n, int d, uint32_t magic) {
   return (int)(q - (q * (uint32_t)d > (uint32_t)n ? 1u : 0u));
 }
 
+// Workgroups are dealt round-robin to the 8 XCDs (one L2 each); where neighbouring ones share what they read or write,
+// give every XCD a contiguous range.  The grid is a multiple of 8.
+__device__ __forceinline__ int xcd_contiguous_block(unsigned block, unsigned blocks) {
+  const int per_xcd = blocks >> 3;
+  return (block & 7) * per_xcd + (block >> 3);
+}
+
 __device__ __forceinline__ uint32_t wave_or32(uint32_t x) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) x |= __shfl_xor(x, o);

@@ -83,12 +83,7 @@ __device__ __forceinline__ f32x4 mfma16(const Frag4& a, const Frag4& b, f32x4 c)
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a.v, b.v, c, 0, 0, 0);
 }
 
-// Workgroups are dealt round-robin to the 8 XCDs (one L2 each); neighbouring groups share rows, so give every XCD a
-// contiguous range.  The grid is a multiple of 8.
-__device__ __forceinline__ int xcd_contiguous_block(unsigned block, unsigned blocks) {
-  const int per_xcd = blocks >> 3;
-  return (block & 7) * per_xcd + (block >> 3);
-}
+// (see xcd_contiguous_block(block, blocks): neighbouring groups share rows)
 __device__ __forceinline__ int xcd_contiguous_block() { return xcd_contiguous_block(blockIdx.x, gridDim.x); }
 
 // The wave's strip, and the tiles of its group.  PL: places for tiles in LDS, RAG: N is not a multiple of 16 (only then
