@@ -396,7 +396,8 @@ __global__ __launch_bounds__(kRevThreads) void plan_reverse_kernel(PlanParams p,
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int gpi = p.groups_per_image;
   const int shares = (gpi + own - 1) / own;
-  const int b = blockIdx.x / shares, first = (blockIdx.x - b * shares) * own, last = min(first + own, gpi);
+  const int block = gridDim.x % 8 == 0 ? xcd_contiguous_block(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int b = block / shares, first = (block - b * shares) * own, last = min(first + own, gpi);
   const size_t strip0 = (size_t)b * p.strips_per_image;
   const unsigned long long* row = p.touch + (strip0 + min(tid, p.strips_per_image - 1)) * p.touch_stride;
   unsigned long long w[1 + kRevInline];
