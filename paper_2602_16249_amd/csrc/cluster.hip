@@ -5,7 +5,7 @@
 //
 // Per image the tokens are sorted by the 64-bit word (curve key << 32 | token
 // index): unique words, so the order is exact and ties go to the lower index.
-// Chunks of up to 2048 words are sorted by one workgroup each (a bitonic network
+// Chunks of 512, 1024 or 2048 words are sorted by one workgroup each (a bitonic network
 // whose words stay in registers, or in LDS where there are very many chunks).  Up
 // to 16 chunks an image's order then follows in one more launch: a word's place is
 // its place in its chunk plus the number of smaller words in every other chunk (binary
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kSortThreads) void cluster_sort_chunk_lds_kernel(Cl
 // words between (the lanes of a wave hold neighbouring words, so they read neighbouring places).  The steps of the U
 // searches alternate: each is a chain of reads.
 constexpr int kMaxRankChunks = 16;
-template <int U>
+template <int CH, int U>
 __device__ __forceinline__ int count_in_chunks(const word_t (&split)[kMaxRankChunks][64], const word_t* w, int chunks, int own,
                                                int first, word_t word) {
   int c[U], s[U], n[U];
@@ -267,16 +267,16 @@ __device__ __forceinline__ int count_in_chunks(const word_t (&split)[kMaxRankChu
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     s[u] += split[c[u]][s[u]] < word ? 1 : 0;  // (s <= 63 here)
-    from[u] = w + (size_t)c[u] * kChunk + max(s[u] - 1, 0) * 32 + 1;
+    from[u] = w + (size_t)c[u] * CH + max(s[u] - 1, 0) * (CH / 64) + 1;
   }
-  // words below it among the 31 after the last such
+  // words below it among those after the last such
 #pragma unroll
-  for (int step = 16; step >= 1; step >>= 1)
+  for (int step = CH / 128; step >= 1; step >>= 1)
 #pragma unroll
     for (int u = 0; u < U; ++u) n[u] += from[u][n[u] + step - 1] < word ? step : 0;
   int count = 0;
 #pragma unroll
-  for (int u = 0; u < U; ++u) count += s[u] == 0 || first + u >= chunks ? 0 : (s[u] - 1) * 32 + 1 + n[u];
+  for (int u = 0; u < U; ++u) count += s[u] == 0 || first + u >= chunks ? 0 : (s[u] - 1) * (CH / 64) + 1 + n[u];
   return count;
 }
 
@@ -288,23 +288,30 @@ __device__ __forceinline__ int count_in_chunks(const word_t (&split)[kMaxRankChu
 // Bound by the chains of reads and by the scattered writes of the order and the clusters: 16 images of 8 chunks 13.8 us with
 // one search after the other, 11.9 with seven at a time, 10.0 with an image's workgroups on one XCD, whose L2 then joins the
 // writes to a line (and reads the words once).  (Comparing 32-bit keys, as earlier chunks have the lower numbers: 10 - 10.6.)
+// CH: words of a chunk.  Small batches leave most CUs without a chunk of 2048, and a chunk's sort is a chain that shorter
+// chunks shorten: a run of 512 words to a workgroup as long as that makes no more than 8 chunks an image (whole clustering
+// with chunks of 2048 / 1024 / 512: 16 images of 4096 tokens 15.7 / 14.4 / 13.8 us, 64 17.7 / 15.0 / 15.4, 256 35.6 / 38.3 /
+// 40.4), two runs beyond (4 images of 8192 16.0 / 14.0 / 13.8, 16 17.3 / 14.3 / 14.6, 64 25.1 / 26.6 / 30.4; 4 images of
+// 16384 17.3 / 15.3, 16 22.4 / 23.5; 14 us are the host's share of two launches).
+constexpr int kFewChunks512 = 512, kFewChunks1024 = 192;
+template <int CH>
 __global__ __launch_bounds__(256) void cluster_rank_kernel(ClusterParams p, int chunks) {
   __shared__ word_t split[kMaxRankChunks][64];
-  // (an image has 8 workgroups per chunk)
-  const unsigned block = (unsigned)xcd_contiguous_block(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+  unsigned block = blockIdx.y * gridDim.x + blockIdx.x;
+  if (gridDim.x * gridDim.y % 8 == 0) block = (unsigned)xcd_contiguous_block(block, gridDim.x * gridDim.y);
   const int b = block / gridDim.x, part = block - b * gridDim.x;
   const word_t* w = p.words + (size_t)b * p.npad;
   const int at = part * 256 + threadIdx.x;  // place among the chunks' words (a workgroup stays inside one chunk)
-  const int own = part / (kChunk / 256);
+  const int own = part / (CH / 256);
   const word_t word = w[at];
-  for (int i = threadIdx.x; i < chunks * 64; i += 256) split[i >> 6][i & 63] = w[(size_t)i * (kChunk / 64)];
+  for (int i = threadIdx.x; i < chunks * 64; i += 256) split[i >> 6][i & 63] = w[(size_t)i * (CH / 64)];
   __syncthreads();
-  int place = at - own * kChunk;
-  if (chunks == 2) place += count_in_chunks<1>(split, w, chunks, own, 1, word);
-  else if (chunks <= 5) place += count_in_chunks<4>(split, w, chunks, own, 1, word);
-  else if (chunks <= 8) place += count_in_chunks<7>(split, w, chunks, own, 1, word);
+  int place = at - own * CH;
+  if (chunks == 2) place += count_in_chunks<CH, 1>(split, w, chunks, own, 1, word);
+  else if (chunks <= 5) place += count_in_chunks<CH, 4>(split, w, chunks, own, 1, word);
+  else if (chunks <= 8) place += count_in_chunks<CH, 7>(split, w, chunks, own, 1, word);
   else
-    for (int o = 1; o < chunks; o += 8) place += count_in_chunks<8>(split, w, chunks, own, o, word);
+    for (int o = 1; o < chunks; o += 8) place += count_in_chunks<CH, 8>(split, w, chunks, own, o, word);
   if (word != ~0ull) emit(p, b, word, place);
 }
 
@@ -390,9 +397,23 @@ static hipError_t launch_images(const ClusterParams& p, int B, hipStream_t strea
     return hipGetLastError();
   }
   const int chunks = (N + kChunk - 1) / kChunk;
+#define AFFMAE_RANK(CH)                                                                                            \
+  AFFMAE_LAUNCH("cluster_rank_kernel", stream, cluster_rank_kernel<CH>, dim3((N + CH - 1) / CH * (CH / 256), B), dim3(256), 0, stream, \
+                p, (N + CH - 1) / CH)
+  const long long few = (long long)B * ((N + 511) / 512), mid = (long long)B * ((N + 1023) / 1024);
+  if (N <= 8 * 512 && few <= kFewChunks512) {
+    AFFMAE_SORT(2, 1, false, (N + 511) / 512, false);
+    AFFMAE_RANK(512);
+    return hipGetLastError();
+  }
+  if (N <= kMaxRankChunks * 1024 && mid <= kFewChunks1024) {
+    AFFMAE_SORT(2, 2, false, (N + 1023) / 1024, false);
+    AFFMAE_RANK(1024);
+    return hipGetLastError();
+  }
   if (chunks <= kMaxRankChunks) {
     AFFMAE_SORT_CHUNKS(chunks, false);
-    AFFMAE_LAUNCH("cluster_rank_kernel", stream, cluster_rank_kernel, dim3(chunks * (kChunk / 256), B), dim3(256), 0, stream, p, chunks);
+    AFFMAE_RANK(kChunk);
     return hipGetLastError();
   }
   const int chunk = kChunk;
@@ -402,6 +423,7 @@ static hipError_t launch_images(const ClusterParams& p, int B, hipStream_t strea
   AFFMAE_SORT_CHUNKS(p.npad / chunk, true);
 #undef AFFMAE_SORT_CHUNKS
 #undef AFFMAE_SORT
+#undef AFFMAE_RANK
   for (int k = chunk * 2; k <= p.npad; k <<= 1) {
     int j = k >> 1;
     while (j >= chunk) {  // up to three steps per pass over global memory

@@ -105,6 +105,20 @@ def test_cluster_many_chunks(B, N):
     assert np.array_equal(cid, rcid)
 
 
+@pytest.mark.parametrize("B,N", [(64, 4096), (65, 4096), (85, 2049), (103, 2050), (38, 4100), (39, 4100), (12, 16384), (13, 16384)])
+def test_cluster_chunk_sizes(B, N):
+    """The largest batches whose images are sorted in chunks of 512 and of 1024 words, and the next: a lattice, so that words of
+    different chunks share keys, with a part of the points beyond the frame's far corner, where the largest key is."""
+    print(f"case chunk sizes B={B} N={N}", flush=True)
+    rng = np.random.default_rng(B + N)
+    coords = rng.integers(0, 50, size=(B, N, 2)).astype(np.float32)
+    coords[:, ::7] += 100.0
+    order, cid = _gpu_cluster(coords, 64, (0.0, 0.0, 50.0, 50.0))
+    rorder, rcid = oracle.cluster(coords, 64, (0.0, 0.0, 50.0, 50.0))
+    assert np.array_equal(order, rorder)
+    assert np.array_equal(cid, rcid)
+
+
 def test_cluster_many_small_images():
     """2^24 images of two tokens: the batch is cut, as a launch cannot have 256 threads for each image of such a batch."""
     B = 1 << 24
