@@ -16,8 +16,9 @@
 //             lanes), dz_j = w_j (d_j - sum_i w_i d_i) with d_i = g_i - g_ref relative to the neighbour of largest
 //             weight (differences first: the form does not cancel when one weight saturates), its part of dp
 //             (distances relative to the nearest neighbour's, for the same reason), and keeps w, dz and the token of every (anchor, neighbour) pair.  dfeat and dscore are then
-//             gathered, not scattered: the pairs are filed per token (the list builder of the virtual-token
-//             backward) and every token adds up w * dout, respectively dz, over its own list.
+//             gathered, not scattered: every token adds up w * dout, respectively dz, over the pairs that name it, which
+//             one launch sorts by token and sums (pair_sum.hip; rows that are no whole 16-byte pieces, and tables of
+//             very many pairs a token, file the pairs per token first, by the list builder of the virtual-token backward).
 #include <algorithm>
 #include <type_traits>
 

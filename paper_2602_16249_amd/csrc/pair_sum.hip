@@ -10,6 +10,8 @@
 // read, per 16 pairs of a token, the list, then the weights it named, then the rows; at C = 64 (bf16) half of the 16
 // lanes that a token got had no channels.  8 images, 16384 tokens, 4096 anchors, K = 48, C = 64: 20.4 + 29.1 us and 4.6 for
 // dp (which one workgroup of this launch adds up now); 26.5 us as here.
+// (512 workgroups there, all places that 256 CUs have, and one more: in one of six measurements, on cards of one kind, the launch
+// took 20 us longer, as if some of the last had waited for a whole other one.  440 workgroups of 298 tokens: 33.8 us.)
 // Bound by the chain of the sort (12 of its 16 us a workgroup: the anchors' masks, the pairs they point to, their weights:
 // each step waits for memory) and then by the rows.  Two workgroups of 1024 threads per CU: 36.8 us with one (71
 // registers).  Which anchors to look at is told by a bit for each 64th of the image: 43.7 us with the lowest and highest

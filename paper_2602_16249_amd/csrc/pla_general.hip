@@ -2,8 +2,9 @@
 // Cluster Attention and Fast Decoder KNN", the FlashNbhdAttn equation), gather
 // formulation: one wave per token, the neighbours' rows fetched straight from
 // global memory.  This path makes no assumption about the table (any indices,
-// repeats allowed: every slot is its own softmax column) and serves fp32 storage
-// and every head size; the cluster-tiled kernels cover the clustered bf16 case.
+// repeats allowed: every slot is its own softmax column) and serves both storage
+// types and every head size; the cluster-tiled kernels cover clustered bf16 tables with heads of 32 channels and, in
+// calls large enough to fill the chip that come with a plan, fp32 and heads of 16 and 64 (pla_cluster_wide.hip).
 //
 // Lane layout, all three kernels: a head's row of D channels is PP = D / E pieces of 16 bytes (E = 4 fp32 or 8
 // bf16 channels); lane (r, c) = (lane / PP, lane % PP) holds piece c of the r-th of the 64 / PP rows of a trip, so a
