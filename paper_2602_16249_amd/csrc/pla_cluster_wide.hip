@@ -58,6 +58,7 @@ __device__ __forceinline__ float wide_exp(float x) {
 // A row of K fp32 values, the place that "no neighbour" points to and one that nobody reads; an odd number of words.
 __host__ __device__ __forceinline__ int wide_row(int K) { return (K + 2) | 1; }
 constexpr int kMostWideRow = 67;
+constexpr uint32_t kNotHeld = 0x7fc05a5au;  // a NaN that no arithmetic here makes
 
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
@@ -539,7 +540,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   const float lse = (p.lse_in + w.heads0(p.t))[(uint32_t)((RAG ? min(r, w.nq - 1) : r) * p.t.H)];
   bias_rows.put(p, w, rows, RW);
-  for (int i = w.lane; i < 16 * RW; i += kWave) ds_rows[i] = 0.f;  // (pairs that the plan does not hold: dS is 0)
+  // pairs that the plan does not hold: dS is 0.  (kLateD: a mark, as p dP may be 0 where p is not, and D p is still to be taken off)
+  for (int i = w.lane; i < 16 * RW; i += kWave) ds_rows[i] = kLateD ? __uint_as_float(kNotHeld) : 0.f;
   char *row = reinterpret_cast<char*>(rows + r * RW), *ds_row = reinterpret_cast<char*>(ds_rows + r * RW);
   int k_off[R::U], c_off[4][R::U];
 #pragma unroll
@@ -653,7 +655,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int i = w.lane; i < w.nq * K; i += kWave) {
       const int qi = fast_div(i, p.k_magic), j = i - qi * K;
       float ds = ds_rows[qi * RW + j];
-      if (kLateD) ds = fmaf(-ds_rows[qi * RW + K], rows[qi * RW + j], ds);
+      if (kLateD) ds = __float_as_uint(ds) == kNotHeld ? 0.f : fmaf(-ds_rows[qi * RW + K], rows[qi * RW + j], ds);
       Elem<T>::store(dst + ((uint32_t)qi * p.t.H * K + j), ds);
     }
   }

@@ -60,3 +60,18 @@ def check_attention(w, nbr, dtype, scale, near=None, S=0, M=0, blank=False, tol=
     bad = {n: e for n, e in errs.items() if not (e <= (LSE_TOL if n == "lse" else tol))}
     assert not bad, f"errors above tolerance {tol}: {bad} (all: {errs})"
     return errs
+
+
+def kernels_of(f):
+    """f()'s result, and the names of the kernels that it launched (through the instrumented build of the same sources)."""
+    aff.use_timed_library(True)
+    try:
+        aff.timing_enable(True)
+        aff.timing_reset()
+        result = f()
+        torch.cuda.synchronize()
+        return result, set(aff.timing_read())
+    finally:
+        aff.timing_enable(False)
+        aff.timing_reset()
+        aff.use_timed_library(False)

@@ -9,7 +9,7 @@ import torch
 
 import oracle
 import paper_2602_16249_amd as aff
-from helpers import LSE_TOL, TOL, check_attention, rel_err, run_gpu_attention, run_oracle_attention, to_dev
+from helpers import LSE_TOL, TOL, check_attention, kernels_of, rel_err, run_gpu_attention, run_oracle_attention, to_dev
 from workloads import CONFIGS, make_features, make_workload, random_neighbours
 
 pytestmark = pytest.mark.gpu
@@ -636,3 +636,34 @@ def test_plans_for_other_types_and_heads(dtype, d, B, N, H, K, S, M, blank):
     # logits with a standard deviation of 8: scores below 64, whose products and sum round to 2^-19 a few times over, as does lse, so
     # that p = exp(s - lse) is off by up to 1e-5; p (dP - D) and its sums over terms of both signs by a few times that
     check_attention(w, nbr, dtype, 8.0 / np.sqrt(d), near=near, S=S, M=M, blank=blank, use_plan=True, tol=4e-5 if dtype == "f32" else None)
+
+
+@pytest.mark.parametrize("dtype,d,K", [("bf16", 16, 24), ("bf16", 64, 37), ("f32", 16, 37), ("f32", 64, 48)])
+def test_slots_that_the_plan_does_not_hold_in_fp32_products(dtype, d, K):
+    """As test_slots_that_the_plan_does_not_hold, for the kernels with products on fp32 operands: dbias of such a slot is 0
+    whatever the bias there is."""
+    print(f"case foreign neighbours {dtype} d={d} K={K}", flush=True)
+    B, N, H, S, M = 16, 1024, 4, 64, 3
+    G = N // S
+    rng = np.random.default_rng(K + d)
+    near = np.stack([np.arange(M) + min(max(c - 1, 0), G - M) for c in range(G)]).astype(np.int32)
+    cand = (near[:, :, None] * S + np.arange(S)).reshape(G, M * S)[np.arange(N) // S]
+    nbr = np.take_along_axis(cand, np.argsort(rng.random((N, M * S)), axis=1)[:, :K], axis=1)
+    foreign = np.zeros((N, K), bool)
+    foreign[::2, 1::5] = True
+    nbr = np.where(foreign, np.where(np.arange(N) < N // 2, N - 1, 0)[:, None], nbr).astype(np.int32)
+    w = make_features(B, N, H, d, K, dtype, rng)
+    q, k, v, dout, bias = (to_dev(w[n], dtype) for n in ("q", "k", "v", "dout", "bias"))
+    nbr_d, near_d = (torch.from_numpy(np.broadcast_to(x, (B, *x.shape)).copy()).cuda() for x in (nbr, near))
+    plan = aff.affmae_pla_plan(nbr_d, near_d, S, M)
+    scale = 1.0 / np.sqrt(d)
+
+    def run():
+        out, lse = aff.affmae_pla_fwd(q, k, v, bias, nbr_d, scale, near_d, S, M, plan=plan)
+        return aff.affmae_pla_bwd(q, k, v, bias, nbr_d, out, lse, dout, scale, near_d, S, M, plan=plan)["dbias"]
+
+    dbias, kernels = kernels_of(run)
+    assert "pla_bwd_wide_query_kernel" in kernels
+    f = torch.from_numpy(foreign).cuda()[None, :, None].expand(B, N, H, K)
+    assert (bias[f] != 0).float().mean() > 0.9
+    assert (dbias[f] == 0).all() and (dbias[~f] != 0).float().mean() > 0.9
