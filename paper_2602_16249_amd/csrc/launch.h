@@ -63,8 +63,7 @@ hipError_t launch_pair_gather(const void* dout, const float* weights, const int3
 struct PairSumArgs {
   const int32_t* pair_token;
   int B, Nv, pairs_per_image, row_pairs;  // row_pairs consecutive pairs belong to a row of dout
-  // every group_size consecutive pairs: bit i is set where one names a token of the image's i-th part of pair_part(Nv) tokens
-  const unsigned long long* group_parts;
+  const uint2* group_cells;  // every group_size consecutive pairs: PairCells::bits of the tokens that they name, or-ed
   int group_size;
   const void* dout;
   const float *weights, *extra;
@@ -76,7 +75,14 @@ struct PairSumArgs {
   int dp_n;
   float* dp;
 };
-inline int pair_part(int Nv) { return (Nv + 63) / 64; }
+// The cells of consecutive tokens that an image is seen in: up to 64, a bit each, or up to 1024 in rows of 32, a bit (x) per row
+// and a bit (y) per column.
+struct PairCells {
+  int size;  // tokens; 0: no cells
+  uint32_t magic;
+  int rows;  // the second kind
+};
+PairCells pair_sum_cells(int B, int Nv, int pairs_per_image);
 bool pair_sum_takes(const PairSumArgs& a);
 hipError_t launch_pair_sum(const PairSumArgs& a, hipStream_t stream);
 constexpr size_t kPairSumMostParts = 131072;  // (128 values a thread; more parts of dp take two launches of their own)

@@ -444,7 +444,7 @@ __global__ __launch_bounds__(256) void merge_bwd_kernel(const T* __restrict__ fe
                                                        int B, int N, int C, int K, int n_keep, float p,
                                                        float* __restrict__ wpair, float* __restrict__ dzpair,
                                                        int32_t* __restrict__ pair_token, int2* __restrict__ pair_bounds,
-                                                       int part, uint32_t part_magic,
+                                                       PairCells cells,
                                                        float* __restrict__ dp_part) {
   __shared__ float g_all[4][kWave];
   const int lane = threadIdx.x & (kWave - 1);
@@ -516,13 +516,12 @@ __global__ __launch_bounds__(256) void merge_bwd_kernel(const T* __restrict__ fe
     pair_token[pair] = nb.b * N + nb.idx;
   }
   if (lane == 0 && dp_part) dp_part[slot] = dpv;
-  if (part) {  // which of the image's 64 parts of `part` tokens the anchor's pairs name (lanes >= K hold the anchor's token)
-    const int at = exact_div(nb.idx, part, part_magic);
+  if (cells.size) {  // which cells of the image the anchor's pairs name (lanes >= K hold the anchor's token)
+    const int at = exact_div(nb.idx, cells.size, cells.magic);
     const uint32_t bit = 1u << (at & 31);
-    uint32_t lo = at < 32 ? bit : 0u, hi = at < 32 ? 0u : bit;
-    lo = wave_or32(lo);
-    hi = wave_or32(hi);
-    if (lane == 0) pair_bounds[slot] = make_int2((int)lo, (int)hi);
+    const uint32_t x = cells.rows ? 1u << (at >> 5) : at < 32 ? bit : 0u, y = cells.rows || at >= 32 ? bit : 0u;
+    const uint32_t x_all = wave_or32(x), y_all = wave_or32(y);
+    if (lane == 0) pair_bounds[slot] = make_int2((int)x_all, (int)y_all);
     return;
   }
   // the lowest and highest token of the anchor's pairs, for the list builder (lanes >= K hold the anchor's token)
@@ -630,14 +629,15 @@ hipError_t launch_merge_bwd(const MergeArgs& a, hipStream_t stream) {
   const int pp = lanes_per_row(a);
   PairSumArgs s = {};
   s.pair_token = pair_token; s.B = a.B; s.Nv = a.N; s.pairs_per_image = a.n_keep * a.K; s.row_pairs = a.K;
-  s.group_parts = reinterpret_cast<const unsigned long long*>(pair_bounds); s.group_size = a.K;
+  s.group_cells = reinterpret_cast<const uint2*>(pair_bounds); s.group_size = a.K;
   s.dout = a.dout; s.weights = wpair; s.extra = dzpair; s.C = a.C; s.dtype = a.dtype;
   s.dfeat = a.dfeat; s.extra_sum = a.dscore; s.list = list;
   const bool one = pair_sum_takes(s);
+  const PairCells cells = one ? pair_sum_cells(a.B, a.N, s.pairs_per_image) : PairCells{0, 0u, 0};
 #define AFFMAE_MERGE_BWD(T, P)                                                                                     \
   AFFMAE_LAUNCH("merge_bwd_kernel", stream, (merge_bwd_kernel<T, P>), grid, dim3(256), 0, stream, (const T*)a.feat, \
                 a.coords, a.score, a.nbr_idx, a.anchor_idx, (const T*)a.dout, a.B, a.N, a.C, a.K, a.n_keep, a.p, \
-                wpair, dzpair, pair_token, pair_bounds, one ? pair_part(a.N) : 0, div_magic(pair_part(a.N)), dp_part)
+                wpair, dzpair, pair_token, pair_bounds, cells, dp_part)
   AFFMAE_MERGE_ROWS(AFFMAE_MERGE_BWD)
 #undef AFFMAE_MERGE_BWD
   if (a.dp && one && anchors <= kPairSumMostParts) {

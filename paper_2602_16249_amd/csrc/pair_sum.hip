@@ -14,7 +14,7 @@
 // took 20 us longer, as if some of the last had waited for a whole other one.  440 workgroups of 298 tokens: 33.8 us.)
 // Bound by the chain of the sort (12 of its 16 us a workgroup: the anchors' masks, the pairs they point to, their weights:
 // each step waits for memory) and then by the rows.  Two workgroups of 1024 threads per CU: 36.8 us with one (71
-// registers).  Which anchors to look at is told by a bit for each 64th of the image: 43.7 us with the lowest and highest
+// registers).  Which anchors to look at is told by the cells of the image that their pairs name: 43.7 us with the lowest and highest
 // token, which along a space-filling curve often lie far apart (of 4096 anchors 282 for 121 that do have a pair in 256 tokens).
 // (The virtual tokens' backward, whose queries lie anywhere, would look at all pairs in every workgroup: 64.7 us for 17.3 +
 // 39.0 + 4.7, 48 images of 8192 queries with 4 candidates.)
@@ -36,13 +36,14 @@ constexpr int kSumGroups = 8192;    // groups of pairs that a workgroup lists at
 
 struct SumParams {
   const int32_t* pair_token;  // [B * ppi]: the pair's token, b * Nv + t
-  const unsigned long long* parts;  // which of the 64 parts of the image (of `part` tokens) every `gs` consecutive pairs name
+  const uint2* group_cells;   // which cells every `gs` consecutive pairs name
+  PairCells cells;
   const uint4* dout;          // [B * ppi / row_pairs] rows of `pieces` 16-byte pieces
   const float *weights, *extra;
   uint4* dfeat;
   float* extra_sum;
   int32_t* list;              // room for all pairs: the lists that do not fit LDS
-  int B, Nv, ppi, groups, gs, part, range, ranges, pieces, row_pairs;
+  int B, Nv, ppi, groups, gs, range, ranges, pieces, row_pairs;
   uint32_t gs_magic, row_magic;
   const float* dp_part;       // dp = their sum, by the workgroup behind the last range's, or nullptr
   int dp_n;
@@ -67,6 +68,9 @@ __device__ __forceinline__ uint4 pack_piece(const float (&a)[8]) {
   if constexpr (sizeof(T) == 2) return make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]), pack_bf16x2(a[6], a[7]));
   else return make_uint4(__float_as_uint(a[0]), __float_as_uint(a[1]), __float_as_uint(a[2]), __float_as_uint(a[3]));
 }
+
+// bits lo .. hi, 0 <= lo <= hi < 32
+__device__ __forceinline__ uint32_t bit_range(int lo, int hi) { return (~0u >> (31 - (hi - lo))) << lo; }
 
 // Sum of the parts in the order of launch_sum_parts (one workgroup).
 __device__ __forceinline__ void sum_parts(const float* part, int n, float* out, float* wave_sums) {
@@ -112,10 +116,20 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
   if (tid == 0) s_hits = 0;
 
   // fn(tokens, pairs, in) for four pairs at a time, all lanes of a wave together, of the groups that name a token of the range's
-  // parts of the image
+  // cells
   int32_t* glist = reinterpret_cast<int32_t*>(entry);
-  const int part_lo = t0 / p.part, part_hi = (t0 + span - 1) / p.part;
-  const unsigned long long own_parts = (part_hi - part_lo >= 63 ? ~0ull : (2ull << (part_hi - part_lo)) - 1ull) << part_lo;
+  uint2 own;  // the range's cells
+  {
+    const int lo_cell = exact_div(t0, p.cells.size, p.cells.magic), hi_cell = exact_div(t0 + span - 1, p.cells.size, p.cells.magic);
+    const int r0 = lo_cell >> 5, r1 = hi_cell >> 5, c0 = lo_cell & 31, c1 = hi_cell & 31;
+    if (p.cells.rows) {
+      own.x = bit_range(r0, r1);
+      own.y = hi_cell - lo_cell >= 31 ? ~0u : r0 == r1 ? bit_range(c0, c1) : bit_range(c0, 31) | bit_range(0, c1);
+    } else {
+      own.x = r0 == 0 ? bit_range(c0, r1 == 0 ? c1 : 31) : 0u;
+      own.y = r1 == 1 ? bit_range(r0 == 1 ? c0 : 0, c1) : 0u;
+    }
+  }
   auto each_pair = [&](auto&& fn) {
     for (int g0 = 0; g0 < p.groups; g0 += kSumGroups) {
       __syncthreads();  // the list before has been walked (and, the first time, the counters are set)
@@ -124,7 +138,9 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
       const int g1 = min(g0 + kSumGroups, p.groups);
       for (int gw = g0 + wave * kWave; gw < g1; gw += kSumThreads) {
         const int g = gw + lane;
-        const bool in = g < g1 && (p.parts[(size_t)b * p.groups + min(g, g1 - 1)] & own_parts) != 0ull;
+        const uint2 named = p.group_cells[(size_t)b * p.groups + min(g, g1 - 1)];
+        const bool x = (named.x & own.x) != 0u, y = (named.y & own.y) != 0u;
+        const bool in = g < g1 && (p.cells.rows ? x && y : x || y);
         const unsigned long long mask = __ballot(in);
         int at = 0;
         if (lane == 0) at = atomicAdd(&s_listed, (int)__popcll(mask));
@@ -304,9 +320,28 @@ bool pair_sum_takes(const PairSumArgs& a) {
   return true;
 }
 
+// Tokens of a workgroup: two workgroups per CU, but no more pairs than fit with a quarter to spare.
+static int pair_sum_range(int B, int Nv, int pairs_per_image) {
+  const int want = std::max(1, (512 + B - 1) / B);
+  const long long fit = std::max(1ll, (long long)kSumCap * 3 / 4 * Nv / std::max(1, pairs_per_image));
+  return (int)std::min({std::max(64ll, ((long long)Nv + want - 1) / want), fit, (long long)kSumRange});
+}
+// A bit per range where there are no more than 64 of them; else rows, and a quarter of a range, so that the columns tell
+// neighbouring ranges apart, or as much as 1024 cells need.  (One of 64 parts of the image, a bit each, whatever the ranges are: with
+// one image of 262144 tokens, 64 channels, 65536 anchors of 48 pairs the whole backward took 176 us, and with 16384 tokens 19.4;
+// as here 148 and 18.8.  Rows for 64 ranges as well, an anchor's pairs lying in several: one image of 4096 tokens 14.6 instead of 14.1.)
+PairCells pair_sum_cells(int B, int Nv, int pairs_per_image) {
+  const int range = pair_sum_range(B, Nv, pairs_per_image);
+  PairCells c;
+  c.rows = (Nv + range - 1) / range > 64;
+  c.size = c.rows ? std::max((Nv + 1023) / 1024, range / 4) : (Nv + 63) / 64;
+  c.magic = div_magic(c.size);
+  return c;
+}
+
 hipError_t launch_pair_sum(const PairSumArgs& a, hipStream_t stream) {
   SumParams p;
-  p.pair_token = a.pair_token; p.parts = a.group_parts; p.part = pair_part(a.Nv);
+  p.pair_token = a.pair_token; p.group_cells = a.group_cells; p.cells = pair_sum_cells(a.B, a.Nv, a.pairs_per_image);
   p.dout = static_cast<const uint4*>(a.dout); p.weights = a.weights; p.extra = a.extra;
   p.dfeat = static_cast<uint4*>(a.dfeat); p.extra_sum = a.extra_sum; p.list = a.list;
   p.B = a.B; p.Nv = a.Nv; p.ppi = a.pairs_per_image; p.row_pairs = a.row_pairs; p.row_magic = div_magic(a.row_pairs);
@@ -314,10 +349,7 @@ hipError_t launch_pair_sum(const PairSumArgs& a, hipStream_t stream) {
   p.pieces = (int)((size_t)a.C * (a.dtype == 1 ? 2 : 4) / 16);
   p.dp_part = a.dp_part; p.dp_n = a.dp_n; p.dp = a.dp;
   const int g = p.pieces <= 4 ? 4 : p.pieces <= 8 ? 8 : 16;
-  // tokens of a workgroup: two workgroups per CU, but no more pairs than fit with a quarter to spare
-  const int want = std::max(1, (512 + a.B - 1) / a.B);
-  const long long fit = std::max(1ll, (long long)kSumCap * 3 / 4 * a.Nv / std::max(1, a.pairs_per_image));
-  p.range = (int)std::min({std::max(64ll, ((long long)a.Nv + want - 1) / want), fit, (long long)kSumRange});
+  p.range = pair_sum_range(a.B, a.Nv, a.pairs_per_image);
   const int turn = kSumThreads / g;  // tokens at a time, with G lanes each: whole turns
   if (p.range > turn) p.range = p.range / turn * turn;
   p.ranges = (a.Nv + p.range - 1) / p.range;

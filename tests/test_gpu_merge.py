@@ -213,3 +213,42 @@ def test_merge_sums_per_token(dtype, B, N, C, K, n_keep, few):
         # fp32 sums of up to n_keep K terms (here at most 5e4, of both signs): 1e-5 of the largest holds as elsewhere
         assert np.abs(got - rg[name]).max() <= TOL[dtype] * np.abs(rg[name]).max(), name
     assert abs(float(g["dp"].cpu()) - rg["dp"]) <= TOL[dtype] * rg["dp_abs"]
+
+
+def _check_merge_bwd(dtype, coords, feat, dout, score, nbr, n_keep, p=0.3):
+    """Backward on the GPU against the oracle; the sums of a token have up to 5e4 terms of both signs, whose fp32 roundings stay below
+    1e-5 of the largest value as elsewhere."""
+    tdt = torch.float32
+    if dtype == "bf16":
+        feat, dout, tdt = bf16_round(feat), bf16_round(dout), torch.bfloat16
+    anchors = oracle.merge_select(score, n_keep)
+    up = lambda x: torch.from_numpy(x).cuda()
+    g = aff.affmae_merge_bwd(up(feat).to(tdt), up(coords), up(score), up(nbr), up(anchors), up(dout).to(tdt), p)
+    torch.cuda.synchronize()
+    rg = oracle.merge_bwd(coords, feat, score, nbr, anchors, dout, p)
+    for name in ("dfeat", "dscore"):
+        got = g[name].float().cpu().numpy().astype(np.float64)
+        assert np.abs(got - rg[name]).max() <= TOL[dtype] * np.abs(rg[name]).max(), name
+    assert abs(float(g["dp"].cpu()) - rg["dp"]) <= TOL[dtype] * rg["dp_abs"]
+
+
+def _two_places(B, N, K, rng):
+    """Neighbour tables as along a curve: half of a token's neighbours around itself, half around some other place of the image."""
+    own = np.arange(N)[None, :, None] + rng.permuted(np.tile(np.arange(K), (B, N, 1)), axis=2)[..., : K - K // 2] - K // 2
+    other = rng.integers(0, N, size=(B, N, 1)) + rng.permuted(np.tile(np.arange(K), (B, N, 1)), axis=2)[..., : K // 2]
+    return (np.concatenate([own, other], axis=2) % N).astype(np.int32)
+
+
+@pytest.mark.parametrize("B,N,K,n_keep", [
+    (1, 4096, 12, 1024),    # 64 ranges of tokens, the most whose cells have a bit each
+    (1, 4160, 12, 1024),    # 65: rows and columns of cells
+    (2, 9001, 16, 3000),
+    (1, 40001, 8, 9000),    # more than 1024 ranges' worth of cells: as many as there can be, the last short
+    (5, 700, 16, 200),      # a dozen ranges an image
+])
+def test_merge_finds_the_anchors_of_a_range(B, N, K, n_keep):
+    print(f"case merge cells B={B} N={N} K={K} n_keep={n_keep}", flush=True)
+    rng = np.random.default_rng(N + K)
+    coords = rng.uniform(0, 30, size=(B, N, 2)).astype(np.float32)
+    feat, dout = (rng.normal(size=(B, n, 8)).astype(np.float32) for n in (N, n_keep))
+    _check_merge_bwd("f32", coords, feat, dout, rng.normal(size=(B, N)).astype(np.float32), _two_places(B, N, K, rng), n_keep)
