@@ -70,7 +70,8 @@ struct PairSumArgs {
   int C, dtype;
   void* dfeat;
   float* extra_sum;
-  int32_t* list;  // workspace [B * pairs_per_image]
+  int32_t* list;    // workspace [B * pairs_per_image]: lists that do not fit LDS
+  int32_t* crowds;  // workspace, Nv words an image, where shape.front > 0: see Crowds
   const float* dp_part;
   int dp_n;
   float* dp;
@@ -82,9 +83,22 @@ struct PairCells {
   uint32_t magic;
   int rows;  // the second kind
 };
-PairCells pair_sum_cells(int B, int Nv, int pairs_per_image);
+struct PairSumShape {
+  PairCells cells;
+  int range, ranges;  // tokens of a workgroup, workgroups of an image
+  uint32_t range_magic;
+  int front;   // workgroups, a multiple of 8 and at least B, that set up `crowds` beforehand; 0: nothing to set up
+  int extras;  // more workgroups an image, for the parts of crowded ranges
+};
+PairSumShape pair_sum_shape(const PairSumArgs& a);
+// An image's words of `crowds`: [0] the number of its items, [1] words of `list` in use (0), then its items: a range, or part `part` of
+// `parts` of as many tokens each.  Where the anchors of any range have more than kSumCrowd pairs, ranges go into parts of kSumPart,
+// as about as many pairs name a range's tokens as its anchors have (8 images, 16384 tokens of a jittered grid, a quarter kept at random:
+// 110 more or less, standard deviation; of 20480 ranges with 3072 on average none has more than 4256, whose anchors have at most 4416).
+constexpr int kSumCrowd = 4608, kSumPart = 4096, kSumMostParts = 64, kSumMostRanges = 1024;
+__host__ __device__ __forceinline__ int sum_item(int range, int part, int parts) { return (range * kSumMostParts + part) * kSumMostParts + parts - 1; }
 bool pair_sum_takes(const PairSumArgs& a);
-hipError_t launch_pair_sum(const PairSumArgs& a, hipStream_t stream);
+hipError_t launch_pair_sum(const PairSumArgs& a, const PairSumShape& shape, hipStream_t stream);
 constexpr size_t kPairSumMostParts = 131072;  // (128 values a thread; more parts of dp take two launches of their own)
 
 // Neighbourhood merging (merge.hip): anchor selection, location-aware aggregation, backward.

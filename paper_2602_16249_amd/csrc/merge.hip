@@ -17,8 +17,8 @@
 //             weight (differences first: the form does not cancel when one weight saturates), its part of dp
 //             (distances relative to the nearest neighbour's, for the same reason), and keeps w, dz and the token of every (anchor, neighbour) pair.  dfeat and dscore are then
 //             gathered, not scattered: every token adds up w * dout, respectively dz, over the pairs that name it, which
-//             one launch sorts by token and sums (pair_sum.hip; rows that are no whole 16-byte pieces, and tables of
-//             very many pairs a token, file the pairs per token first, by the list builder of the virtual-token backward).
+//             one launch sorts by token and sums (pair_sum.hip; rows that are no whole 16-byte pieces
+//             have the pairs filed per token first, by the list builder of the virtual-token backward).
 #include <algorithm>
 #include <type_traits>
 
@@ -31,12 +31,6 @@ namespace affmae {
 namespace {
 
 inline unsigned round_up8(long long blocks) { return (unsigned)((blocks + 7) / 8 * 8); }
-__device__ __forceinline__ long long xcd_contiguous_block() {
-  // workgroups are dealt round-robin to the 8 XCDs (one L2 each): consecutive anchors share rows, so every XCD
-  // gets a contiguous range; the grid is a multiple of 8
-  const unsigned per_xcd = gridDim.x >> 3;
-  return (long long)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-}
 
 // Order-preserving 32-bit pattern of a finite score: a larger score has a larger pattern; -0 and +0 share one.
 __device__ __forceinline__ uint32_t score_key(float s) {
@@ -372,7 +366,7 @@ __global__ __launch_bounds__(256) void merge_fwd_kernel(const T* __restrict__ fe
                                                        const int32_t* __restrict__ anchor, int B, int N, int C, int K,
                                                        int n_keep, float p, T* __restrict__ out) {
   const int lane = threadIdx.x & (kWave - 1);
-  const long long slot = xcd_contiguous_block() * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const long long slot = (long long)xcd_contiguous_block(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if (slot >= (long long)B * n_keep) return;  // wave-uniform
   const Nbr nb = load_neighbour(coords, score, nbr, anchor, slot, N, K, n_keep, p, lane);
   const T* rows = feat + (size_t)nb.b * N * C;
@@ -436,6 +430,57 @@ __global__ __launch_bounds__(256) void merge_fwd_kernel(const T* __restrict__ fe
   }
 }
 
+// For pair_sum.hip, whose workgroups own equal ranges of an image's tokens: a workgroup per image, in front of the others and
+// beside them, counts the anchors of every range and lists the ranges, in parts where anchors crowd.
+struct Crowds {
+  int front, range, ranges;  // as in PairSumShape
+  uint32_t range_magic;
+  int32_t* words;
+};
+__device__ __forceinline__ void split_crowds(const Crowds& s, const int32_t* __restrict__ anchor, int B, int N, int K, int n_keep) {
+  __shared__ int count[kSumMostRanges], most, heavy, light;
+  const int b = blockIdx.x;
+  if (b >= B) return;
+  int32_t* words = s.words + (size_t)b * N;
+  if (threadIdx.x == 0) words[1] = 0;
+  if (s.ranges > kSumMostRanges) return;  // (then they are taken as they are)
+  for (int r = threadIdx.x; r < s.ranges; r += 256) count[r] = 0;
+  if (threadIdx.x == 0) most = heavy = light = 0;
+  __syncthreads();
+  for (int i0 = threadIdx.x; i0 < n_keep; i0 += 8 * 256) {
+    int tok[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) tok[u] = anchor[(size_t)b * n_keep + min(i0 + u * 256, n_keep - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (i0 + u * 256 < n_keep) atomicAdd(&count[exact_div(min(max(tok[u], 0), N - 1), s.range, s.range_magic)], 1);
+  }
+  __syncthreads();
+  for (int r = threadIdx.x; r < s.ranges; r += 256) atomicMax(&most, count[r]);
+  __syncthreads();
+  const bool crowded = (long long)most * K > kSumCrowd;
+  if (!crowded) {
+    for (int r = threadIdx.x; r < s.ranges; r += 256) words[2 + r] = sum_item(r, 0, 1);
+    if (threadIdx.x == 0) words[0] = s.ranges;
+    return;
+  }
+  // the ranges with much to do first
+  auto parts_of = [&](int r) { return (int)min((long long)kSumMostParts, ((long long)count[r] * K + kSumPart - 1) / kSumPart); };
+  for (int r = threadIdx.x; r < s.ranges; r += 256)
+    if (count[r] * (long long)K >= kSumPart / 2) atomicAdd(&light, parts_of(r));
+  __syncthreads();
+  const int lights = light;
+  __syncthreads();
+  for (int r = threadIdx.x; r < s.ranges; r += 256) {
+    const int parts = max(1, parts_of(r));
+    const bool much = count[r] * (long long)K >= kSumPart / 2;
+    const int at = much ? atomicAdd(&heavy, parts) : atomicAdd(&light, 1);
+    for (int part = 0; part < parts; ++part) words[2 + at + part] = sum_item(r, part, parts);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) words[0] = light;
+}
+
 template <typename T, int PP>
 __global__ __launch_bounds__(256) void merge_bwd_kernel(const T* __restrict__ feat, const float* __restrict__ coords,
                                                        const float* __restrict__ score,
@@ -445,11 +490,15 @@ __global__ __launch_bounds__(256) void merge_bwd_kernel(const T* __restrict__ fe
                                                        float* __restrict__ wpair, float* __restrict__ dzpair,
                                                        int32_t* __restrict__ pair_token, int2* __restrict__ pair_bounds,
                                                        PairCells cells,
-                                                       float* __restrict__ dp_part) {
+                                                       float* __restrict__ dp_part, Crowds crowds) {
   __shared__ float g_all[4][kWave];
+  if ((int)blockIdx.x < crowds.front) {  // the whole workgroup
+    split_crowds(crowds, anchor, B, N, K, n_keep);
+    return;
+  }
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const long long slot = xcd_contiguous_block() * 4 + wave;
+  const long long slot = (long long)xcd_contiguous_block(blockIdx.x - crowds.front, gridDim.x - crowds.front) * 4 + wave;
   if (slot >= (long long)B * n_keep) return;  // wave-uniform; no workgroup barrier below
   float* g = g_all[wave];
   const Nbr nb = load_neighbour(coords, score, nbr, anchor, slot, N, K, n_keep, p, lane);
@@ -624,20 +673,21 @@ hipError_t launch_merge_bwd(const MergeArgs& a, hipStream_t stream) {
   float* dp_part = a.dp ? reinterpret_cast<float*>(ws + L.dp_off) : nullptr;
   float* dp_part2 = reinterpret_cast<float*>(ws + L.dp2_off);
   const size_t tokens = (size_t)a.B * a.N, anchors = (size_t)a.B * a.n_keep;
-  const dim3 grid(round_up8(((long long)anchors + 3) / 4));
   const bool pieces = merge_pieces(a, a.feat, a.dout);
   const int pp = lanes_per_row(a);
   PairSumArgs s = {};
   s.pair_token = pair_token; s.B = a.B; s.Nv = a.N; s.pairs_per_image = a.n_keep * a.K; s.row_pairs = a.K;
   s.group_cells = reinterpret_cast<const uint2*>(pair_bounds); s.group_size = a.K;
   s.dout = a.dout; s.weights = wpair; s.extra = dzpair; s.C = a.C; s.dtype = a.dtype;
-  s.dfeat = a.dfeat; s.extra_sum = a.dscore; s.list = list;
+  s.dfeat = a.dfeat; s.extra_sum = a.dscore; s.list = list; s.crowds = offset;
   const bool one = pair_sum_takes(s);
-  const PairCells cells = one ? pair_sum_cells(a.B, a.N, s.pairs_per_image) : PairCells{0, 0u, 0};
+  const PairSumShape shape = one ? pair_sum_shape(s) : PairSumShape{};
+  const Crowds crowds = {shape.front, shape.range, shape.ranges, shape.range_magic, offset};
+  const dim3 grid(shape.front + round_up8(((long long)anchors + 3) / 4));
 #define AFFMAE_MERGE_BWD(T, P)                                                                                     \
   AFFMAE_LAUNCH("merge_bwd_kernel", stream, (merge_bwd_kernel<T, P>), grid, dim3(256), 0, stream, (const T*)a.feat, \
                 a.coords, a.score, a.nbr_idx, a.anchor_idx, (const T*)a.dout, a.B, a.N, a.C, a.K, a.n_keep, a.p, \
-                wpair, dzpair, pair_token, pair_bounds, cells, dp_part)
+                wpair, dzpair, pair_token, pair_bounds, shape.cells, dp_part, crowds)
   AFFMAE_MERGE_ROWS(AFFMAE_MERGE_BWD)
 #undef AFFMAE_MERGE_BWD
   if (a.dp && one && anchors <= kPairSumMostParts) {
@@ -646,7 +696,7 @@ hipError_t launch_merge_bwd(const MergeArgs& a, hipStream_t stream) {
     const hipError_t e = launch_sum_parts(dp_part, anchors, dp_part2, a.dp, stream);
     if (e != hipSuccess) return e;
   }
-  if (one) return launch_pair_sum(s, stream);
+  if (one) return launch_pair_sum(s, shape, stream);
   hipError_t e = launch_pair_lists(pair_token, a.B, a.N, a.n_keep * a.K, offset, list, stream,
                                    reinterpret_cast<const int32_t*>(pair_bounds), a.K);
   if (e != hipSuccess) return e;

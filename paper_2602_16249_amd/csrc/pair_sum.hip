@@ -10,12 +10,19 @@
 // read, per 16 pairs of a token, the list, then the weights it named, then the rows; at C = 64 (bf16) half of the 16
 // lanes that a token got had no channels.  8 images, 16384 tokens, 4096 anchors, K = 48, C = 64: 20.4 + 29.1 us and 4.6 for
 // dp (which one workgroup of this launch adds up now); 26.5 us as here.
-// (512 workgroups there, all places that 256 CUs have, and one more: in one of six measurements, on cards of one kind, the launch
-// took 20 us longer, as if some of the last had waited for a whole other one.  440 workgroups of 298 tokens: 33.8 us.)
+// (440 workgroups of 298 tokens: 33.8 us.)
 // Bound by the chain of the sort (12 of its 16 us a workgroup: the anchors' masks, the pairs they point to, their weights:
 // each step waits for memory) and then by the rows.  Two workgroups of 1024 threads per CU: 36.8 us with one (71
 // registers).  Which anchors to look at is told by the cells of the image that their pairs name: 43.7 us with the lowest and highest
 // token, which along a space-filling curve often lie far apart (of 4096 anchors 282 for 121 that do have a pair in 256 tokens).
+// Where anchors crowd, a range has up to K pairs a token and its neighbours none: then the workgroups take the items that the launch before
+// has listed, ranges with much to do first and in parts, the ranges without anchors last.  The same 8 images, us, whole backward, the
+// two launches before / every workgroup its own range, with lists in memory where they do not fit / as here: anchors in a quarter of
+// the frame 95 / 185 / 69, in a disc 97 / 183 / 79, by a smooth function of the place and some noise 95 / 177 / 67, at random 76 / 53 / 54.
+// Parts of 3072 pairs instead of 4096: 77, 86, 81 (three fifths of a part's time are the chain); further parts behind all first
+// ones instead of in front of the light ranges: 87, 86, 84.
+// Places for 5120 pairs (the noted pairs make room for `extra`): with 4096 a range of the anchors at random did not fit in 3 of
+// 40 batches, which then took 20 us longer.
 // (The virtual tokens' backward, whose queries lie anywhere, would look at all pairs in every workgroup: 64.7 us for 17.3 +
 // 39.0 + 4.7, 48 images of 8192 queries with 4 candidates.)
 #include <algorithm>
@@ -30,9 +37,9 @@ namespace affmae {
 namespace {
 
 constexpr int kSumThreads = 1024, kSumWaves = kSumThreads / kWave;
-constexpr int kSumCap = 4096;       // pairs of a workgroup's tokens that have a place in LDS
-constexpr int kSumRange = 1024;     // most tokens of a workgroup
-constexpr int kSumGroups = 8192;    // groups of pairs that a workgroup lists at a time
+constexpr int kSumCap = 5 * kSumThreads;  // pairs of a workgroup's tokens that have a place in LDS
+constexpr int kSumRange = 1024;           // most tokens of a workgroup
+constexpr int kSumGroups = 8192;          // groups of pairs that a workgroup lists at a time
 
 struct SumParams {
   const int32_t* pair_token;  // [B * ppi]: the pair's token, b * Nv + t
@@ -42,10 +49,10 @@ struct SumParams {
   const float *weights, *extra;
   uint4* dfeat;
   float* extra_sum;
-  int32_t* list;              // room for all pairs: the lists that do not fit LDS
-  int B, Nv, ppi, groups, gs, range, ranges, pieces, row_pairs;
+  int32_t *crowds, *list;     // as in PairSumArgs
+  int B, Nv, ppi, groups, gs, range, ranges, extras, pieces, row_pairs;
   uint32_t gs_magic, row_magic;
-  const float* dp_part;       // dp = their sum, by the workgroup behind the last range's, or nullptr
+  const float* dp_part;       // dp = their sum, by one more workgroup, or nullptr
   int dp_n;
   float* dp;
 };
@@ -96,29 +103,38 @@ __device__ __forceinline__ void sum_parts(const float* part, int n, float* out, 
 template <typename T, int G, bool SPLIT>
 __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void pair_sum_kernel(SumParams p) {
   __shared__ uint2 entry[kSumCap];  // row (its first piece in the image's dout), weight; before that: the listed groups
-  __shared__ float entry_extra[kSumCap];
-  __shared__ uint32_t hit_pair[kSumCap];  // pairs of the own tokens as they are found
+  __shared__ uint32_t hit_pair[kSumCap];  // pairs of the own tokens as they are found; then `extra` of the entries
   __shared__ uint16_t hit_token[kSumCap];
+  float* const entry_extra = reinterpret_cast<float*>(hit_pair);
   __shared__ int32_t cnt[kSumRange];  // pairs per token; then the next free place of each; then where its list ends
-  __shared__ int32_t wave_total[kSumWaves], wave_below[kSumWaves];
-  __shared__ int32_t s_listed, s_hits;
+  __shared__ int32_t wave_total[kSumWaves];
+  __shared__ int32_t s_listed, s_hits, s_far;
   static_assert(kSumGroups * 4 <= kSumCap * 8, "the listed groups lie in the entries' place");
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  if ((int)blockIdx.x == p.B * p.ranges) {  // (only there with dp_part)
+  if (p.dp_part && blockIdx.x == gridDim.x - 1) {
     sum_parts(p.dp_part, p.dp_n, p.dp, reinterpret_cast<float*>(wave_total));
     return;
   }
-  const int b = blockIdx.x / p.ranges, rg = blockIdx.x - b * p.ranges;
-  const int t0 = rg * p.range, span = min(p.range, p.Nv - t0);  // >= 1
-  const int first = b * p.Nv + t0;
-  const int lo = b * p.ppi, hi = lo + p.ppi;  // the image's pairs
+  // a range of an image's tokens, or a part of it
+  const int at_extra = (int)blockIdx.x - p.B * p.ranges;
+  const int b = at_extra < 0 ? blockIdx.x / p.ranges : at_extra / p.extras;
+  int rg = at_extra < 0 ? blockIdx.x - b * p.ranges : p.ranges + at_extra - b * p.extras, part = 0, parts = 1;
+  if (p.extras) {
+    const int32_t* items = p.crowds + (size_t)b * p.Nv;
+    if (rg >= items[0]) return;  // the whole workgroup
+    const int item = items[2 + rg];
+    parts = (item & (kSumMostParts - 1)) + 1;
+    part = item / kSumMostParts & (kSumMostParts - 1);
+    rg = item / (kSumMostParts * kSumMostParts);
+  }
+  const int each = parts == 1 ? p.range : (min(p.range, p.Nv - rg * p.range) + parts - 1) / parts;
+  const int t0 = rg * p.range + part * each, span = min(each, min((rg + 1) * p.range, p.Nv) - t0);
+  if (span <= 0) return;  // the whole workgroup (more parts than tokens)
+  const int lo = b * p.ppi;  // the image's pairs
   cnt[tid] = 0;
   if (tid == 0) s_hits = 0;
 
-  // fn(tokens, pairs, in) for four pairs at a time, all lanes of a wave together, of the groups that name a token of the range's
-  // cells
-  int32_t* glist = reinterpret_cast<int32_t*>(entry);
-  uint2 own;  // the range's cells
+  uint2 own;  // the cells that hold its tokens
   {
     const int lo_cell = exact_div(t0, p.cells.size, p.cells.magic), hi_cell = exact_div(t0 + span - 1, p.cells.size, p.cells.magic);
     const int r0 = lo_cell >> 5, r1 = hi_cell >> 5, c0 = lo_cell & 31, c1 = hi_cell & 31;
@@ -130,6 +146,9 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
       own.y = r1 == 1 ? bit_range(r0 == 1 ? c0 : 0, c1) : 0u;
     }
   }
+  const int first = b * p.Nv + t0;
+  // fn(tokens, pairs, in) for four pairs at a time, all lanes of a wave together, of the groups that name a token of these cells
+  int32_t* glist = reinterpret_cast<int32_t*>(entry);
   auto each_pair = [&](auto&& fn) {
     for (int g0 = 0; g0 < p.groups; g0 += kSumGroups) {
       __syncthreads();  // the list before has been walked (and, the first time, the counters are set)
@@ -212,27 +231,28 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
   }
   const bool fits = total <= kSumCap;
   cnt[tid] = run;
-  // (lists that do not fit, where many pairs name few tokens, go to memory, behind those of all earlier tokens)
-  int32_t* far = p.list;
-  if (!fits) {
-    int below = 0;
-    for (int i = lo + tid; i < hi; i += kSumThreads) below += p.pair_token[i] < first ? 1 : 0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o);
-    if (lane == 0) wave_below[wave] = below;
-    __syncthreads();
-    int start = lo;
-    for (int w = 0; w < kSumWaves; ++w) start += wave_below[w];
-    far += start;
-  }
+  // (lists that do not fit, where many pairs name few tokens, go to memory)
+  if (!fits && tid == 0) s_far = atomicAdd(p.crowds + (size_t)b * p.Nv + 1, total);
   __syncthreads();
+  int32_t* const far = p.list + lo + (fits ? 0 : s_far);
   auto row_of = [&](int pair) { return (uint32_t)exact_div(pair - lo, p.row_pairs, p.row_magic) * (uint32_t)p.pieces; };
   if (fits) {
-    for (int i = tid; i < total; i += kSumThreads) {
-      const int pair = (int)hit_pair[i];
-      const int at = atomicAdd(&cnt[hit_token[i]], 1);
-      entry[at] = make_uint2(row_of(pair), __float_as_uint(p.weights[pair]));
-      if (p.extra) entry_extra[at] = p.extra[pair];
+    constexpr int kMine = kSumCap / kSumThreads;
+    int pair[kMine], at[kMine];
+#pragma unroll
+    for (int u = 0; u < kMine; ++u) {
+      const int i = u * kSumThreads + tid;
+      if (i < total) {
+        pair[u] = (int)hit_pair[i];
+        at[u] = atomicAdd(&cnt[hit_token[i]], 1);
+        entry[at[u]] = make_uint2(row_of(pair[u]), __float_as_uint(p.weights[pair[u]]));
+      }
+    }
+    if (p.extra) {
+      __syncthreads();  // hit_pair has been read
+#pragma unroll
+      for (int u = 0; u < kMine; ++u)
+        if (u * kSumThreads + tid < total) entry_extra[at[u]] = p.extra[pair[u]];
     }
   } else {
     each_pair([&](const int (&tok)[4], const int (&pair)[4], const bool (&in)[4]) {
@@ -308,53 +328,53 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
 
 }  // namespace
 
-// Pairs per token up to which this is the way (on average): beyond, too few tokens' lists fit a workgroup.
-constexpr int kSumMostPairs = kSumCap / 16 * 5 / 8;
-
 bool pair_sum_takes(const PairSumArgs& a) {
   auto al = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
   const size_t row = (size_t)a.C * (a.dtype == 1 ? 2 : 4);
   if (row % 16 || !al(a.dout) || !al(a.dfeat)) return false;
-  if ((long long)(a.pairs_per_image / a.row_pairs) * (long long)(row / 16) >= (1ll << 32)) return false;  // places of an image's rows
-  if ((long long)a.pairs_per_image > (long long)kSumMostPairs * a.Nv) return false;
-  return true;
+  return (long long)(a.pairs_per_image / a.row_pairs) * (long long)(row / 16) < (1ll << 32);  // places of an image's rows
 }
 
-// Tokens of a workgroup: two workgroups per CU, but no more pairs than fit with a quarter to spare.
-static int pair_sum_range(int B, int Nv, int pairs_per_image) {
-  const int want = std::max(1, (512 + B - 1) / B);
-  const long long fit = std::max(1ll, (long long)kSumCap * 3 / 4 * Nv / std::max(1, pairs_per_image));
-  return (int)std::min({std::max(64ll, ((long long)Nv + want - 1) / want), fit, (long long)kSumRange});
-}
-// A bit per range where there are no more than 64 of them; else rows, and a quarter of a range, so that the columns tell
-// neighbouring ranges apart, or as much as 1024 cells need.  (One of 64 parts of the image, a bit each, whatever the ranges are: with
-// one image of 262144 tokens, 64 channels, 65536 anchors of 48 pairs the whole backward took 176 us, and with 16384 tokens 19.4;
-// as here 148 and 18.8.  Rows for 64 ranges as well, an anchor's pairs lying in several: one image of 4096 tokens 14.6 instead of 14.1.)
-PairCells pair_sum_cells(int B, int Nv, int pairs_per_image) {
-  const int range = pair_sum_range(B, Nv, pairs_per_image);
-  PairCells c;
-  c.rows = (Nv + range - 1) / range > 64;
-  c.size = c.rows ? std::max((Nv + 1023) / 1024, range / 4) : (Nv + 63) / 64;
-  c.magic = div_magic(c.size);
-  return c;
+// Lanes per row of `pieces` 16-byte pieces.
+static int pair_sum_lanes(int pieces) { return pieces <= 4 ? 4 : pieces <= 8 ? 8 : 16; }
+
+PairSumShape pair_sum_shape(const PairSumArgs& a) {
+  PairSumShape s;
+  // tokens of a workgroup: two workgroups per CU, but on average no more pairs than three fifths of the places
+  const int want = std::max(1, (512 + a.B - 1) / a.B);
+  const long long fit = std::max(1ll, (long long)(kSumCap * 3 / 5) * a.Nv / std::max(1, a.pairs_per_image));
+  const int range = (int)std::min({std::max(64ll, ((long long)a.Nv + want - 1) / want), fit, (long long)kSumRange});
+  // A bit per range where there are no more than 64 of them; else rows, and a quarter of a range, so that the columns tell
+  // neighbouring ranges apart, or as much as 1024 cells need.  (One of 64 parts of the image, a bit each, whatever the ranges are:
+  // with one image of 262144 tokens, 64 channels, 65536 anchors of 48 pairs the whole backward took 176 us, and with 16384 tokens 19.4;
+  // as here 148 and 18.8.  Rows for 64 ranges as well, an anchor's pairs lying in several: one image of 4096 tokens 14.6 instead of 14.1.)
+  s.cells.rows = (a.Nv + range - 1) / range > 64;
+  s.cells.size = s.cells.rows ? std::max((a.Nv + 1023) / 1024, range / 4) : (a.Nv + 63) / 64;
+  s.cells.magic = div_magic(s.cells.size);
+  const int pieces = (int)((size_t)a.C * (a.dtype == 1 ? 2 : 4) / 16);
+  const int turn = kSumThreads / pair_sum_lanes(pieces);  // tokens at a time, with G lanes each: whole turns
+  s.range = range > turn ? range / turn * turn : range;
+  s.ranges = (a.Nv + s.range - 1) / s.range;
+  s.range_magic = div_magic(s.range);
+  s.front = a.pairs_per_image > kSumCap ? (a.B + 7) / 8 * 8 : 0;
+  s.extras = s.front && s.ranges <= kSumMostRanges && (long long)s.range * a.row_pairs > kSumCrowd ? a.pairs_per_image / kSumPart : 0;
+  return s;
 }
 
-hipError_t launch_pair_sum(const PairSumArgs& a, hipStream_t stream) {
+hipError_t launch_pair_sum(const PairSumArgs& a, const PairSumShape& shape, hipStream_t stream) {
   SumParams p;
-  p.pair_token = a.pair_token; p.group_cells = a.group_cells; p.cells = pair_sum_cells(a.B, a.Nv, a.pairs_per_image);
+  p.pair_token = a.pair_token; p.group_cells = a.group_cells; p.cells = shape.cells;
   p.dout = static_cast<const uint4*>(a.dout); p.weights = a.weights; p.extra = a.extra;
-  p.dfeat = static_cast<uint4*>(a.dfeat); p.extra_sum = a.extra_sum; p.list = a.list;
+  p.dfeat = static_cast<uint4*>(a.dfeat); p.extra_sum = a.extra_sum;
+  p.crowds = a.crowds; p.list = a.list; p.extras = shape.extras;
   p.B = a.B; p.Nv = a.Nv; p.ppi = a.pairs_per_image; p.row_pairs = a.row_pairs; p.row_magic = div_magic(a.row_pairs);
   p.gs = a.group_size; p.groups = a.pairs_per_image / p.gs; p.gs_magic = div_magic(p.gs);
   p.pieces = (int)((size_t)a.C * (a.dtype == 1 ? 2 : 4) / 16);
   p.dp_part = a.dp_part; p.dp_n = a.dp_n; p.dp = a.dp;
-  const int g = p.pieces <= 4 ? 4 : p.pieces <= 8 ? 8 : 16;
-  p.range = pair_sum_range(a.B, a.Nv, a.pairs_per_image);
-  const int turn = kSumThreads / g;  // tokens at a time, with G lanes each: whole turns
-  if (p.range > turn) p.range = p.range / turn * turn;
-  p.ranges = (a.Nv + p.range - 1) / p.range;
+  p.range = shape.range; p.ranges = shape.ranges;
+  const dim3 grid((unsigned)(a.B * (p.ranges + p.extras) + (a.dp_part ? 1 : 0)));
+  const int g = pair_sum_lanes(p.pieces);
   const bool split = p.range * g < kSumThreads / 2;
-  const dim3 grid((unsigned)(a.B * p.ranges + (a.dp_part ? 1 : 0)));
 #define AFFMAE_SUM(T, G, SPLIT) \
   AFFMAE_LAUNCH("pair_sum_kernel", stream, (pair_sum_kernel<T, G, SPLIT>), grid, dim3(kSumThreads), 0, stream, p)
 #define AFFMAE_SUM_G(T, SPLIT)             \

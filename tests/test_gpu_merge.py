@@ -252,3 +252,27 @@ def test_merge_finds_the_anchors_of_a_range(B, N, K, n_keep):
     coords = rng.uniform(0, 30, size=(B, N, 2)).astype(np.float32)
     feat, dout = (rng.normal(size=(B, n, 8)).astype(np.float32) for n in (N, n_keep))
     _check_merge_bwd("f32", coords, feat, dout, rng.normal(size=(B, N)).astype(np.float32), _two_places(B, N, K, rng), n_keep)
+
+
+@pytest.mark.parametrize("dtype,B,N,C,K,n_keep,popular", [
+    ("bf16", 64, 1024, 64, 48, 256, None),    # ranges of 128 tokens, 6144 pairs where all are kept: two parts each
+    ("f32", 64, 1024, 16, 64, 300, None),     # three parts of 43 tokens: fewer than lanes
+    ("bf16", 64, 1000, 128, 64, 250, None),   # a last range that is short
+    ("f32", 16, 8192, 8, 16, 5000, 300),      # a token that all anchors name, between others: more pairs than places by itself
+    ("bf16", 16, 8192, 264, 9, 4500, 0),      # ... the first of its range, in rows of three pieces a lane
+    ("bf16", 16, 8192, 8, 9, 4500, 255),      # ... the last
+    ("bf16", 8, 16384, 64, 48, 4096, None),   # four parts a range, in workgroups of their own
+    ("f32", 1, 140000, 4, 64, 52000, None),   # more ranges than are looked at for crowds
+])
+def test_merge_of_crowded_anchors(dtype, B, N, C, K, n_keep, popular):
+    """Anchors that lie side by side, as where an importance score picks out a structure: several times as many pairs per token
+    as on average."""
+    print(f"case merge crowd {dtype} B={B} N={N} C={C} K={K} n_keep={n_keep} popular={popular}", flush=True)
+    rng = np.random.default_rng(N + C + K)
+    coords = rng.uniform(0, 30, size=(B, N, 2)).astype(np.float32)
+    nbr = ((np.arange(N)[None, :, None] + rng.permuted(np.tile(np.arange(K), (B, N, 1)), axis=2) - K // 2) % N).astype(np.int32)
+    if popular is not None:
+        nbr[:, :, K // 2] = popular  # (a row may then hold it twice: it counts twice)
+    score = (np.where(np.arange(N) < n_keep, 10.0, 0.0)[None] + rng.normal(size=(B, N))).astype(np.float32)
+    feat, dout = (rng.normal(size=(B, n, C)).astype(np.float32) for n in (N, n_keep))
+    _check_merge_bwd(dtype, coords, feat, dout, score, nbr, n_keep)
