@@ -823,7 +823,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 size_t wide_hand_bytes(int K) { return (size_t)64 * wide_row(K) + 64; }
 size_t wide_bwd_bytes(const PlaArgs& a) {
   const size_t strips = (size_t)a.B * ((a.N + 15) / 16);
-  return plan_align(strips * a.H * wide_hand_bytes(a.K)) + plan_align(strips * a.H * 2 * a.d * sizeof(float));
+  return plan_align(strips * a.H * wide_hand_bytes(a.K)) + (a.k_blank ? plan_align(strips * a.H * 2 * a.d * sizeof(float)) : 0);
 }
 
 WideParams wide_params(const PlaArgs& a, const void* plan, const PlanLayout& L) {
@@ -895,10 +895,11 @@ hipError_t wide_bwd(const PlaArgs& a, const void* plan, hipStream_t stream) {
 // 15.6, backward 44 / 42; K = 16 15.0 / 15.6 and 48 / 40), and with few terms dS was 4 % further from 64 bits here (d = 64, K = 9).  From 512 workgroups on, forward and backward together are, K 9 .. 64, S 16 ..
 // 64, bf16 d = 16 1.8 - 2.5 times as fast, d = 64 1.2 - 1.9; fp32 d = 16 1.2 - 2.3, d = 64, K >= 16 1.3 - 2.1, d = 32, K >= 16 1.1 - 1.9
 // (forward alone: fp32 d = 16 0.92 - 1.36, d = 32 0.96 - 1.7).
-// (Forward and backward by the same rule: the backward forms p = exp(s - lse) again, and is nearer to 64 bits where s is
-// rounded as in the forward: dS at K = 9 1.9e-7 off with the forward by the gather kernels, 1.6e-7 with either for both.)
+// (Forward and backward by one rule: the backward forms p = exp(s - lse) again, and is further from 64 bits where s is not rounded as
+// in the forward: fp32, K = 9 .. 64, dq 1.08 - 1.22 times as far with the forward by the gather kernels as with both by them, 0.90 - 0.99 with
+// both by these.  So it asks for nothing that only one direction knows; the workspace is what the gather kernels ask for.)
 constexpr long long kWideBlocks = 256;
-static bool wide_limits(const PlaArgs& a, const void* plan) {
+static bool wide_supported(const PlaArgs& a, const void* plan) {
   if (!plan || reinterpret_cast<uintptr_t>(plan) % 256) return false;
   if (a.dtype == 1 && a.d == kD) return false;
   PlaArgs s = a;  // the plan's own limits
@@ -908,13 +909,13 @@ static bool wide_limits(const PlaArgs& a, const void* plan) {
   // byte offsets, and places in [N,H,K] arrays, inside an image
   if ((long long)a.N * a.H * a.d * (a.dtype == 1 ? 2 : 4) >= (1ll << 32) || (long long)a.N * a.H * a.K >= (1ll << 32)) return false;
   if (a.dtype == 0 && a.d >= 32 && a.K < 16) return false;
-  return (long long)a.B * ((a.N + 16 * kGroup - 1) / (16 * kGroup)) * a.H >= kWideBlocks;
+  if ((long long)a.B * ((a.N + 16 * kGroup - 1) / (16 * kGroup)) * a.H < kWideBlocks) return false;
+  return wide_bwd_bytes(a) <= pla_bwd_general_workspace_bytes(a.B, a.N, a.H, a.K);  // (not with K <= 2 and four heads, say)
 }
-bool pla_fwd_wide_supported(const PlaArgs& a, const void* plan) { return wide_limits(a, plan); }
-// (it needs the forward output, and never asks for more workspace than the gather kernels do)
+bool pla_fwd_wide_supported(const PlaArgs& a, const void* plan) { return wide_supported(a, plan); }
+// (out, which the forward gave, as it did)
 bool pla_bwd_wide_supported(const PlaArgs& a, const void* plan) {
-  return wide_limits(a, plan) && a.out && reinterpret_cast<uintptr_t>(a.out) % 16 == 0 &&
-         wide_bwd_bytes(a) <= pla_bwd_general_workspace_bytes(a.B, a.N, a.H, a.K);
+  return wide_supported(a, plan) && a.out && reinterpret_cast<uintptr_t>(a.out) % 16 == 0;
 }
 
 #define AFFMAE_WIDE(IMPL)                                       \

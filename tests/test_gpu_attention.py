@@ -638,6 +638,28 @@ def test_plans_for_other_types_and_heads(dtype, d, B, N, H, K, S, M, blank):
     check_attention(w, nbr, dtype, 8.0 / np.sqrt(d), near=near, S=S, M=M, blank=blank, use_plan=True, tol=4e-5 if dtype == "f32" else None)
 
 
+@pytest.mark.parametrize("dtype,d,B,N,H,K,blank,wide", [
+    ("bf16", 16, 16, 1024, 4, 2, False, False),   # rows of p would not fit the workspace of the gather kernels
+    ("bf16", 16, 16, 1024, 4, 3, False, True),
+    ("bf16", 64, 16, 1024, 4, 9, False, True),
+    ("bf16", 64, 64, 17, 8, 9, False, False),     # ... nor here, where the strips are half empty
+    ("f32", 16, 16, 1024, 8, 3, True, False),     # ... nor beside the parts of the blank gradients
+    ("f32", 16, 16, 1024, 8, 5, True, True),
+    ("f32", 64, 16, 1024, 4, 24, True, True),
+    ("f32", 32, 1, 1024, 4, 24, False, False),    # too few workgroups
+])
+def test_forward_and_backward_take_the_same_way(dtype, d, B, N, H, K, blank, wide):
+    """fp32 storage and head sizes other than 32 on a plan: the kernels with products on fp32 operands serve both directions or none."""
+    print(f"case ways {dtype} d={d} B={B} N={N} H={H} K={K} blank={blank}", flush=True)
+    S, rng = 16 if N < 64 else 64, np.random.default_rng(K)
+    M = min(-(-N // S), 4)
+    w = make_features(B, N, H, d, K, dtype, rng, blank=blank)
+    nbr, near = oracle.knn(rng.uniform(0, 100, size=(B, N, 2)).astype(np.float32), None, S, M, K)
+    run = lambda: check_attention(w, nbr, dtype, 1.0 / np.sqrt(d), near=near, S=S, M=M, blank=blank, use_plan=True)
+    _, kernels = kernels_of(run)
+    assert ("pla_fwd_wide_kernel" in kernels, "pla_bwd_wide_key_kernel" in kernels) == (wide, wide), kernels
+
+
 @pytest.mark.parametrize("dtype,d,K", [("bf16", 16, 24), ("bf16", 64, 37), ("f32", 16, 37), ("f32", 64, 48)])
 def test_slots_that_the_plan_does_not_hold_in_fp32_products(dtype, d, K):
     """As test_slots_that_the_plan_does_not_hold, for the kernels with products on fp32 operands: dbias of such a slot is 0
