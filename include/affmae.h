@@ -320,9 +320,9 @@ int affmae_pla_plan(const int32_t* nbr_idx, const int32_t* near_clusters, int B,
  *                     (S % 16 == 0, any N, M*S <= 1024): those for bf16 storage
  *                     and d == 32 always, those for fp32 storage and for head sizes
  *                     16 and 64, whose products are fp32 throughout, in calls that
- *                     bring a plan and are large enough (B * ceil(N/64) * H >= 256;
- *                     fp32, d >= 32: K >= 16).  Other calls are served by the
- *                     slower gather kernels, same results.
+ *                     bring a plan and where they are the faster way (never below
+ *                     B * ceil(N/64) * H = 256, nor for few neighbours).  Other
+ *                     calls are served by the gather kernels, same results.
  *                     Inputs must then be finite.  With NULL, S and M are ignored.
  *   plan          in  NULL, or the buffer affmae_pla_plan filled for this
  *                     nbr_idx / near_clusters and these B,N,K,S,M.

@@ -48,7 +48,7 @@ struct WideRows {
 // log2 e = n + f, f rounded once and corrected by the rest of log2 e, 2^f by the hardware, n into the exponent.  Below -104 the
 // result is 0, so x is kept above -150: -inf would leave infinity minus infinity.
 __device__ __forceinline__ float wide_exp(float x) {
-  constexpr float kL = 1.44269504f, kLow = 1.92596299e-8f;  // log2 e = kL + kLow
+  constexpr float kL = 1.44269504f, kLow = 1.92596299e-8f;  // log2 e = 1.442695040888963 = 1.44269502162933 + 0.00000001925963
   x = x < -150.f ? -150.f : x;  // (not a maximum: NaN stays NaN)
   const float n = __builtin_rintf(x * kL);
   const float f = fmaf(x, kLow, fmaf(x, kL, -n));
@@ -890,15 +890,34 @@ hipError_t wide_bwd(const PlaArgs& a, const void* plan, hipStream_t stream) {
 }  // namespace
 
 // Where these kernels are the better way.  Not in a call of fewer workgroups than CUs (a wave per strip of 16 tokens here, per
-// token there): B1 N1000 H1 K48 d32 fp32, us, gather / here: forward 13 / 19, backward 27 / 44.  Nor for few neighbours of 32 fp32
-// channels or more: a row costs the gather kernels as much as the product of its tile's 16 rows costs here (d = 32, K = 9 forward 14.5 /
-// 15.6, backward 44 / 42; K = 16 15.0 / 15.6 and 48 / 40), and with few terms dS was 4 % further from 64 bits here (d = 64, K = 9).  From 512 workgroups on, forward and backward together are, K 9 .. 64, S 16 ..
-// 64, bf16 d = 16 1.8 - 2.5 times as fast, d = 64 1.2 - 1.9; fp32 d = 16 1.2 - 2.3, d = 64, K >= 16 1.3 - 2.1, d = 32, K >= 16 1.1 - 1.9
-// (forward alone: fp32 d = 16 0.92 - 1.36, d = 32 0.96 - 1.7).
+// token there): B1 N1000 H1 K48 d32 fp32, us, gather / here: forward 13 / 19, backward 27 / 44.  Above that it is a matter of the
+// neighbours, as a tile's product costs the same for few as for many, and of how full the last of the rounds of 512 workgroups is that the
+// chip holds: up to 512 .. 767 (1 .. 1.5 rounds) count as `some`, up to 1024 as `most`, and from there on, and near 512, as `full`.
+// Gather kernels' time / here, forward and backward together (forward alone), on tables from masked, uniform and jittered tokens, S =
+// 64, M = 8; S = 16 and 32 have fewer tiles a strip and are up to 1.3 times better:
+//                  full                                 most                            some
+//   bf16 d = 16    K 3 .. 64  1.7 - 3.4 (1.2 - 2.4)     1.6 - 2.2 (1.3 - 1.9)           1.3 - 2.1 (1.0 - 1.5)
+//   bf16 d = 64    K 17 .. 64 1.11 - 2.0 (1.2 - 2.1)    1.0 - 1.12 (1.14 - 1.35)        K < 48 0.93 - 1.04, K >= 48 0.97 - 1.14 (0.88 - 1.04)
+//                  K 9 .. 16  0.96 - 1.2 (0.91 - 1.26)  0.88 - 0.95                     0.77 - 0.93
+//   fp32 d = 64    K 16 .. 64 1.14 - 2.7 (1.3 - 3.0)    1.03 - 1.36 (1.23 - 1.6)        K < 48 0.90 - 1.01, K >= 48 1.16 - 1.35 (1.2 - 1.6)
+//   fp32 d = 32    K 17 .. 64 1.07 - 2.2 (0.93 - 1.7)   K >= 48 1.10 - 1.21 (0.88 - 0.93)   0.90 - 1.2, but the forward 0.71 - 0.92
+//                  K = 16     0.79 - 1.1 (0.67 - 0.97)  K < 48 0.96 - 1.05 (0.87 - 1.0)
+//   fp32 d = 16    K 3 .. 64  0.99 - 3.1 (0.88 - 1.7)   K >= 48 1.28 - 1.53 (0.85 - 0.9)    K < 16 1.05 - 1.16 (1.0); 1.01 - 1.4, but the
+//                                                       K < 48 0.96 - 1.24 (0.8 - 1.1)      forward 0.76 - 1.0, from there on
+// so the rule keeps out what is slower for a step, or for a forward alone by more than 15 %.
+// (fp32 d = 64, K = 9: dS was 4 % further from 64 bits than by the gather kernels.)
 // (Forward and backward by one rule: the backward forms p = exp(s - lse) again, and is further from 64 bits where s is not rounded as
-// in the forward: fp32, K = 9 .. 64, dq 1.08 - 1.22 times as far with the forward by the gather kernels as with both by them, 0.90 - 0.99 with
+// in the forward: fp32, K = 9 .. 64, dq 1.09 - 1.18 times as far with the forward by the gather kernels as with both by them, 0.90 - 0.99 with
 // both by these.  So it asks for nothing that only one direction knows; the workspace is what the gather kernels ask for.)
-constexpr long long kWideBlocks = 256;
+static bool wide_pays(const PlaArgs& a) {
+  const long long blocks = (long long)a.B * ((a.N + 16 * kGroup - 1) / (16 * kGroup)) * a.H;
+  if (blocks < 256) return false;
+  const bool full = blocks >= 1024 || (blocks >= 448 && blocks <= 512), most = full || blocks >= 768;
+  if (a.d == 64) return a.K >= (full ? (a.dtype == 1 ? 9 : 16) : most ? 17 : 48);
+  if (a.dtype == 1) return a.K >= 3;
+  if (a.d == 32) return full ? a.K >= 17 : most && a.K >= 48;
+  return a.K >= 3 && (full || a.K < 16 || (most && a.K >= 48));
+}
 static bool wide_supported(const PlaArgs& a, const void* plan) {
   if (!plan || reinterpret_cast<uintptr_t>(plan) % 256) return false;
   if (a.dtype == 1 && a.d == kD) return false;
@@ -908,9 +927,7 @@ static bool wide_supported(const PlaArgs& a, const void* plan) {
   if (!pla_cluster_supported(s)) return false;
   // byte offsets, and places in [N,H,K] arrays, inside an image
   if ((long long)a.N * a.H * a.d * (a.dtype == 1 ? 2 : 4) >= (1ll << 32) || (long long)a.N * a.H * a.K >= (1ll << 32)) return false;
-  if (a.dtype == 0 && a.d >= 32 && a.K < 16) return false;
-  if ((long long)a.B * ((a.N + 16 * kGroup - 1) / (16 * kGroup)) * a.H < kWideBlocks) return false;
-  return wide_bwd_bytes(a) <= pla_bwd_general_workspace_bytes(a.B, a.N, a.H, a.K);  // (not with K <= 2 and four heads, say)
+  return wide_pays(a) && wide_bwd_bytes(a) <= pla_bwd_general_workspace_bytes(a.B, a.N, a.H, a.K);
 }
 bool pla_fwd_wide_supported(const PlaArgs& a, const void* plan) { return wide_supported(a, plan); }
 // (out, which the forward gave, as it did)

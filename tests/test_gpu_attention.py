@@ -615,15 +615,25 @@ def test_plans_on_both_sides_of_the_tile_table(N, K, S, M):
 
 
 @pytest.mark.parametrize("dtype,d", [("f32", 16), ("f32", 32), ("f32", 64), ("bf16", 16), ("bf16", 64)])
-@pytest.mark.parametrize("B,N,H,K,S,M,blank", [  # (at least 256 workgroups: below, the gather kernels serve these calls)
+@pytest.mark.parametrize("B,N,H,K,S,M,blank", [  # (448 to 512 workgroups: all but the smallest K by the kernels in question)
+    (16, 1024, 2, 48, 64, 8, False),
+    (10, 1000, 3, 37, 64, 8, True),   # a short last strip and token tile, odd K and H
+    (64, 512, 1, 64, 16, 32, True),   # the longest rows; unions of many stages
+    (120, 90, 2, 17, 48, 2, False),   # a group of two strips, the last one short; the fewest neighbours that fp32 d = 32 takes
+    (7, 4099, 1, 24, 32, 6, True),
+    (3, 2064, 5, 33, 64, 5, False),   # the last group of one strip
+    (7, 2051, 2, 3, 64, 2, True),     # the shortest rows (d = 16)
+    (7, 2051, 2, 9, 64, 2, True),     # ... (bf16 d = 64)
+    (7, 2051, 2, 16, 64, 3, True),    # ... (fp32 d = 64)
+    # and where some of the types are served by the gather kernels
     (8, 1024, 2, 48, 64, 8, False),
     (6, 1000, 3, 37, 64, 8, True),    # a short last strip and token tile, odd K and H
     (32, 512, 1, 64, 16, 32, True),   # the longest rows; unions of many stages
     (64, 90, 2, 16, 48, 2, False),    # a group of two strips, the last one short
     (4, 4099, 1, 24, 32, 6, True),
     (2, 2064, 5, 33, 64, 5, False),   # the last group of one strip
-    (2, 2051, 4, 1, 64, 2, True),     # K = 1: the shortest rows (fp32: the gather kernels from d = 32 on)
-    (2, 2051, 4, 16, 64, 3, True),    # the fewest neighbours that fp32 takes here
+    (2, 2051, 4, 1, 64, 2, True),     # K = 1 (the gather kernels)
+    (2, 2051, 4, 16, 64, 3, True),
 ])
 def test_plans_for_other_types_and_heads(dtype, d, B, N, H, K, S, M, blank):
     """fp32 storage, and bf16 with head sizes other than 32, on a plan: products on fp32 operands.  The bar of the gather
@@ -632,7 +642,11 @@ def test_plans_for_other_types_and_heads(dtype, d, B, N, H, K, S, M, blank):
     cfg = CONFIGS["knn_scale" if N % 16 else "mae_pt_s1_1024"].scaled(B=B, N=N, C=H * d, H=H, K=K, S=S, M=M, dtype=dtype)
     w = make_workload(cfg, blank=blank)
     nbr, near = oracle.knn(w["coords"], None, S, M, K)
-    check_attention(w, nbr, dtype, 1.0 / np.sqrt(d), near=near, S=S, M=M, blank=blank, use_plan=True)
+    run = lambda: check_attention(w, nbr, dtype, 1.0 / np.sqrt(d), near=near, S=S, M=M, blank=blank, use_plan=True)
+    kernels = kernels_of(run)[1]
+    if 448 <= B * -(-N // 64) * H <= 512:
+        wide = K >= {("f32", 16): 3, ("f32", 32): 17, ("f32", 64): 16, ("bf16", 16): 3, ("bf16", 64): 9}[dtype, d]
+        assert ("pla_fwd_wide_kernel" in kernels, "pla_bwd_wide_key_kernel" in kernels) == (wide, wide), kernels
     # logits with a standard deviation of 8: scores below 64, whose products and sum round to 2^-19 a few times over, as does lse, so
     # that p = exp(s - lse) is off by up to 1e-5; p (dP - D) and its sums over terms of both signs by a few times that
     check_attention(w, nbr, dtype, 8.0 / np.sqrt(d), near=near, S=S, M=M, blank=blank, use_plan=True, tol=4e-5 if dtype == "f32" else None)
@@ -647,6 +661,19 @@ def test_plans_for_other_types_and_heads(dtype, d, B, N, H, K, S, M, blank):
     ("f32", 16, 16, 1024, 8, 5, True, True),
     ("f32", 64, 16, 1024, 4, 24, True, True),
     ("f32", 32, 1, 1024, 4, 24, False, False),    # too few workgroups
+    ("f32", 32, 16, 1024, 2, 17, False, True),    # 512 workgroups: a full round
+    ("f32", 32, 16, 1024, 2, 16, False, False),
+    ("f32", 32, 9, 1024, 4, 64, False, False),    # 576: little of a second one
+    ("f32", 32, 12, 1024, 4, 48, False, True),    # 768: half of it
+    ("f32", 32, 12, 1024, 4, 47, False, False),
+    ("f32", 16, 9, 1024, 4, 24, False, False),
+    ("f32", 16, 9, 1024, 4, 15, False, True),
+    ("f32", 64, 9, 1024, 4, 48, False, True),
+    ("f32", 64, 9, 1024, 4, 47, False, False),
+    ("bf16", 64, 12, 1024, 4, 16, False, False),
+    ("bf16", 64, 12, 1024, 4, 17, False, True),
+    ("bf16", 64, 16, 1024, 4, 8, False, False),
+    ("bf16", 16, 4, 1024, 4, 3, False, True),     # 256
 ])
 def test_forward_and_backward_take_the_same_way(dtype, d, B, N, H, K, blank, wide):
     """fp32 storage and head sizes other than 32 on a plan: the kernels with products on fp32 operands serve both directions or none."""
