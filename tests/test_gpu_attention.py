@@ -716,3 +716,78 @@ def test_slots_that_the_plan_does_not_hold_in_fp32_products(dtype, d, K):
     f = torch.from_numpy(foreign).cuda()[None, :, None].expand(B, N, H, K)
     assert (bias[f] != 0).float().mean() > 0.9
     assert (dbias[f] == 0).all() and (dbias[~f] != 0).float().mean() > 0.9
+
+
+WIDE_TYPES = [("f32", 16), ("f32", 32), ("f32", 64), ("bf16", 16), ("bf16", 64)]
+
+
+@pytest.mark.parametrize("dtype,d", WIDE_TYPES)
+@pytest.mark.parametrize("strips", [64, 65, 128, 129])
+def test_popular_groups_of_tiles_in_fp32_products(dtype, d, strips):
+    """As test_popular_groups_of_tiles: the key side walks a group's list in parts of 64 strips, two buffers in turn."""
+    print(f"case popular groups {dtype} d={d} strips={strips}", flush=True)
+    B, N, H, K, S, M = 7, 4096, 1, 20, 64, 5
+    G = N // S
+    rng = np.random.default_rng(strips + d)
+    near = np.stack([np.arange(M) + min(max(c - 1, 0), G - M) for c in range(G)]).astype(np.int32)
+    own = int((near == 0).any(axis=1).sum()) * S // 16  # strips around the first cluster
+    far = strips - own
+    first = 8
+    near[first : first + -(-far * 16 // S), M - 1] = 0
+    cand = (near[:, :, None] * S + np.arange(S)).reshape(G, M * S)
+    score = rng.random((N, M * S))
+    named = np.zeros(N, bool)
+    named[first * S : first * S + far * 16] = True
+    score[~named & (np.arange(N) >= first * S), (M - 1) * S :] += 2.0  # (the rest of the last cluster: no neighbour there)
+    nbr = np.take_along_axis(cand[np.arange(N) // S], np.argsort(score, axis=1)[:, :K], axis=1).astype(np.int32)
+    assert (nbr.reshape(N // 16, -1) < S).any(axis=1).sum() == strips
+    w = make_features(B, N, H, d, K, dtype, rng)
+    many = lambda t: np.repeat(t[None], B, axis=0)
+    run = lambda: check_attention(w, many(nbr), dtype, 1.0 / np.sqrt(d), near=many(near), S=S, M=M, use_plan=True)
+    assert "pla_bwd_wide_key_kernel" in kernels_of(run)[1]
+
+
+@pytest.mark.parametrize("dtype,d", WIDE_TYPES)
+@pytest.mark.parametrize("M", [15, 16, 17, 20])
+def test_unions_of_many_tiles_in_fp32_products(dtype, d, M):
+    """Strips of a group with no tile in common: unions of 60, 64, 68 and 80 tiles, whose numbers are fetched 64 at a time."""
+    print(f"case unions {dtype} d={d} M={M}", flush=True)
+    B, N, H, K, S = 4, 4096, 2, 48, 16
+    G = N // S
+    rng = np.random.default_rng(M + d)
+    c = np.arange(G)[:, None]
+    near = ((c % 4) * (G // 4) + (c // 4 + np.arange(M)) % (G // 4)).astype(np.int32)
+    cand = (near[:, :, None] * S + np.arange(S)).reshape(G, M * S)
+    nbr = np.take_along_axis(cand[np.arange(N) // S], np.argsort(rng.random((N, M * S)), axis=1)[:, :K], axis=1).astype(np.int32)
+    assert len(np.unique(nbr[:64] // 16)) == 4 * M
+    w = make_features(B, N, H, d, K, dtype, rng, blank=True)
+    many = lambda t: np.repeat(t[None], B, axis=0)
+    run = lambda: check_attention(w, many(nbr), dtype, 1.0 / np.sqrt(d), near=many(near), S=S, M=M, blank=True, use_plan=True)
+    assert "pla_bwd_wide_query_kernel" in kernels_of(run)[1]
+
+
+def test_exponential_of_the_fp32_products():
+    """The exponential over its range: without queries the scores are the bias, and with unit vectors as values the outputs are exp(bias)
+    over their sum.  The exponential rounds its argument's fraction once (half a unit at 1/2: 2^-26 ln 2 of the result), 2^fraction to one unit
+    (2^-23 at most), the sum and the quotient to half of one each: below 3 2^-23 altogether, and exactly 0 from -104 on."""
+    B, N, H, d, K, S, M = 7, 4096, 1, 32, 32, 64, 1
+    rng = np.random.default_rng(5)
+    x = np.where(rng.random((B, N, H, K)) < 0.05, rng.uniform(-400, -104, size=(B, N, H, K)), -(rng.random((B, N, H, K)) ** 3) * 80.0)
+    x = x.astype(np.float32)
+    x[..., 0] = 0.0
+    nbr = (np.arange(N)[:, None] // S * S + np.arange(K)).astype(np.int32)
+    near = (np.arange(N // S)[:, None]).astype(np.int32)
+    v = np.zeros((B, N, H, d), np.float32)
+    v[:, np.arange(N), 0, np.arange(N) % d] = 1.0
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    q, k, v, bias = up(np.zeros((B, N, H, d), np.float32)), up(rng.normal(size=(B, N, H, d)).astype(np.float32)), up(v), up(x)
+    nbr_d, near_d = (up(np.repeat(t[None], B, axis=0)) for t in (nbr, near))
+    plan = aff.affmae_pla_plan(nbr_d, near_d, S, M)
+    (out, _), kernels = kernels_of(lambda: aff.affmae_pla_fwd(q, k, v, bias, nbr_d, 0.25, near_d, S, M, plan=plan))
+    assert "pla_fwd_wide_kernel" in kernels
+    e = np.exp(x.astype(np.float64))
+    ref = e / e.sum(axis=-1, keepdims=True)
+    got = out.cpu().numpy().astype(np.float64)
+    assert np.all(got[x < -104.0] == 0.0) and (x < -104.0).sum() > 10000
+    some = x > -87.0 + np.log(32.0)  # (normal results)
+    assert np.abs(got[some] / ref[some] - 1.0).max() <= 3 * 2.0 ** -23
