@@ -332,4 +332,46 @@ inline RelSource rel_source(const PlaArgs& a) {
   return s;
 }
 
+// Straight from memory into LDS (lane l's bytes land at dst + 16 l, or + 4 l).  By hand: for the compiler every LDS read might
+// read what such a load still writes, and it would wait for what is on its way before it reads what is there.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"  // (m0 is reserved: written only for the next instruction, never held)
+__device__ __forceinline__ void lds_load16(uint32_t dst, const char* base, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(base) : "m0", "memory");
+}
+__device__ __forceinline__ void lds_load4(uint32_t dst, const char* base, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(dst), "v"(off), "s"(base) : "m0", "memory");
+}
+#pragma clang diagnostic pop
+__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(size_t)(__attribute__((address_space(3))) const char*)p; }
+
+// dk_blank, dv_blank [H,D] = sums over the strips of part [strips][H][2][D], in a fixed order: D / 8 workgroups per (head, which of the
+// two), the i-th of them all, 8 channels each, 32 groups of 8 lanes; group j adds strips j, j + 32, ..., eight loads in flight (one at a
+// time the few workgroups waited for one memory round trip per strip: 7.5 us at 753 strips).  `lds`: 256 words.
+template <int D>
+__device__ __forceinline__ void blank_sums(const float* part, int strips, int H, int i, float* lds, float* dk_blank, float* dv_blank) {
+  constexpr int kParts = D / 8;
+  const int which = (i / kParts) & 1, h = i / (2 * kParts);
+  const int c = i % kParts * 8 + (threadIdx.x & 7), grp = threadIdx.x >> 3;
+  float s = 0.f;
+  for (int sg0 = grp; sg0 < strips; sg0 += 8 * 32) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int sg = sg0 + 32 * u;
+      v[u] = part[(((size_t)min(sg, strips - 1) * H + h) * 2 + which) * D + c];
+      if (sg >= strips) v[u] = 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
+  lds[threadIdx.x] = s;
+  __syncthreads();
+  if (grp == 0) {
+    float t = 0.f;
+    for (int j = 0; j < 32; ++j) t += lds[j * 8 + threadIdx.x];
+    (which ? dv_blank : dk_blank)[h * D + c] = t;
+  }
+}
+
 }  // namespace affmae

@@ -110,6 +110,26 @@ __device__ __forceinline__ float lanes_max(float x, int lane) {
 __device__ __forceinline__ float wave_max(float x) { return lanes_max<1, 32>(x, threadIdx.x & (kWave - 1)); }
 __device__ __forceinline__ float wave_sum(float x) { return lanes_sum<1, 32>(x, threadIdx.x & (kWave - 1)); }
 
+// *out = part[lo] + ... + part[hi - 1] by a workgroup of 1024 threads, in an order that is the same in every launch; part + lo is
+// 16-byte aligned, `acc` LDS.
+__device__ __forceinline__ void sum_parts(const float* __restrict__ part, size_t lo, size_t hi, float (&acc)[16], float* out) {
+  float s = 0.f;
+  const size_t n4 = (hi - lo) / 4;  // whole 16-byte pieces first
+  for (size_t i = threadIdx.x; i < n4; i += 1024) {
+    const float4 v = reinterpret_cast<const float4*>(part + lo)[i];
+    s += (v.x + v.y) + (v.z + v.w);
+  }
+  for (size_t i = lo + n4 * 4 + threadIdx.x; i < hi; i += 1024) s += part[i];
+  s = wave_sum(s);
+  if ((threadIdx.x & (kWave - 1)) == 0) acc[threadIdx.x / kWave] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float t = 0.f;
+    for (int w = 0; w < 16; ++w) t += acc[w];
+    *out = t;
+  }
+}
+
 // Orders LDS traffic between the lanes of one wave (no workgroup barrier).
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");

@@ -79,25 +79,6 @@ __device__ __forceinline__ uint4 pack_piece(const float (&a)[8]) {
 // bits lo .. hi, 0 <= lo <= hi < 32
 __device__ __forceinline__ uint32_t bit_range(int lo, int hi) { return (~0u >> (31 - (hi - lo))) << lo; }
 
-// Sum of the parts in the order of launch_sum_parts (one workgroup).
-__device__ __forceinline__ void sum_parts(const float* part, int n, float* out, float* wave_sums) {
-  float s = 0.f;
-  const int n4 = n / 4;
-  for (int i = threadIdx.x; i < n4; i += kSumThreads) {
-    const float4 v = reinterpret_cast<const float4*>(part)[i];
-    s += (v.x + v.y) + (v.z + v.w);
-  }
-  for (int i = n4 * 4 + threadIdx.x; i < n; i += kSumThreads) s += part[i];
-  s = wave_sum(s);
-  if ((threadIdx.x & (kWave - 1)) == 0) wave_sums[threadIdx.x / kWave] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float t = 0.f;
-    for (int w = 0; w < kSumWaves; ++w) t += wave_sums[w];
-    *out = t;
-  }
-}
-
 // G: lanes per row (4, 8 or 16).  SPLIT: a wave per token, its 64 / G groups of lanes taking the token's pairs in turn
 // (ranges of so few tokens that a group of lanes per token would leave lanes idle); otherwise G lanes per token.
 template <typename T, int G, bool SPLIT>
@@ -112,7 +93,8 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
   static_assert(kSumGroups * 4 <= kSumCap * 8, "the listed groups lie in the entries' place");
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   if (p.dp_part && blockIdx.x == gridDim.x - 1) {
-    sum_parts(p.dp_part, p.dp_n, p.dp, reinterpret_cast<float*>(wave_total));
+    __shared__ float acc[kSumWaves];
+    sum_parts(p.dp_part, 0, (size_t)p.dp_n, acc, p.dp);
     return;
   }
   // a range of an image's tokens, or a part of it

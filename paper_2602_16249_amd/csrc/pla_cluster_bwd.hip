@@ -384,9 +384,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 // ------------------------------------------------------------------------------------------------
 // What is left to add up behind the query-stationary kernel, each in a fixed order, `i` being the workgroup:
 //  rel_dtable[i] = sum over the groups of rel_part[group][i]  (i < rel_entries)
-//  dk_blank, dv_blank [H,32] = sums over the strips of blank_part: four workgroups per (head, which of the two), 8 channels
-//  each, 32 groups of 8 lanes; group j adds strips j, j + 32, ..., eight loads in flight (one at a time the few workgroups
-//  waited for one memory round trip per strip: 7.5 us at 753 strips).
+//  dk_blank, dv_blank = sums over the strips of blank_part
 // As launches of their own, behind the key-stationary kernel, they took 5.0 us (2048 tables of 162 bins) and 3.5 us (753
 // strips, 3 heads) and the gap before them, at the end of a step; here they run beside it.
 __device__ __forceinline__ void side_sums(const BwdParams& p, int i, float* lds) {
@@ -401,28 +399,7 @@ __device__ __forceinline__ void side_sums(const BwdParams& p, int i, float* lds)
     return;
   }
   i -= p.rel_entries;
-  if (i >= p.blank_blocks) return;
-  const int h = i >> 3, which = (i >> 2) & 1;
-  const int c = (i & 3) * 8 + (threadIdx.x & 7), grp = threadIdx.x >> 3;
-  float s = 0.f;
-  for (int sg0 = grp; sg0 < p.strips; sg0 += 8 * 32) {
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int sg = sg0 + 32 * u;
-      v[u] = p.blank_part[(((size_t)min(sg, p.strips - 1) * p.t.H + h) * 2 + which) * kD + c];
-      if (sg >= p.strips) v[u] = 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s += v[u];
-  }
-  lds[threadIdx.x] = s;
-  __syncthreads();
-  if (grp == 0) {
-    float t = 0.f;
-    for (int j = 0; j < 32; ++j) t += lds[j * 8 + threadIdx.x];
-    (which ? p.dv_blank : p.dk_blank)[h * kD + c] = t;
-  }
+  if (i < p.blank_blocks) blank_sums<kD>(p.blank_part, p.strips, p.t.H, i, lds, p.dk_blank, p.dv_blank);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -471,8 +448,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CL == 2 ? 3
   const char* gimg = reinterpret_cast<const char*>(p.dout) + img_off;
   const int hand_pieces = 2 * RH + 4;
   const char* jimg = p.t.jt + mul_u32(strip0, p.t.jt_bytes);
-  const uint32_t lds_strips = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)&strips[0][0][0];
-  const uint32_t lds_jb = (uint32_t)(size_t)(__attribute__((address_space(3))) char*)&jb_all[0][wave][0][0];
+  const uint32_t lds_strips = lds_address(strips);
+  const uint32_t lds_jb = lds_address(jb_all[0][wave]);
   const int rd_off = tile_chunk(r, g) * 16;
   const int tr_off0 = tile_tr_offset(g, r, 0), tr_off1 = tile_tr_offset(g, r, 1);
   const int jb_off = ((r >> 2) * 16 + 4 * g) * 4 + (r & 3);
@@ -481,17 +458,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CL == 2 ? 3
   f32x4 dk[2], dv[2];
 #pragma unroll
   for (int dt = 0; dt < 2; ++dt) dk[dt] = dv[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // The rows come straight from memory into LDS.  By hand: for the compiler every LDS read might read what such a load
-  // still writes, and it would wait for the next chunk before it reads this one.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"  // (m0 is reserved: written only for the next instruction, never held)
-  auto dma16 = [](uint32_t dst, const char* base, uint32_t off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(base) : "m0", "memory");
-  };
-  auto dma4 = [](uint32_t dst, const char* base, uint32_t off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(dst), "v"(off), "s"(base) : "m0", "memory");
-  };
-#pragma clang diagnostic pop
   for (int base = 0; base < n; base += kWave) {
     const int nb = min(kWave, n - base);
     const unsigned long long mine = lane < nb ? list[base + lane] : ~0ull;
@@ -507,18 +473,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CL == 2 ? 3
         uint32_t off = (uint32_t)__builtin_amdgcn_readlane(my_rows, e) + lane_off;
         if (RAG) off = min(off, lane_off_max);
         const uint32_t dst = lds_strips + (uint32_t)((buf * kChunk + wave) * kStrip);
-        dma16(dst, qimg, off);
-        dma16(dst + 1024u, gimg, off);
+        lds_load16(dst, qimg, off);
+        lds_load16(dst + 1024u, gimg, off);
         const char* hand = p.hand + mul_u32((strip0 + (uint32_t)__builtin_amdgcn_readlane(my_strip, e)) * p.t.H + h, p.block_bytes);
 #pragma unroll
         for (int i = 0; i < (CL == 2 ? 3 : 2); ++i)
-          if (lane + i * kWave < hand_pieces) dma16(dst + 2048u + i * 1024u, hand, (uint32_t)(lane + i * kWave) * 16u);
+          if (lane + i * kWave < hand_pieces) lds_load16(dst + 2048u + i * 1024u, hand, (uint32_t)(lane + i * kWave) * 16u);
       }
       const uint32_t on = (uint32_t)(mask >> (c * kChunk));
 #pragma unroll
       for (int i = 0; i < kChunk; ++i)
         if (on & (1u << i))
-          dma4(lds_jb + (uint32_t)((buf * kGroup * kChunk + i) * 256), jimg, (uint32_t)__builtin_amdgcn_readlane(my_jt, c * kChunk + i) + (uint32_t)lane * 8u);
+          lds_load4(lds_jb + (uint32_t)((buf * kGroup * kChunk + i) * 256), jimg, (uint32_t)__builtin_amdgcn_readlane(my_jt, c * kChunk + i) + (uint32_t)lane * 8u);
     };
     auto compute = [&](int c, auto buf) {
       const uint32_t on = (uint32_t)(mask >> (c * kChunk));

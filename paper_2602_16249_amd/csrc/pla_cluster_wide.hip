@@ -132,18 +132,6 @@ struct Chains {
 template <typename T, int D>
 constexpr int chains() { return sizeof(T) == 2 ? 1 : D <= 32 ? 8 : 4; }
 
-// Straight from memory into LDS (lane l's bytes land at dst + 16 l, or + 4 l).  By hand: for the compiler every LDS read might
-// read what such a load still writes, and it would wait for the next stage before it reads this one.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"  // (m0 is reserved: written only for the next instruction, never held)
-__device__ __forceinline__ void lds_load16(uint32_t dst, const char* base, uint32_t off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(off), "s"(base) : "m0", "memory");
-}
-__device__ __forceinline__ void lds_load4(uint32_t dst, const char* base, uint32_t off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(dst), "v"(off), "s"(base) : "m0", "memory");
-}
-#pragma clang diagnostic pop
-__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(size_t)(__attribute__((address_space(3))) const char*)p; }
 // every load into LDS has landed, in every wave
 __device__ __forceinline__ void lds_loads_arrive() {
   __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): rows on their way to LDS count as vector loads
@@ -663,34 +651,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   w.store(p.t, p.dq, acc, p.scale);
 }
 
-// dk_blank, dv_blank [H,D] = sums over the strips of their parts: as side_sums of pla_cluster_bwd.hip
-template <int D>
-__device__ __forceinline__ void wide_blank_sums(const WideParams& p, int i, float* lds) {
-  if (i >= p.blank_blocks) return;
-  constexpr int kParts = D / 8;
-  const int c8 = i % kParts, which = (i / kParts) & 1, h = i / (2 * kParts);
-  const int c = c8 * 8 + (threadIdx.x & 7), grp = threadIdx.x >> 3;
-  float s = 0.f;
-  for (int sg0 = grp; sg0 < p.strips; sg0 += 8 * 32) {
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int sg = sg0 + 32 * u;
-      v[u] = p.blank_part[(((size_t)min(sg, p.strips - 1) * p.t.H + h) * 2 + which) * D + c];
-      if (sg >= p.strips) v[u] = 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s += v[u];
-  }
-  lds[threadIdx.x] = s;
-  __syncthreads();
-  if (grp == 0) {
-    float t = 0.f;
-    for (int j = 0; j < 32; ++j) t += lds[j * 8 + threadIdx.x];
-    (which ? p.dv_blank : p.dk_blank)[h * D + c] = t;
-  }
-}
-
 // Key side: a wave per tile of 16 tokens; the strips that touch any of the workgroup's four tiles go through LDS, a chunk on its
 // way while one is used.
 template <typename T, int D, bool RAG>
@@ -704,7 +664,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int g = lane >> 4, r = lane & 15;
   if ((int)blockIdx.x < p.front) {  // the whole workgroup
-    wide_blank_sums<D>(p, blockIdx.x, reinterpret_cast<float*>(strips));
+    if ((int)blockIdx.x < p.blank_blocks) blank_sums<D>(p.blank_part, p.strips, p.t.H, blockIdx.x, reinterpret_cast<float*>(strips), p.dk_blank, p.dv_blank);
     return;
   }
   const int blk = p.block0 + xcd_contiguous_block(blockIdx.x - p.front, gridDim.x - p.front);

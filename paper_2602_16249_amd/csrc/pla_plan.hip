@@ -19,7 +19,7 @@ struct PlanParams {
   const int32_t* nbr_idx;  // [B,N,K]
   const int32_t* near;     // [B,G,M]
   int N, K, S, M, G;
-  uint32_t s_magic, k_magic, tpc_magic, gpi_magic;
+  uint32_t s_magic, tpc_magic, gpi_magic;
   int strips_per_image, groups_per_image, groups, uni_stride, pos_stride, jt_pairs, touch_stride;
   uint16_t* uni;
   uint8_t* pos;
@@ -474,7 +474,7 @@ hipError_t launch_pla_plan(const int32_t* nbr_idx, const int32_t* near, int B, i
   PlanParams p;
   p.nbr_idx = nbr_idx; p.near = near;
   p.N = N; p.K = K; p.S = S; p.M = M; p.G = (N + S - 1) / S;  // the last cluster may be short
-  p.s_magic = div_magic(S); p.k_magic = div_magic(K); p.tpc_magic = div_magic(S / 16); p.gpi_magic = div_magic(L.groups_per_image);
+  p.s_magic = div_magic(S); p.tpc_magic = div_magic(S / 16); p.gpi_magic = div_magic(L.groups_per_image);
   p.strips_per_image = L.strips_per_image; p.groups_per_image = L.groups_per_image; p.groups = L.groups;
   p.uni_stride = L.uni_stride; p.pos_stride = L.pos_stride; p.jt_pairs = L.jt_pairs; p.touch_stride = L.touch_stride;
   p.uni = reinterpret_cast<uint16_t*>(base + L.uni_off);

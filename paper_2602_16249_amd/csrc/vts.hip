@@ -709,23 +709,6 @@ __global__ __launch_bounds__(256) void vts_bwdg_kernel(const float* __restrict__
 // into out[j]; a second launch with one workgroup adds up those sums.
 constexpr int kDpPer = 16384;
 constexpr size_t kDpInLists = 8 * (size_t)kDpPer;  // up to so many, the sum is one workgroup's, behind those of the lists' launch
-__device__ __forceinline__ void sum_parts(const float* __restrict__ part, size_t lo, size_t hi, float* acc, float* out) {
-  float s = 0.f;
-  const size_t n4 = (hi - lo) / 4;  // the workspace slots are 256-byte aligned: whole 16-byte pieces first
-  for (size_t i = threadIdx.x; i < n4; i += blockDim.x) {
-    const float4 v = reinterpret_cast<const float4*>(part + lo)[i];
-    s += (v.x + v.y) + (v.z + v.w);
-  }
-  for (size_t i = lo + n4 * 4 + threadIdx.x; i < hi; i += blockDim.x) s += part[i];
-  s = wave_sum(s);
-  if ((threadIdx.x & (kWave - 1)) == 0) acc[threadIdx.x / kWave] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float t = 0.f;
-    for (int w = 0; w < 16; ++w) t += acc[w];
-    *out = t;
-  }
-}
 __global__ __launch_bounds__(1024) void vts_dp_kernel(const float* __restrict__ part, size_t n, size_t per,
                                                       float* __restrict__ out) {
   __shared__ float acc[16];
@@ -752,7 +735,8 @@ __global__ __launch_bounds__(kListThreads) void vts_lists_kernel(const int32_t* 
   __shared__ int32_t cnt[kListRange];
   __shared__ int32_t wave_total[kListThreads / kWave], wave_below[kListThreads / kWave];
   if ((int)blockIdx.x == B * ranges) {  // (only there with dp_part)
-    sum_parts(dp_part, 0, (size_t)dp_n, reinterpret_cast<float*>(wave_total), dp);
+    __shared__ float acc[16];
+    sum_parts(dp_part, 0, (size_t)dp_n, acc, dp);
     return;
   }
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
