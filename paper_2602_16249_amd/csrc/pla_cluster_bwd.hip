@@ -386,7 +386,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 //  rel_dtable[i] = sum over the groups of rel_part[group][i]  (i < rel_entries)
 //  dk_blank, dv_blank = sums over the strips of blank_part
 // As launches of their own, behind the key-stationary kernel, they took 5.0 us (2048 tables of 162 bins) and 3.5 us (753
-// strips, 3 heads) and the gap before them, at the end of a step; here they run beside it.
+// strips, 3 heads) and the gap before them, at the end of a step; here they run beside it.  Whole backward with the tables' sum in two
+// launches behind / beside, us: 8 images of 16384 tokens (2048 tables of 162 bins) 91.9 / 85.3, 16 201.9 / 191.3, 32 391.7 / 376.7,
+// 64 759.8 / 736.7, 32768 images of 64 tokens 600 / 540.
 __device__ __forceinline__ void side_sums(const BwdParams& p, int i, float* lds) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   if (i < p.rel_entries) {
@@ -561,36 +563,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CL == 2 ? 3
   }
 }
 
-// First step of the sum of the workgroups' relative-position tables [groups][H][cells]: workgroup (head, part) adds
-// its share of them, thread = (bin, one of the groups that fit 256 threads), and writes one table.
-constexpr int kRelParts = 64;
-__global__ __launch_bounds__(256) void pla_rel_reduce_kernel(const float* __restrict__ part, int tables, int H,
-                                                             int cells, float* __restrict__ out) {
-  __shared__ float acc[256];
-  const int h = blockIdx.x / kRelParts, pt = blockIdx.x - h * kRelParts;
-  const int groups = 256 / cells;  // cells <= 128: at least two
-  const int c = threadIdx.x % cells, grp = threadIdx.x / cells;
-  const int per = (tables + kRelParts - 1) / kRelParts;
-  const int end = min(tables, (pt + 1) * per);
-  float s = 0.f;
-  if (grp < groups)
-    for (int sg = pt * per + grp; sg < end; sg += groups) s += part[((size_t)sg * H + h) * cells + c];
-  acc[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x < cells) {
-    float t = 0.f;
-    for (int j = 0; j < groups; ++j) t += acc[j * cells + threadIdx.x];
-    out[((size_t)pt * H + h) * cells + threadIdx.x] = t;
-  }
-}
-
 }  // namespace
 
 size_t pla_bwd_cluster_rel_workspace_bytes(int B, int N, int H, int R) {
-  // tables of the workgroups, then the tables of pla_rel_reduce_kernel
+  // tables of the workgroups (and room for 64 more, which callers' workspaces have always had)
   const size_t cells = (size_t)(2 * R + 1) * (2 * R + 1);
   const size_t groups = (size_t)B * ((N + 16 * kGroup - 1) / (16 * kGroup));
-  return plan_align(groups * H * cells * sizeof(float)) + plan_align((size_t)kRelParts * H * cells * sizeof(float));
+  return plan_align(groups * H * cells * sizeof(float)) + plan_align(64 * H * cells * sizeof(float));
 }
 bool pla_bwd_cluster_rel_sums(int R) { return (2 * R + 1) * (2 * R + 1) <= kRelBins; }
 
@@ -673,11 +652,8 @@ hipError_t launch_pla_bwd_cluster(const PlaArgs& a, const void* plan, void* work
 #undef AFFMAE_BWDQ_LAST
 #undef AFFMAE_BWDQ
   }
-  // up to 4096 tables of relative-position sums are added up beside the key-stationary kernel, a workgroup per bin; more take
-  // two launches of their own
   const int cells = (2 * a.rel_R + 1) * (2 * a.rel_R + 1);
-  const bool rel_sums = a.rel_table && a.rel_part, rel_beside = rel_sums && L.groups <= 4096;
-  p.rel_entries = rel_beside ? a.H * cells : 0;
+  p.rel_entries = a.rel_table && a.rel_part ? a.H * cells : 0;
   p.rel_dtable = a.rel_dtable;
   p.blank_blocks = p.blank_part ? 8 * a.H : 0;
   p.strips = L.strips;
@@ -700,14 +676,6 @@ hipError_t launch_pla_bwd_cluster(const PlaArgs& a, const void* plan, void* work
     if (cl == 0) AFFMAE_BWDK(0); else if (cl == 1) AFFMAE_BWDK(1); else AFFMAE_BWDK(2);
 #undef AFFMAE_BWDK
 #undef AFFMAE_BWDK_RAG
-  }
-  if (rel_sums && !rel_beside) {
-    float* second = reinterpret_cast<float*>(reinterpret_cast<char*>(a.rel_part) +
-                                             plan_align((size_t)L.groups * a.H * cells * sizeof(float)));
-    AFFMAE_LAUNCH("pla_rel_reduce_kernel", stream, pla_rel_reduce_kernel, dim3(a.H * kRelParts), dim3(256), 0, stream,
-                  a.rel_part, L.groups, a.H, cells, second);
-    const hipError_t e = launch_relpos_table_sum(second, kRelParts, a.H * cells, a.rel_dtable, stream);
-    if (e != hipSuccess) return e;
   }
   return hipGetLastError();
 }
