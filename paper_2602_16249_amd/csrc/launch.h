@@ -91,7 +91,7 @@ struct PairSumShape {
   int extras;  // more workgroups an image, for the parts of crowded ranges
 };
 PairSumShape pair_sum_shape(const PairSumArgs& a);
-// An image's words of `crowds`: [0] the number of its items, [1] words of `list` in use (0), then its items: a range, or part `part` of
+// An image's words of `crowds`: [0] words of `list` in use (0), then its ranges + extras items (-1: none): a range, or part `part` of
 // `parts` of as many tokens each.  Where the anchors of any range have more than kSumCrowd pairs, ranges go into parts of kSumPart,
 // as about as many pairs name a range's tokens as its anchors have (8 images, 16384 tokens of a jittered grid, a quarter kept at random:
 // 110 more or less, standard deviation; of 20480 ranges with 3072 on average none has more than 4256, whose anchors have at most 4416).

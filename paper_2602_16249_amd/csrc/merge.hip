@@ -433,19 +433,20 @@ __global__ __launch_bounds__(256) void merge_fwd_kernel(const T* __restrict__ fe
 // For pair_sum.hip, whose workgroups own equal ranges of an image's tokens: a workgroup per image, in front of the others and
 // beside them, counts the anchors of every range and lists the ranges, in parts where anchors crowd.
 struct Crowds {
-  int front, range, ranges;  // as in PairSumShape
+  int front, range, ranges, extras;  // as in PairSumShape
   uint32_t range_magic;
   int32_t* words;
 };
 __device__ __forceinline__ void split_crowds(const Crowds& s, const int32_t* __restrict__ anchor, int B, int N, int K, int n_keep) {
-  __shared__ int count[kSumMostRanges], most, heavy, light;
+  extern __shared__ int count[];  // [ranges]; then:
+  int &most = count[s.ranges], &heavy = count[s.ranges + 1], &light = count[s.ranges + 2];
   const int b = blockIdx.x;
   if (b >= B) return;
   int32_t* words = s.words + (size_t)b * N;
-  if (threadIdx.x == 0) words[1] = 0;
-  if (s.ranges > kSumMostRanges) return;  // (then they are taken as they are)
+  if (threadIdx.x == 0) words[0] = 0;
+  if (s.extras == 0) return;  // (the ranges are taken as they are)
   for (int r = threadIdx.x; r < s.ranges; r += 256) count[r] = 0;
-  if (threadIdx.x == 0) most = heavy = light = 0;
+  if (threadIdx.x < 3) count[s.ranges + threadIdx.x] = 0;
   __syncthreads();
   for (int i0 = threadIdx.x; i0 < n_keep; i0 += 8 * 256) {
     int tok[8];
@@ -460,25 +461,22 @@ __device__ __forceinline__ void split_crowds(const Crowds& s, const int32_t* __r
   __syncthreads();
   const bool crowded = (long long)most * K > kSumCrowd;
   if (!crowded) {
-    for (int r = threadIdx.x; r < s.ranges; r += 256) words[2 + r] = sum_item(r, 0, 1);
-    if (threadIdx.x == 0) words[0] = s.ranges;
+    for (int r = threadIdx.x; r < s.ranges + s.extras; r += 256) words[1 + r] = r < s.ranges ? sum_item(r, 0, 1) : -1;
     return;
   }
   // the ranges with much to do first
   auto parts_of = [&](int r) { return (int)min((long long)kSumMostParts, ((long long)count[r] * K + kSumPart - 1) / kSumPart); };
   for (int r = threadIdx.x; r < s.ranges; r += 256)
     if (count[r] * (long long)K >= kSumPart / 2) atomicAdd(&light, parts_of(r));
-  __syncthreads();
-  const int lights = light;
-  __syncthreads();
+  __syncthreads();  // (`light` goes on behind them)
   for (int r = threadIdx.x; r < s.ranges; r += 256) {
     const int parts = max(1, parts_of(r));
     const bool much = count[r] * (long long)K >= kSumPart / 2;
     const int at = much ? atomicAdd(&heavy, parts) : atomicAdd(&light, 1);
-    for (int part = 0; part < parts; ++part) words[2 + at + part] = sum_item(r, part, parts);
+    for (int part = 0; part < parts; ++part) words[1 + at + part] = sum_item(r, part, parts);
   }
   __syncthreads();
-  if (threadIdx.x == 0) words[0] = light;
+  for (int i = light + threadIdx.x; i < s.ranges + s.extras; i += 256) words[1 + i] = -1;
 }
 
 template <typename T, int PP>
@@ -682,10 +680,11 @@ hipError_t launch_merge_bwd(const MergeArgs& a, hipStream_t stream) {
   s.dfeat = a.dfeat; s.extra_sum = a.dscore; s.list = list; s.crowds = offset;
   const bool one = pair_sum_takes(s);
   const PairSumShape shape = one ? pair_sum_shape(s) : PairSumShape{};
-  const Crowds crowds = {shape.front, shape.range, shape.ranges, shape.range_magic, offset};
+  const Crowds crowds = {shape.front, shape.range, shape.ranges, shape.extras, shape.range_magic, offset};
+  const size_t crowd_lds = shape.extras ? (shape.ranges + 3) * sizeof(int) : 0;
   const dim3 grid(shape.front + round_up8(((long long)anchors + 3) / 4));
 #define AFFMAE_MERGE_BWD(T, P)                                                                                     \
-  AFFMAE_LAUNCH("merge_bwd_kernel", stream, (merge_bwd_kernel<T, P>), grid, dim3(256), 0, stream, (const T*)a.feat, \
+  AFFMAE_LAUNCH("merge_bwd_kernel", stream, (merge_bwd_kernel<T, P>), grid, dim3(256), crowd_lds, stream, (const T*)a.feat, \
                 a.coords, a.score, a.nbr_idx, a.anchor_idx, (const T*)a.dout, a.B, a.N, a.C, a.K, a.n_keep, a.p, \
                 wpair, dzpair, pair_token, pair_bounds, shape.cells, dp_part, crowds)
   AFFMAE_MERGE_ROWS(AFFMAE_MERGE_BWD)

@@ -18,9 +18,10 @@
 // Where anchors crowd, a range has up to K pairs a token and its neighbours none: then the workgroups take the items that the launch before
 // has listed, ranges with much to do first and in parts, the ranges without anchors last.  The same 8 images, us, whole backward, the
 // two launches before / every workgroup its own range, with lists in memory where they do not fit / as here: anchors in a quarter of
-// the frame 95 / 185 / 69, in a disc 97 / 183 / 79, by a smooth function of the place and some noise 95 / 177 / 67, at random 76 / 53 / 54.
-// Parts of 3072 pairs instead of 4096: 77, 86, 81 (three fifths of a part's time are the chain); further parts behind all first
-// ones instead of in front of the light ranges: 87, 86, 84.
+// the frame 95 / 185 / 68, in a disc 97 / 183 / 78, by a smooth function of the place and some noise 95 / 177 / 67, at random 76 / 52.5 / 53.
+// Before the groups' cells came four at a time, the first with the item: 69, 79, 68, 54, and one image of 262144 tokens 166 for 154; with parts
+// of 3072 pairs instead of 4096 77, 86, 81 (three fifths of a part's time are the chain); with further parts behind all first ones
+// instead of in front of the light ranges 87, 86, 84.
 // Places for 5120 pairs (the noted pairs make room for `extra`): with 4096 a range of the anchors at random did not fit in 3 of
 // 40 batches, which then took 20 us longer.
 // (The virtual tokens' backward, whose queries lie anywhere, would look at all pairs in every workgroup: 64.7 us for 17.3 +
@@ -101,10 +102,14 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
   const int at_extra = (int)blockIdx.x - p.B * p.ranges;
   const int b = at_extra < 0 ? blockIdx.x / p.ranges : at_extra / p.extras;
   int rg = at_extra < 0 ? blockIdx.x - b * p.ranges : p.ranges + at_extra - b * p.extras, part = 0, parts = 1;
+  // cells of the image's first groups: on their way while the item is
+  const uint2* group_cells = p.group_cells + (size_t)b * p.groups;
+  uint2 first_cells[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) first_cells[u] = group_cells[min(u * kSumThreads + tid, p.groups - 1)];
   if (p.extras) {
-    const int32_t* items = p.crowds + (size_t)b * p.Nv;
-    if (rg >= items[0]) return;  // the whole workgroup
-    const int item = items[2 + rg];
+    const int item = p.crowds[(size_t)b * p.Nv + 1 + rg];
+    if (item < 0) return;  // the whole workgroup
     parts = (item & (kSumMostParts - 1)) + 1;
     part = item / kSumMostParts & (kSumMostParts - 1);
     rg = item / (kSumMostParts * kSumMostParts);
@@ -131,23 +136,34 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
   const int first = b * p.Nv + t0;
   // fn(tokens, pairs, in) for four pairs at a time, all lanes of a wave together, of the groups that name a token of these cells
   int32_t* glist = reinterpret_cast<int32_t*>(entry);
-  auto each_pair = [&](auto&& fn) {
+  auto each_pair = [&](auto loaded, auto&& fn) {
     for (int g0 = 0; g0 < p.groups; g0 += kSumGroups) {
       __syncthreads();  // the list before has been walked (and, the first time, the counters are set)
       if (tid == 0) s_listed = 0;
       __syncthreads();
       const int g1 = min(g0 + kSumGroups, p.groups);
-      for (int gw = g0 + wave * kWave; gw < g1; gw += kSumThreads) {
-        const int g = gw + lane;
-        const uint2 named = p.group_cells[(size_t)b * p.groups + min(g, g1 - 1)];
-        const bool x = (named.x & own.x) != 0u, y = (named.y & own.y) != 0u;
-        const bool in = g < g1 && (p.cells.rows ? x && y : x || y);
-        const unsigned long long mask = __ballot(in);
+      for (int gw = g0 + wave * kWave; gw < g1; gw += 4 * kSumThreads) {
+        uint2 named[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          named[u] = decltype(loaded)::value && gw < kSumThreads ? first_cells[u] : group_cells[min(gw + u * kSumThreads + lane, g1 - 1)];
+        unsigned long long mask[4];
+        int found = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const bool x = (named[u].x & own.x) != 0u, y = (named[u].y & own.y) != 0u;
+          mask[u] = __ballot(gw + u * kSumThreads + lane < g1 && (p.cells.rows ? x && y : x || y));
+          found += __popcll(mask[u]);
+        }
         int at = 0;
-        if (lane == 0) at = atomicAdd(&s_listed, (int)__popcll(mask));
+        if (lane == 0) at = atomicAdd(&s_listed, found);
         at = __builtin_amdgcn_readfirstlane(at);
-        const int place = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, (uint32_t)at));
-        if (in) glist[place] = g;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int place = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask[u], (uint32_t)at));
+          if ((mask[u] >> lane) & 1ull) glist[place] = gw + u * kSumThreads + lane;
+          at += __popcll(mask[u]);
+        }
       }
       __syncthreads();
       const int items = s_listed * p.gs;
@@ -168,7 +184,7 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
   };
 
   // the own tokens' pairs: counted and noted
-  each_pair([&](const int (&tok)[4], const int (&pair)[4], const bool (&in)[4]) {
+  each_pair(std::true_type{}, [&](const int (&tok)[4], const int (&pair)[4], const bool (&in)[4]) {
     unsigned long long mask[4];
     int found = 0;
 #pragma unroll
@@ -214,7 +230,7 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
   const bool fits = total <= kSumCap;
   cnt[tid] = run;
   // (lists that do not fit, where many pairs name few tokens, go to memory)
-  if (!fits && tid == 0) s_far = atomicAdd(p.crowds + (size_t)b * p.Nv + 1, total);
+  if (!fits && tid == 0) s_far = atomicAdd(p.crowds + (size_t)b * p.Nv, total);
   __syncthreads();
   int32_t* const far = p.list + lo + (fits ? 0 : s_far);
   auto row_of = [&](int pair) { return (uint32_t)exact_div(pair - lo, p.row_pairs, p.row_magic) * (uint32_t)p.pieces; };
@@ -237,7 +253,7 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
         if (u * kSumThreads + tid < total) entry_extra[at[u]] = p.extra[pair[u]];
     }
   } else {
-    each_pair([&](const int (&tok)[4], const int (&pair)[4], const bool (&in)[4]) {
+    each_pair(std::false_type{}, [&](const int (&tok)[4], const int (&pair)[4], const bool (&in)[4]) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int rel = tok[u] - first;
