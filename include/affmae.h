@@ -271,7 +271,7 @@ int affmae_knn_static(const float* coords, const int32_t* cluster_id, int B, int
  * attention kernels (paper, Sec. "Limitations": neighbourhood tables are cached
  * per encoder stage; the plan is that cache in the layout the tiled kernels read,
  * built once per table and passed to every forward and backward call that uses
- * the table).  Optional: without a plan the attention calls rebuild it in their
+ * the table).  Optional: without a plan the calls for bf16 and d == 32 rebuild it in their
  * workspace on every call.
  *
  *   nbr_idx, near_clusters  in  as produced by affmae_knn with cluster_id == NULL

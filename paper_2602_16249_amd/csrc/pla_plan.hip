@@ -376,14 +376,12 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(PlanParams p) {
 // files the strips of its own groups, and sorts these lists in LDS.
 // Bound by the chain of these steps in each workgroup, which grows with the image's tiles, against counting with atomics
 // in the strip kernel and four more launches (zero, scan, fill, sort: 4 - 6 us each, of the whole batch).  Whole plan, K =
-// 48, one launch and four: one image of 64 / 256 / 512 / 1024 tiles 14 / 15 / 16 / 17 us and 19 / 19 / 20 / 20 us; 1024
-// tiles, 4 / 8 / 16 / 32 images 24 / 34 / 50 / 85 us and 28 / 38 / 57 / 94 us, both with a strip kernel that took 3 to 40 us
-// longer.  (With the touch tables read twice and the
-// lists sorted in memory 28 / 37 / 54 / 93 us; with a list per token tile instead of per group, and the pairs of every
-// strip sorted by tile, 30 / 42 / 62 / 102 us; with a list's places from broadcast lanes instead of LDS reads, as now, 0.5 -
-// 0.8 us less than the figures above.)  Beyond 1024 tiles a thread would serve several strips.
-// Images of a few tiles take a workgroup each and give it little to do (1 tile: 15 / 25 us at 1024 / 2048 images against
-// 16 / 18; 4 tiles: 15 / 22 us at 768 / 1536 against 17 / 20): below 16 tiles, up to 768.
+// 48, one launch and four: one image of 64 / 256 / 512 / 1024 tiles 10 / 11 / 12.5 / 12.5 us and 19 us; 1024 tiles, 4 / 8 / 16 / 32
+// images 15 / 19 / 26 / 39 us and 21 / 26 / 35 / 53 us.  (Not faster: the touch tables read twice and the lists sorted in memory; a
+// list per token tile instead of per group; a list's places from LDS instead of broadcast lanes.)  Beyond 1024 tiles a thread would
+// serve several strips.
+// Images of a few tiles take a workgroup each and give it little to do (1 tile: 8 / 15 / 24 us at 256 / 1024 / 2048 images against
+// 19; 4 tiles: 15 / 23 us at 768 / 1536 against 19 / 21; 16 tiles 24 / 38 us against 29 / 41): below 16 tiles, up to 768.
 constexpr int kRevThreads = 1024, kRevGroups = kRevThreads / kGroup, kRevGroupsFew = 4, kRevImagesFew = 768;
 constexpr int kRevSorted = 1024;  // entries of a workgroup's lists that are in LDS at a time
 static_assert(kRevSorted >= kRevThreads, "room for a group's list of all the image's strips");
