@@ -9,7 +9,7 @@
 // whose rows then come from the CU's own cache.  Before, one launch wrote every token's list to memory and a second one
 // read, per 16 pairs of a token, the list, then the weights it named, then the rows; at C = 64 (bf16) half of the 16
 // lanes that a token got had no channels.  8 images, 16384 tokens, 4096 anchors, K = 48, C = 64: 20.4 + 29.1 us and 4.6 for
-// dp (which one workgroup of this launch adds up now); 26.5 us as here.
+// dp (which one workgroup of this launch adds up now); 25.5 us as here.
 // (440 workgroups of 298 tokens: 33.8 us.)
 // Bound by the chain of the sort (12 of its 16 us a workgroup: the anchors' masks, the pairs they point to, their weights:
 // each step waits for memory) and then by the rows.  Two workgroups of 1024 threads per CU: 36.8 us with one (71

@@ -857,15 +857,15 @@ hipError_t wide_bwd(const PlaArgs& a, const void* plan, hipStream_t stream) {
 // Gather kernels' time / here, forward and backward together (forward alone), on tables from masked, uniform and jittered tokens, S =
 // 64, M = 8; S = 16 and 32 have fewer tiles a strip and are up to 1.3 times better:
 //                  full                                 most                            some
-//   bf16 d = 16    K 3 .. 64  1.7 - 3.4 (1.2 - 2.4)     1.6 - 2.2 (1.3 - 1.9)           1.3 - 2.1 (1.0 - 1.5)
+//   bf16 d = 16    K 3 .. 64  1.7 - 3.4 (1.3 - 2.4)     1.6 - 2.2 (1.3 - 1.9)           1.3 - 1.7 (1.0 - 1.5)
 //   bf16 d = 64    K 17 .. 64 1.11 - 2.0 (1.2 - 2.1)    1.0 - 1.12 (1.14 - 1.35)        K < 48 0.93 - 1.04, K >= 48 0.97 - 1.14 (0.88 - 1.04)
 //                  K 9 .. 16  0.96 - 1.2 (0.91 - 1.26)  0.88 - 0.95                     0.77 - 0.93
 //   fp32 d = 64    K 16 .. 64 1.14 - 2.7 (1.3 - 3.0)    1.03 - 1.36 (1.23 - 1.6)        K < 48 0.90 - 1.01, K >= 48 1.16 - 1.35 (1.2 - 1.6)
 //   fp32 d = 32    K 17 .. 64 1.07 - 2.2 (0.93 - 1.7)   K >= 48 1.10 - 1.21 (0.88 - 0.93)   0.90 - 1.2, but the forward 0.71 - 0.92
 //                  K = 16     0.79 - 1.1 (0.67 - 0.97)  K < 48 0.96 - 1.05 (0.87 - 1.0)
-//   fp32 d = 16    K 3 .. 64  0.99 - 3.1 (0.88 - 1.7)   K >= 48 1.28 - 1.53 (0.85 - 0.9)    K < 16 1.05 - 1.16 (1.0); 1.01 - 1.4, but the
+//   fp32 d = 16    K 3 .. 64  0.99 - 3.1 (0.88 - 1.7)   K >= 48 1.28 - 1.53 (0.85 - 0.9)    K < 16 1.05 - 1.16 (1.0); 1.01 - 1.45, but the
 //                                                       K < 48 0.96 - 1.24 (0.8 - 1.1)      forward 0.76 - 1.0, from there on
-// so the rule keeps out what is slower for a step, or for a forward alone by more than 15 %.
+// so the rule keeps out what is slower for a step by more than 4 %, or for a forward alone by more than 15 %.
 // (fp32 d = 64, K = 9: dS was 4 % further from 64 bits than by the gather kernels.)
 // (Forward and backward by one rule: the backward forms p = exp(s - lse) again, and is further from 64 bits where s is not rounded as
 // in the forward: fp32, K = 9 .. 64, dq 1.09 - 1.18 times as far with the forward by the gather kernels as with both by them, 0.90 - 0.99 with
