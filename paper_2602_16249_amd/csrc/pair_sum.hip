@@ -19,9 +19,10 @@
 // has listed, ranges with much to do first and in parts, the ranges without anchors last.  The same 8 images, us, whole backward, the
 // two launches before / every workgroup its own range, with lists in memory where they do not fit / as here: anchors in a quarter of
 // the frame 95 / 185 / 68, in a disc 97 / 183 / 78, by a smooth function of the place and some noise 95 / 177 / 67, at random 76 / 52.5 / 53.
-// Before the groups' cells came four at a time, the first with the item: 69, 79, 68, 54, and one image of 262144 tokens 166 for 154; with parts
-// of 3072 pairs instead of 4096 77, 86, 81 (three fifths of a part's time are the chain); with further parts behind all first ones
-// instead of in front of the light ranges 87, 86, 84.
+// With parts of 3072 pairs instead of 4096 77, 86, 81 (three fifths of a part's time are the chain); with further parts behind all first
+// ones instead of in front of the light ranges 87, 86, 84.
+// Cells of more than 1024 groups come four at a time (one image of 262144 tokens, 65536 anchors: 155 us, one at a time 166); of fewer,
+// the three that do not exist cost 0.8 us (16 images of 4096 tokens, this launch: 22.7 and 23.5).
 // Places for 5120 pairs (the noted pairs make room for `extra`): with 4096 a range of the anchors at random did not fit in 3 of
 // 40 batches, which then took 20 us longer.
 // (The virtual tokens' backward, whose queries lie anywhere, would look at all pairs in every workgroup: 64.7 us for 17.3 +
@@ -102,11 +103,7 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
   const int at_extra = (int)blockIdx.x - p.B * p.ranges;
   const int b = at_extra < 0 ? blockIdx.x / p.ranges : at_extra / p.extras;
   int rg = at_extra < 0 ? blockIdx.x - b * p.ranges : p.ranges + at_extra - b * p.extras, part = 0, parts = 1;
-  // cells of the image's first groups: on their way while the item is
   const uint2* group_cells = p.group_cells + (size_t)b * p.groups;
-  uint2 first_cells[4];
-#pragma unroll
-  for (int u = 0; u < 4; ++u) first_cells[u] = group_cells[min(u * kSumThreads + tid, p.groups - 1)];
   if (p.extras) {
     const int item = p.crowds[(size_t)b * p.Nv + 1 + rg];
     if (item < 0) return;  // the whole workgroup
@@ -136,35 +133,38 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
   const int first = b * p.Nv + t0;
   // fn(tokens, pairs, in) for four pairs at a time, all lanes of a wave together, of the groups that name a token of these cells
   int32_t* glist = reinterpret_cast<int32_t*>(entry);
-  auto each_pair = [&](auto loaded, auto&& fn) {
+  auto each_pair = [&](auto&& fn) {
     for (int g0 = 0; g0 < p.groups; g0 += kSumGroups) {
       __syncthreads();  // the list before has been walked (and, the first time, the counters are set)
       if (tid == 0) s_listed = 0;
       __syncthreads();
       const int g1 = min(g0 + kSumGroups, p.groups);
-      for (int gw = g0 + wave * kWave; gw < g1; gw += 4 * kSumThreads) {
-        uint2 named[4];
+      auto list_groups = [&](auto at_a_time) {
+        constexpr int kU = decltype(at_a_time)::value;
+        for (int gw = g0 + wave * kWave; gw < g1; gw += kU * kSumThreads) {
+          uint2 named[kU];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-          named[u] = decltype(loaded)::value && gw < kSumThreads ? first_cells[u] : group_cells[min(gw + u * kSumThreads + lane, g1 - 1)];
-        unsigned long long mask[4];
-        int found = 0;
+          for (int u = 0; u < kU; ++u) named[u] = group_cells[min(gw + u * kSumThreads + lane, g1 - 1)];
+          unsigned long long mask[kU];
+          int found = 0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const bool x = (named[u].x & own.x) != 0u, y = (named[u].y & own.y) != 0u;
-          mask[u] = __ballot(gw + u * kSumThreads + lane < g1 && (p.cells.rows ? x && y : x || y));
-          found += __popcll(mask[u]);
+          for (int u = 0; u < kU; ++u) {
+            const bool x = (named[u].x & own.x) != 0u, y = (named[u].y & own.y) != 0u;
+            mask[u] = __ballot(gw + u * kSumThreads + lane < g1 && (p.cells.rows ? x && y : x || y));
+            found += __popcll(mask[u]);
+          }
+          int at = 0;
+          if (lane == 0) at = atomicAdd(&s_listed, found);
+          at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+          for (int u = 0; u < kU; ++u) {
+            const int place = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask[u], (uint32_t)at));
+            if ((mask[u] >> lane) & 1ull) glist[place] = gw + u * kSumThreads + lane;
+            at += __popcll(mask[u]);
+          }
         }
-        int at = 0;
-        if (lane == 0) at = atomicAdd(&s_listed, found);
-        at = __builtin_amdgcn_readfirstlane(at);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int place = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask[u], (uint32_t)at));
-          if ((mask[u] >> lane) & 1ull) glist[place] = gw + u * kSumThreads + lane;
-          at += __popcll(mask[u]);
-        }
-      }
+      };
+      if (g1 - g0 <= kSumThreads) list_groups(std::integral_constant<int, 1>{}); else list_groups(std::integral_constant<int, 4>{});
       __syncthreads();
       const int items = s_listed * p.gs;
       for (int i0 = 0; i0 < items; i0 += 4 * kSumThreads) {
@@ -184,7 +184,7 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
   };
 
   // the own tokens' pairs: counted and noted
-  each_pair(std::true_type{}, [&](const int (&tok)[4], const int (&pair)[4], const bool (&in)[4]) {
+  each_pair([&](const int (&tok)[4], const int (&pair)[4], const bool (&in)[4]) {
     unsigned long long mask[4];
     int found = 0;
 #pragma unroll
@@ -236,24 +236,26 @@ __global__ __launch_bounds__(kSumThreads) __attribute__((amdgpu_waves_per_eu(8, 
   auto row_of = [&](int pair) { return (uint32_t)exact_div(pair - lo, p.row_pairs, p.row_magic) * (uint32_t)p.pieces; };
   if (fits) {
     constexpr int kMine = kSumCap / kSumThreads;
-    int pair[kMine], at[kMine];
+    int at[kMine];
+    float extra[kMine];
 #pragma unroll
     for (int u = 0; u < kMine; ++u) {
       const int i = u * kSumThreads + tid;
       if (i < total) {
-        pair[u] = (int)hit_pair[i];
+        const int pair = (int)hit_pair[i];
         at[u] = atomicAdd(&cnt[hit_token[i]], 1);
-        entry[at[u]] = make_uint2(row_of(pair[u]), __float_as_uint(p.weights[pair[u]]));
+        if (p.extra) extra[u] = p.extra[pair];
+        entry[at[u]] = make_uint2(row_of(pair), __float_as_uint(p.weights[pair]));
       }
     }
     if (p.extra) {
       __syncthreads();  // hit_pair has been read
 #pragma unroll
       for (int u = 0; u < kMine; ++u)
-        if (u * kSumThreads + tid < total) entry_extra[at[u]] = p.extra[pair[u]];
+        if (u * kSumThreads + tid < total) entry_extra[at[u]] = extra[u];
     }
   } else {
-    each_pair(std::false_type{}, [&](const int (&tok)[4], const int (&pair)[4], const bool (&in)[4]) {
+    each_pair([&](const int (&tok)[4], const int (&pair)[4], const bool (&in)[4]) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int rel = tok[u] - first;
